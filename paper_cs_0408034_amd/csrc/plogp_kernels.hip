@@ -158,22 +158,8 @@ __global__ void __launch_bounds__(256) k_interp(DeviceTables T, int t, const u64
 
 // ---------------------------------------------------------------- one strategy at n points
 
-// sum_{j=1}^{P-1} g(j m) in the block order of SUM_BLOCK.
-__device__ double chain_sum(const LdsTable &tab, u64 m, uint32_t P)
-{
-    double done = 0.0, run = 0.0;
-    u64 z = 0;
-    for (uint32_t j = 1; j <= P - 1; ++j) {
-        z += m;
-        run = run + gap_at(tab, (double)z);
-        if (j % SUM_BLOCK == 0) {
-            done = done + run;
-            run = 0.0;
-        }
-    }
-    return done + run;
-}
-
+// Every row but the Scatter and Gather chains, which add up to P - 1 gaps per point and have a
+// kernel of their own (k_eval_chain).
 __global__ void __launch_bounds__(256) k_eval(DeviceTables T, int t, int id, const u64 *dm,
                                               const uint32_t *dP, const u64 *ds, size_t n,
                                               double *out)
@@ -189,8 +175,6 @@ __global__ void __launch_bounds__(256) k_eval(DeviceTables T, int t, int id, con
     const u64 s = seg ? ds[i] : 0;
     const u64 lim = 1ull << 53;
     bool ok = m > 0 && m < lim && P >= 2 && (!seg || (s > 0 && s <= m));
-    if (ok && (id == 11 || id == 14))
-        ok = (u64)(P - 1) <= (lim - 1) / m;
     if (ok && (id == 12 || id == 15))
         ok = m <= ((lim - 1) >> (ceil_log2(P) > 0 ? ceil_log2(P) - 1 : 0));
     if (!ok) {
@@ -219,7 +203,6 @@ __global__ void __launch_bounds__(256) k_eval(DeviceTables T, int t, int id, con
     case 7: r = __builtin_fma(fl, gm, cl * L); break;
     case 8: r = __builtin_fma(fl, gm, cl * R); break;
     case 9: r = __builtin_fma(fl, gs * k, cl * L); break;
-    case 11: case 14: r = __builtin_fma(q, L, chain_sum(tab, m, P)); break;
     case 16: r = 2.0 * __builtin_fma(q, g1, L); break;
     case 17: r = 2.0 * __builtin_fma(fl, g1, cl * L); break;
     default: {
@@ -440,6 +423,35 @@ struct ChainCtx {
     const int *blk_off;
 };
 
+// Builds the table as intervals in LDS (chain_lds(n) bytes at `lds`) from the raw samples: the
+// slopes are the same expression as everywhere.  The caller synchronises.
+constexpr size_t CHAIN_PAD = 14;                                   // entries beside the 4 n of the table
+
+__device__ __forceinline__ void stage_intervals(ChainCtx &C, double *lds, const DeviceTables &T, int t)
+{
+    const int n = T.n;
+    f64x2 *YS = reinterpret_cast<f64x2 *>(lds);                    // n + 2 entries
+    double *X = lds + 2 * (n + 2);                                 // n + 6 entries, +inf from n + 1 on
+    double *W = X + (n + 6);                                       // n + 2 entries
+    const double *gx = T.x + (size_t)t * n, *gy = T.y + (size_t)t * n;
+    for (int i = threadIdx.x; i < n + 6; i += blockDim.x) {
+        // interval i starts at sample i - 1; interval 0 is the clamp below the first sample
+        const double x0 = i == 0 ? 0.0 : i <= n ? gx[i - 1] : INFINITY;
+        X[i] = x0;
+        if (i < n + 2) {
+            f64x2 ys;
+            ys.x = i == 0 ? gy[0] : i <= n ? gy[i - 1] : 0.0;
+            ys.y = (i == 0 || i > n) ? 0.0 : interval_slope(gx, gy, n, i - 1);
+            YS[i] = ys;
+            W[i] = i < n ? gx[i] - x0 : INFINITY;
+        }
+    }
+    C.YS = YS;
+    C.X = X;
+    C.W = W;
+    C.n = n;
+}
+
 // Intervals of U sizes at once: for each the number of samples not above it
 // (0 = the virtual interval).  The searches run side by side, so that the LDS
 // latencies of one halving step overlap.
@@ -658,30 +670,10 @@ __device__ __forceinline__ void chain_body(const DeviceTables &T, const DeviceGr
 {
     __shared__ unsigned next_item;
     const int t = block_id / wg_per_table, wg = block_id % wg_per_table;
-    const int n = T.n;
-    // the table as intervals, built from the raw samples (the slopes are those of the
-    // tuning's first step: the same expression): YS[0..n+1] = {gap, slope}, X[0..n+5] =
-    // interval starts (0, the samples, +inf ...), W = widths
-    f64x2 *YS = reinterpret_cast<f64x2 *>(chain_lds);              // n + 2 entries
-    double *X = chain_lds + 2 * (n + 2);                           // n + 6 entries, +inf from n + 1 on
-    double *W = X + (n + 6);                                       // n + 2 entries
-    {
-        const double *gx = T.x + (size_t)t * n, *gy = T.y + (size_t)t * n;
-        for (int i = threadIdx.x; i < n + 6; i += blockDim.x) {
-            // interval i starts at sample i - 1; interval 0 is the clamp below the first sample
-            const double x0 = i == 0 ? 0.0 : i <= n ? gx[i - 1] : INFINITY;
-            X[i] = x0;
-            if (i < n + 2) {
-                f64x2 ys;
-                ys.x = i == 0 ? gy[0] : i <= n ? gy[i - 1] : 0.0;
-                ys.y = (i == 0 || i > n) ? 0.0 : interval_slope(gx, gy, n, i - 1);
-                YS[i] = ys;
-                W[i] = i < n ? gx[i] - x0 : INFINITY;
-            }
-        }
-        if (threadIdx.x == 0)
-            next_item = 0u;
-    }
+    ChainCtx C;
+    stage_intervals(C, chain_lds, T, t);
+    if (threadIdx.x == 0)
+        next_item = 0u;
     __syncthreads();
     const int lane = threadIdx.x & 63;
     const int n_mg = (G.n_mu + 63) / 64;      // groups of 64 distinct sizes
@@ -689,11 +681,6 @@ __device__ __forceinline__ void chain_body(const DeviceTables &T, const DeviceGr
     const unsigned n_units = (unsigned)((G.n_blk - n_single + CHAIN_U - 1) / CHAIN_U);
     const unsigned n_items = n_single_items + n_units * (unsigned)n_mg;
     const unsigned W_ = (unsigned)wg_per_table;
-    ChainCtx C;
-    C.YS = YS;
-    C.X = X;
-    C.W = W;
-    C.n = n;
     C.n_blk = G.n_blk;
     C.n_m = (size_t)G.n_mu;
     C.blk_mask = G.blk_mask;
@@ -841,6 +828,160 @@ __global__ void k_chain_blocks(DeviceTables T, DeviceGrid G, Scratch S, int wg_p
         __syncthreads();                  // every wave is done with the table as intervals
         terms_body(T, G, S, wg_per_table, 0, terms_mode, (int)blockIdx.x, chain_lds);
     }
+}
+
+// ---------------------------------------------------------------- the chain row at n points
+
+// g((64 b + 1) m) + ... + g((64 b + terms) m) added in ascending j from +0.0, `terms` <= 64 of them
+// in this lane (the loop runs to the wave's largest).  What counts here is the number of
+// instructions: the sum and the distance are pinned to their registers after every term (left to
+// itself the compiler carries a copy of every state variable past each branch: 300 000 points
+// 102 us instead of 78); a test four sizes ahead that skips the comparisons costs more than it
+// saves (90 us), and so does fetching the next interval before it is entered (89 us).
+template <bool FULL>
+__device__ __forceinline__ double chain_block_sum(const ChainCtx &C, u64 b, u64 m, int terms)
+{
+    const double md = (double)m;
+    const double z0[1] = {(double)((b * SUM_BLOCK + 1) * m)};
+    int iz[1];
+    chain_locate<1>(C.X, C.n, z0, iz);
+    int i = iz[0];
+    double d = z0[0] - C.X[i], w = C.W[i];
+    f64x2 ys = C.YS[i];
+    double run = 0.0;
+    auto step = [&](bool use) {
+        const double g = run + __builtin_fma(ys.y, d, ys.x);
+        run = FULL || use ? g : run;
+        d += md;
+        asm volatile("" : "+v"(run), "+v"(d));
+    };
+    auto cross = [&] {
+        if (d >= w) {
+            d -= w;
+            ++i;
+            w = C.W[i];
+            ys = C.YS[i];
+            if (d >= w) {                         // several intervals on
+                double yi, si;
+                chain_skip_ahead(C, i, d, w, yi, si);
+                ys.x = yi;
+                ys.y = si;
+            }
+        }
+    };
+    if (FULL) {
+#pragma unroll 1
+        for (int k = 0; k < SUM_BLOCK; k += 8) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                cross();
+                step(true);
+            }
+        }
+    } else {
+        for (int k = 0; __ballot(k < terms) != 0; ++k) {
+            if (k < terms)
+                cross();
+            step(k < terms);
+        }
+    }
+    return run;
+}
+
+// Table 2, chain row (and its Gather twin) at n independent points: fma(P-1, L, sum_{j<P} g(j m)).
+// A sum is blocks of SUM_BLOCK terms that do not depend on one another, and points ask for very
+// different numbers of them: a workgroup takes as many points as it has threads, sorts them by
+// the number of complete blocks, and deals (block index, point) pairs to the lanes, equal block
+// indices side by side (they cross about as many intervals of the table per term).  Block totals
+// go to LDS, EVAL_LEVELS block indices at a time; the thread of a point adds its totals in
+// ascending order, then the incomplete block it walks itself.  Bound by the fp64 and scalar
+// instructions of the walk (about 60 cycles per 64 terms, half of them for lanes that enter their
+// next interval); the incomplete blocks are 11 of the 78 us that 300 000 points with P up to 1024
+// take on a table of 64 samples (555 us with a thread that walks its point alone and searches the
+// table per term).  Four or sixteen block indices at a time, or 512 points, are no faster.
+constexpr int EVAL_LEVELS = 8;
+constexpr int EVAL_BIG_THREADS = 384;    // the largest multiple of 64 whose totals fit beside 4096 samples
+
+__global__ void __launch_bounds__(EVAL_BIG_THREADS) k_eval_chain(DeviceTables T, int t, const u64 *dm, const uint32_t *dP,
+                                                     size_t n, double *out)
+{
+    extern __shared__ __align__(16) double eval_lds[];
+    __shared__ unsigned above[EVAL_LEVELS + 2], slot[EVAL_LEVELS + 1], most;
+    const int threads = (int)blockDim.x, tid = (int)threadIdx.x;
+    double *tot = eval_lds;                                        // [EVAL_LEVELS][threads]
+    u64 *m_of = reinterpret_cast<u64 *>(tot + (size_t)EVAL_LEVELS * threads);
+    unsigned short *order = reinterpret_cast<unsigned short *>(m_of + threads);
+    ChainCtx C;
+    stage_intervals(C, reinterpret_cast<double *>(order + threads), T, t);
+    const size_t i = (size_t)blockIdx.x * threads + tid;
+    const u64 m = i < n ? dm[i] : 0;
+    const uint32_t P = i < n ? dP[i] : 0;
+    const u64 lim = 1ull << 53;
+    const bool ok = m > 0 && m < lim && P >= 2 && (u64)(P - 1) <= (lim - 1) / m;
+    const uint32_t full = ok ? (P - 1u) / SUM_BLOCK : 0u;
+    const int tail = ok ? (int)((P - 1u) % SUM_BLOCK) : 0;
+    m_of[tid] = ok ? m : 1;
+    if (tid == 0)
+        most = 0u;
+    __syncthreads();
+    atomicMax(&most, full);
+    __syncthreads();
+    const uint32_t levels = most;
+    double done = 0.0;
+    for (uint32_t b0 = 0; b0 < levels; b0 += EVAL_LEVELS) {
+        // complete blocks of this point among b0 .. b0 + EVAL_LEVELS - 1
+        const int mine = full <= b0 ? 0 : (full - b0 < EVAL_LEVELS ? (int)(full - b0) : EVAL_LEVELS);
+        if (tid <= EVAL_LEVELS)
+            slot[tid] = 0u;
+        __syncthreads();
+        const unsigned rank = atomicAdd(&slot[mine], 1u);          // among the points with as many
+        __syncthreads();
+        if (tid == 0) {                                            // above[k]: points with k or more
+            unsigned acc = 0;
+            above[EVAL_LEVELS + 1] = 0u;
+            for (int k = EVAL_LEVELS; k >= 0; --k) {
+                acc += slot[k];
+                above[k] = acc;
+            }
+        }
+        __syncthreads();
+        order[above[mine + 1] + rank] = (unsigned short)tid;       // most blocks first
+        __syncthreads();
+        // level k's pairs are the first above[k + 1] points of that order
+        unsigned total = 0;
+#pragma unroll
+        for (int k = 0; k < EVAL_LEVELS; ++k)
+            total += above[k + 1];
+        for (unsigned e0 = (unsigned)tid & ~63u; e0 < total; e0 += (unsigned)threads) {
+            unsigned r = e0 + ((unsigned)tid & 63u);
+            const bool real = r < total;
+            r = real ? r : total - 1u;
+            int k = 0;
+#pragma unroll
+            for (int u = 0; u < EVAL_LEVELS - 1; ++u) {
+                const unsigned c = above[u + 1];
+                if (k == u && r >= c) {
+                    r -= c;
+                    k = u + 1;
+                }
+            }
+            const int p = order[r];
+            const double v = chain_block_sum<true>(C, (u64)b0 + k, m_of[p], SUM_BLOCK);
+            if (real)
+                tot[(size_t)k * threads + p] = v;
+        }
+        __syncthreads();
+        for (int k = 0; k < mine; ++k)
+            done = done + tot[(size_t)k * threads + tid];
+    }
+    const double rest = chain_block_sum<false>(C, full, m_of[tid], tail);
+    if (i < n)
+        out[i] = ok ? __builtin_fma((double)(P - 1u), T.L[t], done + rest) : NAN;
+}
+
+static size_t eval_chain_lds(int n, int threads)
+{
+    return ((size_t)EVAL_LEVELS * threads + threads + threads / 4 + 4 * (size_t)n + CHAIN_PAD) * sizeof(double);
 }
 
 // The Scatter-chain sums of one (table, distinct m) in one workgroup, for tables of few
@@ -3832,7 +3973,7 @@ __global__ void __launch_bounds__(256) k_more_planes(DeviceTables T, DeviceGrid 
 
 static const size_t kMaxTableLds = (size_t)3 * 4096 * sizeof(double) + 96 +
                                    (size_t)2 * SWEEP_M_MAX_S * sizeof(double);   // + g(s), 1/s in k_terms
-static const size_t kMaxChainLds = (size_t)4 * 4096 * sizeof(double) + 112;   // + interval widths
+static const size_t kMaxChainLds = ((size_t)4 * 4096 + CHAIN_PAD) * sizeof(double);   // + interval widths
 
 static DeviceInfo g_device = {256, (size_t)160 * 1024};
 
@@ -3857,6 +3998,9 @@ hipError_t kernels_init()
     if (e != hipSuccess) return e;
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_eval),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxTableLds);
+    if (e != hipSuccess) return e;
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_eval_chain), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)eval_chain_lds(4096, EVAL_BIG_THREADS));
     if (e != hipSuccess) return e;
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_terms),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxTableLds);
@@ -3916,6 +4060,14 @@ hipError_t launch_eval(const DeviceTables &T, int table, int strategy, const uin
 {
     if (n == 0) return hipSuccess;
     if ((n + 255) / 256 > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    if (strategy == 11 || strategy == 14) {
+        // a big table leaves room for one workgroup per compute unit: a large one then
+        const int threads = T.n > 512 ? EVAL_BIG_THREADS : 256;
+        hipLaunchKernelGGL(k_eval_chain, dim3((unsigned)((n + threads - 1) / threads)), dim3(threads),
+                           eval_chain_lds(T.n, threads), st, T, table, reinterpret_cast<const u64 *>(d_m), d_P, n,
+                           d_out);
+        return hipGetLastError();
+    }
     const size_t lds = (size_t)3 * T.n * sizeof(double);
     const unsigned blocks = (unsigned)((n + 255) / 256);
     hipLaunchKernelGGL(k_eval, dim3(blocks), dim3(256), lds, st, T, table, strategy,
@@ -4115,7 +4267,7 @@ bool plan_tune(const DeviceTables &T, const DeviceGrid &G, bool terms_only, Tune
     p.chain = chain;
     // a big table fills most of the LDS of a CU: one large workgroup per CU then, which
     // stays for its whole share of the work (the table is staged once)
-    p.chain_lds = (size_t)4 * T.n * D + 112;
+    p.chain_lds = ((size_t)4 * T.n + CHAIN_PAD) * D;
     const bool big = p.chain_lds > 32768;
     // few samples, few blocks, enough distinct sizes: a workgroup per (table, m) forms all
     // its sums, the prefix over the blocks included

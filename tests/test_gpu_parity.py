@@ -599,3 +599,47 @@ def test_random_batches(seed):
         seed, sizes.shape[1], n_tables, n_m, len(P), int(P[-1]), len(s), mask)
     print(what, flush=True)
     assert_tables_equal(gpu_tune(wl), want, what)
+
+
+# ------------------------------------------------------------------ the chain row at scattered points
+
+@pytest.mark.parametrize("n_x,n_points,p_top", [
+    (2, 1, 66), (64, 255, 1026), (64, 256, 513), (64, 257, 577), (200, 1000, 129), (512, 300, 2000),
+    (513, 385, 1500), (4096, 700, 1100), (64, 130, 70000),
+])
+def test_chain_row_at_points_around_block_ends(n_x, n_points, p_top):
+    # complete blocks are dealt eight block indices at a time and the rest of a sum is walked by
+    # the point's own thread: process counts at and next to the ends of blocks and of eight of
+    # them, workgroups with one point, a full one and one more, both sizes of workgroup (tables
+    # of up to 512 samples and larger ones), points outside the domain among the others
+    torch = torch_cuda()
+    plogp = _plogp()
+    rng = np.random.default_rng(n_x + n_points)
+    x = np.unique(np.floor(2.0 ** rng.uniform(0, 20, 6 * n_x)))
+    x = np.append(x, x[-1] + 1.0 + np.arange(max(0, n_x - len(x))))[:n_x]
+    y = np.abs(30.0 + 0.1 * x * (1.0 + 0.3 * rng.standard_normal(len(x))))
+    edges = np.array([2, 3, 63, 64, 65, 66, 128, 129, 130, 512, 513, 514, 576, 577, 578, 1025])
+    P = np.where(rng.random(n_points) < 0.5, rng.choice(edges[edges <= p_top], n_points),
+                 rng.integers(2, p_top + 1, n_points)).astype(np.uint32)
+    P[-1] = p_top
+    m = np.maximum(np.floor(2.0 ** rng.uniform(0, 22, n_points)), 1.0).astype(np.uint64)
+    if n_points > 100:
+        P[5], m[6], m[7] = 1, 0, 1 << 53
+        P[8], m[8] = 64, ((1 << 53) - 1) // 63                  # the largest size allowed
+        P[9], m[9] = 65, ((1 << 53) - 1) // 63                  # and one process too many
+    tab = plogp.plogp_load_table(x, y, 7.5)
+    out = torch.empty(n_points, dtype=torch.float64, device="cuda")
+    dm, dP = _dev(m, np.uint64), _dev(P, np.uint32)
+    for sid in (11, 14):
+        plogp.plogp_eval_strategy(tab, 0, sid, dm.data_ptr(), dP.data_ptr(), 0, n_points, out.data_ptr(),
+                                  stream_handle())
+        torch.cuda.synchronize()
+        got = out.cpu().numpy()
+        bad = (P < 2) | (m == 0) | (m >= (1 << 53))
+        bad |= (P.astype(object) - 1) * m.astype(object) >= (1 << 53)
+        bad = bad.astype(bool)
+        assert np.isnan(got[bad]).all() and (n_points <= 100 or bad.sum() == 4)
+        want = np.array([oracle.eval_strategy(x, y, 7.5, sid, int(mv), int(pv), 0)
+                         for mv, pv in zip(m[~bad], P[~bad])])
+        assert (got[~bad].view(np.uint64) == want.view(np.uint64)).all(), "row %d" % sid
+    tab.free()
