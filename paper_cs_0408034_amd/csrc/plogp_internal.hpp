@@ -134,7 +134,7 @@ struct ScratchLayout {
     size_t total;                  // bytes of the block
 };
 
-enum TunePath : int { TUNE_TABLE_LANES = 0, TUNE_ROW = 1, TUNE_FUSED = 2, TUNE_STAGED = 3 };
+enum TunePath : int { TUNE_TABLE_LANES = 0, TUNE_ROW = 1, TUNE_TILE = 2, TUNE_STAGED = 3 };
 
 // Everything the host decides about one tune call before the first launch: the path, every
 // launch shape, and the scratch each kernel of that path reads or writes (one source for the
@@ -149,8 +149,9 @@ struct TunePlan {
     // whole-row path
     int row_two;
     size_t row_lds;
-    // lane-per-m batch path
-    int fused_mchunks;
+    // tile path (a table and tile_m message sizes per workgroup)
+    int tile_m, n_tiles;
+    size_t tile_lds;
     // staged path
     int lanes_s, lanes_p, pairs, terms_mode, n_chunks, n_mchunks, terms_wg;
     int chain, chain_row, together, row_together, terms_in_chain, chain_threads;

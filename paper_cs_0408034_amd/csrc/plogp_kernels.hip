@@ -1349,6 +1349,15 @@ __device__ __forceinline__ Best decide_scatter(uint32_t mask, double q, double c
     return b;
 }
 
+// Barrier: a one-byte fan-in and fan-out, flat or binomial (bits 3 and 4 of `extra`).
+__device__ __forceinline__ Best decide_barrier(uint32_t extra, double q, double fl, double cl, double L, double g1)
+{
+    Best b = {INFINITY, 0u, 0xFFFFFFFFu};
+    if (extra & 8u) consider(b, 2.0 * __builtin_fma(q, g1, L), 16, 0);
+    if (extra & 16u) consider(b, 2.0 * __builtin_fma(fl, g1, cl * L), 17, 0);
+    return b;
+}
+
 // sum_{j=1}^{P-1} g(j m) for (m index mi, P index pi) from the block sums
 __device__ __forceinline__ double chain_sum_of(const DeviceGrid &G, const Scratch &S, int t, int mi,
                                                int pi, uint32_t P)
@@ -2259,265 +2268,476 @@ k_sweep_s(DeviceTables T, DeviceGrid G, Scratch S, plogp_cell_dev *out, int n_pt
         store_cell(o, decide_scatter(mask, qv, (double)cli, gm, L, s11, s12));
 }
 
-// ---- whole path in one kernel, for batches of many tables -----------------
+// ---- whole path of a tile of message sizes of one table in one workgroup -------
 //
-// One workgroup per (table, 256 message sizes), one lane per m, everything of
-// that (table, m) row in the lane: g(m), the segment terms, the Scatter-chain sum walked along j while P ascends (the sum
-// for a P is ready exactly when its cells are written), the binomial sum grown
-// term by term with ceil(log2 P).  P and s are wave-uniform loops; P goes in
-// chunks of FUSED_PC so that A and B are formed once per (m, s, chunk).  The
-// cells of a chunk are transposed through LDS so that a store instruction writes
-// 64-byte runs instead of 64 separate records.  No scratch in global memory:
-// the only HBM traffic is the tables in and the decision table out.  Used when
-// there are enough (table, m) rows to fill the chip, at most FUSED_NS candidates
-// and few blocks of the chain sum.
-constexpr int FUSED_NS = 24;
-constexpr int FUSED_PC = 4;
+// Batches of tables that do not share their sample sizes (or are too few for lanes over
+// tables).  A workgroup takes one table and up to TILE_MAX_M message sizes and does every step
+// for them with LDS between the steps: the table as intervals; the candidates; the terms of
+// every (m, s); the Scatter-chain sums; then the cells, lanes over (m, P) in the order of the
+// output, so that a wave stores whole cache lines.
+//
+// The chain sums are most of the work.  Their items are (block of SUM_BLOCK terms, m); within a
+// block most items stay inside one interval of the table or enter one other, and only the first
+// blocks cross many.  A wave that mixes the kinds pays for the worst: some lane enters an
+// interval at almost every term, and the branch, its LDS reads and the scalar bookkeeping cost
+// more than the terms.  So every item is first placed (one search) and put on the list of its
+// kind: no crossing (three fp64 instructions per term), one crossing at a term known beforehand
+// (the two intervals sit in registers, the change is six selects on an integer compare, no
+// branch), more (a search per term, eight side by side, over the few intervals in question).
+//
+// 333 tables of 57 samples x 203 sizes x 37 process counts up to 1500, 19 candidates, 80 MB of
+// cells: 79 us (a lane per message size that walks its whole row alone took 175; 10 000 rows x
+// 1000 process counts 2500 us, now the row path's 82).  Bound by instruction issue: 5000 per wave,
+// half of them for the chain sums (search 28 %, one crossing 12 %, none 8 %), 18 % for the cells.
+// Tried: lists for two and three crossings as well, and the searched terms spread over all
+// threads through LDS (94 us: more lists, more waves with idle lanes).
+constexpr int TILE_THREADS = 256;
+constexpr int TILE_MAX_M = TILE_THREADS / 8;
+constexpr int TILE_NS = 24;              // candidates at most
+constexpr int TILE_MAX_BLK = 32;         // blocks of the chain sum at most
+constexpr size_t TILE_STATIC_LDS = 256;  // room for the counters
+constexpr long TILE_MIN_ROWS = 12;       // (table, m) rows per compute unit at least
 
-// X[0] = 0 (virtual interval below the first sample, gap y_0, slope 0),
-// X[1..n] = samples, X[n+1] = X[n+2] = +inf; YS[i] = {gap, slope} of interval i.
-__device__ __forceinline__ int lds_interval(const double *X, int n, double z)
-{
-    return last_not_above(X + 1, n, z) + (z >= X[1] ? 1 : 0);
-}
-
-__device__ __forceinline__ double lds_gap(const double *X, const double2 *YS, int n, double z)
-{
-    const int i = lds_interval(X, n, z);
-    const double2 ys = YS[i];
-    return __builtin_fma(ys.y, z - X[i], ys.x);
-}
-
-__global__ void __launch_bounds__(256) k_fused(DeviceTables T, DeviceGrid G, plogp_cell_dev *out,
-                                               int n_mchunks)
-{
-    extern __shared__ __align__(16) double fused_lds[];
-    __shared__ double sS[FUSED_NS], sG[FUSED_NS], sR[FUSED_NS];
-    __shared__ double sG1;
-    // per wave and plane: 64 rows x FUSED_PC cells, rows padded by one cell
-    __shared__ uint4 stage[4][2][64 * (FUSED_PC + 1)];
-
-    const int t = blockIdx.x / n_mchunks, mc = blockIdx.x % n_mchunks;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int n = T.n;
-    double2 *YS = reinterpret_cast<double2 *>(fused_lds);      // n + 2 entries
-    double *X = fused_lds + 2 * (n + 2);                       // n + 3 entries
-    const double L = T.L[t];
+// Where the arrays of a workgroup start in LDS, in 8-byte slots.  The lists of the chain items lie
+// where A and B of every (m, s) go afterwards.
+struct TileLds {
+    int ab, list, c, gs, rcp, gm, amin, md, sum2, tot, part, mask, sv, sp, off, slots;
+    int nsp;             // candidates, padded to a multiple of four
+    __host__ __device__ TileLds(int n, int n_s, int n_P, int n_blk, int cl_max, int M)
     {
-        const double *gx = T.x + (size_t)t * n, *gy = T.y + (size_t)t * n;
-        for (int i = threadIdx.x; i < n; i += blockDim.x) {
-            X[i + 1] = gx[i];
-            YS[i + 1] = make_double2(gy[i], interval_slope(gx, gy, n, i));
-        }
-        if (threadIdx.x == 0) {
-            X[0] = 0.0;
-            X[n + 1] = INFINITY;
-            X[n + 2] = INFINITY;
-            YS[0] = make_double2(gy[0], 0.0);
-            YS[n + 1] = make_double2(0.0, 0.0);
-        }
+        nsp = (n_s + 3) & ~3;
+        int at = 4 * n + (int)CHAIN_PAD;
+        ab = list = at;
+        const int after = list + M * n_blk;
+        at += 2 * M * nsp;
+        at = at > after ? at : after;
+        c = at; at += nsp;
+        gs = at; at += nsp;
+        rcp = at; at += nsp;
+        gm = at; at += M;
+        amin = at; at += M;
+        md = at; at += M;
+        sum2 = at; at += M * (cl_max + 1);
+        tot = at; at += M * n_blk;
+        part = at; at += M * n_P;
+        mask = at; at += n_blk;
+        sv = at; at += (nsp + 1) / 2;
+        sp = at; at += (n_P + 1) / 2;
+        off = at; at += (n_blk + 1) / 2;
+        slots = at;
     }
-    __syncthreads();
-    if ((int)threadIdx.x < G.n_s) {
-        const double sd = (double)G.s[threadIdx.x];
-        const double g = lds_gap(X, YS, n, sd);
-        sS[threadIdx.x] = sd;
-        sG[threadIdx.x] = g;
-        sR[threadIdx.x] = 1.0 / sd;
+};
+
+// An item of the chain sums on a list: size within the tile, block, interval of its first term.
+__device__ __forceinline__ unsigned tile_item(int ml, int b, int i)
+{
+    return (unsigned)ml | (unsigned)b << 5 | (unsigned)i << 10;
+}
+
+// The points of the blocks in this wave at which some lane's running sum is wanted (bit r: after
+// r terms).  The lanes hold few different blocks b, and `wanted` depends on the block alone.
+__device__ __forceinline__ u64 tile_any_wanted(int b, u64 wanted)
+{
+    u64 any = 0;
+    for (u64 todo = __ballot(1); todo != 0;) {
+        const int l = __builtin_ctzll(todo);
+        const int bl = __builtin_amdgcn_readlane(b, l);
+        any |= (u64)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)wanted, l) |
+               (u64)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(wanted >> 32), l) << 32;
+        todo &= ~__ballot(b == bl);
     }
-    if (threadIdx.x == 0)
-        sG1 = lds_gap(X, YS, n, 1.0);
-    __syncthreads();
+    return any;
+}
 
-    const int mi = mc * blockDim.x + threadIdx.x;
-    const bool active = mi < G.n_m;
-    const u64 m = G.m[active ? mi : 0];
-    const double md = (double)m;
-    const u64 lim = active ? (m < G.s_cap ? m : G.s_cap) : 0;
-    const double limd = (double)lim;       // exact: at most m < 2^53 (0 for an idle lane)
-    const uint32_t mask = G.mask;
-    const double g1 = sG1;
-    const double gm = lds_gap(X, YS, n, md);
-
-    // candidates that compete for some lane of the wave (they ascend), and the
-    // minimum over s of A = g(s) k for this m (rows 2 and 9 are monotone in A)
-    int wave_nv = 0;
-    double amin = INFINITY;
-    for (int si = 0; si < G.n_s; ++si) {
-        const double sd = sS[si];
-        const bool valid = sd <= limd;
-        if (__ballot(valid) == 0)
+// One item per lane whose terms stay in their interval (ONE: enter the next one).  `real` lanes store.
+template <bool ONE>
+__device__ __forceinline__ void tile_walk(const ChainCtx &C, unsigned item, bool real, const double *m_of, int M,
+                                          const u64 *blk_mask, const int *blk_off, int n_P, double *part, double *tot)
+{
+    const int ml = (int)(item & 31u), b = (int)((item >> 5) & 31u), i = (int)(item >> 10);
+    const double md = m_of[ml];
+    const double z0 = (double)(b * SUM_BLOCK + 1) * md;                      // exact: an integer below 2^53
+    double d = z0 - C.X[i], md_enter = 0.0;
+    f64x2 ys = C.YS[i], ys_next = ys;
+    int enters = 0;
+    if (ONE) {
+        // the first term in the next interval (the rounded quotient of two integers below 2^53
+        // does not reach an integer it is not equal to), and the way there
+        const double start = C.X[i + 1];
+        enters = (int)ceil((start - z0) / md);
+        md_enter = md - (start - C.X[i]);
+        ys_next = C.YS[i + 1];
+    }
+    const u64 wanted = real ? blk_mask[b] : 0ull;
+    double *out = part + ml * n_P + blk_off[b];
+    u64 any = tile_any_wanted(b, wanted);
+    double run = 0.0;
+    auto step = [&](int k) {
+        run = run + __builtin_fma(ys.y, d, ys.x);
+        if (ONE) {
+            const bool now = enters == k + 1;
+            d += now ? md_enter : md;
+            ys.x = now ? ys_next.x : ys.x;
+            ys.y = now ? ys_next.y : ys.y;
+        } else {
+            d += md;
+        }
+    };
+    int k = 0;
+    for (;;) {
+        const int hit = any != 0 ? __builtin_ctzll(any) : SUM_BLOCK;
+#pragma unroll 1
+        for (; k + 8 <= hit; k += 8) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                step(k + u);
+        }
+#pragma unroll 1
+        for (; k < hit; ++k)
+            step(k);
+        if (hit == SUM_BLOCK)
             break;
-        wave_nv = si + 1;
-        if (valid && (mask & 0x204u)) {
-            double A, B, C;
-            segment_terms(md, sd, sR[si], sG[si], L, A, B, C);
-            amin = min_f64(amin, A);
+        if ((wanted >> hit) & 1ull)
+            *out++ = run;
+        any &= any - 1;
+    }
+    if (real)
+        tot[b * M + ml] = run;
+}
+
+// One item per lane whose terms enter several intervals: every term gets a search of its own,
+// eight side by side, over the intervals between those of the first and the last term.
+__device__ __forceinline__ void tile_search(const ChainCtx &C, unsigned item, bool real, const double *m_of, int M,
+                                            const u64 *blk_mask, const int *blk_off, int n_P, double *part,
+                                            double *tot)
+{
+    constexpr int V = 8;
+    const int ml = (int)(item & 31u), b = (int)((item >> 5) & 31u), i0 = (int)(item >> 10);
+    const double md = m_of[ml];
+    double zb = (double)(b * SUM_BLOCK + 1) * md;
+    int reach = 1;                             // a power of two: the last term lies below interval i0 + reach
+    {
+        const double last[1] = {__builtin_fma((double)(SUM_BLOCK - 1), md, zb)};
+        int il[1];
+        chain_locate<1>(C.X, C.n, last, il);
+        while (__ballot(il[0] - i0 >= reach) != 0)
+            reach <<= 1;
+    }
+    const u64 wanted = real ? blk_mask[b] : 0ull;
+    double *out = part + ml * n_P + blk_off[b];
+    const u64 any = tile_any_wanted(b, wanted);
+    double run = 0.0;
+#pragma unroll 1
+    for (int k = 0; k < SUM_BLOCK; k += V) {
+        double z[V];
+        int i[V];
+#pragma unroll
+        for (int c = 0; c < V; ++c) {
+            z[c] = __builtin_fma((double)c, md, zb);
+            i[c] = i0;
+        }
+        for (int half = reach >> 1; half > 0; half >>= 1) {
+            double x[V];
+#pragma unroll
+            for (int c = 0; c < V; ++c) {
+                const int at = i[c] + half;
+                x[c] = C.X[at < C.n + 1 ? at : C.n + 1];       // +inf past the last interval
+            }
+#pragma unroll
+            for (int c = 0; c < V; ++c)
+                i[c] = x[c] <= z[c] ? i[c] + half : i[c];
+        }
+        double g[V];
+#pragma unroll
+        for (int c = 0; c < V; ++c) {
+            const f64x2 ys = C.YS[i[c]];
+            g[c] = __builtin_fma(ys.y, z[c] - C.X[i[c]], ys.x);
+        }
+        if (((any >> k) & 0xFFull) != 0) {
+#pragma unroll
+            for (int c = 0; c < V; ++c) {
+                if ((wanted >> (k + c)) & 1ull)
+                    *out++ = run;
+                run = run + g[c];
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < V; ++c)
+                run = run + g[c];
+        }
+        zb = __builtin_fma((double)V, md, zb);
+    }
+    if (real)
+        tot[b * M + ml] = run;
+}
+
+__global__ void __launch_bounds__(TILE_THREADS) k_tile(DeviceTables T, DeviceGrid G, plogp_cell_dev *out, int n_tiles,
+                                                       int M)
+{
+    // (a name of its own: under a name that another kernel declares without it the alignment is lost,
+    // and 16-byte reads of misaligned LDS take twice the kernel's time)
+    extern __shared__ __align__(16) double tile_lds[];
+    __shared__ unsigned count[3], next_wave, nv_tile;
+    __shared__ double sh_g1;
+    const int n_s = G.n_s, n_P = G.n_P, n_blk = G.n_blk, cl_max = G.cl_max;
+    const TileLds A(T.n, n_s, n_P, n_blk, cl_max, M);
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int t = (int)blockIdx.x / n_tiles, m0 = (int)blockIdx.x % n_tiles * M;
+    const int n_m = G.n_m - m0 < M ? G.n_m - m0 : M;           // sizes of this tile
+    const uint32_t mask = G.mask, extra = G.extra;
+    const bool chain = (G.need & (1u << 11)) != 0, binom = (G.need & (1u << 12)) != 0;
+    f64x2 *sAB = reinterpret_cast<f64x2 *>(tile_lds + A.ab);
+    double *sC = tile_lds + A.c, *sG = tile_lds + A.gs, *sR = tile_lds + A.rcp, *sGm = tile_lds + A.gm, *sM = tile_lds + A.md;
+    double *sAmin = tile_lds + A.amin;
+    double *sum2 = tile_lds + A.sum2, *tot = tile_lds + A.tot, *part = tile_lds + A.part;
+    u64 *sMask = reinterpret_cast<u64 *>(tile_lds + A.mask);
+    unsigned *list = reinterpret_cast<unsigned *>(tile_lds + A.list);
+    uint32_t *sSv = reinterpret_cast<uint32_t *>(tile_lds + A.sv), *sP = reinterpret_cast<uint32_t *>(tile_lds + A.sp);
+    int *sOff = reinterpret_cast<int *>(tile_lds + A.off);
+    const double L = T.L[t];
+    ChainCtx C;
+    stage_intervals(C, tile_lds, T, t);
+    for (int p = tid; p < n_P; p += TILE_THREADS)
+        sP[p] = G.P[p];
+    for (int b = tid; b < n_blk; b += TILE_THREADS) {
+        sMask[b] = G.blk_mask[b];
+        sOff[b] = G.blk_off[b];
+    }
+    if (tid < n_m)
+        sM[tid] = (double)G.m[m0 + tid];
+    if (tid < 3)
+        count[tid] = 0u;
+    if (tid == 64)
+        next_wave = 0u;
+    if (tid == 65)
+        nv_tile = 0u;
+    __syncthreads();
+
+    // what needs the table only: g(s), g(m), g(1), the terms g(2^j m), the places of the chain items
+    auto gap = [&](double z) {
+        const double zz[1] = {z};
+        int i[1];
+        chain_locate<1>(C.X, C.n, zz, i);
+        const f64x2 ys = C.YS[i[0]];
+        return __builtin_fma(ys.y, z - C.X[i[0]], ys.x);
+    };
+    if (tid < A.nsp) {
+        const bool there = tid < n_s;
+        const double sd = there ? (double)G.s[tid] : 1.0;
+        const double gs = there ? gap(sd) : 0.0;
+        sG[tid] = gs;
+        sR[tid] = 1.0 / sd;
+        sC[tid] = gs + L;
+        sSv[tid] = there ? (uint32_t)sd : 0u;
+    }
+    if (tid >= 64 && tid < 64 + n_m)
+        sGm[tid - 64] = gap(sM[tid - 64]);
+    if (tid == 128)
+        sh_g1 = gap(1.0);
+    if (binom)
+        for (int ml = tid >> 3; ml < n_m; ml += TILE_THREADS / 8)
+            for (int j = tid & 7; j < cl_max; j += 8)
+                sum2[ml * (cl_max + 1) + j + 1] = gap(sM[ml] * (double)(1ull << j));  // exact: below 2^53
+    const int n_items = chain ? n_m * n_blk : 0;
+    {
+        const int step_b = TILE_THREADS / n_m, step_m = TILE_THREADS % n_m;
+        int b = tid / n_m, ml = tid % n_m;     // the next item of this thread: b n_m + ml
+        for (int e0 = wave * 64; e0 < n_items; e0 += 2 * TILE_THREADS) {       // two searches side by side
+            double z[2], md[2];
+            int i[2], bb[2], mm[2];
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                bb[c] = b;
+                mm[c] = ml;
+                md[c] = sM[ml];
+                z[c] = (double)(b * SUM_BLOCK + 1) * md[c];
+                b += step_b;
+                ml += step_m;
+                if (ml >= n_m) {
+                    ml -= n_m;
+                    ++b;
+                }
+            }
+            chain_locate<2>(C.X, C.n, z, i);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const double last = __builtin_fma((double)(SUM_BLOCK - 1), md[c], z[c]);
+                int kind = last < C.X[i[c] + 1] ? 0 : (last < C.X[i[c] + 2] ? 1 : 2);
+                kind = bb[c] < n_blk ? kind : 3;
+                const unsigned v = tile_item(mm[c], bb[c], i[c]);
+#pragma unroll
+                for (int h = 0; h < 3; ++h) {
+                    const u64 who = __ballot(kind == h);
+                    if (who == 0)
+                        continue;
+                    unsigned at = 0;
+                    if (lane == 0)
+                        at = atomicAdd(&count[h], (unsigned)__builtin_popcountll(who));
+                    at = __builtin_amdgcn_readfirstlane(at);
+                    at = __builtin_amdgcn_mbcnt_hi((unsigned)(who >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)who, at));
+                    if (kind == h)             // two lists from the front of an array, one from the back
+                        list[h == 0 ? (int)at : (h == 1 ? n_items - 1 - (int)at : n_items + (int)at)] = v;
+                }
+            }
         }
     }
+    __syncthreads();
 
-    // Scatter-chain walk.  Current interval: d = z - start, w = width, {yi, sl};
-    // the next interval's end and {gap, slope} are fetched one crossing ahead.
-    int iv = lds_interval(X, n, md);
-    double xb = X[iv + 1];
-    double d = md - X[iv], w = xb - X[iv];
-    double yi = YS[iv].x, sl = YS[iv].y;
-    double nxb = X[iv + 2];
-    double2 nys = YS[iv + 1];
-    double run = 0.0, done = 0.0;
-    int j_done = 0;
-    double s12 = 0.0;                      // Scatter-binomial sum, grown with ceil(log2 P)
-    int cl_done = 0;
+    // the prefix of g(2^j m)
+    if (binom && tid >= TILE_THREADS - 64 && tid - (TILE_THREADS - 64) < n_m) {
+        double *p = sum2 + (tid - (TILE_THREADS - 64)) * (cl_max + 1), acc = 0.0;
+        p[0] = 0.0;
+        for (int j = 1; j <= cl_max; ++j) {
+            acc = acc + p[j];
+            p[j] = acc;
+        }
+    }
+    if (chain) {
+        // 64 items of a kind at a time, the slowest kind first
+        const unsigned n0 = count[0], n1 = count[1], n2 = count[2];
+        const unsigned w2 = (n2 + 63) / 64, w1 = (n1 + 63) / 64, w0 = (n0 + 63) / 64;
+        for (;;) {
+            unsigned k = 0;
+            if (lane == 0)
+                k = atomicAdd(&next_wave, 1u);
+            k = __builtin_amdgcn_readfirstlane(k);
+            if (k >= w2 + w1 + w0)
+                break;
+            if (k < w2) {
+                const unsigned e = k * 64 + lane;
+                tile_search(C, list[n_items + (e < n2 ? e : n2 - 1)], e < n2, sM, M, sMask, sOff, n_P, part, tot);
+            } else if (k < w2 + w1) {
+                const unsigned e = (k - w2) * 64 + lane;
+                tile_walk<true>(C, list[n_items - 1 - (e < n1 ? e : n1 - 1)], e < n1, sM, M, sMask, sOff, n_P, part, tot);
+            } else {
+                const unsigned e = (k - w2 - w1) * 64 + lane;
+                tile_walk<false>(C, list[e < n0 ? e : n0 - 1], e < n0, sM, M, sMask, sOff, n_P, part, tot);
+            }
+        }
+        __syncthreads();
+        if (tid >= TILE_THREADS - 64 && tid - (TILE_THREADS - 64) < n_m) {     // the finished blocks, in ascending order
+            double *p = tot + (tid - (TILE_THREADS - 64)), acc = 0.0;
+            for (int b = 0; b < n_blk; ++b) {
+                const double v = p[b * M];
+                p[b * M] = acc;
+                acc = acc + v;
+            }
+        }
+    }
+    // the terms of every (m, s): eight threads per message size, TILE_MAX_M sizes at once
+    {
+        const int ml = tid >> 3;
+        double least = INFINITY;
+        int top = 0;
+        if (ml < n_m) {
+            const double md = sM[ml];
+            const double lim = (double)(G.s_cap < (1ull << 53) ? G.s_cap : (1ull << 53));
+            for (int si = tid & 7; si < A.nsp; si += 8) {
+                f64x2 ab = {INFINITY, INFINITY};
+                const double sd = (double)sSv[si];
+                if (si < n_s && sd <= md && sd <= lim) {
+                    double a, bb, cc;
+                    segment_terms(md, sd, sR[si], sG[si], L, a, bb, cc);
+                    ab.x = a;
+                    ab.y = bb;
+                    least = min_f64(least, a);
+                    top = si + 1;
+                }
+                sAB[ml * A.nsp + si] = ab;
+            }
+        }
+#pragma unroll
+        for (int x = 1; x < 8; x <<= 1) {
+            least = min_f64(least, __shfl_xor(least, x));
+            const int other = __shfl_xor(top, x);
+            top = other > top ? other : top;
+        }
+        if (ml < n_m && (tid & 7) == 0) {
+            sAmin[ml] = least;
+            atomicMax(&nv_tile, (unsigned)top);
+        }
+    }
+    __syncthreads();
 
-    const size_t plane = (size_t)G.n_m * G.n_P;
-    plogp_cell_dev *o_tab = out + (size_t)t * G.n_ops * plane;
-    const bool want_chain = (mask & (1u << 11)) != 0, want_binom = (mask & (1u << 12)) != 0;
+    // the cells, in the order of the output
+    const double g1 = sh_g1;
+    const int nv = (int)nv_tile;
+    const size_t plane = (size_t)G.n_m * n_P;
+    plogp_cell_dev *const o0 = out + (size_t)t * G.n_ops * plane + (size_t)m0 * n_P;
     const bool has_b = (mask & 0x3FFu) != 0, has_s = (mask & 0x1C00u) != 0;
-    const int row0 = mc * (int)blockDim.x + wave * 64;         // first m index of this wave
-
-    for (int p0 = 0; p0 < G.n_P; p0 += FUSED_PC) {
-        uint32_t Pv[FUSED_PC];
-        double s11v[FUSED_PC], s12v[FUSED_PC];
-#pragma unroll
-        for (int p = 0; p < FUSED_PC; ++p) {
-            const int pi = p0 + p < G.n_P ? p0 + p : G.n_P - 1;
-            const uint32_t P = G.P[pi];
-            Pv[p] = P;
-            if (want_chain) {
-                const int target = (int)(P - 1);
-                while (j_done < target) {
-                    const int block_end = (j_done / SUM_BLOCK + 1) * SUM_BLOCK;
-                    const int stop = target < block_end ? target : block_end;
-#pragma unroll 4
-                    for (; j_done < stop; ++j_done) {
-                        while (d >= w) {                       // crossed into the next interval
-                            d -= w;
-                            w = nxb - xb;
-                            yi = nys.x;
-                            sl = nys.y;
-                            xb = nxb;
-                            ++iv;
-                            nxb = X[iv + 2];
-                            nys = YS[iv + 1];
-                        }
-                        run = run + __builtin_fma(sl, d, yi);
-                        d += md;
-                    }
-                    if (j_done % SUM_BLOCK == 0) {
-                        done = done + run;
-                        run = 0.0;
-                    }
-                }
-            }
-            s11v[p] = done + run;
-            if (want_binom) {
-                const int cli = ceil_log2(P);
-                while (cl_done < cli) {
-                    s12 = s12 + lds_gap(X, YS, n, (double)(m << cl_done));
-                    ++cl_done;
-                }
-            }
-            s12v[p] = s12;
-        }
-
-        double q[FUSED_PC], fl[FUSED_PC], clL[FUSED_PC];
-        double b5[FUSED_PC];
-        int i5[FUSED_PC];
-#pragma unroll
-        for (int p = 0; p < FUSED_PC; ++p) {
-            q[p] = (double)(Pv[p] - 1);
-            fl[p] = (double)floor_log2(Pv[p]);
-            clL[p] = (double)ceil_log2(Pv[p]) * L;
-            b5[p] = INFINITY;
-            i5[p] = 0;
-        }
-        if (mask & (1u << 5)) {
-            for (int si = 0; si < wave_nv; ++si) {             // wave-uniform
-                const double sd = sS[si];
-                if (sd <= limd) {                              // this lane's m admits s
-                    double A, B, C;
-                    segment_terms(md, sd, sR[si], sG[si], L, A, B, C);
-#pragma unroll
-                    for (int p = 0; p < FUSED_PC; ++p) {
-                        const double T5 = __builtin_fma(q[p], C, B);
-                        i5[p] = T5 < b5[p] ? si : i5[p];
-                        b5[p] = min_f64(b5[p], T5);
-                    }
-                }
-            }
-        }
-        // the chunk's cells go to LDS as [row][cell], then out as 64-byte runs
+    const uint32_t gather = (extra & 7u) << 10;
+    const int dm = TILE_THREADS / n_P, dp = TILE_THREADS % n_P;
+    int ml = tid / n_P, pi = tid % n_P;
+    for (int e0 = tid - lane; e0 < n_m * n_P; e0 += TILE_THREADS) {
+        const bool active = ml < n_m;
+        const int mr = active ? ml : n_m - 1, pr = active ? pi : n_P - 1, e = mr * n_P + pr;
+        const uint32_t P = sP[pr];
+        const int cli = ceil_log2(P);
+        const double q = (double)(P - 1u), fl = (double)floor_log2(P), cl = (double)cli, gm = sGm[mr];
+        plogp_cell_dev *o = o0 + e;
         if (has_b) {
-            Best bc[FUSED_PC];
-            int want[FUSED_PC];
-            double V[FUSED_PC];
-            uint32_t found[FUSED_PC];
-            bool any = false;
+            const f64x2 *ab = sAB + mr * A.nsp;
+            const double clL = cl * L, amin = sAmin[mr];
+            double b5 = INFINITY;
+            int at5 = 0;
+            if (mask & 0x20u) {
+                // four candidates at a time; the four in which the minimum first appeared are
+                // remembered
+                for (int s0 = 0; s0 < nv; s0 += 4) {
+                    double cur = INFINITY;
 #pragma unroll
-            for (int p = 0; p < FUSED_PC; ++p) {
-                const double t2 = amin < INFINITY ? __builtin_fma(q[p], amin, L) : INFINITY;
-                const double t9 = amin < INFINITY ? __builtin_fma(fl[p], amin, clL[p]) : INFINITY;
-                const uint32_t s5 = b5[p] < INFINITY ? (uint32_t)sS[i5[p]] : 0u;
-                bc[p] = decide_bcast(mask, q[p], fl[p], (double)ceil_log2(Pv[p]), gm, L, g1, t2, 0u,
-                                     b5[p], s5, t9, 0u);
-                want[p] = (bc[p].id == 2u || bc[p].id == 9u) ? (int)bc[p].id : 0;
-                V[p] = bc[p].t;
-                found[p] = 0u;
-                any = any || want[p] != 0;
-            }
-            if (__ballot(any) != 0) {
-                first_s_of_flat_or_binomial<FUSED_PC>(
-                    wave_nv, limd, md, L, q, fl, clL, want, V, found,
-                    [&](int si, double &sd, double &rcp_s, double &g) {
-                        sd = sS[si];
-                        rcp_s = sR[si];
-                        g = sG[si];
-                    });
-#pragma unroll
-                for (int p = 0; p < FUSED_PC; ++p)
-                    if (want[p] != 0)
-                        bc[p].s = found[p];
-            }
-#pragma unroll
-            for (int p = 0; p < FUSED_PC; ++p) {
-                union { plogp_cell_dev c; uint4 v; } u;
-                u.c.time = bc[p].t; u.c.s = bc[p].s; u.c.strategy = bc[p].id;
-                stage[wave][0][lane * (FUSED_PC + 1) + p] = u.v;
-            }
-        }
-        if (has_s) {
-#pragma unroll
-            for (int p = 0; p < FUSED_PC; ++p) {
-                const Best r = decide_scatter(mask, q[p], (double)ceil_log2(Pv[p]), gm, L, s11v[p],
-                                              s12v[p]);
-                union { plogp_cell_dev c; uint4 v; } u;
-                u.c.time = r.t; u.c.s = r.s; u.c.strategy = r.id;
-                stage[wave][1][lane * (FUSED_PC + 1) + p] = u.v;
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        {
-            const int pl = lane % FUSED_PC;                    // cell within the run
-            const int pi = p0 + pl;
-#pragma unroll
-            for (int it = 0; it < FUSED_PC; ++it) {
-                const int row = it * (64 / FUSED_PC) + lane / FUSED_PC;
-                const int rmi = row0 + row;
-                if (rmi < G.n_m && pi < G.n_P) {
-                    plogp_cell_dev *o = o_tab + (size_t)rmi * G.n_P + pi;
-                    if (has_b) {
-                        stream_out(o, stage[wave][0][row * (FUSED_PC + 1) + pl]);
-                        o += plane;
-                    }
-                    if (has_s)
-                        stream_out(o, stage[wave][1][row * (FUSED_PC + 1) + pl]);
+                    for (int u = 0; u < 4; ++u)
+                        cur = min_f64(cur, __builtin_fma(q, sC[s0 + u], ab[s0 + u].y));
+                    at5 = cur < b5 ? s0 : at5;
+                    b5 = min_f64(b5, cur);
                 }
             }
+            const double t2 = amin < INFINITY ? __builtin_fma(q, amin, L) : INFINITY;
+            const double t9 = amin < INFINITY ? __builtin_fma(fl, amin, clL) : INFINITY;
+            Best bc = decide_bcast(mask, q, fl, cl, gm, L, g1, t2, 0u, b5, 0u, t9, 0u);
+            if (bc.id == 5u) {
+                int s_at = at5;
+#pragma unroll
+                for (int u = 3; u >= 0; --u)
+                    s_at = __builtin_fma(q, sC[at5 + u], ab[at5 + u].y) == b5 ? at5 + u : s_at;
+                bc.s = sSv[s_at];
+            } else if (bc.id == 2u || bc.id == 9u) {
+                // the first candidate whose value equals the minimum
+                const double mul = bc.id == 2u ? q : fl, add = bc.id == 2u ? L : clL;
+                int si = 0;
+                while (si < nv - 1 && __builtin_fma(mul, ab[si].x, add) != bc.t)
+                    ++si;
+                bc.s = sSv[si];
+            }
+            if (active)
+                store_cell(o, bc);
+            o += plane;
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+        const double s11 = chain ? tot[(int)((P - 1u) / SUM_BLOCK) * M + mr] + part[e] : 0.0;
+        const double s12 = binom ? sum2[mr * (cl_max + 1) + cli] : 0.0;
+        if (has_s) {
+            if (active)
+                store_cell(o, decide_scatter(mask, q, cl, gm, L, s11, s12));
+            o += plane;
+        }
+        if (gather) {                          // the rows of Table 2 under the ids of their Gather twins
+            Best b = decide_scatter(gather, q, cl, gm, L, s11, s12);
+            b.id += 3u;
+            if (active)
+                store_cell(o, b);
+            o += plane;
+        }
+        if (extra & 0x18u) {
+            const Best b = decide_barrier(extra, q, fl, cl, L, g1);
+            if (active)
+                store_cell(o, b);
+        }
+        ml += dm;
+        pi += dp;
+        if (pi >= n_P) {
+            pi -= n_P;
+            ++ml;
+        }
     }
 }
 
@@ -2538,6 +2758,7 @@ constexpr int ROW_MAX_BLK = 32;          // at most 2048 terms of the chain sum
 constexpr int ROW_NS = 64;               // candidates at most
 constexpr int ROW_SPAD = ROW_NS + 8;     // the candidate loops read up to 7 entries past the last
 constexpr int ROW_MAX_N = 512;           // samples at most (LDS per workgroup stays small)
+constexpr long ROW_MAX_ROWS = 32;        // fewer than 512 process counts: (table, m) rows per compute unit
 
 static size_t row_lds_bytes(int n, int n_blk, int n_P)
 {
@@ -3959,11 +4180,7 @@ __global__ void __launch_bounds__(256) k_more_planes(DeviceTables T, DeviceGrid 
         o += plane;
     }
     if (G.extra & 0x18u) {
-        const double g1 = S.g1[t];
-        Best b = {INFINITY, 0u, 0xFFFFFFFFu};
-        if (G.extra & 8u) consider(b, 2.0 * __builtin_fma(q, g1, L), 16, 0);
-        if (G.extra & 16u) consider(b, 2.0 * __builtin_fma(fl, g1, cl * L), 17, 0);
-        store_cell(o, b);
+        store_cell(o, decide_barrier(G.extra, q, fl, cl, L, S.g1[t]));
     }
 }
 
@@ -4011,8 +4228,8 @@ hipError_t kernels_init()
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_terms_chain),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxTableLds);
     if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_fused),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxTableLds);
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_tile), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)(g_device.lds_per_cu - TILE_STATIC_LDS));
     if (e != hipSuccess) return e;
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_score_points),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxTableLds);
@@ -4076,12 +4293,31 @@ hipError_t launch_eval(const DeviceTables &T, int table, int strategy, const uin
     return hipGetLastError();
 }
 
-// Batches with enough (table, m) rows to fill the chip, few candidates and a short
-// chain sum go through the single fused kernel; everything else through the
-// staged kernels.
-static bool use_fused_path(const DeviceTables &T, const DeviceGrid &G)
+// Message sizes per workgroup of the tile path (k_tile): 0 = the path does not take this job.
+// Few candidates, few blocks of the chain sum, enough (table, m) rows: a workgroup takes about 20
+// us from its first load to its last store, however many of them run (tables of 57 samples, 36
+// process counts up to 1500: 1200 rows 24 us against 16 on the staged path, 3600 rows 24 against
+// 27, 12 000 rows 30 against 59).  Smaller tiles to fill the chip do not help: what a workgroup
+// does once per table outweighs them (4000 rows: 27 us with 32 sizes a tile, 43 with eight).
+static int tile_sizes(const DeviceTables &T, const DeviceGrid &G)
 {
-    return (long)T.n_tables * G.n_m >= 8192 && G.n_s <= FUSED_NS && G.n_blk <= 32;
+    if ((long)T.n_tables * G.n_m < TILE_MIN_ROWS * device_info().n_cu || G.n_s > TILE_NS || G.n_blk > TILE_MAX_BLK)
+        return 0;
+    const size_t lds_per_cu = device_info().lds_per_cu;
+    const size_t table = ((size_t)4 * T.n + CHAIN_PAD) * sizeof(double);
+    // a small table: six workgroups per compute unit (333 tables x 203 sizes: 79 us, 80 with four,
+    // 90 with eight); a big one (one workgroup): all the LDS
+    const size_t most = table <= lds_per_cu / 16 ? lds_per_cu / 6 : lds_per_cu;
+    int M = TILE_MAX_M < G.n_m ? TILE_MAX_M : G.n_m;
+    auto bytes = [&](int m) {
+        return (size_t)TileLds(T.n, G.n_s, G.n_P, G.n_blk, G.cl_max, m).slots * sizeof(double) + TILE_STATIC_LDS;
+    };
+    while (M > 1 && bytes(M) > most)
+        --M;
+    if (bytes(M) > lds_per_cu)
+        return 0;
+    const int tiles = (G.n_m + M - 1) / M;               // then the same for every tile, but the last
+    return (G.n_m + tiles - 1) / tiles;
 }
 
 // Few tables, few candidates, few blocks of the chain sum and many process counts: one
@@ -4203,7 +4439,13 @@ bool plan_tune(const DeviceTables &T, const DeviceGrid &G, bool terms_only, Tune
         p.lay.total = lb.at;
         return !lb.too_big;
     }
-    if (fast_ok && !use_fused_path(T, G) && use_row_path(T, G)) {
+    // A row per workgroup while there are few rows or many process counts, else a tile of rows:
+    // 4000 rows x 300 process counts 28.7 us (tiles: 33.9), 10 000 x 300 62 (48), 10 000 x 1000 82
+    // (118), 15 000 x 256 75 (61).
+    const bool by_row = fast_ok && use_row_path(T, G) &&
+                        (G.n_P >= 512 || (long)T.n_tables * G.n_m < ROW_MAX_ROWS * n_cu);
+    const int tile_m = terms_only || by_row ? 0 : tile_sizes(T, G);
+    if (by_row) {
         p.path = TUNE_ROW;
         // two process counts per lane when there are more groups of 64 than waves
         p.row_two = G.n_P > 64 * (ROW_THREADS / 64);
@@ -4211,10 +4453,12 @@ bool plan_tune(const DeviceTables &T, const DeviceGrid &G, bool terms_only, Tune
         p.lay.total = lb.at;
         return true;
     }
-    if (fast_ok && use_fused_path(T, G)) {
-        p.path = TUNE_FUSED;
-        p.fused_mchunks = (G.n_m + 255) / 256;
-        if ((long)T.n_tables * p.fused_mchunks > kMaxLaunch) return false;
+    if (tile_m > 0) {
+        p.path = TUNE_TILE;
+        p.tile_m = tile_m;
+        p.n_tiles = (G.n_m + tile_m - 1) / tile_m;
+        p.tile_lds = (size_t)TileLds(T.n, G.n_s, G.n_P, G.n_blk, G.cl_max, tile_m).slots * D;
+        if ((long)T.n_tables * p.n_tiles > kMaxLaunch) return false;
         p.lay.total = lb.at;
         return true;
     }
@@ -4408,10 +4652,10 @@ hipError_t launch_tune_stage(const TunePlan &p, int stage, const DeviceTables &T
         }
         return hipGetLastError();
     }
-    if (p.path == TUNE_FUSED) {
+    if (p.path == TUNE_TILE) {
         if (stage == TUNE_STAGE_SWEEP)
-            hipLaunchKernelGGL(k_fused, dim3((unsigned)T.n_tables * p.fused_mchunks), dim3(256),
-                               (size_t)3 * T.n * sizeof(double) + 64, st, T, G, d_out, p.fused_mchunks);
+            hipLaunchKernelGGL(k_tile, dim3((unsigned)T.n_tables * p.n_tiles), dim3(TILE_THREADS), p.tile_lds, st, T,
+                               G, d_out, p.n_tiles, p.tile_m);
         return hipGetLastError();
     }
     if (stage == TUNE_STAGE_MORE) {

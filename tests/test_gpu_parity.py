@@ -643,3 +643,39 @@ def test_chain_row_at_points_around_block_ends(n_x, n_points, p_top):
                          for mv, pv in zip(m[~bad], P[~bad])])
         assert (got[~bad].view(np.uint64) == want.view(np.uint64)).all(), "row %d" % sid
     tab.free()
+
+
+# ------------------------------------------------------------------ tiles of message sizes
+
+def _tile_problem(rng, seed):
+    """A job for the path whose workgroups take a table and up to 32 message sizes: at least 3072
+    (table, m) rows (12 per compute unit), at most 24 candidates, at most 32 blocks of the chain
+    sum; tables with sample sizes of their own."""
+    n = int([2, 3, 9, 57, 120, 300, 700, 1500][seed % 8])
+    n_m = int([1, 31, 32, 33, 65, 100, 200, 47][seed % 8])
+    n_tables = -(-3072 // n_m) + int(rng.integers(0, 9))
+    x = np.floor(np.cumsum(rng.integers(1, 3000 if n < 400 else 60, size=(n_tables, n)).astype(np.float64), axis=1))
+    gaps = np.abs(20.0 + x * rng.uniform(0.02, 0.1, size=(n_tables, 1)) * (1.0 + 0.4 * rng.standard_normal(x.shape)))
+    L = rng.uniform(0.0, 90.0, size=n_tables)
+    top = float(x.max()) * float(rng.choice([0.05, 1.0, 20.0]))
+    m = np.maximum(np.floor(np.exp(rng.uniform(np.log(8.0), np.log(max(top, 64.0)), size=n_m)) / 8.0) * 8.0, 8.0)
+    p_hi = int([2, 66, 257, 1026, 1500, 2049, 130, 600][seed % 8])
+    n_P = int(min(p_hi - 1, rng.choice([1, 5, 24, 37, 255, 256, 300])))
+    P = np.sort(rng.choice(np.arange(2, p_hi + 1), size=n_P, replace=False))
+    P[-1] = p_hi                                            # the last block: 1, 64, 1, 63, 32 ... terms
+    P = np.unique(P).astype(np.uint32)
+    s = np.unique(rng.integers(1, 4000, size=int(rng.choice([0, 1, 4, 5, 19, 24]))) * 8).astype(np.uint64)
+    mask = int(rng.choice([ALL_STRATEGIES_MASK, ALL_STRATEGIES_MASK, 0x3FFFF, 0x3FFFF, 0x3FF, 0x1C00, 0x0A25, 1 << 2, 1 << 9,
+                           1 << 11, 1 << 14, 0x36800, int(rng.integers(1, 1 << 18))]))
+    return Workload("tile", x, gaps, L, m.astype(np.uint64), P, s, int(rng.choice([NO_CAP, NO_CAP, 2048])), mask)
+
+
+@pytest.mark.parametrize("seed", range(24))
+def test_random_tiles(seed):
+    rng = np.random.default_rng(5000 + seed)
+    wl = _tile_problem(rng, seed)
+    want, _ = oracle.tune_workload(wl)
+    what = "tile %d: n=%d tables=%d m=%d P=%d (max %d) s=%d mask=%#x" % (
+        seed, wl.sizes.shape[1], wl.n_tables, len(wl.m), len(wl.P), int(wl.P[-1]), len(wl.s), wl.strategy_mask)
+    print(what, flush=True)
+    assert assert_tables_equal(gpu_tune(wl), want, what), "times not bit-identical"
