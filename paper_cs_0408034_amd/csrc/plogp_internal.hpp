@@ -102,10 +102,11 @@ struct Scratch {
     double *pre;      // [n_tables][n_m][n_P]             sum of the blocks finished before each grid P (more than 32 blocks only)
     double *part;     // [n_tables][n_m][n_P]             in-block partial sums at the grid's P
     double *rcp;      // [n_s]                            1/s, rounded
-    double *segC;     // [n_tables][n_s]                  C = g(s) + L
+    double *segC;     // [n_tables][n_s]                  C = g(s) + L (with segA, segB)
     double *segA;     // [n_tables][n_m][n_s]             A = g(s) ceil(m/s), +inf where s does not compete
     double *segB;     // [n_tables][n_m][n_s]             B = g(s) (ceil(m/s) - 1)   (both: n_s <= SWEEP_M_MAX_S only)
     double *amin;     // [n_tables][n_m]                  min over s of A (with segA, segB)
+    double *minG;     // [n_tables][ceil(n_s/64)]         least g(s) of 64 consecutive candidates (n_s > SWEEP_M_MAX_S only)
     int *nv;          // [n_m]                            candidates s <= min(m, s_cap)
     BatchPrep batch;  // shared sample sizes only
     double *batch_ys; // [n+2][n_tables][2]               {gap, slope} by interval (shared sample sizes only)
@@ -128,7 +129,7 @@ const DeviceInfo &device_info();
 // memory, in bytes; every array starts on a 256-byte boundary.  An array the chosen path does
 // not use has offset 0: the first 256 bytes of the block are a spare that nothing reads.
 struct ScratchLayout {
-    size_t g1, gs, gm, sum2, blk, pre, part, rcp, segC, segA, segB, amin, nv;
+    size_t g1, gs, gm, sum2, blk, pre, part, rcp, segC, segA, segB, amin, minG, nv;
     size_t rec, tab, batch_ys;     // table-lane batch path
     size_t score_rows;             // scoring only: 2 doubles per (strategy, m)
     size_t total;                  // bytes of the block

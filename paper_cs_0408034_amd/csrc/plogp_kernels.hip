@@ -119,7 +119,8 @@ __device__ __forceinline__ void segment_terms(double md, double sd, double rcp_s
 {
     double k = ceil(md * rcp_s);
     const double r = __builtin_fma(-k, sd, md);        // exact: m - k s
-    k = r > 0.0 ? k + 1.0 : (r <= -sd ? k - 1.0 : k);
+    // 1, -1 or 0 (their low words are all 0): two selects and an addition
+    k += __hiloint2double(r > 0.0 ? 0x3FF00000 : (r <= -sd ? (int)0xBFF00000 : 0), 0);
     A = gs * k;
     B = gs * (k - 1.0);
     C = gs + L;
@@ -132,6 +133,75 @@ __device__ __forceinline__ double min_f64(double a, double b)
     double r;
     asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
     return r;
+}
+
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_move(double v)
+{
+    int lo = __double2loint(v), hi = __double2hiint(v);
+    lo = __builtin_amdgcn_update_dpp(lo, lo, CTRL, ROW_MASK, 0xf, false);
+    hi = __builtin_amdgcn_update_dpp(hi, hi, CTRL, ROW_MASK, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+
+// Minimum over the 64 lanes of a fully active wave, returned in every lane.
+// DPP butterflies inside each row of 16 lanes (quad permutes, half-row and row
+// mirrors), then the row broadcasts 15 and 31 fold the four rows into lane 63.
+__device__ __forceinline__ double wave_min(double v)
+{
+    v = min_f64(v, dpp_move<0xB1, 0xf>(v));            // quad_perm [1,0,3,2]
+    v = min_f64(v, dpp_move<0x4E, 0xf>(v));            // quad_perm [2,3,0,1]
+    v = min_f64(v, dpp_move<0x141, 0xf>(v));           // row_half_mirror
+    v = min_f64(v, dpp_move<0x140, 0xf>(v));           // row_mirror
+    v = min_f64(v, dpp_move<0x142, 0xa>(v));           // row_bcast:15 into rows 1, 3
+    v = min_f64(v, dpp_move<0x143, 0xc>(v));           // row_bcast:31 into rows 2, 3
+    const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
+    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
+    return __hiloint2double(hi, lo);
+}
+
+// min_f64(a of one half or of the even rows, of the other half or of the odd rows) of two values at
+// once: ROWS = false: the lower lanes get the fold of a over the two halves, the upper ones that of
+// b; ROWS = true: even rows of 16 lanes get the fold of a over pairs of rows, odd ones that of b.
+// (The compiler keeps the two wait states that these permutes need after a vector instruction, but
+// does not see the one inside min_f64's assembly: hence the explicit ones.)
+template <bool ROWS>
+__device__ __forceinline__ double fold_two(double a, double b)
+{
+    asm("s_nop 1" : "+v"(a), "+v"(b));
+    const auto swap = [](int x, int y) {
+        return ROWS ? __builtin_amdgcn_permlane16_swap(x, y, false, false)
+                    : __builtin_amdgcn_permlane32_swap(x, y, false, false);
+    };
+    const auto lo = swap(__double2loint(a), __double2loint(b)), hi = swap(__double2hiint(a), __double2hiint(b));
+    return min_f64(__hiloint2double((int)hi[0], (int)lo[0]), __hiloint2double((int)hi[1], (int)lo[1]));
+}
+
+// v[p] becomes the minimum of v[p] over the 64 lanes, in every lane, for N values at once: the
+// first two steps fold two values into one register pair, which halves the instructions of N
+// wave_min one after the other.
+template <int N>
+__device__ __forceinline__ void wave_min_each(double (&v)[N])
+{
+    constexpr int N2 = (N + 1) / 2, N4 = (N2 + 1) / 2;
+    double half[N2], row[N4];
+#pragma unroll
+    for (int i = 0; i < N2; ++i)
+        half[i] = fold_two<false>(v[2 * i], v[2 * i + 1 < N ? 2 * i + 1 : 2 * i]);
+#pragma unroll
+    for (int i = 0; i < N4; ++i) {
+        double r = fold_two<true>(half[2 * i], half[2 * i + 1 < N2 ? 2 * i + 1 : 2 * i]);
+        r = min_f64(r, dpp_move<0xB1, 0xf>(r));            // within each row of 16 lanes
+        r = min_f64(r, dpp_move<0x4E, 0xf>(r));
+        r = min_f64(r, dpp_move<0x141, 0xf>(r));
+        row[i] = min_f64(r, dpp_move<0x140, 0xf>(r));
+    }
+#pragma unroll
+    for (int p = 0; p < N; ++p) {
+        const int from = 32 * (p % 2) + 16 * (p / 2 % 2);
+        v[p] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(row[p / 4]), from),
+                                __builtin_amdgcn_readlane(__double2loint(row[p / 4]), from));
+    }
 }
 
 // ---------------------------------------------------------------- slopes (table load)
@@ -341,13 +411,23 @@ __device__ __forceinline__ void terms_body(const DeviceTables &T, const DeviceGr
         return;
     // per candidate: g(s), 1/s, C = g(s) + L; shared out over the chunks of this table
     const double L = T.L[t];
-    for (int si = chunk * blockDim.x + threadIdx.x; si < G.n_s; si += n_chunks * blockDim.x) {
-        const double sd = (double)G.s[si];
-        const double gs = gap_at(tab, sd);
-        S.gs[(size_t)t * G.n_s + si] = gs;
-        S.segC[(size_t)t * G.n_s + si] = gs + L;
-        if (t == 0)
-            S.rcp[si] = 1.0 / sd;
+    for (int s0 = chunk * blockDim.x + (threadIdx.x & ~63u); s0 < G.n_s; s0 += n_chunks * blockDim.x) {
+        const int si = s0 + (int)(threadIdx.x & 63u);
+        double gs = INFINITY;
+        if (si < G.n_s) {
+            const double sd = (double)G.s[si];
+            gs = gap_at(tab, sd);
+            S.gs[(size_t)t * G.n_s + si] = gs;
+            if (with_pairs & 1)
+                S.segC[(size_t)t * G.n_s + si] = gs + L;
+            if (t == 0)
+                S.rcp[si] = 1.0 / sd;
+        }
+        if (with_pairs & 4) {              // for the sweep over s: the least g(s) of 64 consecutive candidates
+            gs = wave_min(gs);
+            if ((threadIdx.x & 63u) == 0u)
+                S.minG[(size_t)t * ((G.n_s + 63) / 64) + s0 / 64] = gs;
+        }
     }
     // per (m, s): A = g(s) k and B = g(s)(k-1) for the sweep that runs its lanes over P
     // (there they are wave-uniform), +inf where s does not compete; per m the minimum of A
@@ -1615,33 +1695,6 @@ __global__ void __launch_bounds__(256) k_sweep_m(DeviceTables T, DeviceGrid G, S
     }
 }
 
-// ---- sweep, many candidates: one lane per segment size -----------------------
-
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double dpp_move(double v)
-{
-    int lo = __double2loint(v), hi = __double2hiint(v);
-    lo = __builtin_amdgcn_update_dpp(lo, lo, CTRL, ROW_MASK, 0xf, false);
-    hi = __builtin_amdgcn_update_dpp(hi, hi, CTRL, ROW_MASK, 0xf, false);
-    return __hiloint2double(hi, lo);
-}
-
-// Minimum over the 64 lanes of a fully active wave, returned in every lane.
-// DPP butterflies inside each row of 16 lanes (quad permutes, half-row and row
-// mirrors), then the row broadcasts 15 and 31 fold the four rows into lane 63.
-__device__ __forceinline__ double wave_min(double v)
-{
-    v = min_f64(v, dpp_move<0xB1, 0xf>(v));            // quad_perm [1,0,3,2]
-    v = min_f64(v, dpp_move<0x4E, 0xf>(v));            // quad_perm [2,3,0,1]
-    v = min_f64(v, dpp_move<0x141, 0xf>(v));           // row_half_mirror
-    v = min_f64(v, dpp_move<0x140, 0xf>(v));           // row_mirror
-    v = min_f64(v, dpp_move<0x142, 0xa>(v));           // row_bcast:15 into rows 1, 3
-    v = min_f64(v, dpp_move<0x143, 0xc>(v));           // row_bcast:31 into rows 2, 3
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
-    return __hiloint2double(hi, lo);
-}
-
 // ---- sweep, few candidates, many process counts: one lane per P -----------------
 //
 // A wave takes 64 consecutive process counts of the grid (its lanes) and walks
@@ -1924,54 +1977,58 @@ __global__ void __launch_bounds__(256) k_sweep_p(DeviceTables T, DeviceGrid G, S
     }
 }
 
-constexpr int SWEEP_S_CHUNK = 1024;     // candidates staged in LDS per pass (16 per lane)
-constexpr int SWEEP_S_MAX_WAVES = 8;
-constexpr int SWEEP_S_PASSES = 64;      // passes whose minimum of A is remembered
+// ---- sweep, many candidates: lanes over s, most of them never evaluated --------
+//
+// A workgroup takes one (table, m) and up to SWEEP_S_WAVES groups of GP process counts, one group
+// per wave.  For row 5, min over s of fma(P-1, C, B), the candidates are cut into chunks of 64
+// consecutive ones: rounding is monotone, so fma(P-1, min C, min B) over a chunk is not above any
+// of its values, and a chunk whose bound lies above a value already found cannot hold the minimum
+// (nor tie with it).  The workgroup computes A and B of every candidate of a pass once (B to LDS),
+// the minimum of B per chunk (that of C does not depend on m and comes from the tuning's first
+// step) and the minima of A; a wave then takes, per process count, the smallest of the chunks'
+// first candidates as an upper bound, compares it with the bounds of all chunks (two per lane),
+// and evaluates the chunks that some process count of its group still needs.  On 8192 candidates
+// and 69 process counts that is 7 of 128 chunks per wave on average (1024 sizes up to 1 GiB, one
+// table: kernel 76 -> about 40 us, the call 89 -> 51; with every candidate evaluated it was bound
+// by its fp64 instructions).  What is left, in us of the call: the step before 10, A and B of
+// every candidate 18, upper bounds and bounds 9, the chunks 10, rows 2 and 9 3.  It is bound by
+// latency at 16 waves per compute unit (64 KB of B per workgroup, 110 registers); passes of 4096
+// (100 us), groups of six process counts in two workgroups (67) and loads one step ahead in the
+// filling (56, spills) are slower.
+constexpr int SWEEP_S_WAVES = 8;
+constexpr int SWEEP_S_PASS = 8192;      // candidates per pass: 64 KB of LDS, two workgroups per CU
+constexpr int SWEEP_S_CHUNKS = SWEEP_S_PASS / 64;
+constexpr int SWEEP_S_RANGE = SWEEP_S_PASS / SWEEP_S_WAVES;   // candidates a wave fills
+constexpr int SWEEP_S_RANGES = 64;      // ranges whose minimum of A is remembered
 
-// A workgroup takes one (table, m) and up to SWEEP_S_MAX_WAVES groups of GP
-// process counts, one group per wave; lanes run over the candidates s.  A, B, C
-// of a pass of SWEEP_S_CHUNK candidates are computed once by the whole
-// workgroup into LDS (double-buffered) and read by every wave.  In the loop a
-// wave keeps, per process count, the running minimum of the segmented chain
-// (row 5: one fma and one min per value); per lane it remembers in which pass
-// each row-5 minimum first appeared.  The minimum of A (rows 2 and 9 are monotone
-// in A, and A does not depend on P) is formed once per pass, by wave 0, from the
-// minima that the threads filling the pass leave in LDS.  At the end the row-5
-// minima are reduced across lanes, the winner is chosen in id order, and only for a
-// winning segmented row the smallest s that attains the minimum is looked for:
-// for row 5 among the candidates of the pass the holding lanes remember, for
-// rows 2 and 9 by one ascending walk over the candidates.
 template <int GP>
-__global__ void __launch_bounds__(64 * SWEEP_S_MAX_WAVES)
+__global__ void __launch_bounds__(64 * SWEEP_S_WAVES, 4)
 k_sweep_s(DeviceTables T, DeviceGrid G, Scratch S, plogp_cell_dev *out, int n_ptiles)
 {
-    __shared__ double2 AB[2][SWEEP_S_CHUNK];           // {B, C} of the candidates of a pass
-    __shared__ double Cs[2][SWEEP_S_CHUNK];            // (only the reduction at the end uses it)
-    __shared__ double passMinA[SWEEP_S_PASSES];        // min of A over each of the first passes
-    __shared__ double fillMinA[2][64 * SWEEP_S_MAX_WAVES];   // per filling thread: min of A over its candidates
-    __shared__ double allMinA;                         // min of A over every candidate
+    extern __shared__ __align__(16) double sweep_lds[];          // B of the candidates of a pass
+    __shared__ double minB[SWEEP_S_CHUNKS], firstB[SWEEP_S_CHUNKS], firstC[SWEEP_S_CHUNKS];
+    __shared__ double rangeMinA[SWEEP_S_RANGES];                  // min of A over each of the first ranges
+    __shared__ double fillMinA[SWEEP_S_WAVES];                    // per wave: over the ranges it filled
+    double *sB = sweep_lds;
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int n_waves = blockDim.x >> 6;
     int bid = blockIdx.x;
     const int ptile = bid % n_ptiles;
     bid /= n_ptiles;
     const int mi = bid % G.n_m;
     const int t = bid / G.n_m;
-    const int p0 = (ptile * n_waves + wave) * GP;      // first P index of this wave
+    const int p0 = (ptile * SWEEP_S_WAVES + wave) * GP;           // first P index of this wave
     const bool has_work = p0 < G.n_P;
 
-    const u64 m = G.m[mi];
-    const double md = (double)m;
+    const double md = (double)G.m[mi];
     const double L = T.L[t];
     const uint32_t mask = G.mask;
     const double *gs = S.gs + (size_t)t * G.n_s;
+    const double *minG = S.minG + (size_t)t * ((G.n_s + 63) / 64);
+    const int nv = S.nv[mi];                                      // candidates s <= min(m, s_cap)
 
-    const int nv = S.nv[mi];                           // candidates s <= min(m, s_cap)
-    const int n_chunks = (nv + SWEEP_S_CHUNK - 1) / SWEEP_S_CHUNK;
-
-    double q[GP];                                      // wave-uniform: kept in scalar registers
+    double q[GP];                                                 // wave-uniform: kept in scalar registers
 #pragma unroll
     for (int p = 0; p < GP; ++p) {
         const uint32_t Pv = (p0 + p < G.n_P) ? G.P[p0 + p] : 2u;
@@ -1979,14 +2036,6 @@ k_sweep_s(DeviceTables T, DeviceGrid G, Scratch S, plogp_cell_dev *out, int n_pt
         q[p] = __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(qv)),
                                 __builtin_amdgcn_readfirstlane(__double2loint(qv)));
     }
-    double best5[GP];
-    int blk5[GP];
-#pragma unroll
-    for (int p = 0; p < GP; ++p) {
-        best5[p] = INFINITY;
-        blk5[p] = 0;
-    }
-    double amin = INFINITY;                            // (wave 0 only, the same in its lanes)
     // What lane p < GP needs at the end to decide its cells is asked for now, so that the end
     // of the wave does not wait for device memory: its process count, g(m), g(1), the two
     // Scatter sums.
@@ -2004,258 +2053,263 @@ k_sweep_s(DeviceTables T, DeviceGrid G, Scratch S, plogp_cell_dev *out, int n_pt
             s12 = S.sum2[((size_t)t * G.n_m + mi) * (size_t)(G.cl_max + 1) + ceil_log2(Pv)];
     }
 
-    // Filling a pass: the loads of the per-candidate scalars are issued before the
-    // previous pass is consumed, the arithmetic and the LDS stores come after it.
-    // A workgroup has at least SWEEP_S_CHUNK / FILL_SLOTS threads.
-    constexpr int FILL_SLOTS = 2;
-    double f_s[FILL_SLOTS], f_rcp[FILL_SLOTS], f_gs[FILL_SLOTS];
-    auto fill_load = [&](int c) {
+    double least_A = INFINITY;                                    // over the candidates this thread filled
+    // The minimum of row 5 per process count, the same in every lane.  (The +inf at the start goes
+    // through a vector register: as a constant this compiler moves it into a scalar pair with one
+    // 64-bit literal, which the hardware does not have - it reads as 0.)
+    double V5p[GP], unset = INFINITY;
+    asm("" : "+v"(unset));
 #pragma unroll
-        for (int k = 0; k < FILL_SLOTS; ++k) {
-            const int si = c * SWEEP_S_CHUNK + (int)threadIdx.x + k * (int)blockDim.x;
-            const int idx = si < nv ? si : nv - 1;
-            f_s[k] = (double)G.s[idx];
-            f_rcp[k] = S.rcp[idx];
-            f_gs[k] = gs[idx];
+    for (int p = 0; p < GP; ++p)
+        V5p[p] = unset;
+    int at5 = 0;                                                  // lane p: the first candidate that attains V5p[p]
+    for (int s0 = 0; s0 < nv; s0 += SWEEP_S_PASS) {
+        const int n_here = nv - s0 < SWEEP_S_PASS ? nv - s0 : SWEEP_S_PASS;
+        const int n_chunks = (n_here + 63) >> 6;
+        if (s0 > 0)
+            __syncthreads();                                      // every wave is done with the pass before
+        // this wave's range of the pass, four chunks at a time (their loads side by side)
+        double range_A = INFINITY;
+        for (int c0 = wave * (SWEEP_S_RANGE / 64); c0 < (wave + 1) * (SWEEP_S_RANGE / 64) && c0 < n_chunks; c0 += 4) {
+            const int first = s0 + 64 * c0;
+            auto fill = [&](bool whole) {                         // whole: all 256 candidates compete
+                double f_s[4], f_rcp[4], f_gs[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int si = first + 64 * u + lane, idx = whole || si < nv ? si : nv - 1;
+                    f_s[u] = (double)*reinterpret_cast<const uint32_t *>(G.s + idx);       // below 2^32
+                    f_rcp[u] = S.rcp[idx];
+                    f_gs[u] = gs[idx];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int c = c0 + u;
+                    double A, B, C;
+                    segment_terms(md, f_s[u], f_rcp[u], f_gs[u], L, A, B, C);
+                    range_A = min_f64(range_A, A);                // (past the end: the last one again)
+                    if (whole || c < n_chunks) {
+                        sB[64 * c + lane] = whole || first + 64 * u + lane < nv ? B : INFINITY;
+                        if (lane == 0) {
+                            firstB[c] = B;
+                            firstC[c] = C;
+                        }
+                    }
+                }
+            };
+            if (first + 256 <= nv)
+                fill(true);
+            else
+                fill(false);
         }
-    };
-    auto fill_store = [&](int c) {
-        const int buf = c & 1;
-        double mine_A = INFINITY;
+        if (mask & 0x204u) {
+            const double r = wave_min(range_A);
+            least_A = min_f64(least_A, r);
+            const int range = s0 / SWEEP_S_RANGE + wave;
+            if (lane == 0 && range < SWEEP_S_RANGES)
+                rangeMinA[range] = r;
+        }
+        __syncthreads();
+        // the minimum of B per chunk: four threads to a chunk, each its quarter from an offset of
+        // its own (no two chunks of a wave in one bank)
+        {
+            const int c = (int)threadIdx.x >> 2, part = (int)threadIdx.x & 3;
+            double least = INFINITY;
+            if (c < n_chunks) {
 #pragma unroll
-        for (int k = 0; k < FILL_SLOTS; ++k) {
-            const int e = (int)threadIdx.x + k * (int)blockDim.x;
-            if (e < SWEEP_S_CHUNK) {
-                double A = INFINITY, B = INFINITY, C = 0.0;
-                if (c * SWEEP_S_CHUNK + e < nv)
-                    segment_terms(md, f_s[k], f_rcp[k], f_gs[k], L, A, B, C);
-                AB[buf][e] = make_double2(B, C);           // one 16-byte read per candidate in the loop
-                mine_A = min_f64(mine_A, A);
+                for (int k = 0; k < 16; ++k)
+                    least = min_f64(least, sB[64 * c + 16 * part + ((k + c) & 15)]);
             }
+            least = min_f64(least, __shfl_xor(least, 1));
+            least = min_f64(least, __shfl_xor(least, 2));
+            if (part == 0)
+                minB[c] = least;
         }
-        // A does not depend on the process count: its minimum over a pass is formed from these
-        // per-thread minima by one wave, not by every wave over every candidate
-        fillMinA[buf][threadIdx.x] = mine_A;
-    };
-    if (n_chunks > 0) {
-        fill_load(0);
-        fill_store(0);
-    }
-    __syncthreads();
-    for (int c = 0; c < n_chunks; ++c) {
-        if (c + 1 < n_chunks)
-            fill_load(c + 1);
-        if (has_work) {
-            const int buf = c & 1;
-            const int len = min(SWEEP_S_CHUNK, nv - c * SWEEP_S_CHUNK);
-            const int steps = (len + 63) >> 6;
-            double cur5[GP];
+        __syncthreads();
+        if (!has_work || (mask & 0x20u) == 0)
+            continue;
+        // the chunks that some process count of this wave needs
+        u64 need[SWEEP_S_CHUNKS / 64];
+        {
+            double up[GP];
 #pragma unroll
             for (int p = 0; p < GP; ++p)
-                cur5[p] = INFINITY;
-#pragma unroll 2
-            for (int i = 0; i < steps; ++i) {
-                const double2 bc = AB[buf][64 * i + lane];
+                up[p] = INFINITY;
 #pragma unroll
-                for (int p = 0; p < GP; ++p)
-                    cur5[p] = min_f64(cur5[p], __builtin_fma(q[p], bc.y, bc.x));
+            for (int h = 0; h < SWEEP_S_CHUNKS / 64; ++h) {
+                const int c = 64 * h + lane;
+                if (64 * h < n_chunks) {
+                    const double fb = c < n_chunks ? firstB[c] : INFINITY, fc = c < n_chunks ? firstC[c] : 0.0;
+#pragma unroll
+                    for (int p = 0; p < GP; ++p)
+                        up[p] = min_f64(up[p], __builtin_fma(q[p], fc, fb));
+                }
             }
 #pragma unroll
-            for (int p = 0; p < GP; ++p) {
-                blk5[p] = cur5[p] < best5[p] ? c : blk5[p];
-                best5[p] = min_f64(best5[p], cur5[p]);
-            }
-            if (wave == 0) {                           // wave 0 always has work
-                double curA = INFINITY;
-                for (int k = lane; k < (int)blockDim.x; k += 64)
-                    curA = min_f64(curA, fillMinA[buf][k]);
-                const double pm = wave_min(curA);
-                amin = min_f64(amin, pm);
-                if (lane == 0 && c < SWEEP_S_PASSES)
-                    passMinA[c] = pm;
-                if (lane == 0 && c + 1 == n_chunks)
-                    allMinA = amin;
+            for (int p = 0; p < GP; ++p)
+                up[p] = min_f64(up[p], V5p[p]);
+            wave_min_each<GP>(up);
+#pragma unroll
+            for (int h = 0; h < SWEEP_S_CHUNKS / 64; ++h) {
+                need[h] = 0;
+                const int c = 64 * h + lane;
+                if (64 * h < n_chunks) {
+                    const double lb = minB[c], lc = c < n_chunks ? minG[s0 / 64 + c] + L : 0.0;
+#pragma unroll
+                    for (int p = 0; p < GP; ++p)
+                        need[h] |= __ballot(__builtin_fma(q[p], lc, lb) <= up[p]);
+                    if (n_chunks - 64 * h < 64)
+                        need[h] &= (1ull << (n_chunks - 64 * h)) - 1ull;
+                }
             }
         }
-        if (c + 1 < n_chunks)
-            fill_store(c + 1);
+        double best5[GP], V[GP];
+        int chunk5[GP];                                           // in which chunk this lane's minimum first appeared
+#pragma unroll
+        for (int p = 0; p < GP; ++p) {
+            best5[p] = INFINITY;
+            chunk5[p] = 0;
+        }
+#pragma unroll
+        for (int h = 0; h < SWEEP_S_CHUNKS / 64; ++h) {
+            for (u64 left = need[h]; left != 0; left &= left - 1) {
+                const int c = 64 * h + __builtin_ctzll(left), e = 64 * c + lane;
+                const double B = sB[e], C = gs[s0 + e < nv ? s0 + e : nv - 1] + L;
+#pragma unroll
+                for (int p = 0; p < GP; ++p) {
+                    const double T5 = __builtin_fma(q[p], C, B);
+                    chunk5[p] = T5 < best5[p] ? c : chunk5[p];
+                    best5[p] = min_f64(best5[p], T5);
+                }
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < GP; ++p)
+            V[p] = best5[p];
+        wave_min_each<GP>(V);
+        // the process counts whose minimum this pass lowers: the first candidate that attains it
+#pragma unroll
+        for (int p = 0; p < GP; ++p) {
+            if (!(V[p] < V5p[p]))
+                continue;
+            V5p[p] = V[p];
+            int first = 0x7FFFFFFF;
+            for (u64 holders = __ballot(best5[p] == V[p]); holders != 0; holders &= holders - 1) {
+                const int l = __builtin_ctzll(holders);           // more than one lane only on exact ties
+                const int at = s0 + 64 * __builtin_amdgcn_readlane(chunk5[p], l) + l;
+                first = at < first ? at : first;
+            }
+            at5 = lane == p ? first : at5;
+        }
+    }
+    double V5 = INFINITY;                                         // lane p: of process count p0 + p
+#pragma unroll
+    for (int p = 0; p < GP; ++p)
+        V5 = lane == p ? V5p[p] : V5;
+    if (mask & 0x204u) {
+        if (lane == 0)
+            fillMinA[wave] = least_A;
         __syncthreads();
     }
     if (!has_work)
         return;
-
-    // The minimum of row 5 over the lanes, for all process counts of the group at once: the
-    // lanes leave their minima in LDS (the candidate buffers are free now, every wave has
-    // passed the last barrier), lane p reads the 64 minima of process count p0 + p (the
-    // columns are 65 apart where they fit, so that the lanes hit different banks) and keeps
-    // their minimum.
-    const double Aw = (mask & 0x204u) && n_chunks > 0 ? allMinA : INFINITY;
+    double Aw = INFINITY;
+    if (mask & 0x204u)
+#pragma unroll
+        for (int w = 0; w < SWEEP_S_WAVES; ++w)
+            Aw = min_f64(Aw, fillMinA[w]);
     const bool haveA = Aw < INFINITY;
-    double V5 = INFINITY;
-    if (mask & (1u << 5)) {
-        static_assert(GP <= 12, "columns of the reduction buffer");
-        // per wave 512 doubles of AB and 256 of Cs: 7 + 3 padded columns, or 8 + 4 plain ones
-        constexpr int LD = GP <= 10 ? 65 : 64, NLO = GP <= 10 ? 7 : 8;
-        double *lo = reinterpret_cast<double *>(&AB[0][0]) + wave * 512;
-        double *hi = &Cs[0][0] + wave * 256;
-#pragma unroll
-        for (int p = 0; p < GP; ++p)
-            (p < NLO ? lo + LD * p : hi + LD * (p - NLO))[lane] = best5[p];
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        // in two steps, so that most lanes take part: lane l takes a stretch of the 64 minima of
-        // process count l % GP, then lane p the results of its stretches
-        constexpr int NPART = 64 / GP, PER = (64 + NPART - 1) / NPART;
-        double *mid = &fillMinA[0][0] + wave * 64;     // (free: every wave is past the last pass)
-        if (lane < GP * NPART) {
-            const int pp = lane % GP, part = lane / GP;
-            const double *col = pp < NLO ? lo + LD * pp : hi + LD * (pp - NLO);
-            double v[PER];
-#pragma unroll
-            for (int u = 0; u < PER; ++u)
-                v[u] = col[part * PER + u < 64 ? part * PER + u : 63];
-            double least = v[0];
-#pragma unroll
-            for (int u = 1; u < PER; ++u)
-                least = min_f64(least, v[u]);
-            mid[lane] = least;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        if (lane < GP) {
-#pragma unroll
-            for (int part = 0; part < NPART; ++part)
-                V5 = min_f64(V5, mid[part * GP + lane]);
-        }
-    }
 
     // lanes 0..GP-1 decide one Broadcast cell each: the segmented rows' minima, the
-    // unsegmented rows, arg-min.  The segment size is looked for afterwards, and only in
-    // the cells that a segmented row wins.
+    // unsegmented rows, arg-min.  The segment size of rows 2 and 9 is looked for afterwards, and
+    // only in the cells that they win.
     const double qv = (double)(Pv - 1);
     const int fli = floor_log2(Pv), cli = ceil_log2(Pv);
     const size_t plane = (size_t)G.n_m * G.n_P;
     plogp_cell_dev *o = out + (size_t)t * G.n_ops * plane + (size_t)mi * G.n_P + (mine ? pi : 0);
-    Best bc = {INFINITY, 0u, 0xFFFFFFFFu};
     if (mask & 0x3FFu) {
         const double t2 = ((mask & (1u << 2)) && haveA) ? __builtin_fma(qv, Aw, L) : INFINITY;
         const double t9 = ((mask & (1u << 9)) && haveA)
                               ? __builtin_fma((double)fli, Aw, (double)cli * L) : INFINITY;
-        bc = decide_bcast(mask, qv, (double)fli, (double)cli, gm, L, g1, t2, 0u, V5, 0u, t9, 0u);
-        const unsigned long long need =
-            __ballot(mine && (bc.id == 2u || bc.id == 5u || bc.id == 9u));
-        if (need != 0) {
-            // Row 5: every lane that holds the minimum V of process count p names the pass it
-            // first saw it in; that lane's 16 candidates of the pass are evaluated again, by 16
-            // lanes, and the first that gives V is its earliest.  Four such (process count,
-            // holding lane) queries are worked on at once, one per quarter of the wave; lane p
-            // keeps the smallest index found for process count p and the candidate there.
-            int first_v = 0x7FFFFFFF;
-            double s_v = 0.0;
-            int qc = 0, ql = 0, qp = 0;                    // the query of this lane's quarter
-            double qV = 0.0, qq = 0.0;
-            int nq = 0;                                    // queries waiting (wave-uniform)
+        Best bc = decide_bcast(mask, qv, (double)fli, (double)cli, gm, L, g1, t2, 0u, V5, 0u, t9, 0u);
+        if (mine && bc.id == 5u)
+            bc.s = (uint32_t)G.s[at5];
+        u64 seek = __ballot(mine && (bc.id == 2u || bc.id == 9u));
+        if (seek != 0) {
+            // The first candidate whose value equals the minimum, for all these cells at once.
+            // With a single pass the chunks' minima of B are still there: A = g(s) k is not below
+            // (min B + min g) of its chunk but for roundings (three of them, half an ulp each), so
+            // few chunks can hold it.  After several passes the first range whose minimum of A gives
+            // the value is walked from its start.
             auto from_lane = [&](double v, int l) {
                 return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
                                         __builtin_amdgcn_readlane(__double2loint(v), l));
             };
-            auto flush = [&]() {
-                const bool live = (lane >> 4) < nq;
-                const int si = qc * SWEEP_S_CHUNK + 64 * (lane & 15) + ql;
-                const int idx = si < nv ? si : nv - 1;
-                const double r_s = (double)G.s[idx];
-                double A, B, C;
-                segment_terms(md, r_s, S.rcp[idx], gs[idx], L, A, B, C);
-                const bool hit = live && si < nv && __builtin_fma(qq, C, B) == qV;
-                const unsigned long long hits = __ballot(hit);
-                for (int j = 0; j < nq; ++j) {
-                    const unsigned h = (unsigned)(hits >> (16 * j)) & 0xFFFFu;
-                    if (h == 0u)
+            const double mul_l = bc.id == 2u ? qv : (double)fli, add_l = bc.id == 2u ? L : (double)cli * L;
+            const int n_chunks = (nv + 63) >> 6;
+            u64 may[SWEEP_S_CHUNKS / 64];
+            int c_first = 0;
+            const bool single = nv <= SWEEP_S_PASS;
+            if (single) {
+#pragma unroll
+                for (int h = 0; h < SWEEP_S_CHUNKS / 64; ++h) {
+                    const int c = 64 * h + lane;
+                    may[h] = 0;
+                    if (64 * h >= n_chunks)
                         continue;
-                    const int k = __builtin_ctz(h);
-                    const int cand = __builtin_amdgcn_readlane(qc, 16 * j) * SWEEP_S_CHUNK + 64 * k +
-                                     __builtin_amdgcn_readlane(ql, 16 * j);
-                    const double s_c = from_lane(r_s, 16 * j + k);
-                    if (lane == __builtin_amdgcn_readlane(qp, 16 * j) && cand < first_v) {
-                        first_v = cand;
-                        s_v = s_c;
+                    const double low = c < n_chunks ? (minB[c] + minG[c]) * (1.0 - 0x1p-50) : INFINITY;
+                    for (u64 k = seek; k != 0; k &= k - 1) {
+                        const int p = __builtin_ctzll(k);
+                        may[h] |= __ballot(__builtin_fma(from_lane(mul_l, p), low, from_lane(add_l, p)) <=
+                                           from_lane(bc.t, p));
                     }
                 }
-                nq = 0;
-            };
-            auto push = [&](int p, int l, int c, double V, double q_p) {
-                const bool slot = (lane >> 4) == nq;
-                qc = slot ? c : qc;
-                ql = slot ? l : ql;
-                qp = slot ? p : qp;
-                qV = slot ? V : qV;
-                qq = slot ? q_p : qq;
-                if (++nq == 4)
-                    flush();
-            };
-#pragma unroll
-            for (int p = 0; p < GP; ++p) {
-                if (!((need >> p) & 1ull) || __builtin_amdgcn_readlane((int)bc.id, p) != 5)
-                    continue;                              // wave-uniform
-                const double V = from_lane(bc.t, p);
-                unsigned long long holders = __ballot(best5[p] == V);
-                while (holders != 0) {                     // more than one lane only on exact ties
-                    const int l = __builtin_ctzll(holders);
-                    holders &= holders - 1;
-                    push(p, l, __builtin_amdgcn_readlane(blk5[p], l), V, q[p]);
+            } else {
+                const int n_ranges = (nv + SWEEP_S_RANGE - 1) / SWEEP_S_RANGE;
+                const int known = n_ranges < SWEEP_S_RANGES ? n_ranges : SWEEP_S_RANGES;
+                u64 holds = 0;
+                for (u64 k = seek; k != 0; k &= k - 1) {
+                    const int p = __builtin_ctzll(k);
+                    const u64 in = __ballot(lane < known && __builtin_fma(from_lane(mul_l, p), rangeMinA[lane],
+                                                                          from_lane(add_l, p)) == from_lane(bc.t, p));
+                    holds |= in != 0 ? in : 1ull << (known - 1);   // beyond the ranges remembered
                 }
+                c_first = __builtin_ctzll(holds) * (SWEEP_S_RANGE / 64);
             }
-            if (nq > 0)
-                flush();
-            if (bc.id == 5u)
-                bc.s = first_v < nv ? (uint32_t)s_v : 0u;
-
-            // Rows 2 and 9: the first pass whose minimum of A already gives V holds the
-            // smallest such s; walk that pass in ascending order, 64 candidates at a time
+            while (c_first < n_chunks && seek != 0) {
+                int c[2];                                         // the next two chunks
 #pragma unroll
-            for (int p = 0; p < GP; ++p) {
-                if (!((need >> p) & 1ull))
-                    continue;                              // wave-uniform
-                const int id = __builtin_amdgcn_readlane((int)bc.id, p);
-                if (id == 5)
-                    continue;
-                const double V = from_lane(bc.t, p);
-                int first = 0x7FFFFFFF;
-                double s_first = 0.0;                      // the candidate at index `first`
-                const uint32_t Pp = G.P[p0 + p];
-                const double flp = (double)floor_log2(Pp);
-                const double clLp = (double)ceil_log2(Pp) * L;
-                const double mul = id == 2 ? q[p] : flp;
-                const double add = id == 2 ? L : clLp;
-                int c0 = 0;
-                const int known = n_chunks < SWEEP_S_PASSES ? n_chunks : SWEEP_S_PASSES;
-                while (c0 < known && __builtin_fma(mul, passMinA[c0], add) != V)
-                    ++c0;
-                for (int base = c0 * SWEEP_S_CHUNK; base < nv && first == 0x7FFFFFFF; base += 256) {
-                    // four groups of 64 candidates per round trip to memory
-                    double sdv[4], rcv[4], gsv[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int si = base + 64 * u + lane;
-                        const int idx = si < nv ? si : nv - 1;
-                        sdv[u] = (double)G.s[idx];
-                        rcv[u] = S.rcp[idx];
-                        gsv[u] = gs[idx];
+                for (int u = 0; u < 2; ++u) {
+                    if (single) {
+                        while (c_first < n_chunks && ((may[c_first >> 6] >> (c_first & 63)) & 1ull) == 0) {
+                            const u64 rest = may[c_first >> 6] >> (c_first & 63);
+                            c_first = rest != 0 ? c_first + __builtin_ctzll(rest) : (c_first | 63) + 1;
+                        }
                     }
+                    c[u] = c_first < n_chunks ? c_first : n_chunks - 1;
+                    ++c_first;
+                }
+                double sdv[2], A[2];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        double A, B, C;
-                        segment_terms(md, sdv[u], rcv[u], gsv[u], L, A, B, C);
-                        const bool hit = base + 64 * u + lane < nv && __builtin_fma(mul, A, add) == V;
-                        const unsigned long long hits = __ballot(hit);
-                        if (hits != 0 && first == 0x7FFFFFFF) {
-                            first = base + 64 * u + __builtin_ctzll(hits);
-                            s_first = from_lane(sdv[u], __builtin_ctzll(hits));
+                for (int u = 0; u < 2; ++u) {
+                    const int si = 64 * c[u] + lane, idx = si < nv ? si : nv - 1;
+                    sdv[u] = (double)*reinterpret_cast<const uint32_t *>(G.s + idx);
+                    double B, C;
+                    segment_terms(md, sdv[u], S.rcp[idx], gs[idx], L, A[u], B, C);
+                    A[u] = si < nv ? A[u] : INFINITY;
+                }
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    for (u64 k = seek; k != 0; k &= k - 1) {
+                        const int p = __builtin_ctzll(k);
+                        const u64 hits = __ballot(__builtin_fma(from_lane(mul_l, p), A[u], from_lane(add_l, p)) ==
+                                                  from_lane(bc.t, p));
+                        if (hits != 0) {
+                            const uint32_t sv = (uint32_t)from_lane(sdv[u], __builtin_ctzll(hits));
+                            bc.s = lane == p ? sv : bc.s;
+                            seek &= ~(1ull << p);
                         }
                     }
                 }
-                if (lane == p)
-                    bc.s = first < nv ? (uint32_t)s_first : 0u;
             }
         }
         if (mine)
@@ -4241,6 +4295,11 @@ hipError_t kernels_init()
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_score_fused<false>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)g_device.lds_per_cu);
     if (e != hipSuccess) return e;
+    for (const void *k : {reinterpret_cast<const void *>(k_sweep_s<6>), reinterpret_cast<const void *>(k_sweep_s<9>),
+                          reinterpret_cast<const void *>(k_sweep_s<12>)}) {
+        e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, SWEEP_S_PASS * (int)sizeof(double));
+        if (e != hipSuccess) return e;
+    }
     const void *batch_kernels[4] = {
         reinterpret_cast<const void *>(k_batch_t<BATCH_T_PC, BATCH_T_PS, false, false>),
         reinterpret_cast<const void *>(k_batch_t<BATCH_T_PC, BATCH_T_PS, false, true>),
@@ -4389,6 +4448,7 @@ Scratch bind_scratch(void *base, const ScratchLayout &lay)
     S.segA = reinterpret_cast<double *>(b + lay.segA);
     S.segB = reinterpret_cast<double *>(b + lay.segB);
     S.amin = reinterpret_cast<double *>(b + lay.amin);
+    S.minG = reinterpret_cast<double *>(b + lay.minG);
     S.nv = reinterpret_cast<int *>(b + lay.nv);
     S.batch.rec = reinterpret_cast<double *>(b + lay.rec);
     S.batch.tab = reinterpret_cast<double *>(b + lay.tab);
@@ -4483,7 +4543,7 @@ bool plan_tune(const DeviceTables &T, const DeviceGrid &G, bool terms_only, Tune
     // than the thirteen dependent loads of a search in device memory (6.9 us)
     const size_t pair_lds = pairs ? (size_t)2 * G.n_s * D : 0;
     const bool stage_s = G.n_s > 0 && G.n_s <= 1024 && tab_lds + pair_lds + (size_t)G.n_s * D <= kMaxTableLds;
-    p.terms_mode = (pairs ? 1 : 0) | (stage_s ? 2 : 0);
+    p.terms_mode = (pairs ? 1 : 0) | (stage_s ? 2 : 0) | (lanes_s && !terms_only ? 4 : 0);
     p.terms_lds = tab_lds + pair_lds + (stage_s ? (size_t)G.n_s * D : 0);
     // a workgroup stages the whole table: with a big table one workgroup fits a CU, so no
     // more workgroups than CUs
@@ -4571,7 +4631,7 @@ bool plan_tune(const DeviceTables &T, const DeviceGrid &G, bool terms_only, Tune
             // 8 waves per workgroup (two per SIMD, so that two workgroups share a CU); the
             // process counts per wave are chosen so that one workgroup covers all of them if
             // it can
-            const int waves = SWEEP_S_MAX_WAVES;
+            const int waves = SWEEP_S_WAVES;
             p.sweep_gp = G.n_P <= 6 * waves ? 6 : (G.n_P <= 9 * waves ? 9 : 12);
             p.sweep_ptiles = p.sweep_gp == 12 ? (G.n_P + 12 * waves - 1) / (12 * waves) : 1;
             if ((long)T.n_tables * G.n_m * p.sweep_ptiles > kMaxLaunch) return false;
@@ -4608,10 +4668,11 @@ bool plan_tune(const DeviceTables &T, const DeviceGrid &G, bool terms_only, Tune
     p.lay.part = lb.take(D, chain ? nt : 0, n_mu, n_P);
     p.lay.pre = lb.take(D, chain && G.blk_is_prefix ? nt : 0, n_mu, n_P);
     p.lay.rcp = lb.take(D, n_s);
-    p.lay.segC = lb.take(D, nt, n_s);
+    p.lay.segC = lb.take(D, pairs ? nt : 0, n_s);
     p.lay.segA = lb.take(D, pairs ? nt : 0, n_m, n_s);
     p.lay.segB = lb.take(D, pairs ? nt : 0, n_m, n_s);
     p.lay.amin = lb.take(D, pairs ? nt : 0, n_m);
+    p.lay.minG = lb.take(D, lanes_s && !terms_only ? nt : 0, (n_s + 63) / 64);
     p.lay.nv = lb.take(sizeof(int), n_m);
     if (terms_only)
         p.lay.score_rows = lb.take(D, 13, n_m, 2);
@@ -4702,14 +4763,11 @@ hipError_t launch_tune_stage(const TunePlan &p, int stage, const DeviceTables &T
             break;
         if (p.lanes_s) {
             const unsigned rows = (unsigned)T.n_tables * G.n_m;
-            const dim3 threads(64 * SWEEP_S_MAX_WAVES);
-            if (p.sweep_gp == 6)
-                hipLaunchKernelGGL(k_sweep_s<6>, dim3(rows), threads, 0, st, T, G, S, d_out, 1);
-            else if (p.sweep_gp == 9)
-                hipLaunchKernelGGL(k_sweep_s<9>, dim3(rows), threads, 0, st, T, G, S, d_out, 1);
-            else
-                hipLaunchKernelGGL(k_sweep_s<12>, dim3(rows * p.sweep_ptiles), threads, 0, st, T, G, S, d_out,
-                                   p.sweep_ptiles);
+            const dim3 threads(64 * SWEEP_S_WAVES);
+            const int pass = G.n_s < SWEEP_S_PASS ? (G.n_s + 63) / 64 * 64 : SWEEP_S_PASS;
+            const auto kern = p.sweep_gp == 6 ? k_sweep_s<6> : (p.sweep_gp == 9 ? k_sweep_s<9> : k_sweep_s<12>);
+            hipLaunchKernelGGL(kern, dim3(rows * p.sweep_ptiles), threads, (size_t)pass * sizeof(double), st, T, G, S,
+                               d_out, p.sweep_ptiles);
         } else if (p.lanes_p) {
             const bool all = G.mask == 0x1FFFu;
             for (int t0 = 0; t0 < T.n_tables; t0 += 65535) {

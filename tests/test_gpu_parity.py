@@ -679,3 +679,30 @@ def test_random_tiles(seed):
         seed, wl.sizes.shape[1], wl.n_tables, len(wl.m), len(wl.P), int(wl.P[-1]), len(wl.s), wl.strategy_mask)
     print(what, flush=True)
     assert assert_tables_equal(gpu_tune(wl), want, what), "times not bit-identical"
+
+
+# ------------------------------------------------------------------ many candidates, chunks left out by their bounds
+
+@pytest.mark.parametrize("n_s,n_P,shape", [
+    (257, 3, "rise"), (320, 49, "noise"), (1000, 72, "flat"), (4160, 73, "fall"), (8191, 9, "rise"), (8192, 10, "tie"),
+    (8193, 70, "noise"), (16448, 5, "fall"), (20000, 97, "rise"), (9000, 8, "tie"), (70000, 4, "noise"),
+])
+def test_many_candidates_chunks_and_passes(n_s, n_P, shape):
+    # 64 candidates to a chunk, 8192 to a pass, 64 ranges of 1024 remembered: numbers of candidates
+    # at and around these; gap curves whose best segment size sits at either end, wanders, or ties
+    # over many sizes; sizes at which only part of a chunk or of a pass competes
+    rng = np.random.default_rng(n_s + n_P)
+    x = np.array([1.0, 100.0, 700.0, 5000.0, 40000.0, 300000.0])
+    gaps = np.stack([{"rise": 5.0 + 0.01 * x, "flat": np.full(6, 7.0), "fall": 900.0 - 0.002 * x, "tie": x / 4.0,
+                      "noise": 20.0 + 0.02 * x * rng.uniform(0.3, 2.0, 6)}[shape] * f for f in (1.0, 1.5)])
+    step = 8 if n_s < 30000 else 4
+    s = (step * np.arange(1, n_s + 1)).astype(np.uint64)
+    top = int(s[-1])
+    m = np.array([4, 8, 64, 512, 520, 1024, 4096, top // 8 * 4, top, top + 4, 3 * top, 1 << 22, 1 << 30, (1 << 40) + 4],
+                 dtype=np.uint64)
+    P = np.unique(np.concatenate([[2, 3, 4], rng.integers(2, 5000, size=4 * n_P)]))[:n_P].astype(np.uint32)
+    for mask, cap in ((ALL_STRATEGIES_MASK, NO_CAP), (1 << 5, top // 2), ((1 << 2) | (1 << 9), NO_CAP), (0x225, 600)):
+        wl = Workload("chunks", np.repeat(x[None], 2, axis=0), gaps, np.array([3.0, 0.0]), m, P, s, cap, mask)
+        wl.dtype_size = 4
+        want, _ = oracle.tune_workload(wl)
+        assert assert_tables_equal(gpu_tune(wl), want, "%s n_s=%d mask %x" % (shape, n_s, mask)), "times not bit-identical"
