@@ -76,6 +76,29 @@ def test_random_tables(shape, p_same, key_mode):
     check(random_cells(np.random.default_rng(sum(shape) + key_mode), *shape, p_same=p_same), key_mode)
 
 
+def test_slices_of_many_tables_over_a_big_grid():
+    # 262 144 cells leave two slices of the tables, 600 tables more than a slice may hold: three
+    # slices then.  Table t > 0 differs from table 0 in strategy where t % 3 == 0 and the cell is
+    # a multiple of 5, in segment size where t % 7 == 0; its times are 1 + t / 1024 against 1.
+    torch = torch_cuda()
+    nt, n = 600, 262144
+    t = torch.arange(nt, device="cuda").view(-1, 1)
+    c = torch.arange(n, device="cuda").view(1, -1)
+    cells = torch.empty((nt, n, 2), dtype=torch.float64, device="cuda")
+    cells[..., 0] = 1.0 + t / 1024.0
+    keys = cells.view(torch.int64)[..., 1]
+    other = ((t % 3 == 0) & (t > 0) & (c % 5 == 0))
+    keys[:] = torch.where(other, 4, 3) << 32 | torch.where((t % 7 == 0) & (t > 0), 16, 8)
+    shape = np.zeros((1, 1, 512, 512), dtype=oracle.CELL_DTYPE)
+    shape = np.broadcast_to(shape, (nt, 1, 512, 512))
+    for key_mode in (0, 1):
+        agree, dev, tab = gpu_robustness(shape, key_mode, d_cells=cells)
+        same = (~other if key_mode == 0 else ~other & ~((t % 7 == 0) & (t > 0))).cpu().numpy()
+        assert (agree.reshape(-1) == same[1:].sum(0)).all()
+        assert (tab == same.sum(1)).all() and tab[0] == n
+        assert (dev == (nt - 1) / 1024.0).all()
+
+
 def test_optional_outputs_are_left_alone():
     cells = random_cells(np.random.default_rng(3), 7, 2, 11, 13, 0.5)
     want_a, _, _ = orb.robustness(cells, 1)
