@@ -2538,8 +2538,8 @@ __global__ void __launch_bounds__(TILE_THREADS) k_tile(DeviceTables T, DeviceGri
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int t = (int)blockIdx.x / n_tiles, m0 = (int)blockIdx.x % n_tiles * M;
     const int n_m = G.n_m - m0 < M ? G.n_m - m0 : M;           // sizes of this tile
-    const uint32_t mask = G.mask, extra = G.extra;
-    const bool chain = (G.need & (1u << 11)) != 0, binom = (G.need & (1u << 12)) != 0;
+    const uint32_t mask = G.mask;
+    const bool chain = (mask & (1u << 11)) != 0, binom = (mask & (1u << 12)) != 0;
     f64x2 *sAB = reinterpret_cast<f64x2 *>(tile_lds + A.ab);
     double *sC = tile_lds + A.c, *sG = tile_lds + A.gs, *sR = tile_lds + A.rcp, *sGm = tile_lds + A.gm, *sM = tile_lds + A.md;
     double *sAmin = tile_lds + A.amin;
@@ -2719,7 +2719,6 @@ __global__ void __launch_bounds__(TILE_THREADS) k_tile(DeviceTables T, DeviceGri
     const size_t plane = (size_t)G.n_m * n_P;
     plogp_cell_dev *const o0 = out + (size_t)t * G.n_ops * plane + (size_t)m0 * n_P;
     const bool has_b = (mask & 0x3FFu) != 0, has_s = (mask & 0x1C00u) != 0;
-    const uint32_t gather = (extra & 7u) << 10;
     const int dm = TILE_THREADS / n_P, dp = TILE_THREADS % n_P;
     int ml = tid / n_P, pi = tid % n_P;
     for (int e0 = tid - lane; e0 < n_m * n_P; e0 += TILE_THREADS) {
@@ -2769,23 +2768,8 @@ __global__ void __launch_bounds__(TILE_THREADS) k_tile(DeviceTables T, DeviceGri
         }
         const double s11 = chain ? tot[(int)((P - 1u) / SUM_BLOCK) * M + mr] + part[e] : 0.0;
         const double s12 = binom ? sum2[mr * (cl_max + 1) + cli] : 0.0;
-        if (has_s) {
-            if (active)
-                store_cell(o, decide_scatter(mask, q, cl, gm, L, s11, s12));
-            o += plane;
-        }
-        if (gather) {                          // the rows of Table 2 under the ids of their Gather twins
-            Best b = decide_scatter(gather, q, cl, gm, L, s11, s12);
-            b.id += 3u;
-            if (active)
-                store_cell(o, b);
-            o += plane;
-        }
-        if (extra & 0x18u) {
-            const Best b = decide_barrier(extra, q, fl, cl, L, g1);
-            if (active)
-                store_cell(o, b);
-        }
+        if (has_s && active)
+            store_cell(o, decide_scatter(mask, q, cl, gm, L, s11, s12));
         ml += dm;
         pi += dp;
         if (pi >= n_P) {
@@ -4504,7 +4488,7 @@ bool plan_tune(const DeviceTables &T, const DeviceGrid &G, bool terms_only, Tune
     // (118), 15 000 x 256 75 (61).
     const bool by_row = fast_ok && use_row_path(T, G) &&
                         (G.n_P >= 512 || (long)T.n_tables * G.n_m < ROW_MAX_ROWS * n_cu);
-    const int tile_m = terms_only || by_row ? 0 : tile_sizes(T, G);
+    const int tile_m = fast_ok && !by_row ? tile_sizes(T, G) : 0;
     if (by_row) {
         p.path = TUNE_ROW;
         // two process counts per lane when there are more groups of 64 than waves
