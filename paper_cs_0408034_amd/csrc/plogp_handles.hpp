@@ -23,7 +23,7 @@ int ensure_init();
 struct plogp_table {
     size_t n_tables = 0, n = 0;
     bool shared_x = false;      // every table has the sample sizes of the first one
-    double *d_x = nullptr, *d_y = nullptr, *d_slope = nullptr, *d_L = nullptr;
+    double *d_x = nullptr, *d_y = nullptr, *d_slope = nullptr, *d_L = nullptr;    // one allocation, from d_x
     plogp::DeviceTables view() const
     {
         plogp::DeviceTables v;
@@ -49,6 +49,7 @@ struct plogp_grid {
     uint64_t s_cap = 0;
     uint32_t mask = 0;
     int n_ops = 0, n_blk = 0, last_terms = 0, cl_max = 0;
+    void *d_block = nullptr;    // the one allocation that holds the arrays below
     uint64_t *d_m = nullptr, *d_s = nullptr, *d_mu = nullptr;
     uint32_t *d_P = nullptr;
     int *d_m_map = nullptr;
