@@ -2350,7 +2350,8 @@ constexpr int TILE_MAX_M = TILE_THREADS / 8;
 constexpr int TILE_NS = 24;              // candidates at most
 constexpr int TILE_MAX_BLK = 32;         // blocks of the chain sum at most
 constexpr size_t TILE_STATIC_LDS = 256;  // room for the counters
-constexpr long TILE_MIN_ROWS = 12;       // (table, m) rows per compute unit at least
+constexpr long TILE_MIN_ROWS = 16;       // (table, m) rows per compute unit at least (more than TILE_FEW_N samples: twice)
+constexpr int TILE_FEW_N = 512;
 
 // Where the arrays of a workgroup start in LDS, in 8-byte slots.  The lists of the chain items lie
 // where A and B of every (m, s) go afterwards.
@@ -2796,7 +2797,7 @@ constexpr int ROW_MAX_BLK = 32;          // at most 2048 terms of the chain sum
 constexpr int ROW_NS = 64;               // candidates at most
 constexpr int ROW_SPAD = ROW_NS + 8;     // the candidate loops read up to 7 entries past the last
 constexpr int ROW_MAX_N = 512;           // samples at most (LDS per workgroup stays small)
-constexpr long ROW_MAX_ROWS = 32;        // fewer than 512 process counts: (table, m) rows per compute unit
+constexpr long ROW_MAX_ROWS = 32;        // (table, m) rows per compute unit: 256 to 511 process counts (fewer: half)
 
 static size_t row_lds_bytes(int n, int n_blk, int n_P)
 {
@@ -4358,7 +4359,7 @@ hipError_t launch_eval(const DeviceTables &T, int table, int strategy, const uin
 // does once per table outweighs them (4000 rows: 27 us with 32 sizes a tile, 43 with eight).
 static int tile_sizes(const DeviceTables &T, const DeviceGrid &G)
 {
-    if ((long)T.n_tables * G.n_m < TILE_MIN_ROWS * device_info().n_cu || G.n_s > TILE_NS || G.n_blk > TILE_MAX_BLK)
+    if ((long)T.n_tables * G.n_m < (T.n <= TILE_FEW_N ? 1 : 2) * TILE_MIN_ROWS * device_info().n_cu || G.n_s > TILE_NS || G.n_blk > TILE_MAX_BLK)
         return 0;
     const size_t lds_per_cu = device_info().lds_per_cu;
     const size_t table = ((size_t)4 * T.n + CHAIN_PAD) * sizeof(double);
@@ -4377,12 +4378,12 @@ static int tile_sizes(const DeviceTables &T, const DeviceGrid &G)
     return (G.n_m + tiles - 1) / tiles;
 }
 
-// Few tables, few candidates, few blocks of the chain sum and many process counts: one
-// workgroup per (table, m) does the whole path (k_row).
+// Few candidates, few blocks of the chain sum, few samples: one workgroup per (table, m) can do
+// the whole path (k_row).
 static bool use_row_path(const DeviceTables &T, const DeviceGrid &G)
 {
-    return G.n_s <= ROW_NS && G.n_blk <= ROW_MAX_BLK && T.n <= ROW_MAX_N && G.n_P >= 256 &&
-           (long)T.n_tables * G.n_m >= 256 && (long)T.n_tables * G.n_m <= 65535 * 16;
+    return G.n_s <= ROW_NS && G.n_blk <= ROW_MAX_BLK && T.n <= ROW_MAX_N &&
+           (long)T.n_tables * G.n_m <= 65535 * 16;
 }
 
 // LDS of a k_batch_t workgroup: 64 tables by interval, their g(s), the output staging.
@@ -4497,11 +4498,15 @@ bool plan_tune(const DeviceTables &T, const DeviceGrid &G, bool terms_only, Tune
         p.lay.total = lb.at;
         return !lb.too_big;
     }
-    // A row per workgroup while there are few rows or many process counts, else a tile of rows:
-    // 4000 rows x 300 process counts 28.7 us (tiles: 33.9), 10 000 x 300 62 (48), 10 000 x 1000 82
-    // (118), 15 000 x 256 75 (61).
+    // A row per workgroup while there are few rows or many process counts.  It is one launch where
+    // the staged path has two or three, and a small job is their latency: 64 sizes x 49 process
+    // counts, 13 candidates 5.6 us (staged: 10 to 13), 20 x 16 x 34 7.5 (27), 1000 x 40 (up to
+    // 1500) x 34 9.5 (16), 3000 x 24 x 34 17 (32), 4000 x 36 x 34 28 (30); 6000 rows 39 (39) and
+    // 10 000 62 (55).  Against tiles: 4000 rows x 12 process counts 20 (21), x 127 23 (30), 6000 x 36
+    // 39 (26); 4000 x 300 29 (34), 10 000 x 300 62 (48); 10 000 x 1000 82 (118).
+    const long rows = (long)T.n_tables * G.n_m;
     const bool by_row = fast_ok && use_row_path(T, G) &&
-                        (G.n_P >= 512 || (long)T.n_tables * G.n_m < ROW_MAX_ROWS * n_cu);
+                        (G.n_P >= 512 || rows < (G.n_P >= 256 ? ROW_MAX_ROWS : ROW_MAX_ROWS / 2) * n_cu);
     const int tile_m = fast_ok && !by_row ? tile_sizes(T, G) : 0;
     if (by_row) {
         p.path = TUNE_ROW;

@@ -648,12 +648,12 @@ def test_chain_row_at_points_around_block_ends(n_x, n_points, p_top):
 # ------------------------------------------------------------------ tiles of message sizes
 
 def _tile_problem(rng, seed):
-    """A job for the path whose workgroups take a table and up to 32 message sizes: at least 3072
-    (table, m) rows (12 per compute unit), at most 24 candidates, at most 32 blocks of the chain
-    sum; tables with sample sizes of their own."""
+    """A job for the path whose workgroups take a table and up to 32 message sizes: at least 4096
+    (table, m) rows (16 per compute unit; 32 with more than 512 samples), at most 24 candidates, at
+    most 32 blocks of the chain sum; tables with sample sizes of their own."""
     n = int([2, 3, 9, 57, 120, 300, 700, 1500][seed % 8])
     n_m = int([1, 31, 32, 33, 65, 100, 200, 47][seed % 8])
-    n_tables = -(-3072 // n_m) + int(rng.integers(0, 9))
+    n_tables = -(-(4096 if n <= 512 else 8192) // n_m) + int(rng.integers(0, 9))
     x = np.floor(np.cumsum(rng.integers(1, 3000 if n < 400 else 60, size=(n_tables, n)).astype(np.float64), axis=1))
     gaps = np.abs(20.0 + x * rng.uniform(0.02, 0.1, size=(n_tables, 1)) * (1.0 + 0.4 * rng.standard_normal(x.shape)))
     L = rng.uniform(0.0, 90.0, size=n_tables)
@@ -706,3 +706,23 @@ def test_many_candidates_chunks_and_passes(n_s, n_P, shape):
         wl.dtype_size = 4
         want, _ = oracle.tune_workload(wl)
         assert assert_tables_equal(gpu_tune(wl), want, "%s n_s=%d mask %x" % (shape, n_s, mask)), "times not bit-identical"
+
+
+@pytest.mark.parametrize("n_m,n_P,p_hi,n_s,n", [
+    (1, 1, 2, 0, 2), (3, 2, 66, 1, 9), (64, 49, 50, 13, 21), (20, 63, 65, 64, 64), (33, 64, 129, 8, 200),
+    (5, 65, 2048, 34, 512), (255, 16, 17, 34, 64), (257, 127, 128, 63, 64), (100, 255, 700, 9, 40),
+])
+@pytest.mark.parametrize("mask", [ALL_STRATEGIES_MASK, 0xA9, 0x3FF, 0x1C00, 0x0A25])
+def test_small_jobs_a_row_per_workgroup(n_m, n_P, p_hi, n_s, n, mask):
+    # the path whose workgroups take a (table, m) row, from one row and one process count on: lanes,
+    # groups of 64 process counts and candidates at and around their limits, two tables
+    rng = np.random.default_rng(n_m * 1000 + n_P)
+    x = np.unique(np.floor(np.cumsum(rng.integers(1, 900, size=n).astype(np.float64))))
+    gaps = np.abs(25.0 + np.outer([0.03, 0.11], x) * (1.0 + 0.3 * rng.standard_normal((2, len(x)))))
+    m = np.maximum(np.floor(np.exp(rng.uniform(np.log(8.0), np.log(40.0 * x[-1]), size=n_m)) / 8.0) * 8.0, 8.0)
+    P = np.sort(rng.choice(np.arange(2, p_hi + 1), size=n_P, replace=False)).astype(np.uint32)
+    s = (8 * np.sort(rng.choice(np.arange(1, 4000), size=n_s, replace=False))).astype(np.uint64)
+    wl = Workload("small rows", np.repeat(x[None], 2, axis=0), gaps, np.array([4.0, 60.0]), m.astype(np.uint64), P, s,
+                  NO_CAP, mask)
+    want, _ = oracle.tune_workload(wl)
+    assert assert_tables_equal(gpu_tune(wl), want, "small rows, mask %x" % mask), "times not bit-identical"
