@@ -52,7 +52,6 @@ UNSEG_FLOPS = {0: 3, 1: 3, 3: 3, 4: 3, 6: 4, 7: 4, 8: 4, 10: 3, 11: 4, 12: 3}
 # are taken again; the line names its source.
 OFFLINE_COUNTERS = {
     2: {"kernel": "k_row", "hbm_bytes": 0.336e6 + 34.317e6, "valu_insts": 4.864e6},
-    3: {"kernel": "k_sweep_s", "hbm_bytes": 4.022e6 + 2.681e6, "valu_insts": 33.84e6},
     4: {"kernel": "k_batch_t", "hbm_bytes": 87.199e6 + 1966.357e6, "valu_insts": 175.7e6},
     5: {"kernel": "k_chain_blocks", "hbm_bytes": 1.840e6 + 73.784e6, "valu_insts": 25.60e6},
 }
@@ -81,6 +80,11 @@ def algorithmic_work(wl):
     sweep = 3 * pairs * n_P * n_seg + 5 * pairs + unseg * nt * n_m * n_P
     seg5 = 1 if (mask >> 5) & 1 else 0
     sweep_x = 3 * pairs * n_P * seg5 + (pairs if mask & 0x204 else 0) + 5 * pairs + unseg * nt * n_m * n_P
+    if n_s > 256:
+        # the sweep over many candidates bounds chunks of 64 of them (two bounds of 3 flop) and leaves
+        # out most; which it evaluates depends on the data and is not counted, and a fraction by
+        # delivered work would mean nothing
+        sweep = sweep_x = 6 * (pairs // 64) * n_P * seg5 + 6 * pairs + unseg * nt * n_m * n_P
     # the planes of Gather and Barrier (rows beyond the tables; none in the five configs)
     planes = [bool(mask & b) for b in (0x3FF, 0x1C00, 0xE000, 0x30000)]
     more_bytes = c["output_bytes"] * sum(planes[2:]) // max(sum(planes), 1)
