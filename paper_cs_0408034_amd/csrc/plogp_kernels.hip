@@ -2236,10 +2236,15 @@ k_sweep_s(DeviceTables T, DeviceGrid G, Scratch S, plogp_cell_dev *out, int n_pt
         u64 seek = __ballot(mine && (bc.id == 2u || bc.id == 9u));
         if (seek != 0) {
             // The first candidate whose value equals the minimum, for all these cells at once.
-            // With a single pass the chunks' minima of B are still there: A = g(s) k is not below
-            // (min B + min g) of its chunk but for roundings (three of them, half an ulp each), so
-            // few chunks can hold it.  After several passes the first range whose minimum of A gives
-            // the value is walked from its start.
+            // With a single pass the chunks' minima of B are still there: exactly, g(s) k is
+            // g(s) (k - 1) + g(s), so A is not below min B + min g of its chunk but for roundings, and
+            // few chunks can hold it.  g(s) has either sign (a falling table goes on falling past its
+            // last sample).  Where it is not negative, A >= (B + g)(1 - 2u), u = 2^-53, and a sum below
+            // zero is below A anyhow; where it is, A >= B + g - 2u(|B| + |g|), and neither of these two
+            // is larger than that of the minimum, which is not above it.  So A needs 2u(|min B| +
+            // |min g|) of room and the two roundings of the bound itself half of that each; it is given
+            // 8u.  After several passes the first range whose minimum of A gives the value is walked
+            // from its start.
             auto from_lane = [&](double v, int l) {
                 return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
                                         __builtin_amdgcn_readlane(__double2loint(v), l));
@@ -2256,7 +2261,8 @@ k_sweep_s(DeviceTables T, DeviceGrid G, Scratch S, plogp_cell_dev *out, int n_pt
                     may[h] = 0;
                     if (64 * h >= n_chunks)
                         continue;
-                    const double low = c < n_chunks ? (minB[c] + minG[c]) * (1.0 - 0x1p-50) : INFINITY;
+                    const double lb = c < n_chunks ? minB[c] : INFINITY, lg = c < n_chunks ? minG[c] : 0.0;
+                    const double low = (lb + lg) - 0x1p-50 * (fabs(lb) + fabs(lg));
                     for (u64 k = seek; k != 0; k &= k - 1) {
                         const int p = __builtin_ctzll(k);
                         may[h] |= __ballot(__builtin_fma(from_lane(mul_l, p), low, from_lane(add_l, p)) <=

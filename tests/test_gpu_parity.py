@@ -708,6 +708,25 @@ def test_many_candidates_chunks_and_passes(n_s, n_P, shape):
         assert assert_tables_equal(gpu_tune(wl), want, "%s n_s=%d mask %x" % (shape, n_s, mask)), "times not bit-identical"
 
 
+@pytest.mark.parametrize("n_s,last", [(600, 1000.0), (8192, 14000.0), (9000, 14000.0), (17000, 40000.0)])
+@pytest.mark.parametrize("mask", [ALL_STRATEGIES_MASK, 0x204, 1 << 2, 1 << 9])
+def test_many_candidates_whose_gap_falls_below_zero(n_s, last, mask):
+    # samples are not negative, but the line through the last two goes on falling beyond them: the
+    # candidates' g changes sign inside the list, and the best of rows 2 and 9 is one of large |g| k
+    rng = np.random.default_rng(n_s)
+    x = np.array([1.0, last])
+    gaps = np.array([[104.0, 52.0], [103.64280263405897, 51.69110966029943], [80.0, 0.5], [60.0, 59.0]])
+    s = (8 * np.arange(1, n_s + 1)).astype(np.uint64)
+    ends = 8 * (64 * rng.integers(1, n_s // 64, 24) + 1)            # the last competing chunk holds one candidate
+    m = np.unique(np.concatenate([ends, ends - 8, 8 * rng.integers(1, 3 * n_s, 24), [3080]])).astype(np.uint64)
+    P = np.array([2, 3, 4, 7, 31, 64, 302, 1023, 1500], dtype=np.uint32)
+    wl = Workload("falling", np.repeat(x[None], 4, axis=0), gaps, np.array([3.0, 3.0, 0.0, 900.0]), m, P, s, NO_CAP, mask)
+    want, _ = oracle.tune_workload(wl)
+    segmented = (want["strategy"][:, 0] == 2) | (want["strategy"][:, 0] == 9)
+    assert (want["time"][:, 0][segmented] < 0.0).sum() > 100
+    assert assert_tables_equal(gpu_tune(wl), want, "falling n_s=%d mask %x" % (n_s, mask)), "times not bit-identical"
+
+
 @pytest.mark.parametrize("n_m,n_P,p_hi,n_s,n", [
     (1, 1, 2, 0, 2), (3, 2, 66, 1, 9), (64, 49, 50, 13, 21), (20, 63, 65, 64, 64), (33, 64, 129, 8, 200),
     (5, 65, 2048, 34, 512), (255, 16, 17, 34, 64), (257, 127, 128, 63, 64), (100, 255, 700, 9, 40),
