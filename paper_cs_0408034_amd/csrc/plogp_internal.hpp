@@ -230,6 +230,10 @@ hipError_t launch_score_stage(int stage, const TunePlan &plan, const DeviceTable
                               const Scratch &S, double *rows, const double *d_meas, const uint32_t *d_seg,
                               double *d_pred, void *d_verdict, void *d_scores, hipStream_t st);
 
+// Tables (beside table 0) that one workgroup of the robustness summary walks: n_tables up to 2^24
+// make at most 65535 slices of that length, the limit of a launch in y.
+int robust_chunk(size_t cells, int n_tables);
+
 // Robustness summary of n_tables decision tables of `cells` records each (table 0 is the
 // reference).  d_max_dev and d_table_agree may be null.  cells < 2^40 and n_tables >= 1 are
 // the caller's to check.

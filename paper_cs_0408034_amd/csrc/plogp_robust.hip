@@ -32,7 +32,8 @@ struct RobustShape {
 typedef double f64x2_t __attribute__((ext_vector_type(2)));
 
 constexpr long ROBUST_FILL = 8;          // workgroups per compute unit
-constexpr int ROBUST_MAX_CHUNK = 256;    // tables of a slice (their counts are kept in LDS)
+constexpr int ROBUST_MAX_CHUNK = 264;    // tables of a slice (their counts are kept in LDS): 65535 slices in
+                                         // y are enough for 2^24 tables
 
 __global__ void __launch_bounds__(256) k_robust_clear(RobustShape R, uint32_t *agree, u64 *max_dev,
                                                       uint32_t *table_agree)
@@ -127,6 +128,20 @@ __global__ void __launch_bounds__(256) k_robust(RobustShape R, const f64x2_t *__
 
 }  // namespace
 
+int robust_chunk(size_t cells, int n_tables)
+{
+    if (n_tables < 2) return 1;
+    // enough workgroups to fill the chip: slices of the tables when the grid is small
+    const u64 cell_wg = (cells + 255) / 256;
+    long slices = (long)((ROBUST_FILL * device_info().n_cu + cell_wg - 1) / cell_wg);
+    if (slices > n_tables - 1) slices = n_tables - 1;
+    if (slices < 1) slices = 1;
+    long chunk = (n_tables - 1 + slices - 1) / slices;
+    if (chunk > 8)
+        chunk = (chunk + 7) / 8 * 8;               // whole groups of records in flight
+    return (int)(chunk < ROBUST_MAX_CHUNK ? chunk : ROBUST_MAX_CHUNK);
+}
+
 hipError_t launch_robustness(size_t cells, int n_tables, const plogp_cell_dev *d_cells, int key_mode,
                              uint32_t *d_agree, double *d_max_dev, uint32_t *d_table_agree,
                              hipStream_t st)
@@ -136,18 +151,8 @@ hipError_t launch_robustness(size_t cells, int n_tables, const plogp_cell_dev *d
     R.n_tables = n_tables;
     R.strict = key_mode == 1 ? 1 : 0;
     const u64 cell_wg = (cells + 255) / 256;
-    // enough workgroups to fill the chip: slices of the tables when the grid is small
-    long slices = 1;
-    if (n_tables > 1) {
-        slices = (long)((ROBUST_FILL * device_info().n_cu + cell_wg - 1) / cell_wg);
-        if (slices > n_tables - 1) slices = n_tables - 1;
-        if (slices < 1) slices = 1;
-    }
-    long chunk = n_tables > 1 ? (n_tables - 1 + slices - 1) / slices : 1;
-    if (chunk > 8)
-        chunk = (chunk + 7) / 8 * 8;               // whole groups of records in flight
-    R.t_chunk = (int)(chunk < ROBUST_MAX_CHUNK ? chunk : ROBUST_MAX_CHUNK);
-    slices = n_tables > 1 ? (n_tables - 1 + R.t_chunk - 1) / R.t_chunk : 0;
+    R.t_chunk = robust_chunk(cells, n_tables);
+    const long slices = n_tables > 1 ? (n_tables - 1 + R.t_chunk - 1) / R.t_chunk : 0;
     u64 clear_items = cells > (u64)n_tables ? cells : (u64)n_tables;
     {
         hipLaunchKernelGGL(k_robust_clear, dim3((unsigned)((clear_items + 255) / 256)), dim3(256), 0, st,

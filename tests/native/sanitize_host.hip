@@ -116,6 +116,14 @@ int main()
                 CHECK(l.segA != 0 && l.segB != 0 && l.amin != 0 && G.n_s > 0);
         }
     }
+
+    // ---- slices of tables of the robustness summary: a launch dimension, at any number of tables
+    const int n_robust[] = {1, 2, 9, 2001, 16776960, 16776961, 16776962, 1 << 24};
+    for (int n : n_robust)
+        for (size_t cells = 1; cells <= ((size_t)1 << 32) - 256; cells = cells * 3 + 5) {
+            const int chunk = plogp::robust_chunk(cells, n);
+            CHECK(chunk >= 1 && (n - 1 + (long)chunk - 1) / chunk <= 65535);
+        }
     std::printf("host sanitizer pass: %ld plans laid out\n", plans);
     return 0;
 }

@@ -99,6 +99,24 @@ def test_slices_of_many_tables_over_a_big_grid():
         assert (dev == (nt - 1) / 1024.0).all()
 
 
+def test_the_largest_number_of_tables():
+    # 2^24 tables of one cell: as many slices as a launch may have in y, each as long as it may be.
+    # Table t differs from table 0 in strategy where t % 3 == 1, its times are 1 + t / 2^24.
+    torch = torch_cuda()
+    nt = 1 << 24
+    t = torch.arange(nt, device="cuda")
+    cells = torch.empty((nt, 2), dtype=torch.float64, device="cuda")
+    cells[:, 0] = 1.0 + t.double() / nt
+    cells.view(torch.int64)[:, 1] = torch.where(t % 3 == 1, 4, 3) << 32 | 8
+    shape = np.broadcast_to(np.zeros((1, 1, 1, 1), dtype=oracle.CELL_DTYPE), (nt, 1, 1, 1))
+    for with_tables in (True, False):
+        agree, dev, tab = gpu_robustness(shape, 0, with_tables=with_tables, d_cells=cells)
+        assert agree[0, 0, 0] == nt - 1 - (nt + 1) // 3
+        assert dev[0, 0, 0] == (nt - 1) / nt
+        if with_tables:
+            assert (tab == (t % 3 != 1).cpu().numpy()).all()
+
+
 def test_optional_outputs_are_left_alone():
     cells = random_cells(np.random.default_rng(3), 7, 2, 11, 13, 0.5)
     want_a, _, _ = orb.robustness(cells, 1)
