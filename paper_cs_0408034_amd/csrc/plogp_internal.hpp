@@ -158,7 +158,7 @@ struct TunePlan {
     int chain, chain_row, together, row_together, terms_in_chain, chain_threads;
     int n_single, n_search, chain_wg, n_chain_wg, n_mgroups;
     size_t terms_lds, chain_lds, both_lds, crow_lds;
-    int sweep_gp, sweep_ptiles;    // lanes over s
+    int sweep_gp, sweep_dense, sweep_ptiles;    // lanes over s
     int ppl, n_pg, n_w;            // lanes over P
     int n_mg, n_pcg;               // lanes over m
 };

@@ -1998,11 +1998,11 @@ __global__ void __launch_bounds__(256) k_sweep_p(DeviceTables T, DeviceGrid G, S
 constexpr int SWEEP_S_WAVES = 8;
 constexpr int SWEEP_S_PASS = 8192;      // candidates per pass: 64 KB of LDS, two workgroups per CU
 constexpr int SWEEP_S_CHUNKS = SWEEP_S_PASS / 64;
-constexpr int SWEEP_S_RANGE = SWEEP_S_PASS / SWEEP_S_WAVES;   // candidates a wave fills
+constexpr int SWEEP_S_RANGE = SWEEP_S_PASS / SWEEP_S_WAVES;   // candidates of a whole pass that a wave fills
 constexpr int SWEEP_S_RANGES = 64;      // ranges whose minimum of A is remembered
 
-template <int GP>
-__global__ void __launch_bounds__(64 * SWEEP_S_WAVES, 4)
+template <int GP, int OCC>
+__global__ void __launch_bounds__(64 * SWEEP_S_WAVES, OCC)
 k_sweep_s(DeviceTables T, DeviceGrid G, Scratch S, plogp_cell_dev *out, int n_ptiles)
 {
     extern __shared__ __align__(16) double sweep_lds[];          // B of the candidates of a pass
@@ -2068,35 +2068,43 @@ k_sweep_s(DeviceTables T, DeviceGrid G, Scratch S, plogp_cell_dev *out, int n_pt
         const int n_chunks = (n_here + 63) >> 6;
         if (s0 > 0)
             __syncthreads();                                      // every wave is done with the pass before
-        // this wave's range of the pass, four chunks at a time (their loads side by side)
+        // this wave's range of the pass, four chunks at a time (their loads side by side): an eighth
+        // of the chunks when one pass takes them all (1000 candidates x 250 sizes x 69 process counts:
+        // 18.2 us, 19.3 when the first wave fills all 1000), SWEEP_S_RANGE candidates else, so that a
+        // range whose minimum is remembered below has a place of its own
+        const int per_wave = nv <= SWEEP_S_PASS ? (n_chunks + SWEEP_S_WAVES - 1) / SWEEP_S_WAVES : SWEEP_S_RANGE / 64;
+        const int c_end = (wave + 1) * per_wave < n_chunks ? (wave + 1) * per_wave : n_chunks;
         double range_A = INFINITY;
-        for (int c0 = wave * (SWEEP_S_RANGE / 64); c0 < (wave + 1) * (SWEEP_S_RANGE / 64) && c0 < n_chunks; c0 += 4) {
+        for (int c0 = wave * per_wave; c0 < c_end; c0 += 4) {
             const int first = s0 + 64 * c0;
             auto fill = [&](bool whole) {                         // whole: all 256 candidates compete
-                double f_s[4], f_rcp[4], f_gs[4];
+                uint32_t f_s[4];
+                double f_rcp[4], f_gs[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
+                    if (!whole && c0 + u >= c_end)
+                        continue;
                     const int si = first + 64 * u + lane, idx = whole || si < nv ? si : nv - 1;
-                    f_s[u] = (double)*reinterpret_cast<const uint32_t *>(G.s + idx);       // below 2^32
+                    f_s[u] = *reinterpret_cast<const uint32_t *>(G.s + idx);               // below 2^32
                     f_rcp[u] = S.rcp[idx];
                     f_gs[u] = gs[idx];
                 }
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int c = c0 + u;
+                    if (!whole && c >= c_end)
+                        continue;
                     double A, B, C;
-                    segment_terms(md, f_s[u], f_rcp[u], f_gs[u], L, A, B, C);
+                    segment_terms(md, (double)f_s[u], f_rcp[u], f_gs[u], L, A, B, C);
                     range_A = min_f64(range_A, A);                // (past the end: the last one again)
-                    if (whole || c < n_chunks) {
-                        sB[64 * c + lane] = whole || first + 64 * u + lane < nv ? B : INFINITY;
-                        if (lane == 0) {
-                            firstB[c] = B;
-                            firstC[c] = C;
-                        }
+                    sB[64 * c + lane] = whole || first + 64 * u + lane < nv ? B : INFINITY;
+                    if (lane == 0) {
+                        firstB[c] = B;
+                        firstC[c] = C;
                     }
                 }
             };
-            if (first + 256 <= nv)
+            if (c0 + 4 <= c_end && first + 256 <= nv)
                 fill(true);
             else
                 fill(false);
@@ -2326,6 +2334,25 @@ k_sweep_s(DeviceTables T, DeviceGrid G, Scratch S, plogp_cell_dev *out, int n_pt
         return;
     if (mask & 0x1C00u)
         store_cell(o, decide_scatter(mask, qv, (double)cli, gm, L, s11, s12));
+}
+
+// The kernel for gp process counts per wave.  Few process counts go two or four to a wave, so that
+// more waves take part (10 of them, 1000 candidates x 1500 sizes: the call 28 us by two, 34 by
+// six).  Up to four, registers allow three workgroups per CU; six fit only if four registers are
+// spilled, which pays where three workgroups find work and room in LDS (`dense`; 40 process counts,
+// 1000 candidates x 1500 sizes: 39 us with two workgroups, 36 with three; 8192 candidates, two
+// workgroups either way: 60 without the spilling, 62 with it).
+static auto sweep_s_kernel(int gp, bool dense)
+{
+    return gp == 2 ? k_sweep_s<2, 6> : gp == 4 ? k_sweep_s<4, 6> : gp == 6 ? (dense ? k_sweep_s<6, 6> : k_sweep_s<6, 4>)
+           : gp == 9 ? k_sweep_s<9, 4> : k_sweep_s<12, 4>;
+}
+
+// LDS of a workgroup: B of the candidates of a pass; with_static: the arrays the kernel declares too.
+static size_t sweep_s_lds(int n_s, bool with_static)
+{
+    const int pass = n_s < SWEEP_S_PASS ? (n_s + 63) / 64 * 64 : SWEEP_S_PASS;
+    return ((size_t)pass + (with_static ? 3 * SWEEP_S_CHUNKS + SWEEP_S_RANGES + SWEEP_S_WAVES : 0)) * sizeof(double);
 }
 
 // ---- whole path of a tile of message sizes of one table in one workgroup -------
@@ -4300,11 +4327,12 @@ hipError_t kernels_init()
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_score_fused<false>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)g_device.lds_per_cu);
     if (e != hipSuccess) return e;
-    for (const void *k : {reinterpret_cast<const void *>(k_sweep_s<6>), reinterpret_cast<const void *>(k_sweep_s<9>),
-                          reinterpret_cast<const void *>(k_sweep_s<12>)}) {
-        e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, SWEEP_S_PASS * (int)sizeof(double));
-        if (e != hipSuccess) return e;
-    }
+    for (const int gp : {2, 4, 6, 9, 12})
+        for (const bool dense : {false, true}) {
+            const void *k = reinterpret_cast<const void *>(sweep_s_kernel(gp, dense));
+            e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, SWEEP_S_PASS * (int)sizeof(double));
+            if (e != hipSuccess) return e;
+        }
     const void *batch_kernels[4] = {
         reinterpret_cast<const void *>(k_batch_t<BATCH_T_PC, BATCH_T_PS, false, false>),
         reinterpret_cast<const void *>(k_batch_t<BATCH_T_PC, BATCH_T_PS, false, true>),
@@ -4637,11 +4665,14 @@ bool plan_tune(const DeviceTables &T, const DeviceGrid &G, bool terms_only, Tune
     }
     if (!terms_only) {
         if (lanes_s) {
-            // 8 waves per workgroup (two per SIMD, so that two workgroups share a CU); the
-            // process counts per wave are chosen so that one workgroup covers all of them if
-            // it can
+            // 8 waves per workgroup (two per SIMD, so that two or three workgroups share a CU);
+            // as few process counts per wave as let one workgroup cover all of them, if it can
             const int waves = SWEEP_S_WAVES;
-            p.sweep_gp = G.n_P <= 6 * waves ? 6 : (G.n_P <= 9 * waves ? 9 : 12);
+            p.sweep_gp = 12;
+            for (int gp : {9, 6, 4, 2})
+                if (G.n_P <= gp * waves) p.sweep_gp = gp;
+            // three workgroups per CU where there are enough of them and their LDS leaves room
+            p.sweep_dense = (long)T.n_tables * G.n_m > 2 * n_cu && 3 * sweep_s_lds(G.n_s, true) <= dev.lds_per_cu;
             p.sweep_ptiles = p.sweep_gp == 12 ? (G.n_P + 12 * waves - 1) / (12 * waves) : 1;
             if ((long)T.n_tables * G.n_m * p.sweep_ptiles > kMaxLaunch) return false;
         } else if (lanes_p) {
@@ -4773,10 +4804,9 @@ hipError_t launch_tune_stage(const TunePlan &p, int stage, const DeviceTables &T
         if (p.lanes_s) {
             const unsigned rows = (unsigned)T.n_tables * G.n_m;
             const dim3 threads(64 * SWEEP_S_WAVES);
-            const int pass = G.n_s < SWEEP_S_PASS ? (G.n_s + 63) / 64 * 64 : SWEEP_S_PASS;
-            const auto kern = p.sweep_gp == 6 ? k_sweep_s<6> : (p.sweep_gp == 9 ? k_sweep_s<9> : k_sweep_s<12>);
-            hipLaunchKernelGGL(kern, dim3(rows * p.sweep_ptiles), threads, (size_t)pass * sizeof(double), st, T, G, S,
-                               d_out, p.sweep_ptiles);
+            const auto kern = sweep_s_kernel(p.sweep_gp, p.sweep_dense != 0);
+            hipLaunchKernelGGL(kern, dim3(rows * p.sweep_ptiles), threads, sweep_s_lds(G.n_s, false), st, T, G, S, d_out,
+                               p.sweep_ptiles);
         } else if (p.lanes_p) {
             const bool all = G.mask == 0x1FFFu;
             for (int t0 = 0; t0 < T.n_tables; t0 += 65535) {

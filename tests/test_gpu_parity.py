@@ -708,6 +708,25 @@ def test_many_candidates_chunks_and_passes(n_s, n_P, shape):
         assert assert_tables_equal(gpu_tune(wl), want, "%s n_s=%d mask %x" % (shape, n_s, mask)), "times not bit-identical"
 
 
+@pytest.mark.parametrize("n_P", [16, 17, 32, 33, 48, 49, 72])
+@pytest.mark.parametrize("n_m,n_s", [(256, 577), (257, 577), (300, 5500)])
+def test_many_candidates_groups_of_process_counts(n_P, n_m, n_s):
+    # a wave takes 2, 4, 6 or 9 process counts, eight waves all of them; more than 512 (table, size)
+    # rows and LDS for three workgroups per compute unit (up to about 6500 candidates) take a
+    # kernel of fewer registers.  577 candidates: ten chunks, two to a wave and none to the last three
+    rng = np.random.default_rng(n_P * 1000 + n_m)
+    x = np.array([1.0, 90.0, 2000.0, 30000.0, 500000.0])
+    gaps = 20.0 + 0.02 * x * rng.uniform(0.3, 2.0, (2, 5))
+    m = (8 * np.unique(np.floor(np.exp(rng.uniform(0.0, np.log(1 << 20), 2 * n_m))))[:n_m]).astype(np.uint64)
+    m = np.concatenate([m, 8 * rng.integers(1, 1 << 20, n_m - len(m)).astype(np.uint64)])
+    P = np.sort(rng.choice(np.arange(2, 900), size=n_P, replace=False)).astype(np.uint32)
+    s = (8 * np.arange(1, n_s + 1)).astype(np.uint64)
+    wl = Workload("groups", np.repeat(x[None], 2, axis=0), gaps, np.array([7.0, 60.0]), m, P, s, NO_CAP,
+                  ALL_STRATEGIES_MASK)
+    want, _ = oracle.tune_workload(wl)
+    assert assert_tables_equal(gpu_tune(wl), want, "n_P=%d" % n_P), "times not bit-identical"
+
+
 @pytest.mark.parametrize("n_s,last", [(600, 1000.0), (8192, 14000.0), (9000, 14000.0), (17000, 40000.0)])
 @pytest.mark.parametrize("mask", [ALL_STRATEGIES_MASK, 0x204, 1 << 2, 1 << 9])
 def test_many_candidates_whose_gap_falls_below_zero(n_s, last, mask):
