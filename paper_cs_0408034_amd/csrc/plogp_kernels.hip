@@ -503,8 +503,7 @@ struct ChainCtx {
     const int *blk_off;
 };
 
-// Builds the table as intervals in LDS (chain_lds(n) bytes at `lds`) from the raw samples: the
-// slopes are the same expression as everywhere.  The caller synchronises.
+// Builds the table as intervals in LDS (4 n + CHAIN_PAD doubles at `lds`).  The caller synchronises.
 constexpr size_t CHAIN_PAD = 14;                                   // entries beside the 4 n of the table
 
 __device__ __forceinline__ void stage_intervals(ChainCtx &C, double *lds, const DeviceTables &T, int t)
@@ -513,7 +512,7 @@ __device__ __forceinline__ void stage_intervals(ChainCtx &C, double *lds, const 
     f64x2 *YS = reinterpret_cast<f64x2 *>(lds);                    // n + 2 entries
     double *X = lds + 2 * (n + 2);                                 // n + 6 entries, +inf from n + 1 on
     double *W = X + (n + 6);                                       // n + 2 entries
-    const double *gx = T.x + (size_t)t * n, *gy = T.y + (size_t)t * n;
+    const double *gx = T.x + (size_t)t * n, *gy = T.y + (size_t)t * n, *gs = T.slope + (size_t)t * n;
     for (int i = threadIdx.x; i < n + 6; i += blockDim.x) {
         // interval i starts at sample i - 1; interval 0 is the clamp below the first sample
         const double x0 = i == 0 ? 0.0 : i <= n ? gx[i - 1] : INFINITY;
@@ -521,7 +520,7 @@ __device__ __forceinline__ void stage_intervals(ChainCtx &C, double *lds, const 
         if (i < n + 2) {
             f64x2 ys;
             ys.x = i == 0 ? gy[0] : i <= n ? gy[i - 1] : 0.0;
-            ys.y = (i == 0 || i > n) ? 0.0 : interval_slope(gx, gy, n, i - 1);
+            ys.y = (i == 0 || i > n) ? 0.0 : gs[i - 1];
             YS[i] = ys;
             W[i] = i < n ? gx[i] - x0 : INFINITY;
         }
@@ -912,6 +911,33 @@ __global__ void k_chain_blocks(DeviceTables T, DeviceGrid G, Scratch S, int wg_p
 
 // ---------------------------------------------------------------- the chain row at n points
 
+// g at V sizes that lie in intervals i0 .. i0 + reach - 1 (reach: a power of two, the same in every
+// lane): the searches run side by side.
+template <int V>
+__device__ __forceinline__ void gaps_within(const ChainCtx &C, int i0, int reach, const double (&z)[V], double (&g)[V])
+{
+    int i[V];
+#pragma unroll
+    for (int c = 0; c < V; ++c)
+        i[c] = i0;
+    for (int half = reach >> 1; half > 0; half >>= 1) {
+        double x[V];
+#pragma unroll
+        for (int c = 0; c < V; ++c) {
+            const int at = i[c] + half;
+            x[c] = C.X[at < C.n + 1 ? at : C.n + 1];       // +inf past the last interval
+        }
+#pragma unroll
+        for (int c = 0; c < V; ++c)
+            i[c] = x[c] <= z[c] ? i[c] + half : i[c];
+    }
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+        const f64x2 ys = C.YS[i[c]];
+        g[c] = __builtin_fma(ys.y, z[c] - C.X[i[c]], ys.x);
+    }
+}
+
 // g((64 b + 1) m) + ... + g((64 b + terms) m) added in ascending j from +0.0, `terms` <= 64 of them
 // in this lane (the loop runs to the wave's largest).  What counts here is the number of
 // instructions: the sum and the distance are pinned to their registers after every term (left to
@@ -968,28 +994,60 @@ __device__ __forceinline__ double chain_block_sum(const ChainCtx &C, u64 b, u64 
     return run;
 }
 
+// g((64 b + 1) m) + ... + g((64 b + terms) m), terms < 64 of them in this lane (0: none).
+__device__ __forceinline__ double chain_rest_sum(const ChainCtx &C, u64 b, u64 m, int terms)
+{
+    constexpr int V = 8;
+    const double md = (double)m;
+    double zb = (double)((b * SUM_BLOCK + 1) * m);
+    const double ends[2] = {zb, terms > 0 ? __builtin_fma((double)(terms - 1), md, zb) : zb};
+    int at[2], reach = 1;
+    chain_locate<2>(C.X, C.n, ends, at);
+    while (__ballot(at[1] - at[0] >= reach) != 0)
+        reach <<= 1;
+    double run = 0.0;
+#pragma unroll 1
+    for (int k = 0; __ballot(k < terms) != 0; k += V) {
+        double z[V], g[V];
+#pragma unroll
+        for (int c = 0; c < V; ++c)
+            z[c] = __builtin_fma((double)c, md, zb);
+        gaps_within<V>(C, at[0], reach, z, g);
+#pragma unroll
+        for (int c = 0; c < V; ++c)
+            run = k + c < terms ? run + g[c] : run;
+        zb = __builtin_fma((double)V, md, zb);
+    }
+    return run;
+}
+
 // Table 2, chain row (and its Gather twin) at n independent points: fma(P-1, L, sum_{j<P} g(j m)).
 // A sum is blocks of SUM_BLOCK terms that do not depend on one another, and points ask for very
 // different numbers of them: a workgroup takes as many points as it has threads, sorts them by
 // the number of complete blocks, and deals (block index, point) pairs to the lanes, equal block
 // indices side by side (they cross about as many intervals of the table per term).  Block totals
-// go to LDS, EVAL_LEVELS block indices at a time; the thread of a point adds its totals in
-// ascending order, then the incomplete block it walks itself.  Bound by the fp64 and scalar
-// instructions of the walk (about 60 cycles per 64 terms, half of them for lanes that enter their
-// next interval); the incomplete blocks are 11 of the 78 us that 300 000 points with P up to 1024
-// take on a table of 64 samples (555 us with a thread that walks its point alone and searches the
-// table per term).  Four or sixteen block indices at a time, or 512 points, are no faster.
-constexpr int EVAL_LEVELS = 8;
-constexpr int EVAL_BIG_THREADS = 384;    // the largest multiple of 64 whose totals fit beside 4096 samples
+// go to LDS, LEVELS block indices at a time; the thread of a point adds its totals in ascending
+// order, then the incomplete block it forms itself: on a table of few samples by the same walk, else
+// with a search per term, eight side by side, because nearly every term enters another interval
+// there (300 000 points with P up to 64: 64 samples 19 us walked, 35 searched; 4096 samples 291 and
+// 88; at 512 as fast, and with P up to 16 30 and 20).
+//
+// Bound by the fp64 and scalar instructions of the walk (300 000 points with P up to 1024, 64
+// samples: 79 us; 555 with a thread that walks its point alone and searches the table per term).
+// LEVELS: eight when there are few points, whose blocks would not fill the chip otherwise (3000
+// points, 64 samples: 51 us, 57 with four), four when there are many on a table that leaves LDS for
+// few waves (512 samples: 142 us, 185 with eight).
+constexpr int EVAL_SEARCH_N = 256;       // more samples: the rest of a sum is searched for
 
-__global__ void __launch_bounds__(EVAL_BIG_THREADS) k_eval_chain(DeviceTables T, int t, const u64 *dm, const uint32_t *dP,
-                                                     size_t n, double *out)
+template <int LEVELS>
+__global__ void __launch_bounds__(LEVELS == 4 ? 768 : 384)
+k_eval_chain(DeviceTables T, int t, const u64 *dm, const uint32_t *dP, size_t n, double *out)
 {
     extern __shared__ __align__(16) double eval_lds[];
-    __shared__ unsigned above[EVAL_LEVELS + 2], slot[EVAL_LEVELS + 1], most;
+    __shared__ unsigned above[LEVELS + 2], slot[LEVELS + 1], most;
     const int threads = (int)blockDim.x, tid = (int)threadIdx.x;
-    double *tot = eval_lds;                                        // [EVAL_LEVELS][threads]
-    u64 *m_of = reinterpret_cast<u64 *>(tot + (size_t)EVAL_LEVELS * threads);
+    double *tot = eval_lds;                                        // [LEVELS][threads]
+    u64 *m_of = reinterpret_cast<u64 *>(tot + (size_t)LEVELS * threads);
     unsigned short *order = reinterpret_cast<unsigned short *>(m_of + threads);
     ChainCtx C;
     stage_intervals(C, reinterpret_cast<double *>(order + threads), T, t);
@@ -1008,18 +1066,18 @@ __global__ void __launch_bounds__(EVAL_BIG_THREADS) k_eval_chain(DeviceTables T,
     __syncthreads();
     const uint32_t levels = most;
     double done = 0.0;
-    for (uint32_t b0 = 0; b0 < levels; b0 += EVAL_LEVELS) {
-        // complete blocks of this point among b0 .. b0 + EVAL_LEVELS - 1
-        const int mine = full <= b0 ? 0 : (full - b0 < EVAL_LEVELS ? (int)(full - b0) : EVAL_LEVELS);
-        if (tid <= EVAL_LEVELS)
+    for (uint32_t b0 = 0; b0 < levels; b0 += LEVELS) {
+        // complete blocks of this point among b0 .. b0 + LEVELS - 1
+        const int mine = full <= b0 ? 0 : (full - b0 < LEVELS ? (int)(full - b0) : LEVELS);
+        if (tid <= LEVELS)
             slot[tid] = 0u;
         __syncthreads();
         const unsigned rank = atomicAdd(&slot[mine], 1u);          // among the points with as many
         __syncthreads();
         if (tid == 0) {                                            // above[k]: points with k or more
             unsigned acc = 0;
-            above[EVAL_LEVELS + 1] = 0u;
-            for (int k = EVAL_LEVELS; k >= 0; --k) {
+            above[LEVELS + 1] = 0u;
+            for (int k = LEVELS; k >= 0; --k) {
                 acc += slot[k];
                 above[k] = acc;
             }
@@ -1030,7 +1088,7 @@ __global__ void __launch_bounds__(EVAL_BIG_THREADS) k_eval_chain(DeviceTables T,
         // level k's pairs are the first above[k + 1] points of that order
         unsigned total = 0;
 #pragma unroll
-        for (int k = 0; k < EVAL_LEVELS; ++k)
+        for (int k = 0; k < LEVELS; ++k)
             total += above[k + 1];
         for (unsigned e0 = (unsigned)tid & ~63u; e0 < total; e0 += (unsigned)threads) {
             unsigned r = e0 + ((unsigned)tid & 63u);
@@ -1038,7 +1096,7 @@ __global__ void __launch_bounds__(EVAL_BIG_THREADS) k_eval_chain(DeviceTables T,
             r = real ? r : total - 1u;
             int k = 0;
 #pragma unroll
-            for (int u = 0; u < EVAL_LEVELS - 1; ++u) {
+            for (int u = 0; u < LEVELS - 1; ++u) {
                 const unsigned c = above[u + 1];
                 if (k == u && r >= c) {
                     r -= c;
@@ -1054,14 +1112,15 @@ __global__ void __launch_bounds__(EVAL_BIG_THREADS) k_eval_chain(DeviceTables T,
         for (int k = 0; k < mine; ++k)
             done = done + tot[(size_t)k * threads + tid];
     }
-    const double rest = chain_block_sum<false>(C, full, m_of[tid], tail);
+    const double rest = C.n > EVAL_SEARCH_N ? chain_rest_sum(C, full, m_of[tid], tail)
+                                            : chain_block_sum<false>(C, full, m_of[tid], tail);
     if (i < n)
         out[i] = ok ? __builtin_fma((double)(P - 1u), T.L[t], done + rest) : NAN;
 }
 
-static size_t eval_chain_lds(int n, int threads)
+static size_t eval_chain_lds(int n, int levels, int threads)
 {
-    return ((size_t)EVAL_LEVELS * threads + threads + threads / 4 + 4 * (size_t)n + CHAIN_PAD) * sizeof(double);
+    return ((size_t)levels * threads + threads + threads / 4 + 4 * (size_t)n + CHAIN_PAD) * sizeof(double);
 }
 
 // The Scatter-chain sums of one (table, distinct m) in one workgroup, for tables of few
@@ -2517,30 +2576,11 @@ __device__ __forceinline__ void tile_search(const ChainCtx &C, unsigned item, bo
     double run = 0.0;
 #pragma unroll 1
     for (int k = 0; k < SUM_BLOCK; k += V) {
-        double z[V];
-        int i[V];
+        double z[V], g[V];
 #pragma unroll
-        for (int c = 0; c < V; ++c) {
+        for (int c = 0; c < V; ++c)
             z[c] = __builtin_fma((double)c, md, zb);
-            i[c] = i0;
-        }
-        for (int half = reach >> 1; half > 0; half >>= 1) {
-            double x[V];
-#pragma unroll
-            for (int c = 0; c < V; ++c) {
-                const int at = i[c] + half;
-                x[c] = C.X[at < C.n + 1 ? at : C.n + 1];       // +inf past the last interval
-            }
-#pragma unroll
-            for (int c = 0; c < V; ++c)
-                i[c] = x[c] <= z[c] ? i[c] + half : i[c];
-        }
-        double g[V];
-#pragma unroll
-        for (int c = 0; c < V; ++c) {
-            const f64x2 ys = C.YS[i[c]];
-            g[c] = __builtin_fma(ys.y, z[c] - C.X[i[c]], ys.x);
-        }
+        gaps_within<V>(C, i0, reach, z, g);
         if (((any >> k) & 0xFFull) != 0) {
 #pragma unroll
             for (int c = 0; c < V; ++c) {
@@ -4302,8 +4342,11 @@ hipError_t kernels_init()
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_eval),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxTableLds);
     if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_eval_chain), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)eval_chain_lds(4096, EVAL_BIG_THREADS));
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_eval_chain<4>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)eval_chain_lds(4096, 4, 768));
+    if (e != hipSuccess) return e;
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_eval_chain<8>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)eval_chain_lds(4096, 8, 384));
     if (e != hipSuccess) return e;
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_terms),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxTableLds);
@@ -4370,11 +4413,15 @@ hipError_t launch_eval(const DeviceTables &T, int table, int strategy, const uin
     if (n == 0) return hipSuccess;
     if ((n + 255) / 256 > 0x7FFFFFFFull) return hipErrorInvalidValue;
     if (strategy == 11 || strategy == 14) {
-        // a big table leaves room for one workgroup per compute unit: a large one then
-        const int threads = T.n > 512 ? EVAL_BIG_THREADS : 256;
-        hipLaunchKernelGGL(k_eval_chain, dim3((unsigned)((n + threads - 1) / threads)), dim3(threads),
-                           eval_chain_lds(T.n, threads), st, T, table, reinterpret_cast<const u64 *>(d_m), d_P, n,
-                           d_out);
+        // many: a full chip with one workgroup of 384 points per compute unit, as a big table leaves
+        // room for (a small one leaves room for enough waves anyhow: 256 samples 103 us, 107 as many).
+        // More points per workgroup then stage the table less often (300 000 points with P up to 1024,
+        // 1500 samples: 313 us with 768, 468 with 384; 600 samples 203 with 256, 227 with 384)
+        const bool many = n > (size_t)384 * device_info().n_cu && T.n > EVAL_SEARCH_N;
+        const int levels = many ? 4 : 8, threads = T.n <= (many ? 640 : 512) ? 256 : many ? 768 : 384;
+        hipLaunchKernelGGL(many ? k_eval_chain<4> : k_eval_chain<8>, dim3((unsigned)((n + threads - 1) / threads)),
+                           dim3(threads), eval_chain_lds(T.n, levels, threads), st, T, table,
+                           reinterpret_cast<const u64 *>(d_m), d_P, n, d_out);
         return hipGetLastError();
     }
     const size_t lds = (size_t)3 * T.n * sizeof(double);

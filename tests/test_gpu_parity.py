@@ -645,6 +645,40 @@ def test_chain_row_at_points_around_block_ends(n_x, n_points, p_top):
     tab.free()
 
 
+@pytest.mark.parametrize("n_x", [64, 256, 257, 640, 641, 1500, 4096])
+def test_chain_row_at_many_points(n_x):
+    # more than 384 points per compute unit: from 257 samples on the rest of a sum is searched for,
+    # not walked, four block indices are dealt at a time, and workgroups take 256 or 768 points.
+    # Every 61st point and the last ones against the oracle, all of them against the smaller launch
+    torch = torch_cuda()
+    plogp = _plogp()
+    rng = np.random.default_rng(n_x)
+    n_points = 384 * torch.cuda.get_device_properties(0).multi_processor_count + 1
+    x = np.unique(np.floor(2.0 ** rng.uniform(0, 20, 8 * n_x)))
+    x = np.append(x, x[-1] + 1.0 + np.arange(max(0, n_x - len(x))))[:n_x]
+    y = np.abs(30.0 + 0.1 * x * (1.0 + 0.3 * rng.standard_normal(n_x)))
+    P = rng.integers(1, rng.choice([18, 66, 700], n_points)).astype(np.uint32)
+    m = np.maximum(np.floor(2.0 ** rng.uniform(0, 22, n_points)), 1.0).astype(np.uint64)
+    tab = plogp.plogp_load_table(x, y, 7.5)
+    out = torch.empty(n_points, dtype=torch.float64, device="cuda")
+    half = torch.empty(n_points, dtype=torch.float64, device="cuda")
+    dm, dP = _dev(m, np.uint64), _dev(P, np.uint32)
+    plogp.plogp_eval_strategy(tab, 0, 11, dm.data_ptr(), dP.data_ptr(), 0, n_points, out.data_ptr(), stream_handle())
+    k = n_points // 2
+    plogp.plogp_eval_strategy(tab, 0, 11, dm.data_ptr(), dP.data_ptr(), 0, k, half.data_ptr(), stream_handle())
+    plogp.plogp_eval_strategy(tab, 0, 11, dm[k:].data_ptr(), dP[k:].data_ptr(), 0, n_points - k, half[k:].data_ptr(),
+                              stream_handle())
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    assert (np.isnan(got) == (P < 2)).all()
+    assert (got.view(np.uint64) == half.cpu().numpy().view(np.uint64))[P >= 2].all()
+    some = np.unique(np.concatenate([np.arange(0, n_points, 61), np.arange(n_points - 300, n_points)]))
+    some = some[P[some] >= 2]
+    want = np.array([oracle.eval_strategy(x, y, 7.5, 11, int(mv), int(pv), 0) for mv, pv in zip(m[some], P[some])])
+    assert (got[some].view(np.uint64) == want.view(np.uint64)).all()
+    tab.free()
+
+
 # ------------------------------------------------------------------ tiles of message sizes
 
 def _tile_problem(rng, seed):
