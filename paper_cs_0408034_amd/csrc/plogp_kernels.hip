@@ -504,8 +504,13 @@ struct ChainCtx {
 };
 
 // Builds the table as intervals in LDS (4 n + CHAIN_PAD doubles at `lds`).  The caller synchronises.
+// The slopes are formed here (the same expression as everywhere) where many tables are staged once
+// or twice each, or read (SLOPES) where every workgroup stages the same one, from its cache (one
+// point at a table of 64 samples 7.2 us, 7.7 with the divisions; 400 tables of 4096 samples 81 us
+// with a third more bytes to read, 73 with the divisions).
 constexpr size_t CHAIN_PAD = 14;                                   // entries beside the 4 n of the table
 
+template <bool SLOPES = false>
 __device__ __forceinline__ void stage_intervals(ChainCtx &C, double *lds, const DeviceTables &T, int t)
 {
     const int n = T.n;
@@ -520,7 +525,7 @@ __device__ __forceinline__ void stage_intervals(ChainCtx &C, double *lds, const 
         if (i < n + 2) {
             f64x2 ys;
             ys.x = i == 0 ? gy[0] : i <= n ? gy[i - 1] : 0.0;
-            ys.y = (i == 0 || i > n) ? 0.0 : gs[i - 1];
+            ys.y = (i == 0 || i > n) ? 0.0 : SLOPES ? gs[i - 1] : interval_slope(gx, gy, n, i - 1);
             YS[i] = ys;
             W[i] = i < n ? gx[i] - x0 : INFINITY;
         }
@@ -1050,7 +1055,7 @@ k_eval_chain(DeviceTables T, int t, const u64 *dm, const uint32_t *dP, size_t n,
     u64 *m_of = reinterpret_cast<u64 *>(tot + (size_t)LEVELS * threads);
     unsigned short *order = reinterpret_cast<unsigned short *>(m_of + threads);
     ChainCtx C;
-    stage_intervals(C, reinterpret_cast<double *>(order + threads), T, t);
+    stage_intervals<true>(C, reinterpret_cast<double *>(order + threads), T, t);
     const size_t i = (size_t)blockIdx.x * threads + tid;
     const u64 m = i < n ? dm[i] : 0;
     const uint32_t P = i < n ? dP[i] : 0;
@@ -2432,11 +2437,13 @@ static size_t sweep_s_lds(int n_s, bool with_static)
 // branch), more (a search per term, eight side by side, over the few intervals in question).
 //
 // 333 tables of 57 samples x 203 sizes x 37 process counts up to 1500, 19 candidates, 80 MB of
-// cells: 79 us (a lane per message size that walks its whole row alone took 175; 10 000 rows x
-// 1000 process counts 2500 us, now the row path's 82).  Bound by instruction issue: 5000 per wave,
-// half of them for the chain sums (search 28 %, one crossing 12 %, none 8 %), 18 % for the cells.
-// Tried: lists for two and three crossings as well, and the searched terms spread over all
-// threads through LDS (94 us: more lists, more waves with idle lanes).
+// cells: 78 us (a lane per message size that walks its whole row alone took 175; 10 000 rows x
+// 1000 process counts 2500 us, now the row path's 82).  Bound by instruction issue, half of it for
+// the chain sums.  With few process counts a tile has few items, often all of them of the searched
+// kind and less than a wave of them: eight lanes share each of those (6 process counts up to 100:
+// 39 us, 48 with a lane per item, 43 with a lane per message size).
+// Tried: lists for two and three crossings as well, and the searched terms of large jobs spread
+// over all threads through LDS (94 us: more lists, more waves with idle lanes).
 constexpr int TILE_THREADS = 256;
 constexpr int TILE_MAX_M = TILE_THREADS / 8;
 constexpr int TILE_NS = 24;              // candidates at most
@@ -2444,6 +2451,7 @@ constexpr int TILE_MAX_BLK = 32;         // blocks of the chain sum at most
 constexpr size_t TILE_STATIC_LDS = 256;  // room for the counters
 constexpr long TILE_MIN_ROWS = 16;       // (table, m) rows per compute unit at least (more than TILE_FEW_N samples: twice)
 constexpr int TILE_FEW_N = 512;
+constexpr unsigned TILE_SHARED = 64;     // up to so many searched items: eight lanes to each
 
 // Where the arrays of a workgroup start in LDS, in 8-byte slots.  The lists of the chain items lie
 // where A and B of every (m, s) go afterwards.
@@ -2552,6 +2560,18 @@ __device__ __forceinline__ void tile_walk(const ChainCtx &C, unsigned item, bool
         tot[b * M + ml] = run;
 }
 
+// A power of two, the same in every lane: the last of a block's terms, which starts at z0 in interval
+// i0, lies below interval i0 + reach.
+__device__ __forceinline__ int tile_reach(const ChainCtx &C, double z0, double md, int i0)
+{
+    const double last[1] = {__builtin_fma((double)(SUM_BLOCK - 1), md, z0)};
+    int il[1], reach = 1;
+    chain_locate<1>(C.X, C.n, last, il);
+    while (__ballot(il[0] - i0 >= reach) != 0)
+        reach <<= 1;
+    return reach;
+}
+
 // One item per lane whose terms enter several intervals: every term gets a search of its own,
 // eight side by side, over the intervals between those of the first and the last term.
 __device__ __forceinline__ void tile_search(const ChainCtx &C, unsigned item, bool real, const double *m_of, int M,
@@ -2562,14 +2582,7 @@ __device__ __forceinline__ void tile_search(const ChainCtx &C, unsigned item, bo
     const int ml = (int)(item & 31u), b = (int)((item >> 5) & 31u), i0 = (int)(item >> 10);
     const double md = m_of[ml];
     double zb = (double)(b * SUM_BLOCK + 1) * md;
-    int reach = 1;                             // a power of two: the last term lies below interval i0 + reach
-    {
-        const double last[1] = {__builtin_fma((double)(SUM_BLOCK - 1), md, zb)};
-        int il[1];
-        chain_locate<1>(C.X, C.n, last, il);
-        while (__ballot(il[0] - i0 >= reach) != 0)
-            reach <<= 1;
-    }
+    const int reach = tile_reach(C, zb, md, i0);
     const u64 wanted = real ? blk_mask[b] : 0ull;
     double *out = part + ml * n_P + blk_off[b];
     const u64 any = tile_any_wanted(b, wanted);
@@ -2599,8 +2612,56 @@ __device__ __forceinline__ void tile_search(const ChainCtx &C, unsigned item, bo
         tot[b * M + ml] = run;
 }
 
-__global__ void __launch_bounds__(TILE_THREADS) k_tile(DeviceTables T, DeviceGrid G, plogp_cell_dev *out, int n_tiles,
-                                                       int M)
+// The same for few items: eight lanes to an item, a lane searches for eight of the terms.  The sum is
+// handed from lane to lane (every lane adds its terms in every round; in round r the r-th lane of an
+// item holds the sum of the terms before its own).
+__device__ __forceinline__ void tile_search_shared(const ChainCtx &C, unsigned item, bool real, const double *m_of, int M,
+                                                   const u64 *blk_mask, const int *blk_off, int n_P, double *part,
+                                                   double *tot)
+{
+    constexpr int V = SUM_BLOCK / 8;
+    const int q = (int)threadIdx.x & 7;
+    const int ml = (int)(item & 31u), b = (int)((item >> 5) & 31u), i0 = (int)(item >> 10);
+    const double md = m_of[ml], zb = (double)(b * SUM_BLOCK + 1) * md;
+    const int reach = tile_reach(C, zb, md, i0);
+    const double zq = __builtin_fma((double)(V * q), md, zb);
+    double z[V], g[V];
+#pragma unroll
+    for (int c = 0; c < V; ++c)
+        z[c] = __builtin_fma((double)c, md, zq);
+    gaps_within<V>(C, i0, reach, z, g);
+    const u64 wanted = real ? blk_mask[b] : 0ull;
+    // (32-bit shifts: a 64-bit one whose amount sits in the last register of the wave's allocation does
+    // not read that register on this hardware, and the compiler does not know)
+    const unsigned lo = (unsigned)wanted, hi = (unsigned)(wanted >> 32), shift = V * (q & 3);
+    const unsigned half = q < 4 ? lo : hi;
+    const unsigned mine = half >> shift & 0xFFu;
+    double *out = part + ml * n_P + blk_off[b] + __builtin_popcount(half & ((1u << shift) - 1u)) +
+                  (q < 4 ? 0 : __builtin_popcount(lo));
+    double run = 0.0;
+#pragma unroll 1
+    for (int r = 0; r < 8; ++r) {
+        if (r > 0)
+            run = dpp_move<0x111, 0xf>(run);       // row_shr:1
+        if (__ballot(q == r && mine != 0u) != 0) {
+#pragma unroll
+            for (int c = 0; c < V; ++c) {
+                if (q == r && ((mine >> c) & 1u))
+                    *out++ = run;
+                run = run + g[c];
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < V; ++c)
+                run = run + g[c];
+        }
+    }
+    if (real && q == 7)
+        tot[b * M + ml] = run;
+}
+
+__global__ void __launch_bounds__(TILE_THREADS, 6) k_tile(DeviceTables T, DeviceGrid G, plogp_cell_dev *out, int n_tiles,
+                                                          int M)
 {
     // (a name of its own: under a name that another kernel declares without it the alignment is lost,
     // and 16-byte reads of misaligned LDS take twice the kernel's time)
@@ -2723,7 +2784,8 @@ __global__ void __launch_bounds__(TILE_THREADS) k_tile(DeviceTables T, DeviceGri
     if (chain) {
         // 64 items of a kind at a time, the slowest kind first
         const unsigned n0 = count[0], n1 = count[1], n2 = count[2];
-        const unsigned w2 = (n2 + 63) / 64, w1 = (n1 + 63) / 64, w0 = (n0 + 63) / 64;
+        const unsigned per2 = n2 <= TILE_SHARED ? 8u : 64u;
+        const unsigned w2 = (n2 + per2 - 1) / per2, w1 = (n1 + 63) / 64, w0 = (n0 + 63) / 64;
         for (;;) {
             unsigned k = 0;
             if (lane == 0)
@@ -2731,7 +2793,10 @@ __global__ void __launch_bounds__(TILE_THREADS) k_tile(DeviceTables T, DeviceGri
             k = __builtin_amdgcn_readfirstlane(k);
             if (k >= w2 + w1 + w0)
                 break;
-            if (k < w2) {
+            if (k < w2 && per2 == 8u) {
+                const unsigned e = k * 8 + (lane >> 3);
+                tile_search_shared(C, list[n_items + (e < n2 ? e : n2 - 1)], e < n2, sM, M, sMask, sOff, n_P, part, tot);
+            } else if (k < w2) {
                 const unsigned e = k * 64 + lane;
                 tile_search(C, list[n_items + (e < n2 ? e : n2 - 1)], e < n2, sM, M, sMask, sOff, n_P, part, tot);
             } else if (k < w2 + w1) {
@@ -4440,13 +4505,16 @@ hipError_t launch_eval(const DeviceTables &T, int table, int strategy, const uin
 // does once per table outweighs them (4000 rows: 27 us with 32 sizes a tile, 43 with eight).
 static int tile_sizes(const DeviceTables &T, const DeviceGrid &G)
 {
-    if ((long)T.n_tables * G.n_m < (T.n <= TILE_FEW_N ? 1 : 2) * TILE_MIN_ROWS * device_info().n_cu || G.n_s > TILE_NS || G.n_blk > TILE_MAX_BLK)
+    const bool few = T.n <= TILE_FEW_N;
+    if ((long)T.n_tables * G.n_m < (few ? 1 : 2) * TILE_MIN_ROWS * device_info().n_cu || G.n_s > TILE_NS ||
+        G.n_blk > TILE_MAX_BLK)
         return 0;
     const size_t lds_per_cu = device_info().lds_per_cu;
     const size_t table = ((size_t)4 * T.n + CHAIN_PAD) * sizeof(double);
-    // a small table: six workgroups per compute unit (333 tables x 203 sizes: 79 us, 80 with four,
-    // 90 with eight); a big one (one workgroup): all the LDS
-    const size_t most = table <= lds_per_cu / 16 ? lds_per_cu / 6 : lds_per_cu;
+    // a small table: six workgroups per compute unit (333 tables of 57 samples x 203 sizes: 79 us, 80
+    // with four, 90 with eight); a table of up to about 640 samples: three (500 samples, 200 process
+    // counts: 274 us, 563 with one); a bigger one: all the LDS
+    const size_t most = table <= lds_per_cu / 16 ? lds_per_cu / 6 : table <= lds_per_cu / 8 ? lds_per_cu / 3 : lds_per_cu;
     int M = TILE_MAX_M < G.n_m ? TILE_MAX_M : G.n_m;
     auto bytes = [&](int m) {
         return (size_t)TileLds(T.n, G.n_s, G.n_P, G.n_blk, G.cl_max, m).slots * sizeof(double) + TILE_STATIC_LDS;
@@ -4456,6 +4524,16 @@ static int tile_sizes(const DeviceTables &T, const DeviceGrid &G)
     if (bytes(M) > lds_per_cu)
         return 0;
     const int tiles = (G.n_m + M - 1) / M;               // then the same for every tile, but the last
+    // Every tile stages its table, and a big table leaves room for one workgroup per compute unit: the
+    // staged path, which stages it once for all sizes, is faster except where one tile holds all of a
+    // table's sizes or there is no chain sum (333 tables x 203 sizes, staged and in tiles: 4096
+    // samples, 6 process counts 133 and 381 us, without the chain 79 and 204; 600 samples, 200 process
+    // counts 297 and 604, without the chain 60 and 45; 400 tables x 21 sizes: 1500 samples, 37 process
+    // counts 81 and 48, 200 process counts 109 and 122, without the chain 19 and 15, 4096 samples 31
+    // and 43).
+    const bool chain = (G.mask & (1u << 11)) != 0;
+    if (!few && !(tiles == 1 ? (chain ? G.n_P <= 64 : T.n <= 2048) : !chain && T.n <= 1024))
+        return 0;
     return (G.n_m + tiles - 1) / tiles;
 }
 

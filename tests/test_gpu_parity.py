@@ -715,6 +715,36 @@ def test_random_tiles(seed):
     assert assert_tables_equal(gpu_tune(wl), want, what), "times not bit-identical"
 
 
+@pytest.mark.parametrize("n,n_m,p_hi,n_P,mask", [
+    (300, 32, 65, 9, ALL_STRATEGIES_MASK),     # two blocks, the second of one term: 64 items, all of them searched
+    (300, 32, 129, 9, ALL_STRATEGIES_MASK),    # three blocks: 96, a lane each
+    (300, 31, 64, 40, 0x1C00),                 # one block, most of its points wanted
+    (300, 33, 200, 300, ALL_STRATEGIES_MASK),  # tiles of 17 and 16; four blocks, every point wanted
+    (512, 40, 256, 255, ALL_STRATEGIES_MASK),  # three workgroups' worth of LDS: tiles of fewer sizes
+    (320, 64, 2049, 100, ALL_STRATEGIES_MASK), # 33 blocks: one too many
+    (640, 21, 1500, 64, ALL_STRATEGIES_MASK),  # a big table, one tile to it: as many process counts as
+    (700, 21, 1500, 65, ALL_STRATEGIES_MASK),  # it may have, and one more
+    (1024, 65, 300, 30, 0x3FF), (1025, 65, 300, 30, 0x3FF),     # without chain sums: several tiles
+    (2048, 30, 300, 30, 0x13FF), (2049, 30, 300, 30, 0x13FF),   # and one
+])
+@pytest.mark.parametrize("dense", [True, False])
+def test_tiles_at_the_edges_of_their_rules(n, n_m, p_hi, n_P, mask, dense):
+    # dense: samples 8 apart, so that a block of the chain sum crosses many intervals at every size;
+    # else 2000 apart, most blocks of small sizes stay in one
+    rng = np.random.default_rng(n + n_m + p_hi)
+    n_tables = -(-(4096 if n <= 512 else 8192) // n_m) + 3
+    step = 8 if dense else 2000
+    x = np.cumsum(rng.integers(1, step + 1, size=(n_tables, n)), axis=1).astype(np.float64)
+    gaps = np.abs(20.0 + x * rng.uniform(0.02, 0.1, size=(n_tables, 1)) * (1.0 + 0.4 * rng.standard_normal(x.shape)))
+    m = 8 * np.sort(rng.integers(1, max(2, int(x[:, -1].max()) // 64), size=n_m))
+    P = np.union1d(np.sort(rng.choice(np.arange(2, p_hi), size=min(n_P - 1, p_hi - 2), replace=False)), [p_hi])
+    s = (8 * np.unique(rng.integers(1, 2000, size=17))).astype(np.uint64)
+    wl = Workload("tiles", x, gaps, rng.uniform(0.0, 90.0, size=n_tables), m.astype(np.uint64), P.astype(np.uint32), s,
+                  NO_CAP, mask)
+    want, _ = oracle.tune_workload(wl)
+    assert assert_tables_equal(gpu_tune(wl), want, "tiles n=%d m=%d P=%d" % (n, n_m, len(P))), "times not bit-identical"
+
+
 # ------------------------------------------------------------------ many candidates, chunks left out by their bounds
 
 @pytest.mark.parametrize("n_s,n_P,shape", [
