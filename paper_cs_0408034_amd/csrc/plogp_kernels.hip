@@ -2935,7 +2935,7 @@ constexpr int ROW_MAX_BLK = 32;          // at most 2048 terms of the chain sum
 constexpr int ROW_NS = 64;               // candidates at most
 constexpr int ROW_SPAD = ROW_NS + 8;     // the candidate loops read up to 7 entries past the last
 constexpr int ROW_MAX_N = 512;           // samples at most (LDS per workgroup stays small)
-constexpr long ROW_MAX_ROWS = 32;        // (table, m) rows per compute unit: 256 to 511 process counts (fewer: half)
+constexpr long ROW_MAX_ROWS = 32;        // (table, m) rows per compute unit: 256 to 511 process counts (fewer: half, or less)
 
 static size_t row_lds_bytes(int n, int n_blk, int n_P)
 {
@@ -4658,14 +4658,23 @@ bool plan_tune(const DeviceTables &T, const DeviceGrid &G, bool terms_only, Tune
         return !lb.too_big;
     }
     // A row per workgroup while there are few rows or many process counts.  It is one launch where
-    // the staged path has two or three, and a small job is their latency: 64 sizes x 49 process
-    // counts, 13 candidates 5.6 us (staged: 10 to 13), 20 x 16 x 34 7.5 (27), 1000 x 40 (up to
-    // 1500) x 34 9.5 (16), 3000 x 24 x 34 17 (32), 4000 x 36 x 34 28 (30); 6000 rows 39 (39) and
-    // 10 000 62 (55).  Against tiles: 4000 rows x 12 process counts 20 (21), x 127 23 (30), 6000 x 36
-    // 39 (26); 4000 x 300 29 (34), 10 000 x 300 62 (48); 10 000 x 1000 82 (118).
+    // the staged path has two or three, and a small job is their latency.  Whole calls on tables of 64
+    // samples, all 13 rows, staged in brackets (1000 rows and more: sums up to 64 terms for 12, 1500
+    // for 36, 256 for 255 process counts): 64 sizes x 49 process counts x 13 candidates 5.6 us (10),
+    // 20 x 16 x 34 7.5 (27), 1000 x 12 x 13 6.5 (15), 1000 x 36 x 37 9.8 (17), 3000 x 12 x 37 17 (33),
+    // 4000 x 255 x 13 24 (29), 6000 x 36 x 37 39 (39), 10 000 62 (55).  Tables of 512 samples gain more
+    // (4000 x 12 x 13 21 (38)), although every workgroup forms their slopes.  Against tiles: 4000 rows x
+    // 12 process counts 20 (21), x 127 23 (30), 6000 x 36 39 (26); 4000 x 300 29 (34), 10 000 x 300 62
+    // (48); 10 000 x 1000 82 (118).
+    // Chain sums for few cells are the one kind of row that the staged path does cheaper from fewer
+    // rows on, the longer the sums the fewer, where neither the table nor the candidates are many (36
+    // process counts, 13 candidates: up to 1500 2000 rows 15 (15), 3000 21 (20), 4000 27 (23); up to 700
+    // 3000 rows 18 (18), 4000 23 (20); 256 samples, up to 1500 30 (29), 37 candidates 27 (29), 12
+    // process counts 3000 rows 21 (23)).
     const long rows = (long)T.n_tables * G.n_m;
+    const long few_cells = G.n_P >= 32 && G.n_P < 64 && T.n <= 128 && G.n_s <= 16 ? G.n_blk / 4 : 0;
     const bool by_row = fast_ok && use_row_path(T, G) &&
-                        (G.n_P >= 512 || rows < (G.n_P >= 256 ? ROW_MAX_ROWS : ROW_MAX_ROWS / 2) * n_cu);
+                        (G.n_P >= 512 || rows < (G.n_P >= 256 ? ROW_MAX_ROWS : ROW_MAX_ROWS / 2 - few_cells) * n_cu);
     const int tile_m = fast_ok && !by_row ? tile_sizes(T, G) : 0;
     if (by_row) {
         p.path = TUNE_ROW;

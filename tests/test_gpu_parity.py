@@ -492,9 +492,10 @@ def test_random_problems_with_big_tables(seed):
 
 
 def _row_problem(rng):
-    """A job for the path that does a whole (table, m) row in one workgroup: at least 256
-    rows, at least 256 process counts up to 2048 at most (32 blocks of the chain sum), at
-    most 64 candidates, at most 512 samples."""
+    """A job for the path that does a whole (table, m) row in one workgroup (up to 8192 rows of 256
+    process counts and more, any number from 512 on): at most 32 blocks of the chain sum (process
+    counts up to 2048), at most 64 candidates, at most 512 samples.  The sizes of small jobs are
+    test_small_jobs_a_row_per_workgroup's."""
     n = int(rng.choice([2, 7, 64, 200, 512]))
     x = np.unique(np.floor(np.cumsum(rng.integers(1, 3000, size=n).astype(np.float64))))
     while len(x) < 2:
@@ -679,12 +680,35 @@ def test_chain_row_at_many_points(n_x):
     tab.free()
 
 
+@pytest.mark.parametrize("n_m,n_P,p_hi,n_s,n", [
+    (2559, 36, 1500, 13, 64), (2560, 36, 1500, 13, 64),   # 24 blocks of the chain sum: ten rows a compute unit
+    (2560, 31, 1500, 13, 64), (2560, 36, 1500, 17, 64), (2560, 36, 1500, 13, 129),    # no longer one of these
+    (4095, 49, 50, 16, 128), (4096, 49, 50, 25, 128),     # one block: sixteen, then the staged path
+    (2600, 63, 2049, 16, 21), (3000, 64, 2049, 16, 21),   # 33 blocks; 64 process counts
+    (8192, 300, 400, 25, 64), (600, 600, 700, 65, 200),   # lanes over process counts, one and two to a lane
+])
+@pytest.mark.parametrize("mask", [ALL_STRATEGIES_MASK, 0x0A25])
+def test_where_the_row_path_ends(n_m, n_P, p_hi, n_s, n, mask):
+    rng = np.random.default_rng(n_m * 100 + n_P + n_s)
+    x = np.unique(np.floor(np.cumsum(rng.integers(1, 900, size=n).astype(np.float64))))
+    gaps = np.abs(25.0 + 0.07 * x[None] * (1.0 + 0.3 * rng.standard_normal((1, len(x)))))
+    m = np.maximum(np.floor(np.exp(rng.uniform(np.log(8.0), np.log(40.0 * x[-1]), size=n_m)) / 8.0) * 8.0, 8.0)
+    P = np.union1d(np.sort(rng.choice(np.arange(2, p_hi), size=n_P - 1, replace=False)), [p_hi]).astype(np.uint32)
+    s = (8 * np.sort(rng.choice(np.arange(1, 4000), size=n_s, replace=False))).astype(np.uint64)
+    wl = Workload("row end", x[None], gaps, np.array([60.0]), m.astype(np.uint64), P, s, NO_CAP, mask)
+    want, _ = oracle.tune_workload(wl)
+    assert assert_tables_equal(gpu_tune(wl), want, "%d x %d, mask %x" % (n_m, n_P, mask)), "times not bit-identical"
+
+
 # ------------------------------------------------------------------ tiles of message sizes
 
 def _tile_problem(rng, seed):
-    """A job for the path whose workgroups take a table and up to 32 message sizes: at least 4096
-    (table, m) rows (16 per compute unit; 32 with more than 512 samples), at most 24 candidates, at
-    most 32 blocks of the chain sum; tables with sample sizes of their own."""
+    """A job of at least 4096 (table, m) rows (16 per compute unit; 32 with more than 512 samples) and
+    at most 24 candidates whose tables have sample sizes of their own.  The kernel whose workgroups
+    take a table and up to 32 message sizes takes ten of the 24 seeds: those without a Gather or
+    Barrier row, of at most 32 blocks of the chain sum, up to 512 samples (and few larger tables).  The
+    others go to the staged path or, from 256 process counts on, to a row per workgroup.
+    test_tiles_at_the_edges_of_their_rules has the former's limits."""
     n = int([2, 3, 9, 57, 120, 300, 700, 1500][seed % 8])
     n_m = int([1, 31, 32, 33, 65, 100, 200, 47][seed % 8])
     n_tables = -(-(4096 if n <= 512 else 8192) // n_m) + int(rng.integers(0, 9))
@@ -716,6 +740,8 @@ def test_random_tiles(seed):
 
 
 @pytest.mark.parametrize("n,n_m,p_hi,n_P,mask", [
+    (2, 1, 66, 5, ALL_STRATEGIES_MASK),        # a tile of one size
+    (9, 31, 600, 24, ALL_STRATEGIES_MASK), (57, 33, 1026, 37, ALL_STRATEGIES_MASK), (120, 200, 2048, 250, ALL_STRATEGIES_MASK),
     (300, 32, 65, 9, ALL_STRATEGIES_MASK),     # two blocks, the second of one term: 64 items, all of them searched
     (300, 32, 129, 9, ALL_STRATEGIES_MASK),    # three blocks: 96, a lane each
     (300, 31, 64, 40, 0x1C00),                 # one block, most of its points wanted
