@@ -4660,7 +4660,7 @@ bool plan_tune(const DeviceTables &T, const DeviceGrid &G, bool terms_only, Tune
     // A row per workgroup while there are few rows or many process counts.  It is one launch where
     // the staged path has two or three, and a small job is their latency.  Whole calls on tables of 64
     // samples, all 13 rows, staged in brackets (1000 rows and more: sums up to 64 terms for 12, 1500
-    // for 36, 256 for 255 process counts): 64 sizes x 49 process counts x 13 candidates 5.6 us (10),
+    // for 36, 256 for 255 process counts): 64 sizes x 49 process counts x 13 candidates 5.9 us (13),
     // 20 x 16 x 34 7.5 (27), 1000 x 12 x 13 6.5 (15), 1000 x 36 x 37 9.8 (17), 3000 x 12 x 37 17 (33),
     // 4000 x 255 x 13 24 (29), 6000 x 36 x 37 39 (39), 10 000 62 (55).  Tables of 512 samples gain more
     // (4000 x 12 x 13 21 (38)), although every workgroup forms their slopes.  Against tiles: 4000 rows x

@@ -100,7 +100,7 @@ int main()
             ++plans;
             const plogp::ScratchLayout &l = plan.lay;
             const size_t offs[] = {l.g1, l.gs, l.gm, l.sum2, l.blk, l.pre, l.part, l.rcp, l.segC, l.segA, l.segB,
-                                   l.amin, l.nv, l.rec, l.tab, l.batch_ys, l.score_rows};
+                                   l.amin, l.minG, l.nv, l.rec, l.tab, l.batch_ys, l.score_rows};
             for (size_t o : offs)
                 CHECK(o < l.total && o % 256 == 0);
             CHECK(plan.path >= 0 && plan.path <= 3);
@@ -114,6 +114,8 @@ int main()
                 CHECK(plan.path == plogp::TUNE_STAGED || (plan.path == plogp::TUNE_TABLE_LANES && lanes_may));
             if (plan.path == plogp::TUNE_STAGED && plan.pairs)
                 CHECK(l.segA != 0 && l.segB != 0 && l.amin != 0 && G.n_s > 0);
+            if (plan.path == plogp::TUNE_STAGED && plan.lanes_s && !terms_only)
+                CHECK(l.minG != 0 && l.nv - l.minG >= (size_t)T.n_tables * ((G.n_s + 63) / 64) * sizeof(double));
         }
     }
 

@@ -165,6 +165,50 @@ def test_unusable_segment_size_on_the_one_pass_path():
     assert same_bits(sc["max_abs_err"][others], good_s["max_abs_err"][others])
 
 
+@pytest.mark.parametrize("cfg", [2, 5])                       # a small and a big table
+@pytest.mark.parametrize("mask", [0x1FFF, 0x0224, (1 << 5) | (1 << 9) | (1 << 10)])
+@pytest.mark.parametrize("unusable", [False, True])
+def test_segment_sizes_that_change_along_the_process_counts(cfg, mask, unusable):
+    """The one-pass path keeps g(s) and the number of segments while the segment sizes of 64 process
+    counts are those of the 64 before, and takes them from the segmented row before where both rows
+    have the same sizes.  Sizes here change between the groups of 64 and come back, change inside a
+    group, differ between the strategies in some groups and agree in others; with `unusable`, sizes
+    of zero and beyond the message fill a group or single points before usable ones."""
+    base = make_workload(cfg, n_m=2050, P_subset=list(range(2, 2 + 3 * 64 + 5)))
+    wl = Workload("score", base.sizes, base.gaps, base.L, base.m, base.P, base.s, base.s_cap, mask)
+    rng = np.random.default_rng(cfg + mask)
+    ids = oracle.strategy_ids(mask)
+    meas, _ = make_measurements(wl, seed=cfg)
+    n_m, n_P = len(wl.m), len(wl.P)
+    m = np.asarray(wl.m).astype(np.int64)[:, None]
+    group = np.arange(n_P)[None, :] // 64
+    of = lambda k: np.maximum(1, m // (3 + k))                                 # noqa: E731
+    seg = np.empty((len(ids), n_m, n_P), dtype=np.int64)
+    kind = np.arange(n_m)[:, None] % 5
+    for r in range(len(ids)):
+        there_and_back = of(group % 2)
+        per_row = of(np.where(group % 2 == 0, 1, r % 3))                       # agree, differ, agree, differ
+        per_group_and_row = of((group + r) % 3)                                # row r has what row r + 1 gets next
+        per_point = of(rng.integers(0, 3, (n_m, n_P)))
+        last_of_a_group = of(np.where(np.arange(n_P)[None, :] % 64 == 63, r % 2, 2))
+        seg[r] = np.choose(np.broadcast_to(kind, (n_m, n_P)),
+                           [there_and_back, per_row, per_group_and_row, per_point, last_of_a_group])
+    if not unusable:
+        check(wl, meas, seg.astype(np.uint32))
+        return
+    whole = (rng.random((len(ids), n_m, 4)) < 0.3)[:, :, np.arange(n_P) // 64]
+    points = rng.random(seg.shape) < 0.02
+    bad = np.where(rng.random(seg.shape[:2] + (1,)) < 0.5, 0, np.minimum(2 * m, (1 << 32) - 1)[None])
+    bad = np.where((whole | points) & (bad != seg) & ((bad == 0) | (bad > m[None])), bad, -1)
+    segmented = np.isin(ids, (2, 5, 9))[:, None, None]
+    want, _, _ = oracle.score_grid(wl.sizes[0], wl.gaps[0], float(wl.L[0]), wl.m, wl.P, mask, meas, seg.astype(np.uint32))
+    pred, _, _ = gpu_score(wl, meas, np.where(bad >= 0, bad, seg).astype(np.uint32))
+    nan = (bad >= 0) & segmented
+    assert nan.sum() > 10000
+    assert (np.isnan(pred) == nan).all()
+    assert same_bits(pred[~nan], want[~nan])
+
+
 @pytest.mark.parametrize("mask", [0x3FF, 0x1C00, (1 << 0) | (1 << 3) | (1 << 7), (1 << 11), (1 << 5) | (1 << 12)])
 def test_masks_and_planes(mask):
     base = make_workload(2, m_slice=slice(5, 1024, 101), P_subset=[2, 5, 64, 65, 200])
