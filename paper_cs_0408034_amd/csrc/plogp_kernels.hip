@@ -4785,6 +4785,9 @@ bool plan_tune(const DeviceTables &T, const DeviceGrid &G, bool terms_only, Tune
             // the chain workgroups come first in the grid: they must leave the terms
             // workgroups room on the chip, or those would only start when these are done
             long room = n_cu * (long)(dev.lds_per_cu / (p.both_lds + 512)) - (long)p.terms_wg;
+            // (but a workgroup per CU at least: a table of 1000 samples leaves room for two, and terms of
+            // 512 workgroups left the chain sums of 10 000 sizes to one: 1230 us, 17 now)
+            if (room < n_cu) room = n_cu;
             if (room > 2 * n_cu) room = 2 * n_cu;
             if (wg > room / T.n_tables) wg = room / T.n_tables;
             if (wg < 1) wg = 1;

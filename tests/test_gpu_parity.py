@@ -686,6 +686,7 @@ def test_chain_row_at_many_points(n_x):
     (4095, 49, 50, 16, 128), (4096, 49, 50, 25, 128),     # one block: sixteen, then the staged path
     (2600, 63, 2049, 16, 21), (3000, 64, 2049, 16, 21),   # 33 blocks; 64 process counts
     (8192, 300, 400, 25, 64), (600, 600, 700, 65, 200),   # lanes over process counts, one and two to a lane
+    (5000, 127, 128, 30, 1000),                           # more workgroups of terms than the chip has room for
 ])
 @pytest.mark.parametrize("mask", [ALL_STRATEGIES_MASK, 0x0A25])
 def test_where_the_row_path_ends(n_m, n_P, p_hi, n_s, n, mask):
