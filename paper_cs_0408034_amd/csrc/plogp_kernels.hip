@@ -4519,21 +4519,41 @@ static int tile_sizes(const DeviceTables &T, const DeviceGrid &G)
     auto bytes = [&](int m) {
         return (size_t)TileLds(T.n, G.n_s, G.n_P, G.n_blk, G.cl_max, m).slots * sizeof(double) + TILE_STATIC_LDS;
     };
-    while (M > 1 && bytes(M) > most)
+    // (half the LDS where that makes one tile of all sizes: 400 tables of 500 samples x 21 sizes x 200
+    // process counts 65 us, 72 in two tiles)
+    const bool one_tile = table > lds_per_cu / 16 && M == G.n_m && bytes(M) <= lds_per_cu / 2;
+    while (M > 1 && bytes(M) > most && !one_tile)
         --M;
     if (bytes(M) > lds_per_cu)
         return 0;
     const int tiles = (G.n_m + M - 1) / M;               // then the same for every tile, but the last
     // Every tile stages its table, and a big table leaves room for one workgroup per compute unit: the
-    // staged path, which stages it once for all sizes, is faster except where one tile holds all of a
-    // table's sizes or there is no chain sum (333 tables x 203 sizes, staged and in tiles: 4096
-    // samples, 6 process counts 133 and 381 us, without the chain 79 and 204; 600 samples, 200 process
-    // counts 297 and 604, without the chain 60 and 45; 400 tables x 21 sizes: 1500 samples, 37 process
-    // counts 81 and 48, 200 process counts 109 and 122, without the chain 19 and 15, 4096 samples 31
-    // and 43).
+    // staged path, which stages it once for all sizes, takes these (333 tables x 203 sizes, staged and
+    // in tiles: 4096 samples, 37 process counts up to 300 213 and 416 us, without the chain 79 and 204;
+    // 600 samples, 200 up to 2000 297 and 604), except
+    // - where one tile holds all of a table's sizes (400 tables x 21 sizes: 1500 samples, 37 process
+    //   counts 81 and 48, 200 109 and 122, without the chain 19 and 15, 4096 samples 31 and 43; 600
+    //   samples, 200 process counts 80 and 65);
+    // - without chain sums up to 1024 samples (600: 60 and 45) or few rows (60 tables x 140 sizes, 1500
+    //   samples 19 and 16);
+    // - few process counts and few blocks, up to two of which let the lanes share the searches (12 up to
+    //   64: 1100 samples 120 and 74, 1500 124 and 101, 2500 130 and 213; 1500 samples, 6 up to 100 95 and
+    //   108; 12 up to 200 1100 samples 144 and 109; 10 000 sizes of one table of 2500 samples, 12 up to 64
+    //   62 and 41, of 600 samples, 12 up to 200 25 and 28);
+    // - short sums, few rows and between 1024 and 2048 samples, where the staged path has launches of
+    //   their own for terms and sums (60 tables x 140 sizes, 37 up to 300: 1100 samples 57 and 40, 1000
+    //   samples 35 and 39, 2500 60 and 71; 37 up to 1500, 1500 samples 50 and 64).
     const bool chain = (G.mask & (1u << 11)) != 0;
-    if (!few && !(tiles == 1 ? (chain ? G.n_P <= 64 : T.n <= 2048) : !chain && T.n <= 1024))
-        return 0;
+    const bool few_rows = (long)T.n_tables * G.n_m < 4 * TILE_MIN_ROWS * device_info().n_cu;
+    if (!few) {
+        const bool worth = tiles == 1 ? (chain ? G.n_P <= 64 || T.n <= 1024 : T.n <= 2048)
+                           : !chain ? T.n <= 1024 || (few_rows && T.n <= 2048)
+                                    : (G.n_P < 32 && T.n <= 1280 && G.n_blk <= (few_rows ? 2 : 4)) ||
+                                          (few_rows && G.n_P < 32 && G.n_blk <= 2) ||
+                                          (few_rows && T.n > 1024 && T.n <= 2048 && G.n_blk <= 8);
+        if (!worth)
+            return 0;
+    }
     return (G.n_m + tiles - 1) / tiles;
 }
 

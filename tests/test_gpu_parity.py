@@ -749,17 +749,23 @@ def test_random_tiles(seed):
     (300, 33, 200, 300, ALL_STRATEGIES_MASK),  # tiles of 17 and 16; four blocks, every point wanted
     (512, 40, 256, 255, ALL_STRATEGIES_MASK),  # three workgroups' worth of LDS: tiles of fewer sizes
     (320, 64, 2049, 100, ALL_STRATEGIES_MASK), # 33 blocks: one too many
-    (640, 21, 1500, 64, ALL_STRATEGIES_MASK),  # a big table, one tile to it: as many process counts as
-    (700, 21, 1500, 65, ALL_STRATEGIES_MASK),  # it may have, and one more
-    (1024, 65, 300, 30, 0x3FF), (1025, 65, 300, 30, 0x3FF),     # without chain sums: several tiles
+    (640, 21, 2048, 250, ALL_STRATEGIES_MASK), (1024, 21, 1500, 65, ALL_STRATEGIES_MASK),   # a big table, one tile
+    (1025, 21, 1500, 64, ALL_STRATEGIES_MASK), (1025, 21, 1500, 65, ALL_STRATEGIES_MASK),   # to it
+    (700, 70, 100, 31, ALL_STRATEGIES_MASK), (700, 70, 100, 32, ALL_STRATEGIES_MASK),   # several: two blocks and
+    (1280, 70, 128, 6, ALL_STRATEGIES_MASK), (700, 70, 130, 6, ALL_STRATEGIES_MASK),    # few process counts (four
+    (700, 130, 257, 6, ALL_STRATEGIES_MASK), (1281, 130, 129, 6, ALL_STRATEGIES_MASK),  # for many rows),
+    (1100, 90, 500, 40, ALL_STRATEGIES_MASK), (1100, 90, 520, 40, ALL_STRATEGIES_MASK), # or eight blocks
+    (1024, 130, 300, 30, 0x3FF), (1025, 130, 300, 30, 0x3FF),   # without chain sums: several tiles
+    (2048, 65, 300, 30, 0x3FF), (2049, 65, 300, 30, 0x3FF),     # (few rows)
     (2048, 30, 300, 30, 0x13FF), (2049, 30, 300, 30, 0x13FF),   # and one
 ])
 @pytest.mark.parametrize("dense", [True, False])
 def test_tiles_at_the_edges_of_their_rules(n, n_m, p_hi, n_P, mask, dense):
+    # (tables of more than 512 samples: 8192 rows, or 16 384 where n_m is 130)
     # dense: samples 8 apart, so that a block of the chain sum crosses many intervals at every size;
     # else 2000 apart, most blocks of small sizes stay in one
     rng = np.random.default_rng(n + n_m + p_hi)
-    n_tables = -(-(4096 if n <= 512 else 8192) // n_m) + 3
+    n_tables = -(-(4096 if n <= 512 else 16384 if n_m == 130 else 8192) // n_m) + 3
     step = 8 if dense else 2000
     x = np.cumsum(rng.integers(1, step + 1, size=(n_tables, n)), axis=1).astype(np.float64)
     gaps = np.abs(20.0 + x * rng.uniform(0.02, 0.1, size=(n_tables, 1)) * (1.0 + 0.4 * rng.standard_normal(x.shape)))
