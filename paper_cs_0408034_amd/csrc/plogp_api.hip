@@ -495,7 +495,13 @@ int plogp_tune_grid(const plogp_table *t, plogp_grid *g, plogp_cell *d_out, size
     const DeviceGrid G = g->view();
     TunePlan plan;
     if (!plan_tune(T, G, false, plan)) return PLOGP_ERANGE;
-    if ((rc = ensure_scratch_block(g, plan.lay.total)) != PLOGP_OK) return rc;
+    rc = ensure_scratch_block(g, plan.lay.total);
+    if (rc == PLOGP_ENOMEM) {                           // some jobs have a path that needs next to none
+        const size_t had = plan.lay.total;
+        if (!plan_tune(T, G, false, plan, 0)) return PLOGP_ERANGE;
+        if (plan.lay.total < had) rc = ensure_scratch_block(g, plan.lay.total);
+    }
+    if (rc != PLOGP_OK) return rc;
     HIP_TRY(launch_tune(plan, T, G, bind_scratch(g->scratch_block, plan.lay),
                         reinterpret_cast<plogp_cell_dev *>(d_out), (hipStream_t)stream));
     return PLOGP_OK;
@@ -509,7 +515,7 @@ int plogp_tune_grid_static(const plogp_table *t, const plogp_grid *g, plogp_cell
     const DeviceTables T = t->view();
     const DeviceGrid G = g->view();
     TunePlan plan;
-    if (!plan_tune(T, G, false, plan)) return PLOGP_ERANGE;
+    if (!plan_tune(T, G, false, plan, PLOGP_STATIC_SCRATCH_BYTES)) return PLOGP_ERANGE;
     if (plan.lay.total > (size_t)PLOGP_STATIC_SCRATCH_BYTES) return PLOGP_ETOOBIG;
     void *base = nullptr;
     if ((rc = static_scratch(&base)) != PLOGP_OK) return rc;

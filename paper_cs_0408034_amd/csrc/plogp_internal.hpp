@@ -168,9 +168,11 @@ enum { TUNE_STAGE_TERMS = 0, TUNE_STAGE_CHAIN = 1, TUNE_STAGE_PREFIX = 2, TUNE_S
        TUNE_STAGE_MORE = 4,       // the planes of the rows beyond Tables 1 and 2 (Gather, Barrier)
        TUNE_STAGES = 5 };
 
-// Fills `plan`.  Returns false if a launch dimension or an index of the chosen path would not
-// fit 31 bits (the job is too large for one call).
-bool plan_tune(const DeviceTables &T, const DeviceGrid &G, bool terms_only, TunePlan &plan);
+// Fills `plan`: the fastest path whose scratch is not above `most_scratch`, or the fastest path if
+// no other can do with less.  Returns false if a launch dimension or an index of the chosen path
+// would not fit 31 bits (the job is too large for one call).
+bool plan_tune(const DeviceTables &T, const DeviceGrid &G, bool terms_only, TunePlan &plan,
+               size_t most_scratch = SIZE_MAX);
 // The scratch arrays of a plan inside the block that starts at `base`.
 Scratch bind_scratch(void *base, const ScratchLayout &lay);
 

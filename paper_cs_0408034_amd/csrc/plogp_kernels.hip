@@ -4503,7 +4503,7 @@ hipError_t launch_eval(const DeviceTables &T, int table, int strategy, const uin
 // process counts up to 1500: 1200 rows 24 us against 16 on the staged path, 3600 rows 24 against
 // 27, 12 000 rows 30 against 59).  Smaller tiles to fill the chip do not help: what a workgroup
 // does once per table outweighs them (4000 rows: 27 us with 32 sizes a tile, 43 with eight).
-static int tile_sizes(const DeviceTables &T, const DeviceGrid &G)
+static int tile_sizes(const DeviceTables &T, const DeviceGrid &G, bool only_where_faster)
 {
     const bool few = T.n <= TILE_FEW_N;
     if ((long)T.n_tables * G.n_m < (few ? 1 : 2) * TILE_MIN_ROWS * device_info().n_cu || G.n_s > TILE_NS ||
@@ -4545,7 +4545,7 @@ static int tile_sizes(const DeviceTables &T, const DeviceGrid &G)
     //   samples 35 and 39, 2500 60 and 71; 37 up to 1500, 1500 samples 50 and 64).
     const bool chain = (G.mask & (1u << 11)) != 0;
     const bool few_rows = (long)T.n_tables * G.n_m < 4 * TILE_MIN_ROWS * device_info().n_cu;
-    if (!few) {
+    if (!few && only_where_faster) {
         const bool worth = tiles == 1 ? (chain ? G.n_P <= 64 || T.n <= 1024 : T.n <= 2048)
                            : !chain ? T.n <= 1024 || (few_rows && T.n <= 2048)
                                     : (G.n_P < 32 && T.n <= 1280 && G.n_blk <= (few_rows ? 2 : 4)) ||
@@ -4634,7 +4634,18 @@ Scratch bind_scratch(void *base, const ScratchLayout &lay)
     return S;
 }
 
-bool plan_tune(const DeviceTables &T, const DeviceGrid &G, bool terms_only, TunePlan &p)
+// The tile path's part of a plan: one launch, and no scratch beside the spare.
+static bool plan_tiles(const DeviceTables &T, const DeviceGrid &G, int tile_m, TunePlan &p)
+{
+    p.path = TUNE_TILE;
+    p.tile_m = tile_m;
+    p.n_tiles = (G.n_m + tile_m - 1) / tile_m;
+    p.tile_lds = (size_t)TileLds(T.n, G.n_s, G.n_P, G.n_blk, G.cl_max, tile_m).slots * sizeof(double);
+    p.lay.total = LayoutBuilder().at;
+    return (long)T.n_tables * p.n_tiles <= kMaxLaunch;
+}
+
+static bool plan_fastest(const DeviceTables &T, const DeviceGrid &G, bool terms_only, TunePlan &p)
 {
     p = TunePlan{};
     p.terms_only = terms_only ? 1 : 0;
@@ -4695,7 +4706,7 @@ bool plan_tune(const DeviceTables &T, const DeviceGrid &G, bool terms_only, Tune
     const long few_cells = G.n_P >= 32 && G.n_P < 64 && T.n <= 128 && G.n_s <= 16 ? G.n_blk / 4 : 0;
     const bool by_row = fast_ok && use_row_path(T, G) &&
                         (G.n_P >= 512 || rows < (G.n_P >= 256 ? ROW_MAX_ROWS : ROW_MAX_ROWS / 2 - few_cells) * n_cu);
-    const int tile_m = fast_ok && !by_row ? tile_sizes(T, G) : 0;
+    const int tile_m = fast_ok && !by_row ? tile_sizes(T, G, true) : 0;
     if (by_row) {
         p.path = TUNE_ROW;
         // two process counts per lane when there are more groups of 64 than waves
@@ -4704,15 +4715,8 @@ bool plan_tune(const DeviceTables &T, const DeviceGrid &G, bool terms_only, Tune
         p.lay.total = lb.at;
         return true;
     }
-    if (tile_m > 0) {
-        p.path = TUNE_TILE;
-        p.tile_m = tile_m;
-        p.n_tiles = (G.n_m + tile_m - 1) / tile_m;
-        p.tile_lds = (size_t)TileLds(T.n, G.n_s, G.n_P, G.n_blk, G.cl_max, tile_m).slots * D;
-        if ((long)T.n_tables * p.n_tiles > kMaxLaunch) return false;
-        p.lay.total = lb.at;
-        return true;
-    }
+    if (tile_m > 0)
+        return plan_tiles(T, G, tile_m, p);
     p.path = TUNE_STAGED;
     const size_t tab_lds = (size_t)3 * T.n * D;
     // which sweep runs: lanes over s for many candidates, else lanes over P if the grid
@@ -4875,6 +4879,21 @@ bool plan_tune(const DeviceTables &T, const DeviceGrid &G, bool terms_only, Tune
         p.lay.score_rows = lb.take(D, 13, n_m, 2);
     p.lay.total = lb.at;
     return !lb.too_big;
+}
+
+bool plan_tune(const DeviceTables &T, const DeviceGrid &G, bool terms_only, TunePlan &p, size_t most_scratch)
+{
+    const bool ok = plan_fastest(T, G, terms_only, p);
+    if (terms_only || G.extra != 0 || T.n <= TILE_FEW_N || (ok && p.lay.total <= most_scratch))
+        return ok;
+    // large tables that the staged path is faster for but has no room for: tiles need no scratch
+    const int tile_m = tile_sizes(T, G, false);
+    TunePlan tiles = {};
+    if (tile_m > 0 && plan_tiles(T, G, tile_m, tiles)) {
+        p = tiles;
+        return true;
+    }
+    return ok;
 }
 
 hipError_t launch_tune_stage(const TunePlan &p, int stage, const DeviceTables &T, const DeviceGrid &G,

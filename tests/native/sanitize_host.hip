@@ -68,7 +68,7 @@ int main()
     }
 
     // ---- the launch plan and its scratch layout over many shapes (host arithmetic only)
-    long plans = 0;
+    long plans = 0, leaner = 0;
     for (int it = 0; it < 20000; ++it) {
         plogp::DeviceTables T = {};
         plogp::DeviceGrid G = {};
@@ -112,12 +112,21 @@ int main()
                 CHECK(plan.path == plogp::TUNE_STAGED);
             else if (G.extra != 0)
                 CHECK(plan.path == plogp::TUNE_STAGED || (plan.path == plogp::TUNE_TABLE_LANES && lanes_may));
+            // without room for scratch: the same plan, or tiles of a big table
+            plogp::TunePlan lean;
+            CHECK(plogp::plan_tune(T, G, terms_only != 0, lean, 0));
+            if (lean.path != plan.path) {
+                ++leaner;
+                CHECK(plan.path == plogp::TUNE_STAGED && lean.path == plogp::TUNE_TILE && lean.lay.total == 256);
+                CHECK(!terms_only && G.extra == 0 && T.n > 512 && lean.tile_lds <= 160 * 1024 - 256);
+            }
             if (plan.path == plogp::TUNE_STAGED && plan.pairs)
                 CHECK(l.segA != 0 && l.segB != 0 && l.amin != 0 && G.n_s > 0);
             if (plan.path == plogp::TUNE_STAGED && plan.lanes_s && !terms_only)
                 CHECK(l.minG != 0 && l.nv - l.minG >= (size_t)T.n_tables * ((G.n_s + 63) / 64) * sizeof(double));
         }
     }
+    CHECK(leaner > 0);
 
     // ---- slices of tables of the robustness summary: a launch dimension, at any number of tables
     const int n_robust[] = {1, 2, 9, 2001, 16776960, 16776961, 16776962, 1 << 24};

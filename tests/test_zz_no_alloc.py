@@ -54,6 +54,20 @@ def test_static_scratch_calls_in_a_row_match_the_allocating_entry_point():
         assert got.tobytes() == want.tobytes(), what
 
 
+def test_static_scratch_big_tables_in_tiles():
+    # 333 tables of 600 samples x 203 sizes x 200 process counts: the staged path, which the
+    # allocating entry point takes, needs 130 MB for the sums alone; tiles need none
+    rng = np.random.default_rng(9)
+    x = np.cumsum(rng.integers(1, 4000, size=(333, 600)), axis=1).astype(np.float64)
+    gaps = 20.0 + x * rng.uniform(0.02, 0.1, size=(333, 1)) * (1.0 + 0.4 * rng.random(x.shape))
+    m = 8 * np.sort(rng.integers(1, 1 << 17, size=203))
+    P = np.sort(rng.choice(np.arange(2, 2049), size=200, replace=False))
+    wl = Workload("big tables", x, gaps, rng.uniform(1.0, 90.0, 333), m.astype(np.uint64), P.astype(np.uint32),
+                  (64 << np.arange(19)).astype(np.uint64), (1 << 64) - 1, ALL_STRATEGIES_MASK)
+    want, got = _both(wl)
+    assert got.tobytes() == want.tobytes()
+
+
 def test_static_scratch_refuses_a_job_that_does_not_fit():
     torch = torch_cuda()
     from paper_cs_0408034_amd import plogp
