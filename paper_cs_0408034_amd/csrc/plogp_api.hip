@@ -118,11 +118,8 @@ void plogp_grid::free_scratch()
 
 void plogp_grid::free_cut_scratch()
 {
-    if (cut.counts) (void)hipFree(cut.counts);
-    if (cut.local) (void)hipFree(cut.local);
-    if (cut.flags) (void)hipFree(cut.flags);
-    if (cut.group_total) (void)hipFree(cut.group_total);
-    if (cut.ctl) (void)hipFree(cut.ctl);
+    if (cut_block) (void)hipFree(cut_block);
+    cut_block = nullptr;
     cut = CutScratch{};
     cut_tables = 0;
 }
@@ -156,17 +153,13 @@ int ensure_cut_scratch(plogp_grid *g, size_t n_tables)
     if (g->cut_tables >= n_tables) return PLOGP_OK;
     HIP_TRY(hipDeviceSynchronize());     // an earlier extraction on this handle may still run
     g->free_cut_scratch();
-    const size_t items = cutover_items(g->view(), (int)n_tables);
-    const size_t groups = (items + CUT_SCAN_WG - 1) / CUT_SCAN_WG;
-    hipError_t e;
-    if ((e = hipMalloc((void **)&g->cut.counts, items * sizeof(uint32_t))) != hipSuccess ||
-        (e = hipMalloc((void **)&g->cut.local, items * sizeof(uint32_t))) != hipSuccess ||
-        (e = hipMalloc((void **)&g->cut.flags, items * sizeof(uint32_t))) != hipSuccess ||
-        (e = hipMalloc((void **)&g->cut.group_total, (groups ? groups : 1) * sizeof(uint64_t))) != hipSuccess ||
-        (e = hipMalloc((void **)&g->cut.ctl, cutover_ctl_words(g->view(), (int)n_tables) * sizeof(uint64_t))) != hipSuccess) {
-        g->free_cut_scratch();
+    const DeviceGrid G = g->view();
+    const hipError_t e = hipMalloc(&g->cut_block, cutover_scratch(G, (int)n_tables, nullptr, nullptr));
+    if (e != hipSuccess) {
+        g->cut_block = nullptr;
         return alloc_error(e);
     }
+    (void)cutover_scratch(G, (int)n_tables, g->cut_block, &g->cut);
     g->cut_tables = n_tables;
     return PLOGP_OK;
 }

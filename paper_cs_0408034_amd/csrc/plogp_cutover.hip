@@ -21,13 +21,11 @@
 // lanes of a wave run over consecutive P (coalesced) and, when the grid has
 // fewer than 64 process counts, over consecutive tiles as well.
 //
-// Tables of many rows and at most CUT_ROWS_MAX_M sizes take one pass instead
-// (k_cut_rows): a thread owns a whole row, so a workgroup of 256 consecutive
-// rows owns a contiguous stretch of the output; it reads its rows once, keeps
-// the start flags in registers, learns where its stretch begins from the
-// workgroups before it (their totals, published through one 64-bit word each)
-// and writes its runs - the table is read once, nothing else goes through
-// device memory.
+// Grids of at most CUT_ROWS_MAX_M sizes take two launches instead, which read the table once:
+//   k_cut_rows   a workgroup takes 64 or 16 rows, finds their starts and leaves them packed, in the order
+//                of the output, in scratch, with the number of them;
+//   k_cut_place  adds up the numbers of the groups before and moves the packed starts to their
+//                place, as run records.
 #include "plogp_internal.hpp"
 
 namespace plogp {
@@ -275,27 +273,33 @@ __global__ void __launch_bounds__(256) k_cut_emit(CutShape sh, const plogp_cell_
     }
 }
 
-// ---- one pass, a thread per row ------------------------------------------------
+// ---- one pass over the table, a group of rows to a workgroup ----------------------
 //
-// ctl[0]: the next workgroup number (workgroups number themselves in the order in
-// which they start, so that every lower number belongs to a workgroup that is
-// running or done); ctl[1]: set if a wait was given up; ctl[2 + w]: the status of
-// workgroup w, one word that carries its state in the two top bits (0 nothing
-// yet, 1 the number of runs of its rows, 2 the number of runs of all rows up to
-// and including its own) and the count in the others.  The words are written and
-// read with device-scope atomics: value and state travel together, so no other
-// ordering is needed.  A workgroup publishes state 1 before it waits for anyone,
-// and waits only for lower numbers: every wait ends.  The waits are bounded all
-// the same (spin_limit polls): a workgroup that gives up sets ctl[1] and goes on
-// with a wrong offset rather than hold the device.
-constexpr unsigned long long CUT_STATE_SHIFT = 62, CUT_COUNT_MASK = (1ull << 62) - 1ull;
+// A workgroup takes 64 rows, or 16 where there are few, and a thread `seg` sizes of one (a multiple of
+// 16): rows along the lanes, then sizes along the rest of the wave and the waves.  Every start goes to a pool in LDS with its key and where it was found; once the
+// counts are known the pool leaves in the order of the output, whole cache lines at a time.  A
+// group whose starts do not fit leaves the counts only, and k_cut_place reads its rows once more.
+//
+// Nothing waits for another workgroup: 480 000 rows x 256 sizes (1.97 GB) take 335 + 15 us, of which
+// the bare read is 318, 6.2 TB/s.  With the place of a group's runs learnt from status words of the
+// groups before it, in one launch, a workgroup holds its slot for a trip through the loaded memory
+// system per 64 groups looked at: 397 us with 256 rows to a workgroup and records written by the
+// thread of their row, 436 with 64 rows and packed records (334 without the look-back), 462 with
+// persistent workgroups that look back one group late.  Two or eight waves to a group: 354, 350;
+// 16-byte loads 371; eight or 32 keys in flight: 351, 356.
+// Small jobs: 254 rows x 256 sizes 9.8 us in groups of 16 rows (11.5 in groups of 64; 13 as mark,
+// prefix and emit).
+struct CutRowsArgs {
+    u64 n_rows;
+    int row_bits;          // log2 of the rows of a group
+    int seg, cap;          // sizes of a thread; starts that fit the pool
+    uint2 *keys;           // [groups][cap] starts in the order of the output: (s, strategy), ...
+    uint16_t *sizes;       // [groups][cap] ... and the index of the size
+    uint32_t *row_first;   // [rows] starts of the group before each row
+    uint32_t *count;       // [groups]
+};
 
-__global__ void __launch_bounds__(256) k_cut_rows_clear(u64 *ctl, size_t n)
-{
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n)
-        ctl[i] = 0ull;
-}
+static int cut_rows_lds(int cap, int threads) { return cap * 14 + threads * 4; }
 
 __device__ __forceinline__ u64 wave_sum_u64(u64 v)
 {
@@ -305,175 +309,256 @@ __device__ __forceinline__ u64 wave_sum_u64(u64 v)
     return v;
 }
 
-// NW: 32-bit words of start flags per row (the grid has at most 32 NW sizes).
-template <bool STREAM, int NW>
-__global__ void __launch_bounds__(256) k_cut_rows(CutShape sh, const plogp_cell_dev *cells, const u64 *m,
-                                                  int key_mode, u64 *ctl, u64 *row_offsets,
-                                                  plogp_run_dev *runs, u64 capacity, u64 n_rows,
-                                                  unsigned spin_limit)
+template <bool STREAM>
+__global__ void __launch_bounds__(64 * CUT_ROWS_MAX_WAVES)
+k_cut_rows(CutShape sh, const plogp_cell_dev *cells, int key_mode, CutRowsArgs A)
 {
-    __shared__ unsigned wg_s;
-    __shared__ u64 wave_total[4];
-    __shared__ u64 before_s;
-    __shared__ uint2 kept[CUT_ROWS_KEEP][256];         // the keys of a row's first run starts
-    if (threadIdx.x == 0)
-        wg_s = (unsigned)atomicAdd(ctl, 1ull);
-    __syncthreads();
-    const unsigned wg = wg_s;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const u64 row = (u64)wg * 256 + threadIdx.x;
-    const bool live = row < n_rows;
-    const u64 rr = live ? row : n_rows - 1;            // padding threads read a valid row
-    const u64 plane = rr / (u64)sh.n_P;                // table * n_ops + operation
-    const int pi = (int)(rr % (u64)sh.n_P);
-    const size_t base = (size_t)plane * sh.n_m * sh.n_P + pi;
-
-    // first pass over the row: where a run starts
-    uint32_t bits[NW];
+    extern __shared__ __align__(16) char cut_lds[];
+    __shared__ unsigned n_pool;
+    __shared__ unsigned wave_total[CUT_ROWS_MAX_WAVES];
+    const int threads = (int)blockDim.x, n_waves = threads >> 6;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int rows = 1 << A.row_bits, parts = threads >> A.row_bits;           // parts: of a row's sizes
+    const int my_row = tid & (rows - 1), my_part = tid >> A.row_bits;
+    uint2 *key_of = reinterpret_cast<uint2 *>(cut_lds);                        // [cap]
+    uint32_t *found = reinterpret_cast<uint32_t *>(key_of + A.cap);            // [cap] thread, its start, its size
+    uint32_t *first = found + A.cap;                                           // [threads] starts before (row, part)
+    unsigned short *place = reinterpret_cast<unsigned short *>(first + threads);   // [cap] by order of output
+    const u64 group = blockIdx.x, row = (group << A.row_bits) + my_row;
+    const bool live = row < A.n_rows;
+    const u64 rr = live ? row : A.n_rows - 1;          // padding threads read a valid row
+    const size_t base = (size_t)(rr / (u64)sh.n_P) * sh.n_m * sh.n_P + (size_t)(rr % (u64)sh.n_P);
+    const int m_lo = my_part * A.seg, m_hi = m_lo + A.seg < sh.n_m ? m_lo + A.seg : sh.n_m;
     uint2 prev = make_uint2(0u, 0u);
-    int starts = 0;
+    if (m_lo > 0 && m_lo < sh.n_m)
+        prev = cell_key<STREAM>(cells, base + (size_t)(m_lo - 1) * sh.n_P);
+    if (tid == 0)
+        n_pool = 0u;
+    __syncthreads();
+    unsigned starts = 0;
+    // (as often for every lane: its first lane has the wave's lowest sizes)
+    const int m_wave = __builtin_amdgcn_readfirstlane(m_lo);
+    for (int m0 = m_lo; m_wave + (m0 - m_lo) < sh.n_m && m0 - m_lo < A.seg; m0 += 16) {
+        uint2 key[16];                                 // sixteen keys are fetched before any is compared
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        bits[w] = 0u;
-        if (32 * w >= sh.n_m)
-            continue;                                  // the same for every thread
+        for (int k = 0; k < 16; ++k) {
+            const int mi = m0 + k < sh.n_m ? m0 + k : sh.n_m - 1;
+            key[k] = cell_key<STREAM>(cells, base + (size_t)mi * sh.n_P);
+        }
+        unsigned bits = 0u;
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const int m0 = 32 * w + 16 * half;
-            uint2 key[16];                             // sixteen keys are fetched before any is compared
+        for (int k = 0; k < 16; ++k) {
+            const uint2 before = k > 0 ? key[k > 0 ? k - 1 : 0] : prev;
+            const bool differs = key[k].y != before.y || (key_mode == 1 && key[k].x != before.x);
+            if (m0 + k < m_hi && (differs || m0 + k == 0))
+                bits |= 1u << k;
+        }
+        prev = key[15];
+        bits = live ? bits : 0u;
+        if (__ballot(bits != 0u) == 0)
+            continue;
+        const unsigned mine = (unsigned)__builtin_popcount(bits);
+        unsigned inc = mine;
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const int mi = m0 + k < sh.n_m ? m0 + k : sh.n_m - 1;
-                key[k] = cell_key<STREAM>(cells, base + (size_t)mi * sh.n_P);
-            }
+        for (int d = 1; d < 64; d <<= 1) {
+            const unsigned up = (unsigned)__shfl_up((int)inc, d, 64);
+            inc += lane >= d ? up : 0u;
+        }
+        unsigned at = 0;
+        if (lane == 63)
+            at = atomicAdd(&n_pool, inc);
+        at = (unsigned)__builtin_amdgcn_readlane((int)at, 63) + inc - mine;
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                bool differs = key[k].y != prev.y;
-                if (key_mode == 1)
-                    differs = differs || key[k].x != prev.x;
-                if (m0 + k < sh.n_m && (differs || m0 + k == 0)) {
-                    bits[w] |= 1u << (16 * half + k);
-                    if (starts < CUT_ROWS_KEEP)
-                        kept[starts][threadIdx.x] = key[k];
-                    ++starts;
+        for (int k = 0; k < 16; ++k) {
+            if ((bits >> k) & 1u) {
+                if (at < (unsigned)A.cap) {
+                    key_of[at] = key[k];
+                    found[at] = (unsigned)tid | starts << 10 | (unsigned)(m0 + k) << 20;
                 }
-                prev = key[k];
+                ++at;
+                ++starts;
             }
         }
     }
-    u64 count = live ? (u64)starts : 0ull;
 
-    // the runs before this row: inside the workgroup by a scan, before the workgroup from
-    // the status words of the lower-numbered workgroups
-    u64 inc = count;
+    // the starts before each (row, part), rows first
+    first[my_row * parts + my_part] = starts;
+    __syncthreads();
+    const unsigned count = first[tid];
+    unsigned inc = count;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
-        const u64 up = (u64)__shfl_up((long long)inc, d, 64);
-        if (lane >= d)
-            inc += up;
+        const unsigned up = (unsigned)__shfl_up((int)inc, d, 64);
+        inc += lane >= d ? up : 0u;
     }
     if (lane == 63)
         wave_total[wave] = inc;
     __syncthreads();
-    u64 inside = inc - count, total = 0;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        inside += w < wave ? wave_total[w] : 0ull;
+    unsigned inside = inc - count, total = 0;
+    for (int w = 0; w < n_waves; ++w) {
+        inside += w < wave ? wave_total[w] : 0u;
         total += wave_total[w];
     }
-    if (wave == 0) {
-        u64 before = 0;
-        if (wg > 0) {
-            if (lane == 0)
-                __hip_atomic_store(ctl + 2 + wg, (1ull << CUT_STATE_SHIFT) | total, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            long long j = (long long)wg - 1;           // the nearest workgroup not yet counted
-            unsigned polls = 0;
-            for (;;) {
-                // 64 status words at a time, lane l looks at workgroup j - l
-                const long long idx = j - lane;
-                u64 sv = 2ull << CUT_STATE_SHIFT;      // before workgroup 0: nothing, and final
-                if (idx >= 0)
-                    sv = __hip_atomic_load(ctl + 2 + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const u64 state = sv >> CUT_STATE_SHIFT;
-                const u64 known = __ballot(state != 0ull), final_ = __ballot(state == 2ull);
-                const int stop = final_ ? __builtin_ctzll(final_) : 63;      // counted up to this lane
-                const u64 wanted = (2ull << stop) - 1ull;                    // lanes 0 .. stop
-                if ((known & wanted) == wanted) {
-                    before += wave_sum_u64(lane <= stop ? (sv & CUT_COUNT_MASK) : 0ull);
-                    if (final_)
-                        break;
-                    j -= 64;
-                    continue;
-                }
-                if (++polls > spin_limit) {
-                    if (lane == 0)
-                        atomicExch(ctl + 1, 1ull);
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(4);
-            }
-        }
-        if (lane == 0) {
-            __hip_atomic_store(ctl + 2 + wg, (2ull << CUT_STATE_SHIFT) | (before + total), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-            before_s = before;
-        }
+    first[tid] = inside;                               // (every thread replaces the entry it read)
+    __syncthreads();
+    if (tid < rows && live)
+        A.row_first[row] = first[tid * parts];
+    if (tid == 0)
+        A.count[group] = total;
+    uint2 *keys = A.keys + group * A.cap;
+    if (total > (unsigned)A.cap) {
+        // (there are at most two threads to a start that is kept, so the counts fit)
+        reinterpret_cast<uint32_t *>(keys)[tid] = inside;
+        return;
+    }
+    for (unsigned i = (unsigned)tid; i < total; i += (unsigned)threads) {
+        const unsigned f = found[i], who = f & 1023u;
+        place[first[(who & (unsigned)(rows - 1)) * parts + (who >> A.row_bits)] + ((f >> 10) & 1023u)] = (unsigned short)i;
     }
     __syncthreads();
-    u64 at = before_s + inside;
-    if (!live)
-        return;
-    row_offsets[row] = at;
-    if (row == n_rows - 1)
-        row_offsets[n_rows] = at + count;              // the grand total
-    // second pass: a record per start flag; the keys of the first few were kept, those of the
-    // others are read once more
-    int nth = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        uint32_t b = bits[w];
-        while (b != 0u) {
-            const int k = 32 * w + __builtin_ctz(b);
-            b &= b - 1u;
-            const int mine = nth++;
-            if (at < capacity) {
-                const uint2 key = mine < CUT_ROWS_KEEP ? kept[mine][threadIdx.x]
-                                                       : cell_key<false>(cells, base + (size_t)k * sh.n_P);
-                union {
-                    plogp_run_dev r;
-                    uint4 v;
-                } u;
-                u.r.m_from = m[k];
-                u.r.s = key.x;
-                u.r.strategy = key.y;
-                reinterpret_cast<uint4 *>(runs)[at] = u.v;
-            }
-            ++at;
+    for (unsigned d = (unsigned)tid; d < total; d += (unsigned)threads) {
+        const unsigned i = place[d];
+        keys[d] = key_of[i];
+        A.sizes[group * A.cap + d] = (uint16_t)(found[i] >> 20);
+    }
+}
+
+// `per_wg` groups to a workgroup.  local, before: the prefix of the counts in two levels, or null:
+// then the workgroup adds up the counts before its first group itself.
+__global__ void __launch_bounds__(256) k_cut_place(CutShape sh, const plogp_cell_dev *cells, const u64 *m, int key_mode,
+                                                   CutRowsArgs A, unsigned n_groups, int parts, int per_wg,
+                                                   const uint32_t *local, const u64 *before_of, u64 *row_offsets,
+                                                   plogp_run_dev *runs, u64 capacity)
+{
+    __shared__ u64 size_of[CUT_ROWS_MAX_M];
+    __shared__ u64 wave_sum[4];
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const unsigned g0 = blockIdx.x * (unsigned)per_wg;
+    for (int i = tid; i < sh.n_m; i += 256)
+        size_of[i] = m[i];
+    u64 acc = 0;
+    if (local == nullptr) {
+#pragma unroll 8
+        for (unsigned g = (unsigned)tid; g < g0; g += 256)
+            acc += A.count[g];
+        acc = wave_sum_u64(acc);
+    }
+    if (lane == 0)
+        wave_sum[wave] = acc;
+    __syncthreads();
+    u64 before = local == nullptr ? wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3]
+                                  : before_of[g0 / CUT_SCAN_WG] + local[g0];
+    auto emit = [&](u64 at, int mi, const uint2 &key) {
+        union {
+            plogp_run_dev r;
+            uint4 v;
+        } u;
+        u.r.m_from = size_of[mi];
+        u.r.s = key.x;
+        u.r.strategy = key.y;
+        reinterpret_cast<uint4 *>(runs)[at] = u.v;
+    };
+    for (unsigned g = g0; g < g0 + (unsigned)per_wg && g < n_groups; ++g) {
+        const unsigned total = A.count[g];
+        const uint2 *keys = A.keys + (size_t)g * A.cap;
+        if (tid < 1 << A.row_bits) {
+            const u64 row = ((u64)g << A.row_bits) + tid;
+            if (row < A.n_rows)
+                row_offsets[row] = before + A.row_first[row];
+            if (row == A.n_rows - 1)
+                row_offsets[A.n_rows] = before + total;        // the grand total
         }
+        if (total <= (unsigned)A.cap) {
+            const uint16_t *sizes = A.sizes + (size_t)g * A.cap;
+            for (unsigned d = (unsigned)tid; d < total && before + d < capacity; d += 256)
+                emit(before + d, sizes[d], keys[d]);
+        } else {
+            // a (row, part) of k_cut_rows to a thread: its sizes are read again
+            for (int t = tid; t < parts << A.row_bits; t += 256) {
+                const u64 row = ((u64)g << A.row_bits) + t / parts;
+                if (row >= A.n_rows)
+                    continue;
+                const size_t base = (size_t)(row / (u64)sh.n_P) * sh.n_m * sh.n_P + (size_t)(row % (u64)sh.n_P);
+                const int m_lo = t % parts * A.seg, m_hi = m_lo + A.seg < sh.n_m ? m_lo + A.seg : sh.n_m;
+                u64 at = before + reinterpret_cast<const uint32_t *>(keys)[t];
+                uint2 prev = make_uint2(0u, 0u);
+                if (m_lo > 0 && m_lo < sh.n_m)
+                    prev = cell_key<false>(cells, base + (size_t)(m_lo - 1) * sh.n_P);
+                for (int m0 = m_lo; m0 < m_hi; m0 += 8) {
+                    uint2 key[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k)
+                        key[k] = cell_key<false>(cells, base + (size_t)(m0 + k < m_hi ? m0 + k : m_hi - 1) * sh.n_P);
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        const bool differs = key[k].y != prev.y || (key_mode == 1 && key[k].x != prev.x);
+                        if (m0 + k < m_hi && (differs || m0 + k == 0)) {
+                            if (at < capacity)
+                                emit(at, m0 + k, key[k]);
+                            ++at;
+                        }
+                        prev = key[k];
+                    }
+                }
+            }
+        }
+        before += total;
     }
 }
 
 }  // namespace
 
-bool cutover_by_rows(const DeviceGrid &G, int n_tables)
+static bool cutover_by_rows(const DeviceGrid &G) { return G.n_m <= CUT_ROWS_MAX_M; }
+
+// Starts per row that are kept: a quarter of the cells or six, at most 16; for few rows, whose groups
+// differ more and where a group that is read again is seen, half or twelve, at most 64 (tuned tables
+// hold 2 to 8 starts a row: groups of 64 rows up to 12 a row on 250 sizes, groups of 16 up to 8 on 20
+// sizes and 41 on 500).
+static int cut_keep(const DeviceGrid &G, bool few)
 {
-    // enough rows to fill the chip with one thread each, and few enough sizes for the start
-    // flags of a row to stay in registers
-    const size_t n_rows = (size_t)n_tables * G.n_ops * G.n_P;
-    return G.n_m <= CUT_ROWS_MAX_M && n_rows >= (size_t)128 * device_info().n_cu;
+    const int part = (G.n_m + (few ? 1 : 3)) / (few ? 2 : 4), least = few ? 12 : 6, most = few ? 64 : 16;
+    const int row = part < least ? least : part < most ? part : most;
+    return row < G.n_m ? row : G.n_m;
 }
 
-size_t cutover_ctl_words(const DeviceGrid &G, int n_tables)
-{
-    const size_t n_rows = (size_t)n_tables * G.n_ops * G.n_P;
-    return (n_rows + 255) / 256 + 2;
-}
+// Few rows: groups of 64 would not fill the chip (254 rows x 256 sizes: 10.9 us in groups of 64).
+static size_t cut_few_rows() { return (size_t)256 * device_info().n_cu; }
 
 size_t cutover_items(const DeviceGrid &G, int n_tables)
 {
     const size_t n_tiles = ((size_t)G.n_m + CUT_TM - 1) / CUT_TM;
     return (size_t)n_tables * G.n_ops * G.n_P * n_tiles;
+}
+
+size_t cutover_scratch(const DeviceGrid &G, int n_tables, void *base, CutScratch *C)
+{
+    size_t at = 0;
+    auto take = [&](size_t bytes) {
+        const size_t here = at;
+        at += (bytes + 255) & ~(size_t)255;
+        return reinterpret_cast<void *>(reinterpret_cast<uintptr_t>(base) + here);
+    };
+    CutScratch c = {};
+    const size_t n_rows = (size_t)n_tables * G.n_ops * G.n_P, few = n_rows < cut_few_rows() ? n_rows : cut_few_rows();
+    // (for either size of group: a call with fewer tables on the same block never needs a longer one)
+    size_t counts = (n_rows + 63) / 64;
+    if (counts < (few + 15) / 16) counts = (few + 15) / 16;
+    if (!cutover_by_rows(G)) counts = cutover_items(G, n_tables);
+    c.counts = static_cast<uint32_t *>(take(counts * sizeof(uint32_t)));
+    c.local = static_cast<uint32_t *>(take(counts * sizeof(uint32_t)));
+    c.group_total = static_cast<uint64_t *>(take((counts + CUT_SCAN_WG - 1) / CUT_SCAN_WG * sizeof(uint64_t)));
+    if (cutover_by_rows(G)) {
+        size_t entries = (n_rows + 63) / 64 * 64 * cut_keep(G, false);
+        const size_t few_entries = (few + 15) / 16 * 16 * cut_keep(G, true);
+        if (entries < few_entries) entries = few_entries;
+        c.keys = take(entries * sizeof(uint2));
+        c.sizes = static_cast<uint16_t *>(take(entries * sizeof(uint16_t)));
+        c.row_first = static_cast<uint32_t *>(take(n_rows * sizeof(uint32_t)));
+    } else {
+        c.flags = static_cast<uint32_t *>(take(counts * sizeof(uint32_t)));
+    }
+    if (C) *C = c;
+    return at;
 }
 
 hipError_t launch_cutovers_stage(int stage, const DeviceGrid &G, int n_tables, const plogp_cell_dev *d_cells,
@@ -498,22 +583,45 @@ hipError_t launch_cutovers_stage(int stage, const DeviceGrid &G, int n_tables, c
     if ((sh.n_items + 255) / 256 > 0x7FFFFFFFL || n_groups > 0x7FFFFFFFull) return hipErrorInvalidValue;
     const unsigned blocks = (unsigned)((sh.n_items + 255) / 256);
     const bool fuse = n_groups <= (size_t)CUT_FUSE_MAX;     // the prefix of the group totals inside the last step
-    if (cutover_by_rows(G, n_tables)) {
-        // one pass, a thread per row (stage 0; the other stages have nothing to do)
-        if (stage != 0) return hipSuccess;
-        const size_t n_wg = (n_rows + 255) / 256;
+    if (cutover_by_rows(G)) {
+        const bool few = n_rows < cut_few_rows();
+        CutRowsArgs A;
+        A.n_rows = n_rows;
+        A.row_bits = few ? 4 : 6;
+        const size_t n_wg = (n_rows + (1u << A.row_bits) - 1) >> A.row_bits;
         if (n_wg > 0x7FFFFFFFull) return hipErrorInvalidValue;
-        u64 *ctl = reinterpret_cast<u64 *>(C.ctl);
-        hipLaunchKernelGGL(k_cut_rows_clear, dim3((unsigned)((n_wg + 2 + 255) / 256)), dim3(256), 0, st, ctl,
-                           n_wg + 2);
-        const bool stream = (size_t)n_rows * G.n_m * sizeof(plogp_cell_dev) > ((size_t)256 << 20);
-        const bool wide = G.n_m > 32 * 8;
-        const auto kern = stream ? (wide ? k_cut_rows<true, 16> : k_cut_rows<true, 8>)
-                                 : (wide ? k_cut_rows<false, 16> : k_cut_rows<false, 8>);
-        hipLaunchKernelGGL(kern, dim3((unsigned)n_wg), dim3(256), 0, st, sh, d_cells,
-                           reinterpret_cast<const u64 *>(G.m), key_mode, ctl,
-                           reinterpret_cast<u64 *>(d_row_offsets), reinterpret_cast<plogp_run_dev *>(d_runs),
-                           (u64)capacity, (u64)n_rows, CUT_SPIN_LIMIT);
+        // 16 sizes to a thread, 64 and more on many long rows
+        const int tiles = (G.n_m + 15) / 16, most = few ? 32 : 4, per = (tiles + most - 1) / most;
+        const int wave_parts = 64 >> A.row_bits, waves = ((tiles + per - 1) / per + wave_parts - 1) / wave_parts;
+        const int parts = waves * wave_parts;
+        A.seg = 16 * per;
+        A.cap = cut_keep(G, few) << A.row_bits;
+        A.keys = reinterpret_cast<uint2 *>(C.keys);
+        A.sizes = C.sizes;
+        A.row_first = C.row_first;
+        A.count = C.counts;
+        const bool own_sums = n_wg <= (size_t)CUT_OWN_SUMS;
+        if (stage == 0) {
+            const bool stream = n_rows * G.n_m * sizeof(plogp_cell_dev) > ((size_t)256 << 20);
+            hipLaunchKernelGGL(stream ? k_cut_rows<true> : k_cut_rows<false>, dim3((unsigned)n_wg), dim3(64 * waves),
+                               cut_rows_lds(A.cap, 64 * waves), st, sh, d_cells, key_mode, A);
+        } else if (stage == 1) {
+            if (!own_sums) {
+                const size_t n_sums = (n_wg + CUT_SCAN_WG - 1) / CUT_SCAN_WG;
+                u64 *sums = reinterpret_cast<u64 *>(C.group_total);
+                hipLaunchKernelGGL(k_cut_scan1, dim3((unsigned)n_sums), dim3(CUT_SCAN_THREADS), 0, st, C.counts, C.local,
+                                   n_wg, sums);
+                hipLaunchKernelGGL(k_cut_scan2, dim3(1), dim3(1024), 0, st, sums, n_sums,
+                                   reinterpret_cast<u64 *>(d_row_offsets) + n_rows);
+            }
+        } else {
+            const int per_wg = few ? 1 : 4;
+            hipLaunchKernelGGL(k_cut_place, dim3((unsigned)((n_wg + per_wg - 1) / per_wg)), dim3(256), 0, st, sh, d_cells,
+                               reinterpret_cast<const u64 *>(G.m), key_mode, A, (unsigned)n_wg, parts, per_wg,
+                               own_sums ? nullptr : C.local, reinterpret_cast<const u64 *>(C.group_total),
+                               reinterpret_cast<u64 *>(d_row_offsets), reinterpret_cast<plogp_run_dev *>(d_runs),
+                               (u64)capacity);
+        }
         return hipGetLastError();
     }
     if (stage == 0) {

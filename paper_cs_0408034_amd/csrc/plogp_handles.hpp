@@ -59,8 +59,9 @@ struct plogp_grid {
     // scratch of the tuning and the scoring: one block, laid out per call by the call's plan
     void *scratch_block = nullptr;
     size_t scratch_bytes = 0;
-    // scratch of the cut-over extraction, sized for cut_tables tables
+    // scratch of the cut-over extraction: one block, sized for cut_tables tables
     size_t cut_tables = 0;
+    void *cut_block = nullptr;
     plogp::CutScratch cut = {};
 
     plogp::DeviceGrid view() const;

@@ -201,20 +201,22 @@ constexpr int CUT_SCAN_THREADS = 256;
 constexpr int CUT_SCAN_PER = 8;            // counts per thread of the group scan
 constexpr int CUT_SCAN_WG = CUT_SCAN_THREADS * CUT_SCAN_PER;
 
-// Scratch of the cut-over extraction, one entry per (row, tile) unless noted.
+// Scratch of the cut-over extraction: one entry per (row, tile), or, where rows are taken whole, per
+// group of 64 or 16 rows unless noted.
 struct CutScratch {
-    uint32_t *counts;        // run starts in the tile
+    uint32_t *counts;        // run starts
     uint32_t *local;         // their exclusive prefix inside a group of CUT_SCAN_WG entries
-    uint32_t *flags;         // bit k: cell k of the tile starts a run
-    uint64_t *group_total;   // [groups] totals, then their exclusive prefix
-    uint64_t *ctl;           // one-pass path: [2 + workgroups] numbering, give-up flag, status words
+    uint64_t *group_total;   // totals of those groups, then their exclusive prefix
+    uint32_t *flags;         // tiles: bit k set: cell k of the tile starts a run
+    void *keys;              // rows: the starts in order, (s, strategy) ...
+    uint16_t *sizes;         // ... and the index of the message size
+    uint32_t *row_first;     // [rows] starts of the group before each row
 };
-constexpr int CUT_ROWS_KEEP = 8;           // run starts per row whose keys the one-pass path keeps in LDS
-constexpr int CUT_ROWS_MAX_M = 512;        // sizes per row that the one-pass path keeps flags for
-constexpr unsigned CUT_SPIN_LIMIT = 1u << 22;   // polls before a wait is given up (never reached)
-// Whether the extraction takes the one-pass path, and the words of its control block.
-bool cutover_by_rows(const DeviceGrid &G, int n_tables);
-size_t cutover_ctl_words(const DeviceGrid &G, int n_tables);
+constexpr int CUT_ROWS_MAX_M = 512;        // most sizes of a row that is taken whole
+constexpr int CUT_ROWS_MAX_WAVES = 8;      // waves of a workgroup: 64 rows x 4 parts, 16 rows x 32 parts
+constexpr int CUT_OWN_SUMS = 16384;        // groups whose counts a workgroup adds up itself
+// Bytes of the scratch for n_tables tables (more tables never take less), laid out at `base` in C.
+size_t cutover_scratch(const DeviceGrid &G, int n_tables, void *base, CutScratch *C);
 
 // Number of (row, tile) entries for n_tables tables over grid G.
 size_t cutover_items(const DeviceGrid &G, int n_tables);

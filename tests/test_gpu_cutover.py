@@ -117,6 +117,22 @@ def test_tables_of_many_rows_take_one_pass_and_match_the_definition(shape, p_cha
     check(random_table(rng, nt, n_ops, n_m, n_P, p_change), m, P, key_mode)
 
 
+@pytest.mark.parametrize("shape,p_change", [
+    ((3, 2, 512, 40), 1.0),       # few groups of 64 rows: sixteen waves to a group, starts that do not fit
+    ((3, 2, 241, 11), 0.4),       # sixteen waves, the last with one size; 66 rows: a ragged second group
+    ((2200, 2, 70, 15), 1.0),     # 1032 groups: two waves to a group, read again
+    ((2200, 2, 70, 15), 0.2),     # the same, kept
+    ((1100, 2, 209, 31), 0.06),   # 1066 groups, four waves, the last with seventeen sizes
+    ((350000, 1, 2, 3), 0.5),     # 16 407 groups: their counts go through the two-level prefix
+])
+def test_rows_in_groups_match_the_definition(shape, p_change):
+    rng = np.random.default_rng(sum(shape) + int(100 * p_change))
+    nt, n_ops, n_m, n_P = shape
+    m = np.cumsum(rng.integers(1, 50, size=n_m)).astype(np.uint64)
+    P = (np.arange(n_P) + 2).astype(np.uint32)
+    check(random_table(rng, nt, n_ops, n_m, n_P, p_change), m, P, 1)
+
+
 @pytest.mark.timeout(300)
 def test_full_size_of_config_4_random_decisions():
     """The shape the benchmark times: 10 000 tables x 2 operations x 256 sizes x 24 process
