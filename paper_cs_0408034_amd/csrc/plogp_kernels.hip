@@ -2943,8 +2943,11 @@ static size_t row_lds_bytes(int n, int n_blk, int n_P)
             ROW_SPAD / 2 + (size_t)(n_P + 1) / 2) * sizeof(double);
 }
 
-// PPL: process counts per lane in the Broadcast plane.
-template <bool ALL, int PPL>
+// PPL: process counts per lane in the Broadcast plane.  EXTRA: the planes of Gather and Barrier too,
+// the first from the sums that are in LDS, the second by the waves that wait for them (501 sizes x
+// 300 process counts, 37 candidates, all 18 rows: 11.1 us; terms and sums, sweep and planes in three
+// launches 20.8).
+template <bool ALL, int PPL, bool EXTRA>
 __global__ void __launch_bounds__(ROW_THREADS) k_row(DeviceTables T, DeviceGrid G, plogp_cell_dev *out)
 {
     extern __shared__ double lds[];
@@ -2987,7 +2990,8 @@ __global__ void __launch_bounds__(ROW_THREADS) k_row(DeviceTables T, DeviceGrid 
     }
     const LdsTable tab = {x, y, sl, n};
     const double md = (double)m;
-    const bool chain = (mask & (1u << 11)) != 0, binom = (mask & (1u << 12)) != 0;
+    const uint32_t need = EXTRA ? G.need : mask;       // the sums that some row adds up
+    const bool chain = (need & (1u << 11)) != 0, binom = (need & (1u << 12)) != 0;
 
     if (wave == 0) {
         double A = INFINITY, B = INFINITY, C = 0.0;
@@ -3174,15 +3178,32 @@ __global__ void __launch_bounds__(ROW_THREADS) k_row(DeviceTables T, DeviceGrid 
             }
         }
     }
+    plogp_cell_dev *const srow = orow + ((mask & 0x3FFu) ? plane : 0);
+    const uint32_t gather = EXTRA ? (G.extra & 7u) << 10 : 0u;         // under the ids of its Scatter twins
+    plogp_cell_dev *const grow = srow + ((mask & 0x1C00u) ? plane : 0);
+    if (EXTRA && (G.extra & 0x18u) && wave > 0) {
+        plogp_cell_dev *const brow = grow + (gather ? plane : 0);
+        for (int pi = tid - 64; pi < n_P; pi += ROW_THREADS - 64) {
+            const uint32_t Pv = sP[pi];
+            store_cell(brow + pi, decide_barrier(G.extra, (double)(Pv - 1u), (double)floor_log2(Pv),
+                                                 (double)ceil_log2(Pv), L, g1));
+        }
+    }
     __syncthreads();                   // the chain sums are complete
-    if (mask & 0x1C00u) {
-        plogp_cell_dev *const srow = orow + ((mask & 0x3FFu) ? plane : 0);
+    if ((mask & 0x1C00u) || gather) {
         for (int pi = tid; pi < n_P; pi += ROW_THREADS) {
             const uint32_t Pv = sP[pi];
             const int cli = ceil_log2(Pv), blk = (int)((Pv - 1u) / SUM_BLOCK);
+            const double q = (double)(Pv - 1u), cl = (double)cli;
             const double s11 = chain ? done[blk] + pre[(Pv - 1u) + blk] : 0.0;
             const double s12 = binom ? sum2[cli] : 0.0;
-            store_cell(srow + pi, decide_scatter(mask, (double)(Pv - 1u), (double)cli, gm, L, s11, s12));
+            if (mask & 0x1C00u)
+                store_cell(srow + pi, decide_scatter(mask, q, cl, gm, L, s11, s12));
+            if (EXTRA && gather) {
+                Best b = decide_scatter(gather, q, cl, gm, L, s11, s12);
+                b.id += 3u;
+                store_cell(grow + pi, b);
+            }
         }
     }
 }
@@ -4655,8 +4676,8 @@ static bool plan_fastest(const DeviceTables &T, const DeviceGrid &G, bool terms_
     const size_t nt = (size_t)T.n_tables, n_m = (size_t)G.n_m, n_mu = (size_t)G.n_mu;
     const size_t n_P = (size_t)G.n_P, n_s = (size_t)G.n_s;
     LayoutBuilder lb;
-    // the rows beyond Tables 1 and 2 are formed from the staged path's terms and sums; only the
-    // table-lane kernel writes their planes itself, when the Gather rows are enabled exactly as
+    // the planes of the rows beyond Tables 1 and 2 are written by the staged path's last launch, by
+    // k_row, or by the table-lane kernel, that one only when the Gather rows are enabled exactly as
     // the Scatter rows are (or one of the two patterns is absent): it decides once for both
     const bool fast_ok = !terms_only && G.extra == 0;
     const uint32_t scatter_rows = G.mask & 0x1C00u, gather_rows = (G.extra & 7u) << 10;
@@ -4704,11 +4725,17 @@ static bool plan_fastest(const DeviceTables &T, const DeviceGrid &G, bool terms_
     // process counts 3000 rows 21 (23)).
     const long rows = (long)T.n_tables * G.n_m;
     const long few_cells = G.n_P >= 32 && G.n_P < 64 && T.n <= 128 && G.n_s <= 16 ? G.n_blk / 4 : 0;
-    const bool by_row = fast_ok && use_row_path(T, G) &&
-                        (G.n_P >= 512 || rows < (G.n_P >= 256 ? ROW_MAX_ROWS : ROW_MAX_ROWS / 2 - few_cells) * n_cu);
+    // Masks with Gather or Barrier rows take the same launch in place of the staged path's (as its plan,
+    // with `whole` set), and from twice as many rows on only: one more launch and three reads of the
+    // terms less (all 18 rows, 64 sizes x 49 process counts 5.8 us (16.4), 3900 x 36 33 (33), 5000 x 36
+    // 36 (42), 8000 x 7 44 (44), x 24 46 (54), 9000 x 100 52 (51), 16 000 x 100 88 (78); 300 process counts
+    // 9000 80 (101), 16 000 137 (162)).
+    const bool by_row = !terms_only && use_row_path(T, G) &&
+                        (G.n_P >= 512 || rows / (G.extra ? 2 : 1) < (G.n_P >= 256 ? ROW_MAX_ROWS : ROW_MAX_ROWS / 2 - few_cells) * n_cu);
     const int tile_m = fast_ok && !by_row ? tile_sizes(T, G, true) : 0;
     if (by_row) {
-        p.path = TUNE_ROW;
+        p.path = G.extra == 0 ? TUNE_ROW : TUNE_STAGED;
+        p.whole = G.extra != 0;
         // two process counts per lane when there are more groups of 64 than waves
         p.row_two = G.n_P > 64 * (ROW_THREADS / 64);
         p.row_lds = row_lds_bytes(T.n, G.n_blk, G.n_P);
@@ -4920,10 +4947,13 @@ hipError_t launch_tune_stage(const TunePlan &p, int stage, const DeviceTables &T
         }
         return hipGetLastError();
     }
-    if (p.path == TUNE_ROW) {
+    if (p.path == TUNE_ROW || p.whole) {
         if (stage == TUNE_STAGE_SWEEP) {
             const bool all = G.mask == 0x1FFFu, two = p.row_two != 0;
-            const auto kern = all ? (two ? k_row<true, 2> : k_row<true, 1>) : (two ? k_row<false, 2> : k_row<false, 1>);
+            const auto kern = G.extra == 0 ? (all ? (two ? k_row<true, 2, false> : k_row<true, 1, false>)
+                                                  : (two ? k_row<false, 2, false> : k_row<false, 1, false>))
+                                           : (all ? (two ? k_row<true, 2, true> : k_row<true, 1, true>)
+                                                  : (two ? k_row<false, 2, true> : k_row<false, 1, true>));
             hipLaunchKernelGGL(kern, dim3((unsigned)(T.n_tables * G.n_m)), dim3(ROW_THREADS), p.row_lds, st,
                                T, G, d_out);
         }

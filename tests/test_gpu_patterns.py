@@ -105,6 +105,18 @@ def test_batch_with_process_counts_that_do_not_fill_a_group_of_eight():
     assert assert_tables_equal(gpu_tune(wl), want, "70 tables, 21 process counts"), "times not bit-identical"
 
 
+@pytest.mark.parametrize("n_P", [1, 448, 449, 513, 2048])
+@pytest.mark.parametrize("mask", [EVERY, 0x30000, (1 << 14) | (1 << 17), 0xE000 | 0x800, 0x3FF | (1 << 16)])
+def test_rows_in_one_launch(n_P, mask):
+    """A row per workgroup: the Barrier plane goes to seven of its eight waves (448 lanes), the
+    Gather plane to all; 2048 process counts are the longest sums (32 blocks) it takes."""
+    base = make_workload(2, m_slice=slice(7, 1024, 340))
+    wl = Workload(base.name, base.sizes, base.gaps, base.L, base.m, np.arange(2, n_P + 2, dtype=np.uint32), base.s,
+                  base.s_cap, mask)
+    want, _ = oracle.tune_workload(wl)
+    assert assert_tables_equal(gpu_tune(wl), want, "%d process counts, mask %#x" % (n_P, mask)), "times not bit-identical"
+
+
 @pytest.mark.parametrize("seed", range(6))
 def test_random_problems_with_random_masks(seed):
     rng = np.random.default_rng(9000 + seed)
