@@ -914,34 +914,203 @@ __global__ void k_chain_blocks(DeviceTables T, DeviceGrid G, Scratch S, int wg_p
     }
 }
 
-// ---------------------------------------------------------------- the chain row at n points
+// ---------------------------------------------------------------- block sums of the chain row, a block per lane
 
-// g at V sizes that lie in intervals i0 .. i0 + reach - 1 (reach: a power of two, the same in every
-// lane): the searches run side by side.
+// The points at which the running sum of some lane of the wave is wanted (bit r: after r terms): the
+// lanes' masks or'ed together (all lanes active; 24 instructions, where a loop over the different blocks
+// of the lanes took a dozen for each).
+__device__ __forceinline__ u64 wave_any_wanted(u64 wanted)
+{
+    auto all = [](int v) {
+        v |= __builtin_amdgcn_update_dpp(v, v, 0x111, 0xf, 0xf, false);      // row_shr:1
+        v |= __builtin_amdgcn_update_dpp(v, v, 0x112, 0xf, 0xf, false);      // row_shr:2
+        v |= __builtin_amdgcn_update_dpp(v, v, 0x114, 0xf, 0xf, false);      // row_shr:4
+        v |= __builtin_amdgcn_update_dpp(v, v, 0x118, 0xf, 0xf, false);      // row_shr:8
+        v |= __builtin_amdgcn_update_dpp(v, v, 0x142, 0xa, 0xf, false);      // row_bcast:15
+        v |= __builtin_amdgcn_update_dpp(v, v, 0x143, 0xc, 0xf, false);      // row_bcast:31
+        return (u64)(unsigned)__builtin_amdgcn_readlane(v, 63);
+    };
+    return all((int)(unsigned)wanted) | all((int)(unsigned)(wanted >> 32)) << 32;
+}
+
+// The sum of one block per lane, of size md and first term z0 in interval i, whose terms stay there
+// (ONE: enter the next interval).  The running sums wanted go to *out and on.
+template <bool ONE>
+__device__ __forceinline__ double block_walk(const ChainCtx &C, int i, double md, double z0, u64 wanted, u64 any,
+                                             double *out)
+{
+    double d = z0 - C.X[i], md_enter = 0.0;
+    f64x2 ys = C.YS[i], ys_next = ys;
+    int enters = 0;
+    if (ONE) {
+        // the first term in the next interval (the rounded quotient of two integers below 2^53
+        // does not reach an integer it is not equal to), and the way there
+        const double start = C.X[i + 1];
+        enters = (int)ceil((start - z0) / md);
+        md_enter = md - (start - C.X[i]);
+        ys_next = C.YS[i + 1];
+    }
+    double run = 0.0;
+    auto step = [&](int k) {
+        run = run + __builtin_fma(ys.y, d, ys.x);
+        if (ONE) {
+            const bool now = enters == k + 1;
+            d += now ? md_enter : md;
+            ys.x = now ? ys_next.x : ys.x;
+            ys.y = now ? ys_next.y : ys.y;
+        } else {
+            d += md;
+        }
+    };
+    int k = 0;
+    for (;;) {
+        const int hit = any != 0 ? __builtin_ctzll(any) : SUM_BLOCK;
+#pragma unroll 1
+        for (; k + 8 <= hit; k += 8) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                step(k + u);
+        }
+#pragma unroll 1
+        for (; k < hit; ++k)
+            step(k);
+        if (hit == SUM_BLOCK)
+            break;
+        if ((wanted >> hit) & 1ull)
+            *out++ = run;
+        any &= any - 1;
+    }
+    return run;
+}
+
+// A number of intervals, the same in every lane: the last of a block's terms, which starts at z0 in
+// interval i0, lies below interval i0 + reach.
+__device__ __forceinline__ int block_reach(const ChainCtx &C, double z0, double md, int i0)
+{
+    const double last[1] = {__builtin_fma((double)(SUM_BLOCK - 1), md, z0)};
+    int il[1], reach = 1;
+    chain_locate<1>(C.X, C.n, last, il);
+    while (__ballot(il[0] - i0 >= reach) != 0)
+        reach <<= 1;
+    return reach < C.n + 2 ? reach : C.n + 2;
+}
+
+// Addresses in LDS as numbers: a step of a search is then an addition, a read, a comparison and a select.
+typedef __attribute__((address_space(3))) const double lds_double;
+typedef __attribute__((address_space(3))) const f64x2 lds_f64x2;
+__device__ __forceinline__ unsigned lds_address(const double *p) { return (unsigned)(uintptr_t)(lds_double *)p; }
+__device__ __forceinline__ double lds_read(unsigned at) { return *(lds_double *)(uintptr_t)at; }
+
+// g(z), z in the interval whose start is at `at`.
+__device__ __forceinline__ double gap_in(const ChainCtx &C, unsigned at, double z)
+{
+    const unsigned ys_at = 2u * at + (lds_address((const double *)C.YS) - 2u * lds_address(C.X));
+    const f64x2 ys = *(lds_f64x2 *)(uintptr_t)ys_at;
+    return __builtin_fma(ys.y, z - lds_read(at), ys.x);
+}
+
+// Where the intervals of V sizes start, which lie in i0 .. i0 + reach - 1 (reach: at most n + 2, the
+// same in every lane): the searches run side by side.
+template <int V>
+__device__ __forceinline__ void starts_within(const ChainCtx &C, int i0, int reach, const double (&z)[V], unsigned (&at)[V])
+{
+    // from further below where the table ends before i0 + reach (+inf past the last interval)
+    const unsigned first = lds_address(C.X + (i0 < C.n + 2 - reach ? i0 : C.n + 2 - reach));
+#pragma unroll
+    for (int c = 0; c < V; ++c)
+        at[c] = first;
+    for (int len = reach; len > 1;) {
+        const unsigned half = (unsigned)(len >> 1) * 8u;
+        double x[V];
+#pragma unroll
+        for (int c = 0; c < V; ++c)
+            x[c] = lds_read(at[c] + half);
+#pragma unroll
+        for (int c = 0; c < V; ++c)
+            at[c] = x[c] <= z[c] ? at[c] + half : at[c];
+        len -= len >> 1;
+    }
+}
+
+// g at V such sizes.
 template <int V>
 __device__ __forceinline__ void gaps_within(const ChainCtx &C, int i0, int reach, const double (&z)[V], double (&g)[V])
 {
-    int i[V];
+    unsigned at[V];
+    starts_within<V>(C, i0, reach, z, at);
 #pragma unroll
     for (int c = 0; c < V; ++c)
-        i[c] = i0;
-    for (int half = reach >> 1; half > 0; half >>= 1) {
-        double x[V];
-#pragma unroll
-        for (int c = 0; c < V; ++c) {
-            const int at = i[c] + half;
-            x[c] = C.X[at < C.n + 1 ? at : C.n + 1];       // +inf past the last interval
-        }
+        g[c] = gap_in(C, at[c], z[c]);
+}
+
+// g at V ascending sizes, the first not below interval i, which becomes that of the last (it lies below
+// i + reach, as above).  Bound by instructions, the search's above all: a step of it is five vector
+// instructions and a read of LDS per term, over all the intervals that some lane's block enters.  Of eight
+// terms, few enter more than three intervals: then the bounds between these are read once for all eight
+// and compared with; else there is a search each, over as many intervals as the eight span in some lane.
+// Which of the two is decided for the wave (333 tables of 57 samples x 203 sizes x 37 process counts up to
+// 1500: 76.7 us with a search over the whole block's intervals per term, 68.2 now; 100 tables of 120
+// samples x 200 sizes: 44.5 and 37.0).
+template <int V>
+__device__ __forceinline__ void gaps_ascending(const ChainCtx &C, int &i, int reach, const double (&z)[V], double (&g)[V])
+{
+    const double *X = C.X + i;
+    const double x1 = X[1], x2 = X[2], x3 = X[3];
+    if (__ballot(z[V - 1] >= X[4]) == 0) {
+        const unsigned here = lds_address(X);
+        unsigned at[V];
 #pragma unroll
         for (int c = 0; c < V; ++c)
-            i[c] = x[c] <= z[c] ? i[c] + half : i[c];
-    }
+            at[c] = here + (z[c] >= x3 ? 24u : z[c] >= x2 ? 16u : z[c] >= x1 ? 8u : 0u);
 #pragma unroll
-    for (int c = 0; c < V; ++c) {
-        const f64x2 ys = C.YS[i[c]];
-        g[c] = __builtin_fma(ys.y, z[c] - C.X[i[c]], ys.x);
+        for (int c = 0; c < V; ++c)
+            g[c] = gap_in(C, at[c], z[c]);
+        i += (int)((at[V - 1] - here) >> 3);
+        return;
     }
+    const double last[1] = {z[V - 1]};
+    unsigned at[1];
+    starts_within<1>(C, i, reach, last, at);
+    const int il = (int)((at[0] - lds_address(C.X)) >> 3);
+    int span = 4;
+    while (__ballot(il - i >= span) != 0)
+        span <<= 1;
+    gaps_within<V>(C, i, span < reach ? span : reach, z, g);
+    i = il;
 }
+
+// The same for a block whose terms enter several intervals.
+__device__ __forceinline__ double block_search(const ChainCtx &C, int i, double md, double zb, u64 wanted, u64 any,
+                                               double *out)
+{
+    constexpr int V = 8;
+    const int reach = block_reach(C, zb, md, i);
+    double run = 0.0;
+#pragma unroll 1
+    for (int k = 0; k < SUM_BLOCK; k += V) {
+        double z[V], g[V];
+#pragma unroll
+        for (int c = 0; c < V; ++c)
+            z[c] = __builtin_fma((double)c, md, zb);
+        gaps_ascending<V>(C, i, reach, z, g);
+        if (((any >> k) & 0xFFull) != 0) {
+#pragma unroll
+            for (int c = 0; c < V; ++c) {
+                if ((wanted >> (k + c)) & 1ull)
+                    *out++ = run;
+                run = run + g[c];
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < V; ++c)
+                run = run + g[c];
+        }
+        zb = __builtin_fma((double)V, md, zb);
+    }
+    return run;
+}
+
+// ---------------------------------------------------------------- the chain row at n points
 
 // g((64 b + 1) m) + ... + g((64 b + terms) m) added in ascending j from +0.0, `terms` <= 64 of them
 // in this lane (the loop runs to the wave's largest).  What counts here is the number of
@@ -1010,6 +1179,7 @@ __device__ __forceinline__ double chain_rest_sum(const ChainCtx &C, u64 b, u64 m
     chain_locate<2>(C.X, C.n, ends, at);
     while (__ballot(at[1] - at[0] >= reach) != 0)
         reach <<= 1;
+    reach = reach < C.n + 2 ? reach : C.n + 2;
     double run = 0.0;
 #pragma unroll 1
     for (int k = 0; __ballot(k < terms) != 0; k += V) {
@@ -2434,11 +2604,11 @@ static size_t sweep_s_lds(int n_s, bool with_static)
 // more than the terms.  So every item is first placed (one search) and put on the list of its
 // kind: no crossing (three fp64 instructions per term), one crossing at a term known beforehand
 // (the two intervals sit in registers, the change is six selects on an integer compare, no
-// branch), more (a search per term, eight side by side, over the few intervals in question).
+// branch), more (eight terms side by side, each with the interval it lies in: see gaps_ascending).
 //
 // 333 tables of 57 samples x 203 sizes x 37 process counts up to 1500, 19 candidates, 80 MB of
-// cells: 78 us (a lane per message size that walks its whole row alone took 175; 10 000 rows x
-// 1000 process counts 2500 us, now the row path's 82).  Bound by instruction issue, half of it for
+// cells: 68 us (a lane per message size that walks its whole row alone took 175; 10 000 rows x
+// 1000 process counts 2500 us, now the row path's 82).  Bound by instruction issue, much of it for
 // the chain sums.  With few process counts a tile has few items, often all of them of the searched
 // kind and less than a wave of them: eight lanes share each of those (6 process counts up to 100:
 // 39 us, 48 with a lane per item, 43 with a lane per message size).
@@ -2489,125 +2659,19 @@ __device__ __forceinline__ unsigned tile_item(int ml, int b, int i)
     return (unsigned)ml | (unsigned)b << 5 | (unsigned)i << 10;
 }
 
-// The points of the blocks in this wave at which some lane's running sum is wanted (bit r: after
-// r terms).  The lanes hold few different blocks b, and `wanted` depends on the block alone.
-__device__ __forceinline__ u64 tile_any_wanted(int b, u64 wanted)
-{
-    u64 any = 0;
-    for (u64 todo = __ballot(1); todo != 0;) {
-        const int l = __builtin_ctzll(todo);
-        const int bl = __builtin_amdgcn_readlane(b, l);
-        any |= (u64)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)wanted, l) |
-               (u64)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(wanted >> 32), l) << 32;
-        todo &= ~__ballot(b == bl);
-    }
-    return any;
-}
-
-// One item per lane whose terms stay in their interval (ONE: enter the next one).  `real` lanes store.
-template <bool ONE>
-__device__ __forceinline__ void tile_walk(const ChainCtx &C, unsigned item, bool real, const double *m_of, int M,
-                                          const u64 *blk_mask, const int *blk_off, int n_P, double *part, double *tot)
+// One item per lane, of one kind: no interval entered, one, more.  `real` lanes store.
+template <int KIND>
+__device__ __forceinline__ void tile_sum(const ChainCtx &C, unsigned item, bool real, const double *m_of, int M,
+                                         const u64 *blk_mask, const int *blk_off, int n_P, double *part, double *tot)
 {
     const int ml = (int)(item & 31u), b = (int)((item >> 5) & 31u), i = (int)(item >> 10);
     const double md = m_of[ml];
     const double z0 = (double)(b * SUM_BLOCK + 1) * md;                      // exact: an integer below 2^53
-    double d = z0 - C.X[i], md_enter = 0.0;
-    f64x2 ys = C.YS[i], ys_next = ys;
-    int enters = 0;
-    if (ONE) {
-        // the first term in the next interval (the rounded quotient of two integers below 2^53
-        // does not reach an integer it is not equal to), and the way there
-        const double start = C.X[i + 1];
-        enters = (int)ceil((start - z0) / md);
-        md_enter = md - (start - C.X[i]);
-        ys_next = C.YS[i + 1];
-    }
     const u64 wanted = real ? blk_mask[b] : 0ull;
     double *out = part + ml * n_P + blk_off[b];
-    u64 any = tile_any_wanted(b, wanted);
-    double run = 0.0;
-    auto step = [&](int k) {
-        run = run + __builtin_fma(ys.y, d, ys.x);
-        if (ONE) {
-            const bool now = enters == k + 1;
-            d += now ? md_enter : md;
-            ys.x = now ? ys_next.x : ys.x;
-            ys.y = now ? ys_next.y : ys.y;
-        } else {
-            d += md;
-        }
-    };
-    int k = 0;
-    for (;;) {
-        const int hit = any != 0 ? __builtin_ctzll(any) : SUM_BLOCK;
-#pragma unroll 1
-        for (; k + 8 <= hit; k += 8) {
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                step(k + u);
-        }
-#pragma unroll 1
-        for (; k < hit; ++k)
-            step(k);
-        if (hit == SUM_BLOCK)
-            break;
-        if ((wanted >> hit) & 1ull)
-            *out++ = run;
-        any &= any - 1;
-    }
-    if (real)
-        tot[b * M + ml] = run;
-}
-
-// A power of two, the same in every lane: the last of a block's terms, which starts at z0 in interval
-// i0, lies below interval i0 + reach.
-__device__ __forceinline__ int tile_reach(const ChainCtx &C, double z0, double md, int i0)
-{
-    const double last[1] = {__builtin_fma((double)(SUM_BLOCK - 1), md, z0)};
-    int il[1], reach = 1;
-    chain_locate<1>(C.X, C.n, last, il);
-    while (__ballot(il[0] - i0 >= reach) != 0)
-        reach <<= 1;
-    return reach;
-}
-
-// One item per lane whose terms enter several intervals: every term gets a search of its own,
-// eight side by side, over the intervals between those of the first and the last term.
-__device__ __forceinline__ void tile_search(const ChainCtx &C, unsigned item, bool real, const double *m_of, int M,
-                                            const u64 *blk_mask, const int *blk_off, int n_P, double *part,
-                                            double *tot)
-{
-    constexpr int V = 8;
-    const int ml = (int)(item & 31u), b = (int)((item >> 5) & 31u), i0 = (int)(item >> 10);
-    const double md = m_of[ml];
-    double zb = (double)(b * SUM_BLOCK + 1) * md;
-    const int reach = tile_reach(C, zb, md, i0);
-    const u64 wanted = real ? blk_mask[b] : 0ull;
-    double *out = part + ml * n_P + blk_off[b];
-    const u64 any = tile_any_wanted(b, wanted);
-    double run = 0.0;
-#pragma unroll 1
-    for (int k = 0; k < SUM_BLOCK; k += V) {
-        double z[V], g[V];
-#pragma unroll
-        for (int c = 0; c < V; ++c)
-            z[c] = __builtin_fma((double)c, md, zb);
-        gaps_within<V>(C, i0, reach, z, g);
-        if (((any >> k) & 0xFFull) != 0) {
-#pragma unroll
-            for (int c = 0; c < V; ++c) {
-                if ((wanted >> (k + c)) & 1ull)
-                    *out++ = run;
-                run = run + g[c];
-            }
-        } else {
-#pragma unroll
-            for (int c = 0; c < V; ++c)
-                run = run + g[c];
-        }
-        zb = __builtin_fma((double)V, md, zb);
-    }
+    const u64 any = wave_any_wanted(wanted);
+    const double run = KIND == 2 ? block_search(C, i, md, z0, wanted, any, out)
+                                 : block_walk<KIND == 1>(C, i, md, z0, wanted, any, out);
     if (real)
         tot[b * M + ml] = run;
 }
@@ -2623,7 +2687,7 @@ __device__ __forceinline__ void tile_search_shared(const ChainCtx &C, unsigned i
     const int q = (int)threadIdx.x & 7;
     const int ml = (int)(item & 31u), b = (int)((item >> 5) & 31u), i0 = (int)(item >> 10);
     const double md = m_of[ml], zb = (double)(b * SUM_BLOCK + 1) * md;
-    const int reach = tile_reach(C, zb, md, i0);
+    const int reach = block_reach(C, zb, md, i0);
     const double zq = __builtin_fma((double)(V * q), md, zb);
     double z[V], g[V];
 #pragma unroll
@@ -2798,13 +2862,13 @@ __global__ void __launch_bounds__(TILE_THREADS, 6) k_tile(DeviceTables T, Device
                 tile_search_shared(C, list[n_items + (e < n2 ? e : n2 - 1)], e < n2, sM, M, sMask, sOff, n_P, part, tot);
             } else if (k < w2) {
                 const unsigned e = k * 64 + lane;
-                tile_search(C, list[n_items + (e < n2 ? e : n2 - 1)], e < n2, sM, M, sMask, sOff, n_P, part, tot);
+                tile_sum<2>(C, list[n_items + (e < n2 ? e : n2 - 1)], e < n2, sM, M, sMask, sOff, n_P, part, tot);
             } else if (k < w2 + w1) {
                 const unsigned e = (k - w2) * 64 + lane;
-                tile_walk<true>(C, list[n_items - 1 - (e < n1 ? e : n1 - 1)], e < n1, sM, M, sMask, sOff, n_P, part, tot);
+                tile_sum<1>(C, list[n_items - 1 - (e < n1 ? e : n1 - 1)], e < n1, sM, M, sMask, sOff, n_P, part, tot);
             } else {
                 const unsigned e = (k - w2 - w1) * 64 + lane;
-                tile_walk<false>(C, list[e < n0 ? e : n0 - 1], e < n0, sM, M, sMask, sOff, n_P, part, tot);
+                tile_sum<0>(C, list[e < n0 ? e : n0 - 1], e < n0, sM, M, sMask, sOff, n_P, part, tot);
             }
         }
         __syncthreads();

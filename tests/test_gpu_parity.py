@@ -778,6 +778,23 @@ def test_tiles_at_the_edges_of_their_rules(n, n_m, p_hi, n_P, mask, dense):
     assert assert_tables_equal(gpu_tune(wl), want, "tiles n=%d m=%d P=%d" % (n, n_m, len(P))), "times not bit-identical"
 
 
+@pytest.mark.parametrize("n,m", [(40, 192), (40, 200), (40, 224), (40, 256), (40, 512), (3, 192), (9, 2000), (300, 160),
+                                 (300, 2400)])
+def test_tiles_whose_terms_enter_intervals_at_an_even_pace(n, m):
+    # samples 512 apart: eight terms of size m enter up to three intervals (m = 192), three or four (200,
+    # 224), more (256 on); the table ends inside the sum, or inside its first block (n = 3, 9)
+    rng = np.random.default_rng(n * m)
+    n_tables = 1030
+    x = np.tile(512.0 * np.arange(1, n + 1), (n_tables, 1))
+    gaps = np.abs(20.0 + x * 0.05 * (1.0 + 0.4 * rng.standard_normal(x.shape)))
+    x[:, 0] -= rng.integers(0, 500, size=n_tables)             # the tables share no sample sizes
+    P = np.array([2, 3, 10, 64, 65, 66, 100, 128, 129, 200], dtype=np.uint32)
+    wl = Workload("pace", x, gaps, rng.uniform(0.0, 90.0, size=n_tables), np.array([m, m, m + 8, m], dtype=np.uint64), P,
+                  np.array([8, 16], dtype=np.uint64), NO_CAP, ALL_STRATEGIES_MASK)
+    want, _ = oracle.tune_workload(wl)
+    assert assert_tables_equal(gpu_tune(wl), want, "n=%d m=%d" % (n, m)), "times not bit-identical"
+
+
 # ------------------------------------------------------------------ many candidates, chunks left out by their bounds
 
 @pytest.mark.parametrize("n_s,n_P,shape", [
