@@ -701,6 +701,27 @@ def test_where_the_row_path_ends(n_m, n_P, p_hi, n_s, n, mask):
     assert assert_tables_equal(gpu_tune(wl), want, "%d x %d, mask %x" % (n_m, n_P, mask)), "times not bit-identical"
 
 
+# ------------------------------------------------------------------ prefix of the block sums
+
+@pytest.mark.parametrize("blocks,n_m,n_P", [(33, 15, 9), (97, 1, 300), (128, 16, 600), (129, 17, 600), (256, 5, 40), (257, 33, 40),
+                                            (384, 3, 5), (385, 16, 5), (513, 2, 4096), (513, 2, 4097), (65536, 1, 40),
+                                            (65537, 1, 40)])
+def test_prefix_of_the_block_sums_at_the_edges_of_its_tiles(blocks, n_m, n_P):
+    # tiles of 128 blocks, groups of 16 distinct sizes; block indices in LDS for up to 4096 process counts
+    # and 65 536 blocks; the sum ends with the first term of its last block
+    rng = np.random.default_rng(blocks + n_P)
+    n = 700
+    x = np.cumsum(rng.integers(1, 4000, size=n)).astype(np.float64)[None]
+    gaps = np.abs(20.0 + x * 0.05 * (1.0 + 0.4 * rng.standard_normal(x.shape)))
+    top = 64 * (blocks - 1) + 2
+    P = np.union1d(rng.choice(np.arange(2, top), size=n_P - 1, replace=False), [top]).astype(np.uint32)
+    m = 8 * rng.choice(np.arange(1, 9000), size=n_m, replace=False)
+    wl = Workload("prefix", x, gaps, np.array([37.0]), m.astype(np.uint64), P, np.array([8, 64], dtype=np.uint64), NO_CAP,
+                  ALL_STRATEGIES_MASK)
+    want, _ = oracle.tune_workload(wl)
+    assert assert_tables_equal(gpu_tune(wl), want, "%d blocks" % blocks), "times not bit-identical"
+
+
 # ------------------------------------------------------------------ tiles of message sizes
 
 def _tile_problem(rng, seed):
