@@ -562,6 +562,19 @@ __device__ __forceinline__ void chain_locate(const double *X, int n, const doubl
         i[c] += z[c] >= x_first ? 1 : 0;
 }
 
+// g at U sizes, each by a search of its own.
+template <int U>
+__device__ __forceinline__ void gaps_located(const ChainCtx &C, const double (&z)[U], double (&g)[U])
+{
+    int i[U];
+    chain_locate<U>(C.X, C.n, z, i);
+#pragma unroll
+    for (int c = 0; c < U; ++c) {
+        const f64x2 ys = C.YS[i[c]];
+        g[c] = __builtin_fma(ys.y, z[c] - C.X[i[c]], ys.x);
+    }
+}
+
 // Dense part of the table (small j): after moving into interval i the size is
 // still at or past its end (d >= w), i.e. several intervals on.  Looks four
 // intervals ahead a few times, then searches the rest of the table for the size
@@ -737,6 +750,132 @@ __device__ __forceinline__ void chain_search_block(const ChainCtx &C, int b, u64
         tot[(size_t)b * C.n_m] = run;
 }
 
+// The tuning's first step (see terms_body) in pieces of a wave, on a table that is there as intervals:
+// piece j of workgroup wg of the table; false: it has no more.  sd: the candidates in LDS, or null.
+__device__ __forceinline__ bool terms_piece(const ChainCtx &C, const DeviceTables &T, const DeviceGrid &G,
+                                            const Scratch &S, int t, int wg, int W, int waves, int terms_mode,
+                                            unsigned j, const double *sd)
+{
+    const int lane = threadIdx.x & 63;
+    // 64 message sizes: g(m), the number of candidates, the prefix of g(2^j m)
+    const int n_mw = (G.n_m + 63) / 64, my_mw = n_mw > wg ? (n_mw - wg + W - 1) / W : 0;
+    if (j < (unsigned)my_mw) {
+        const int mi = (wg + (int)j * W) * 64 + lane;
+        if (mi < G.n_m) {
+            const u64 m = G.m[mi];
+            const double z[1] = {(double)m};
+            double g[1];
+            gaps_located<1>(C, z, g);
+            S.gm[(size_t)t * G.n_m + mi] = g[0];
+            const u64 lim = m < G.s_cap ? m : G.s_cap;
+            int lo = 0, hi = G.n_s;
+            if (sd) {                                // from LDS: a step is not a round trip to memory
+                const double limd = (double)lim;
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (sd[mid] <= limd) lo = mid + 1; else hi = mid;
+                }
+            } else {
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (G.s[mid] <= lim) lo = mid + 1; else hi = mid;
+                }
+            }
+            if (t == 0)
+                S.nv[mi] = lo;
+            if (G.need & (1u << 12)) {
+                double *o = S.sum2 + ((size_t)t * G.n_m + mi) * (G.cl_max + 1);   // [m][d]
+                double acc = 0.0;
+                o[0] = 0.0;
+                for (int j0 = 0; j0 < G.cl_max; j0 += 4) {
+                    double z4[4], g4[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        z4[u] = (double)(m << (j0 + u < G.cl_max ? j0 + u : G.cl_max - 1));
+                    gaps_located<4>(C, z4, g4);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        if (j0 + u < G.cl_max) {
+                            acc = acc + g4[u];
+                            o[j0 + u + 1] = acc;
+                        }
+                    }
+                }
+            }
+        }
+        return true;
+    }
+    j -= (unsigned)my_mw;
+    // 64 candidates: g(s), 1/s, C = g(s) + L; the first of all takes g(1) along
+    const double L = T.L[t];
+    const int n_sw = G.n_s > 0 ? (G.n_s + 63) / 64 : 1, my_sw = n_sw > wg ? (n_sw - wg + W - 1) / W : 0;
+    if (j < (unsigned)my_sw) {
+        const int sw = wg + (int)j * W, si = sw * 64 + lane;
+        const double s = si < G.n_s ? (double)G.s[si] : 1.0, z[2] = {s, 1.0};
+        double g[2];
+        gaps_located<2>(C, z, g);
+        if (sw == 0 && lane == 0)
+            S.g1[t] = g[1];
+        if (si < G.n_s) {
+            S.gs[(size_t)t * G.n_s + si] = g[0];
+            if (terms_mode & 1)
+                S.segC[(size_t)t * G.n_s + si] = g[0] + L;
+            if (t == 0)
+                S.rcp[si] = 1.0 / s;
+        }
+        if (terms_mode & 4) {              // for the sweep over s: the least g(s) of 64 consecutive candidates
+            const double least = wave_min(si < G.n_s ? g[0] : INFINITY);
+            if (lane == 0 && G.n_s > 0)
+                S.minG[(size_t)t * n_sw + sw] = least;
+        }
+        return true;
+    }
+    j -= (unsigned)my_sw;
+    // some rows of (m, s) pairs: A = g(s) k and B = g(s)(k-1), +inf where s does not compete, min A
+    const int rows = (G.n_m + W - 1) / W, r_end = (wg + 1) * rows < G.n_m ? (wg + 1) * rows : G.n_m;
+    const int per = (rows + waves - 1) / waves, r0 = wg * rows + (int)j * per;
+    if ((terms_mode & 1) == 0 || (int)j >= waves || r0 >= r_end)
+        return false;
+    constexpr int SL = SWEEP_M_MAX_S / 64;
+    double s[SL], rcp[SL], gs[SL];
+#pragma unroll
+    for (int c = 0; c < SL; ++c) {
+        if (64 * c < G.n_s) {
+            const int si = 64 * c + lane;
+            s[c] = si < G.n_s ? (double)G.s[si] : INFINITY;
+            const double z[1] = {si < G.n_s ? s[c] : 1.0};
+            double g[1];
+            gaps_located<1>(C, z, g);
+            gs[c] = g[0];
+            rcp[c] = 1.0 / z[0];
+        }
+    }
+    for (int mi = r0; mi < r0 + per && mi < r_end; ++mi) {
+        const u64 m = G.m[mi];
+        const double lim = (double)(m < G.s_cap ? m : G.s_cap);
+        const size_t o = ((size_t)t * G.n_m + mi) * G.n_s + lane;
+        double least = INFINITY;
+#pragma unroll
+        for (int c = 0; c < SL; ++c) {
+            if (64 * c < G.n_s) {
+                double A = INFINITY, B = INFINITY, Cs;
+                if (s[c] <= lim) {
+                    segment_terms((double)m, s[c], rcp[c], gs[c], L, A, B, Cs);
+                    least = min_f64(least, A);
+                }
+                if (64 * c + lane < G.n_s) {
+                    S.segA[o + 64 * c] = A;
+                    S.segB[o + 64 * c] = B;
+                }
+            }
+        }
+        least = wave_min(least);
+        if (lane == 0)
+            S.amin[(size_t)t * G.n_m + mi] = least;
+    }
+    return true;
+}
+
 // Work items of one table, in this order: (block b, group of 64 sizes mg) for the
 // n_single leading blocks, one block each -- small j, where the walk crosses
 // many intervals per term and an item takes longest; the first n_search of them
@@ -746,16 +885,28 @@ __device__ __forceinline__ void chain_search_block(const ChainCtx &C, int b, u64
 // them first; inside a workgroup the waves take the next item of its list from
 // a counter in LDS, because how long an item takes depends on how often its
 // sizes cross an interval.
+// TERMS: the workgroups do the tuning's first step as well, in pieces of a wave that come after the
+// items: chains of dependent steps, which leave the vector units idle, for waves that have nothing left
+// while others finish their last item, on the table that is there.  (Behind a barrier, on the table
+// staged and its slopes formed once more, they took 5 to 8 us of a call: 4000 samples, 300 sizes x P up
+// to 65 536 63.6 us, 57.6 now; 4000 x P up to 4000 51 and 45.6; 4096 sizes x 976 process counts 137.4 and
+// 132.1.  A launch of their own takes 13.)
 constexpr int CHAIN_U = 4;           // blocks walked side by side by a lane in the sparse part
+constexpr int CHAIN_MAX_S = 1024;    // candidates kept in LDS for these pieces
 
+template <bool TERMS>
 __device__ __forceinline__ void chain_body(const DeviceTables &T, const DeviceGrid &G, const Scratch &S,
-                                           int wg_per_table, int n_single, int n_search, int block_id,
-                                           double *chain_lds)
+                                           int wg_per_table, int n_single, int n_search, int terms_mode,
+                                           int block_id, double *chain_lds)
 {
     __shared__ unsigned next_item;
     const int t = block_id / wg_per_table, wg = block_id % wg_per_table;
     ChainCtx C;
     stage_intervals(C, chain_lds, T, t);
+    double *const sd = chain_lds + 4 * T.n + CHAIN_PAD;
+    if (TERMS && (terms_mode & 2))
+        for (int si = threadIdx.x; si < G.n_s; si += blockDim.x)
+            sd[si] = (double)G.s[si];
     if (threadIdx.x == 0)
         next_item = 0u;
     __syncthreads();
@@ -776,8 +927,14 @@ __device__ __forceinline__ void chain_body(const DeviceTables &T, const DeviceGr
         k = __builtin_amdgcn_readfirstlane(k);
         // round k of the deal: this workgroup's place is wg, or W_ - 1 - wg in odd rounds
         const unsigned item = k * W_ + ((k & 1u) ? W_ - 1u - (unsigned)wg : (unsigned)wg);
-        if (item >= n_items)
-            break;                        // later rounds lie further on still
+        if (item >= n_items) {            // later rounds lie further on still
+            const unsigned rounds = n_items / W_, in_last = (rounds & 1u) ? W_ - 1u - (unsigned)wg : (unsigned)wg;
+            const unsigned my_items = rounds + (in_last < n_items - rounds * W_ ? 1u : 0u);
+            if (TERMS && terms_piece(C, T, G, S, t, wg, wg_per_table, (int)(blockDim.x >> 6), terms_mode, k - my_items,
+                                     (terms_mode & 2) ? sd : nullptr))
+                continue;
+            break;
+        }
         const bool single = item < n_single_items;
         const unsigned rest = single ? item : item - n_single_items;
         const int u = (int)(rest / (unsigned)n_mg), mg = (int)(rest % (unsigned)n_mg);
@@ -899,19 +1056,12 @@ __device__ __forceinline__ void chain_small_body(const DeviceTables &T, const De
     }
 }
 
-// terms_mode >= 0: a workgroup that has run out of sums goes on with its share of the tuning's
-// first step (as chunk blockIdx.x of wg_per_table per table), in the same LDS: for a big
-// table that step is a few dependent lookups per workgroup, which fit in the time the
-// workgroups wait for the slowest of them anyway, and a launch less.
-__global__ void k_chain_blocks(DeviceTables T, DeviceGrid G, Scratch S, int wg_per_table,
-                               int n_single, int n_search, int terms_mode)
+template <bool TERMS>
+__global__ void __launch_bounds__(1024) k_chain_blocks(DeviceTables T, DeviceGrid G, Scratch S, int wg_per_table,
+                                                       int n_single, int n_search, int terms_mode)
 {
-    extern __shared__ __align__(16) double chain_lds[];
-    chain_body(T, G, S, wg_per_table, n_single, n_search, (int)blockIdx.x, chain_lds);
-    if (terms_mode >= 0) {
-        __syncthreads();                  // every wave is done with the table as intervals
-        terms_body(T, G, S, wg_per_table, 0, terms_mode, (int)blockIdx.x, chain_lds);
-    }
+    extern __shared__ __align__(16) double chain_lds[];   // the table as intervals, the candidates
+    chain_body<TERMS>(T, G, S, wg_per_table, n_single, n_search, terms_mode, (int)blockIdx.x, chain_lds);
 }
 
 // ---------------------------------------------------------------- block sums of the chain row, a block per lane
@@ -1452,7 +1602,7 @@ __global__ void __launch_bounds__(256) k_terms_chain(DeviceTables T, DeviceGrid 
         if (n_single < 0)                 // a small job: terms by search, side by side
             chain_small_body(T, G, S, wg_per_table, (int)blockIdx.x, both_lds);
         else
-            chain_body(T, G, S, wg_per_table, n_single, n_search, (int)blockIdx.x, both_lds);
+            chain_body<false>(T, G, S, wg_per_table, n_single, n_search, 0, (int)blockIdx.x, both_lds);
     } else
         terms_body(T, G, S, n_chunks, n_mchunks, with_pairs, (int)blockIdx.x - n_chain_wg, both_lds);
 }
@@ -4494,7 +4644,7 @@ __global__ void __launch_bounds__(256) k_more_planes(DeviceTables T, DeviceGrid 
 
 static const size_t kMaxTableLds = (size_t)3 * 4096 * sizeof(double) + 96 +
                                    (size_t)2 * SWEEP_M_MAX_S * sizeof(double);   // + g(s), 1/s in k_terms
-static const size_t kMaxChainLds = ((size_t)4 * 4096 + CHAIN_PAD) * sizeof(double);   // + interval widths
+static const size_t kMaxChainLds = ((size_t)4 * 4096 + CHAIN_PAD + CHAIN_MAX_S) * sizeof(double);   // + interval widths
 
 static DeviceInfo g_device = {256, (size_t)160 * 1024};
 
@@ -4529,9 +4679,11 @@ hipError_t kernels_init()
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_terms),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxTableLds);
     if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_chain_blocks),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxChainLds);
-    if (e != hipSuccess) return e;
+    for (const bool terms : {false, true}) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(terms ? k_chain_blocks<true> : k_chain_blocks<false>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxChainLds);
+        if (e != hipSuccess) return e;
+    }
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_terms_chain),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxTableLds);
     if (e != hipSuccess) return e;
@@ -4897,7 +5049,9 @@ static bool plan_fastest(const DeviceTables &T, const DeviceGrid &G, bool terms_
     // (terms beside the per-row chain sums: when the terms need little LDS)
     p.row_together = p.chain_row && p.terms_lds <= 65536;
     // a big table: the workgroups of the chain sums do the terms when they run out of sums
-    p.terms_in_chain = chain && big && !p.chain_row && p.terms_lds <= p.chain_lds;
+    p.terms_in_chain = chain && big && !p.chain_row;
+    if (p.terms_in_chain && stage_s)
+        p.chain_lds += n_s * D;
     if (p.chain_row) {
         if ((long)p.terms_wg + (long)T.n_tables * G.n_mu > kMaxLaunch) return false;
     } else if (chain) {
@@ -5086,9 +5240,9 @@ hipError_t launch_tune_stage(const TunePlan &p, int stage, const DeviceTables &T
                                    p.both_lds, st, T, G, S, p.n_chain_wg, p.chain_wg, p.n_single, p.n_search,
                                    p.n_chunks, p.n_mchunks, p.terms_mode);
             else
-                hipLaunchKernelGGL(k_chain_blocks, dim3((unsigned)p.n_chain_wg), dim3(p.chain_threads),
+                hipLaunchKernelGGL(p.terms_in_chain ? k_chain_blocks<true> : k_chain_blocks<false>, dim3((unsigned)p.n_chain_wg), dim3(p.chain_threads),
                                    p.chain_lds, st, T, G, S, p.chain_wg, p.n_single, p.n_search,
-                                   p.terms_in_chain ? p.terms_mode : -1);
+                                   p.terms_mode);
         }
         break;
     case TUNE_STAGE_PREFIX:

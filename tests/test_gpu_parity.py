@@ -701,6 +701,26 @@ def test_where_the_row_path_ends(n_m, n_P, p_hi, n_s, n, mask):
     assert assert_tables_equal(gpu_tune(wl), want, "%d x %d, mask %x" % (n_m, n_P, mask)), "times not bit-identical"
 
 
+# ------------------------------------------------------------------ terms beside the sums of a big table
+
+@pytest.mark.parametrize("n_tables,n,n_m,n_s,n_P,mask", [
+    (1, 1021, 1, 0, 33, ALL_STRATEGIES_MASK), (1, 1021, 63, 1, 33, ALL_STRATEGIES_MASK), (1, 4096, 65, 63, 40, ALL_STRATEGIES_MASK),
+    (1, 1500, 64, 64, 32, ALL_STRATEGIES_MASK), (2, 1100, 129, 65, 33, 0x1FFF & ~0x1000), (300, 1030, 17, 129, 32, ALL_STRATEGIES_MASK),
+    (3, 2000, 4200, 5, 32, 0x0FFF), (1, 1500, 100, 256, 40, ALL_STRATEGIES_MASK), (1, 1500, 100, 257, 9, ALL_STRATEGIES_MASK),
+    (1, 4096, 70, 1024, 9, 0x1A25), (1, 1500, 70, 1025, 9, ALL_STRATEGIES_MASK), (1, 1500, 257, 20, 5, ALL_STRATEGIES_MASK)])
+def test_terms_beside_the_sums_of_a_big_table(n_tables, n, n_m, n_s, n_P, mask):
+    # groups of 64 sizes, of 64 candidates (and none), rows of (m, s) of up to 256 candidates, each sweep
+    rng = np.random.default_rng(n_m + n_s)
+    x = np.cumsum(rng.integers(1, 60, size=(n_tables, n)), axis=1).astype(np.float64)
+    gaps = np.abs(20.0 + x * 0.05 * (1.0 + 0.4 * rng.standard_normal(x.shape)))
+    P = np.sort(rng.choice(np.arange(2, 150), size=n_P, replace=False)).astype(np.uint32)
+    m = 8 * rng.choice(np.arange(1, 9000), size=n_m, replace=False)
+    s = 8 * np.sort(rng.choice(np.arange(1, 3000), size=n_s, replace=False))
+    wl = Workload("big", x, gaps, rng.uniform(0.0, 90.0, size=n_tables), m.astype(np.uint64), P, s.astype(np.uint64), 16000, mask)
+    want, _ = oracle.tune_workload(wl)
+    assert assert_tables_equal(gpu_tune(wl), want, "n=%d m=%d s=%d" % (n, n_m, n_s)), "times not bit-identical"
+
+
 # ------------------------------------------------------------------ prefix of the block sums
 
 @pytest.mark.parametrize("blocks,n_m,n_P", [(33, 15, 9), (97, 1, 300), (128, 16, 600), (129, 17, 600), (256, 5, 40), (257, 33, 40),
