@@ -1318,7 +1318,38 @@ __device__ __forceinline__ double chain_block_sum(const ChainCtx &C, u64 b, u64 
     return run;
 }
 
-// g((64 b + 1) m) + ... + g((64 b + terms) m), terms < 64 of them in this lane (0: none).
+// As gaps_within, on indices in place of addresses (reach: a power of two).
+template <int V>
+__device__ __forceinline__ void gaps_within_by_index(const ChainCtx &C, int i0, int reach, const double (&z)[V],
+                                                     double (&g)[V])
+{
+    int i[V];
+#pragma unroll
+    for (int c = 0; c < V; ++c)
+        i[c] = i0;
+    for (int half = reach >> 1; half > 0; half >>= 1) {
+        double x[V];
+#pragma unroll
+        for (int c = 0; c < V; ++c) {
+            const int at = i[c] + half;
+            x[c] = C.X[at < C.n + 1 ? at : C.n + 1];       // +inf past the last interval
+        }
+#pragma unroll
+        for (int c = 0; c < V; ++c)
+            i[c] = x[c] <= z[c] ? i[c] + half : i[c];
+    }
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+        const f64x2 ys = C.YS[i[c]];
+        g[c] = __builtin_fma(ys.y, z[c] - C.X[i[c]], ys.x);
+    }
+}
+
+// g((64 b + 1) m) + ... + g((64 b + terms) m), terms < 64 of them in this lane (0: none).  BY_INDEX: for
+// workgroups of 768 threads beside a big table, which the search on addresses made slower (2000 samples,
+// 300 000 points with P up to 300: 219 us by index, 240), while all others gained (3000 points with P up
+// to 64: 600 samples 24.4 us by index, 19.2; 4000 samples 34.3 and 29.1).
+template <bool BY_INDEX>
 __device__ __forceinline__ double chain_rest_sum(const ChainCtx &C, u64 b, u64 m, int terms)
 {
     constexpr int V = 8;
@@ -1329,7 +1360,8 @@ __device__ __forceinline__ double chain_rest_sum(const ChainCtx &C, u64 b, u64 m
     chain_locate<2>(C.X, C.n, ends, at);
     while (__ballot(at[1] - at[0] >= reach) != 0)
         reach <<= 1;
-    reach = reach < C.n + 2 ? reach : C.n + 2;
+    if (!BY_INDEX)
+        reach = reach < C.n + 2 ? reach : C.n + 2;
     double run = 0.0;
 #pragma unroll 1
     for (int k = 0; __ballot(k < terms) != 0; k += V) {
@@ -1337,7 +1369,10 @@ __device__ __forceinline__ double chain_rest_sum(const ChainCtx &C, u64 b, u64 m
 #pragma unroll
         for (int c = 0; c < V; ++c)
             z[c] = __builtin_fma((double)c, md, zb);
-        gaps_within<V>(C, at[0], reach, z, g);
+        if (BY_INDEX)
+            gaps_within_by_index<V>(C, at[0], reach, z, g);
+        else
+            gaps_within<V>(C, at[0], reach, z, g);
 #pragma unroll
         for (int c = 0; c < V; ++c)
             run = k + c < terms ? run + g[c] : run;
@@ -1437,7 +1472,7 @@ k_eval_chain(DeviceTables T, int t, const u64 *dm, const uint32_t *dP, size_t n,
         for (int k = 0; k < mine; ++k)
             done = done + tot[(size_t)k * threads + tid];
     }
-    const double rest = C.n > EVAL_SEARCH_N ? chain_rest_sum(C, full, m_of[tid], tail)
+    const double rest = C.n > EVAL_SEARCH_N ? chain_rest_sum<LEVELS == 4>(C, full, m_of[tid], tail)
                                             : chain_block_sum<false>(C, full, m_of[tid], tail);
     if (i < n)
         out[i] = ok ? __builtin_fma((double)(P - 1u), T.L[t], done + rest) : NAN;
