@@ -154,12 +154,18 @@ int ensure_cut_scratch(plogp_grid *g, size_t n_tables)
     HIP_TRY(hipDeviceSynchronize());     // an earlier extraction on this handle may still run
     g->free_cut_scratch();
     const DeviceGrid G = g->view();
-    const hipError_t e = hipMalloc(&g->cut_block, cutover_scratch(G, (int)n_tables, nullptr, nullptr));
-    if (e != hipSuccess) {
+    size_t most = CUT_SCRATCH_MOST, bytes = cutover_scratch(G, (int)n_tables, most, nullptr, nullptr);
+    hipError_t e;
+    while ((e = hipMalloc(&g->cut_block, bytes)) != hipSuccess) {
         g->cut_block = nullptr;
-        return alloc_error(e);
+        // beside decisions that fill the device: slices of a quarter, down to the shortest
+        most = bytes / 4;
+        const size_t fewer = cutover_scratch(G, (int)n_tables, most, nullptr, nullptr);
+        if (e != hipErrorOutOfMemory || fewer >= bytes) return alloc_error(e);
+        (void)hipGetLastError();
+        bytes = fewer;
     }
-    (void)cutover_scratch(G, (int)n_tables, g->cut_block, &g->cut);
+    (void)cutover_scratch(G, (int)n_tables, most, g->cut_block, &g->cut);
     g->cut_tables = n_tables;
     return PLOGP_OK;
 }

@@ -26,6 +26,7 @@
 //                of the output, in scratch, with the number of them;
 //   k_cut_place  adds up the numbers of the groups before and moves the packed starts to their
 //                place, as run records.
+// A batch whose packed starts would take more than CUT_SCRATCH_MOST goes through them slice by slice.
 #include "plogp_internal.hpp"
 
 namespace plogp {
@@ -290,7 +291,7 @@ __global__ void __launch_bounds__(256) k_cut_emit(CutShape sh, const plogp_cell_
 // Small jobs: 254 rows x 256 sizes 9.8 us in groups of 16 rows (11.5 in groups of 64; 13 as mark,
 // prefix and emit).
 struct CutRowsArgs {
-    u64 n_rows;
+    u64 row0, n_rows;      // the slice: rows row0 .. n_rows - 1; groups and scratch count from row0
     int row_bits;          // log2 of the rows of a group
     int seg, cap;          // sizes of a thread; starts that fit the pool
     uint2 *keys;           // [groups][cap] starts in the order of the output: (s, strategy), ...
@@ -324,7 +325,7 @@ k_cut_rows(CutShape sh, const plogp_cell_dev *cells, int key_mode, CutRowsArgs A
     uint32_t *found = reinterpret_cast<uint32_t *>(key_of + A.cap);            // [cap] thread, its start, its size
     uint32_t *first = found + A.cap;                                           // [threads] starts before (row, part)
     unsigned short *place = reinterpret_cast<unsigned short *>(first + threads);   // [cap] by order of output
-    const u64 group = blockIdx.x, row = (group << A.row_bits) + my_row;
+    const u64 group = blockIdx.x, row = A.row0 + (group << A.row_bits) + my_row;
     const bool live = row < A.n_rows;
     const u64 rr = live ? row : A.n_rows - 1;          // padding threads read a valid row
     const size_t base = (size_t)(rr / (u64)sh.n_P) * sh.n_m * sh.n_P + (size_t)(rr % (u64)sh.n_P);
@@ -402,7 +403,7 @@ k_cut_rows(CutShape sh, const plogp_cell_dev *cells, int key_mode, CutRowsArgs A
     first[tid] = inside;                               // (every thread replaces the entry it read)
     __syncthreads();
     if (tid < rows && live)
-        A.row_first[row] = first[tid * parts];
+        A.row_first[row - A.row0] = first[tid * parts];
     if (tid == 0)
         A.count[group] = total;
     uint2 *keys = A.keys + group * A.cap;
@@ -424,7 +425,8 @@ k_cut_rows(CutShape sh, const plogp_cell_dev *cells, int key_mode, CutRowsArgs A
 }
 
 // `per_wg` groups to a workgroup.  local, before: the prefix of the counts in two levels, or null:
-// then the workgroup adds up the counts before its first group itself.
+// then the workgroup adds up the counts before its first group itself.  The number of runs in
+// the slices before is what the one before left in row_offsets[row0]; this one writes it there again.
 __global__ void __launch_bounds__(256) k_cut_place(CutShape sh, const plogp_cell_dev *cells, const u64 *m, int key_mode,
                                                    CutRowsArgs A, unsigned n_groups, int parts, int per_wg,
                                                    const uint32_t *local, const u64 *before_of, u64 *row_offsets,
@@ -448,6 +450,7 @@ __global__ void __launch_bounds__(256) k_cut_place(CutShape sh, const plogp_cell
     __syncthreads();
     u64 before = local == nullptr ? wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3]
                                   : before_of[g0 / CUT_SCAN_WG] + local[g0];
+    before += A.row0 > 0 ? row_offsets[A.row0] : 0ull;
     auto emit = [&](u64 at, int mi, const uint2 &key) {
         union {
             plogp_run_dev r;
@@ -462,11 +465,11 @@ __global__ void __launch_bounds__(256) k_cut_place(CutShape sh, const plogp_cell
         const unsigned total = A.count[g];
         const uint2 *keys = A.keys + (size_t)g * A.cap;
         if (tid < 1 << A.row_bits) {
-            const u64 row = ((u64)g << A.row_bits) + tid;
+            const u64 row = A.row0 + ((u64)g << A.row_bits) + tid;
             if (row < A.n_rows)
-                row_offsets[row] = before + A.row_first[row];
+                row_offsets[row] = before + A.row_first[row - A.row0];
             if (row == A.n_rows - 1)
-                row_offsets[A.n_rows] = before + total;        // the grand total
+                row_offsets[A.n_rows] = before + total;        // the grand total, or the next slice's first
         }
         if (total <= (unsigned)A.cap) {
             const uint16_t *sizes = A.sizes + (size_t)g * A.cap;
@@ -475,7 +478,7 @@ __global__ void __launch_bounds__(256) k_cut_place(CutShape sh, const plogp_cell
         } else {
             // a (row, part) of k_cut_rows to a thread: its sizes are read again
             for (int t = tid; t < parts << A.row_bits; t += 256) {
-                const u64 row = ((u64)g << A.row_bits) + t / parts;
+                const u64 row = A.row0 + ((u64)g << A.row_bits) + t / parts;
                 if (row >= A.n_rows)
                     continue;
                 const size_t base = (size_t)(row / (u64)sh.n_P) * sh.n_m * sh.n_P + (size_t)(row % (u64)sh.n_P);
@@ -530,7 +533,7 @@ size_t cutover_items(const DeviceGrid &G, int n_tables)
     return (size_t)n_tables * G.n_ops * G.n_P * n_tiles;
 }
 
-size_t cutover_scratch(const DeviceGrid &G, int n_tables, void *base, CutScratch *C)
+static size_t cut_layout(const DeviceGrid &G, int n_tables, size_t n_rows, void *base, CutScratch *C)
 {
     size_t at = 0;
     auto take = [&](size_t bytes) {
@@ -539,7 +542,8 @@ size_t cutover_scratch(const DeviceGrid &G, int n_tables, void *base, CutScratch
         return reinterpret_cast<void *>(reinterpret_cast<uintptr_t>(base) + here);
     };
     CutScratch c = {};
-    const size_t n_rows = (size_t)n_tables * G.n_ops * G.n_P, few = n_rows < cut_few_rows() ? n_rows : cut_few_rows();
+    c.slice_rows = n_rows;
+    const size_t few = n_rows < cut_few_rows() ? n_rows : cut_few_rows();
     // (for either size of group: a call with fewer tables on the same block never needs a longer one)
     size_t counts = (n_rows + 63) / 64;
     if (counts < (few + 15) / 16) counts = (few + 15) / 16;
@@ -559,6 +563,66 @@ size_t cutover_scratch(const DeviceGrid &G, int n_tables, void *base, CutScratch
     }
     if (C) *C = c;
     return at;
+}
+
+size_t cutover_scratch(const DeviceGrid &G, int n_tables, size_t most, void *base, CutScratch *C)
+{
+    const size_t n_rows = (size_t)n_tables * G.n_ops * G.n_P;
+    size_t rows = n_rows;
+    if (cutover_by_rows(G)) {
+        const size_t all = cut_layout(G, n_tables, n_rows, nullptr, nullptr);
+        if (all > most) rows = n_rows / (all / (most ? most : 1) + 1) & ~(size_t)63;
+        if (rows < CUT_SLICE_LEAST) rows = CUT_SLICE_LEAST;
+        if (rows > n_rows) rows = n_rows;
+    }
+    return cut_layout(G, n_tables, rows, base, C);
+}
+
+// Rows taken whole: one stage of rows row0 .. row1 - 1.
+static hipError_t launch_cut_rows(int stage, const CutShape &sh, const DeviceGrid &G, size_t row0, size_t row1,
+                                  const plogp_cell_dev *d_cells, int key_mode, const CutScratch &C,
+                                  u64 *d_row_offsets, void *d_runs, u64 capacity, hipStream_t st)
+{
+    const size_t n_rows = row1 - row0;
+    const bool few = n_rows < cut_few_rows();
+    CutRowsArgs A;
+    A.row0 = row0;
+    A.n_rows = row1;
+    A.row_bits = few ? 4 : 6;
+    const size_t n_wg = (n_rows + (1u << A.row_bits) - 1) >> A.row_bits;
+    if (n_wg > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    // 16 sizes to a thread, 64 and more on many long rows
+    const int tiles = (G.n_m + 15) / 16, most = few ? 32 : 4, per = (tiles + most - 1) / most;
+    const int wave_parts = 64 >> A.row_bits, waves = ((tiles + per - 1) / per + wave_parts - 1) / wave_parts;
+    const int parts = waves * wave_parts;
+    A.seg = 16 * per;
+    A.cap = cut_keep(G, few) << A.row_bits;
+    A.keys = reinterpret_cast<uint2 *>(C.keys);
+    A.sizes = C.sizes;
+    A.row_first = C.row_first;
+    A.count = C.counts;
+    const bool own_sums = n_wg <= (size_t)CUT_OWN_SUMS;
+    if (stage == 0) {
+        const bool stream = n_rows * G.n_m * sizeof(plogp_cell_dev) > ((size_t)256 << 20);
+        hipLaunchKernelGGL(stream ? k_cut_rows<true> : k_cut_rows<false>, dim3((unsigned)n_wg), dim3(64 * waves),
+                           cut_rows_lds(A.cap, 64 * waves), st, sh, d_cells, key_mode, A);
+    } else if (stage == 1) {
+        if (!own_sums) {
+            const size_t n_sums = (n_wg + CUT_SCAN_WG - 1) / CUT_SCAN_WG;
+            u64 *sums = reinterpret_cast<u64 *>(C.group_total);
+            hipLaunchKernelGGL(k_cut_scan1, dim3((unsigned)n_sums), dim3(CUT_SCAN_THREADS), 0, st, C.counts, C.local,
+                               n_wg, sums);
+            // (the closing entry, which k_cut_place writes too, with the slices before)
+            hipLaunchKernelGGL(k_cut_scan2, dim3(1), dim3(1024), 0, st, sums, n_sums, d_row_offsets + row1);
+        }
+    } else {
+        const int per_wg = few ? 1 : 4;
+        hipLaunchKernelGGL(k_cut_place, dim3((unsigned)((n_wg + per_wg - 1) / per_wg)), dim3(256), 0, st, sh, d_cells,
+                           reinterpret_cast<const u64 *>(G.m), key_mode, A, (unsigned)n_wg, parts, per_wg,
+                           own_sums ? nullptr : C.local, reinterpret_cast<const u64 *>(C.group_total),
+                           d_row_offsets, reinterpret_cast<plogp_run_dev *>(d_runs), capacity);
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_cutovers_stage(int stage, const DeviceGrid &G, int n_tables, const plogp_cell_dev *d_cells,
@@ -584,45 +648,16 @@ hipError_t launch_cutovers_stage(int stage, const DeviceGrid &G, int n_tables, c
     const unsigned blocks = (unsigned)((sh.n_items + 255) / 256);
     const bool fuse = n_groups <= (size_t)CUT_FUSE_MAX;     // the prefix of the group totals inside the last step
     if (cutover_by_rows(G)) {
-        const bool few = n_rows < cut_few_rows();
-        CutRowsArgs A;
-        A.n_rows = n_rows;
-        A.row_bits = few ? 4 : 6;
-        const size_t n_wg = (n_rows + (1u << A.row_bits) - 1) >> A.row_bits;
-        if (n_wg > 0x7FFFFFFFull) return hipErrorInvalidValue;
-        // 16 sizes to a thread, 64 and more on many long rows
-        const int tiles = (G.n_m + 15) / 16, most = few ? 32 : 4, per = (tiles + most - 1) / most;
-        const int wave_parts = 64 >> A.row_bits, waves = ((tiles + per - 1) / per + wave_parts - 1) / wave_parts;
-        const int parts = waves * wave_parts;
-        A.seg = 16 * per;
-        A.cap = cut_keep(G, few) << A.row_bits;
-        A.keys = reinterpret_cast<uint2 *>(C.keys);
-        A.sizes = C.sizes;
-        A.row_first = C.row_first;
-        A.count = C.counts;
-        const bool own_sums = n_wg <= (size_t)CUT_OWN_SUMS;
-        if (stage == 0) {
-            const bool stream = n_rows * G.n_m * sizeof(plogp_cell_dev) > ((size_t)256 << 20);
-            hipLaunchKernelGGL(stream ? k_cut_rows<true> : k_cut_rows<false>, dim3((unsigned)n_wg), dim3(64 * waves),
-                               cut_rows_lds(A.cap, 64 * waves), st, sh, d_cells, key_mode, A);
-        } else if (stage == 1) {
-            if (!own_sums) {
-                const size_t n_sums = (n_wg + CUT_SCAN_WG - 1) / CUT_SCAN_WG;
-                u64 *sums = reinterpret_cast<u64 *>(C.group_total);
-                hipLaunchKernelGGL(k_cut_scan1, dim3((unsigned)n_sums), dim3(CUT_SCAN_THREADS), 0, st, C.counts, C.local,
-                                   n_wg, sums);
-                hipLaunchKernelGGL(k_cut_scan2, dim3(1), dim3(1024), 0, st, sums, n_sums,
-                                   reinterpret_cast<u64 *>(d_row_offsets) + n_rows);
+        // the slices before the last go through all stages in the first
+        size_t row0 = 0;
+        for (; row0 + C.slice_rows < n_rows; row0 += C.slice_rows)
+            for (int k = 0; stage == 0 && k < CUT_STAGES; ++k) {
+                const hipError_t e = launch_cut_rows(k, sh, G, row0, row0 + C.slice_rows, d_cells, key_mode, C,
+                                                     reinterpret_cast<u64 *>(d_row_offsets), d_runs, capacity, st);
+                if (e != hipSuccess) return e;
             }
-        } else {
-            const int per_wg = few ? 1 : 4;
-            hipLaunchKernelGGL(k_cut_place, dim3((unsigned)((n_wg + per_wg - 1) / per_wg)), dim3(256), 0, st, sh, d_cells,
-                               reinterpret_cast<const u64 *>(G.m), key_mode, A, (unsigned)n_wg, parts, per_wg,
-                               own_sums ? nullptr : C.local, reinterpret_cast<const u64 *>(C.group_total),
-                               reinterpret_cast<u64 *>(d_row_offsets), reinterpret_cast<plogp_run_dev *>(d_runs),
-                               (u64)capacity);
-        }
-        return hipGetLastError();
+        return launch_cut_rows(stage, sh, G, row0, n_rows, d_cells, key_mode, C,
+                               reinterpret_cast<u64 *>(d_row_offsets), d_runs, capacity, st);
     }
     if (stage == 0) {
         // a table beyond the 256 MB of the last-level cache is streamed

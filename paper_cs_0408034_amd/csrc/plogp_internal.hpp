@@ -211,12 +211,19 @@ struct CutScratch {
     void *keys;              // rows: the starts in order, (s, strategy) ...
     uint16_t *sizes;         // ... and the index of the message size
     uint32_t *row_first;     // [rows] starts of the group before each row
+    size_t slice_rows;       // rows: so many at a time
 };
 constexpr int CUT_ROWS_MAX_M = 512;        // most sizes of a row that is taken whole
 constexpr int CUT_ROWS_MAX_WAVES = 8;      // waves of a workgroup: 64 rows x 4 parts, 16 rows x 32 parts
 constexpr int CUT_OWN_SUMS = 16384;        // groups whose counts a workgroup adds up itself
-// Bytes of the scratch for n_tables tables (more tables never take less), laid out at `base` in C.
-size_t cutover_scratch(const DeviceGrid &G, int n_tables, void *base, CutScratch *C);
+// Scratch that rows taken whole may use: a batch that needs more goes in slices of rows, of 0.8 GB of
+// decisions at least (6 sizes), in which the launches of one slice more are lost (1.73 million rows x 64
+// sizes in two slices 356 us, in one 343; 4.8 million x 6 187 and 183, 14.4 million in four 570 and 649).
+constexpr size_t CUT_SCRATCH_MOST = (size_t)512 << 20;
+constexpr size_t CUT_SLICE_LEAST = 4096;   // rows of a slice at least
+// Bytes of the scratch for n_tables tables or fewer, laid out at `base` in C; rows taken whole stay within
+// `most`, or at CUT_SLICE_LEAST rows to a slice.
+size_t cutover_scratch(const DeviceGrid &G, int n_tables, size_t most, void *base, CutScratch *C);
 
 // Number of (row, tile) entries for n_tables tables over grid G.
 size_t cutover_items(const DeviceGrid &G, int n_tables);

@@ -128,6 +128,31 @@ int main()
     }
     CHECK(leaner > 0);
 
+    // ---- scratch of the cut-over extraction: rows taken whole stay within their limit (or take no more than
+    // a counter, its prefix and the flags of each tile of 16 sizes), and a tighter limit never takes more
+    for (int it = 0; it < 20000; ++it) {
+        plogp::DeviceGrid G = {};
+        G.n_m = pick(0, 1) ? pick(1, 40) : pick(1, 513);
+        G.n_ops = pick(1, 4);
+        G.n_P = pick(0, 1) ? pick(1, 50) : pick(1, 5000);
+        const int n_tables = 1 + (int)(next_u64() % (1ull << pick(0, 24)));
+        const size_t n_rows = (size_t)n_tables * G.n_ops * G.n_P, per_tile = 12 * plogp::cutover_items(G, n_tables);
+        plogp::CutScratch C = {};
+        const size_t bytes = plogp::cutover_scratch(G, n_tables, plogp::CUT_SCRATCH_MOST, nullptr, &C);
+        const size_t limit = per_tile > plogp::CUT_SCRATCH_MOST ? per_tile : plogp::CUT_SCRATCH_MOST;
+        CHECK(bytes <= limit + (limit >> 6));
+        CHECK(C.slice_rows >= 1 && C.slice_rows <= n_rows && (C.slice_rows == n_rows || C.slice_rows % 64 == 0));
+        for (size_t most = bytes / 4, before = bytes;; most = before / 4) {
+            const size_t fewer = plogp::cutover_scratch(G, n_tables, most, nullptr, &C);
+            CHECK(fewer <= before && C.slice_rows >= 1 && C.slice_rows <= n_rows);
+            if (fewer == before) {                    // the shortest slices
+                CHECK(G.n_m > plogp::CUT_ROWS_MAX_M || C.slice_rows == n_rows || C.slice_rows == plogp::CUT_SLICE_LEAST);
+                break;
+            }
+            before = fewer;
+        }
+    }
+
     // ---- slices of tables of the robustness summary: a launch dimension, at any number of tables
     const int n_robust[] = {1, 2, 9, 2001, 16776960, 16776961, 16776962, 1 << 24};
     for (int n : n_robust)

@@ -146,6 +146,25 @@ def test_full_size_of_config_4_random_decisions():
     check(cells, m, P, 1)
 
 
+@pytest.mark.timeout(300)
+def test_more_rows_than_the_scratch_holds_go_in_slices():
+    """8.55 million rows of 6 sizes, whose packed starts would take 64 bytes a row: two slices.  The second
+    counts on from the first, with room for all runs, with room for some of its own and with none for them."""
+    rng = np.random.default_rng(43)
+    n_m, n_P = 6, 3
+    cells = random_table(rng, 2_850_000, 1, n_m, n_P, 0.3)
+    assert cells.size // n_m * 64 > 512 << 20
+    m = (np.arange(n_m, dtype=np.uint64) + 1) * 8
+    P = (np.arange(n_P) + 2).astype(np.uint32)
+    want_off, want_runs = oc.cutovers(cells, m, 1)
+    for cap in (len(want_runs) + 5, 2 * len(want_runs) // 3, len(want_runs) // 3):
+        off, runs = gpu_cutovers(cells, m, P, 1, capacity=cap)
+        assert (off == want_off).all()
+        n = min(cap, len(want_runs))
+        assert (runs[:n] == want_runs[:n]).all()
+        assert (runs[n:].view(np.uint8) == 0xEE).all()
+
+
 def test_one_grid_handle_many_rows_then_fewer_then_many_again():
     """The same handle serves a batch on the one-pass path, a smaller one on the tiled path and
     the first again: whatever a call leaves in the handle's scratch, the next one starts clean."""
