@@ -277,9 +277,10 @@ __global__ void __launch_bounds__(256) k_cut_emit(CutShape sh, const plogp_cell_
 // ---- one pass over the table, a group of rows to a workgroup ----------------------
 //
 // A workgroup takes 64 rows, or 16 where there are few, and a thread `seg` sizes of one (a multiple of
-// 16): rows along the lanes, then sizes along the rest of the wave and the waves.  Every start goes to a pool in LDS with its key and where it was found; once the
-// counts are known the pool leaves in the order of the output, whole cache lines at a time.  A
-// group whose starts do not fit leaves the counts only, and k_cut_place reads its rows once more.
+// 16): rows along the lanes, then sizes along the rest of the wave and the waves.  Every start goes to a
+// pool in LDS with its key and where it was found; once the counts are known the pool leaves in the order
+// of the output, whole cache lines at a time.  A group whose starts do not fit leaves the counts only, and
+// k_cut_place reads its rows once more.
 //
 // Nothing waits for another workgroup: 480 000 rows x 256 sizes (1.97 GB) take 335 + 15 us, of which
 // the bare read is 318, 6.2 TB/s.  With the place of a group's runs learnt from status words of the
@@ -301,6 +302,7 @@ struct CutRowsArgs {
 };
 
 static int cut_rows_lds(int cap, int threads) { return cap * 14 + threads * 4; }
+constexpr int CUT_ROWS_STATIC_LDS = 512;      // more than k_cut_rows has beside that
 
 __device__ __forceinline__ u64 wave_sum_u64(u64 v)
 {
@@ -408,7 +410,7 @@ k_cut_rows(CutShape sh, const plogp_cell_dev *cells, int key_mode, CutRowsArgs A
         A.count[group] = total;
     uint2 *keys = A.keys + group * A.cap;
     if (total > (unsigned)A.cap) {
-        // (there are at most two threads to a start that is kept, so the counts fit)
+        // (there are at most two threads to a start that is kept where a group can have more, so they fit)
         reinterpret_cast<uint32_t *>(keys)[tid] = inside;
         return;
     }
@@ -424,9 +426,10 @@ k_cut_rows(CutShape sh, const plogp_cell_dev *cells, int key_mode, CutRowsArgs A
     }
 }
 
-// `per_wg` groups to a workgroup.  local, before: the prefix of the counts in two levels, or null:
-// then the workgroup adds up the counts before its first group itself.  The number of runs in
-// the slices before is what the one before left in row_offsets[row0]; this one writes it there again.
+// `per_wg` groups to a workgroup.  FEW: groups of 16 rows.  local, before: the prefix of the counts in two
+// levels, or null: then the workgroup adds up the counts before its first group itself.  The number of runs
+// in the slices before is what the one before left in row_offsets[row0]; this one writes it there again.
+template <bool FEW>
 __global__ void __launch_bounds__(256) k_cut_place(CutShape sh, const plogp_cell_dev *cells, const u64 *m, int key_mode,
                                                    CutRowsArgs A, unsigned n_groups, int parts, int per_wg,
                                                    const uint32_t *local, const u64 *before_of, u64 *row_offsets,
@@ -473,7 +476,22 @@ __global__ void __launch_bounds__(256) k_cut_place(CutShape sh, const plogp_cell
         }
         if (total <= (unsigned)A.cap) {
             const uint16_t *sizes = A.sizes + (size_t)g * A.cap;
-            for (unsigned d = (unsigned)tid; d < total && before + d < capacity; d += 256)
+            const u64 room = capacity > before ? capacity - before : 0ull;
+            const unsigned n = total < room ? total : (unsigned)room;
+            unsigned d = (unsigned)tid;
+            for (; FEW && d + 768 < n; d += 1024) {    // four loads before the first store
+                uint2 key[4];
+                int mi[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    key[u] = keys[d + 256 * u];
+                    mi[u] = sizes[d + 256 * u];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    emit(before + d + 256 * u, mi[u], key[u]);
+            }
+            for (; d < n; d += 256)
                 emit(before + d, sizes[d], keys[d]);
         } else {
             // a (row, part) of k_cut_rows to a thread: its sizes are read again
@@ -513,19 +531,58 @@ __global__ void __launch_bounds__(256) k_cut_place(CutShape sh, const plogp_cell
 
 static bool cutover_by_rows(const DeviceGrid &G) { return G.n_m <= CUT_ROWS_MAX_M; }
 
-// Starts per row that are kept: a quarter of the cells or six, at most 16; for few rows, whose groups
-// differ more and where a group that is read again is seen, half or twelve, at most 64 (tuned tables
-// hold 2 to 8 starts a row: groups of 64 rows up to 12 a row on 250 sizes, groups of 16 up to 8 on 20
-// sizes and 41 on 500).
-static int cut_keep(const DeviceGrid &G, bool few)
-{
-    const int part = (G.n_m + (few ? 1 : 3)) / (few ? 2 : 4), least = few ? 12 : 6, most = few ? 64 : 16;
-    const int row = part < least ? least : part < most ? part : most;
-    return row < G.n_m ? row : G.n_m;
-}
-
 // Few rows: groups of 64 would not fill the chip (254 rows x 256 sizes: 10.9 us in groups of 64).
 static size_t cut_few_rows() { return (size_t)256 * device_info().n_cu; }
+
+// Starts that are kept.  Tuned tables hold 2 to 8 a row (groups of 64 rows up to 12 on 250 sizes, groups of
+// 16 up to 8 on 20 sizes and 41 on 500), but a key that holds the segment size changes far more often where
+// the candidates are dense.  A group with more is read again, its records go out a row to a thread, and the
+// call takes twice as long: 480 000 rows x 256 sizes with 18 starts a row 868 us read again, 407 kept; 39 a
+// row 993 and 551; 19 200 rows x 512 sizes with 77 a row 71 and 38.  Room for them costs little, down to
+// three workgroups of four waves per compute unit (480 000 rows x 256 sizes with 6 starts a row: room for 16
+// 358.8 us, for 48 359.8; 384 000 x 512 for 16 585, for 80 590).
+// Where all groups are on the chip at once they share its LDS, whatever that gives: 96 000 rows x 16 sizes,
+// half of the cells starts, 16.6 us (25.7 with room for 6), 48 rows x 512 12.0 (15.5 with room for 64).
+CutRowsShape cutover_rows_shape(const DeviceGrid &G, size_t n_rows, size_t entries)
+{
+    CutRowsShape c;
+    const bool few = n_rows < cut_few_rows();
+    const size_t n_cu = (size_t)device_info().n_cu;
+    c.row_bits = few ? 4 : 6;
+    c.groups = (n_rows + (1u << c.row_bits) - 1) >> c.row_bits;
+    // 16 sizes to a thread, 64 and more on many long rows
+    const int tiles = (G.n_m + 15) / 16, most = few ? 32 : 4, per = (tiles + most - 1) / most;
+    const int wave_parts = 64 >> c.row_bits;
+    c.seg = 16 * per;
+    c.waves = ((tiles + per - 1) / per + wave_parts - 1) / wave_parts;
+    c.parts = c.waves * wave_parts;
+    const int half = (G.n_m + 1) / 2, quarter = (G.n_m + 3) / 4;
+    int row = few ? (half < 12 ? 12 : half < 64 ? half : 64)
+                  : (quarter < 6 ? 6 : quarter < 32 ? quarter : 16 + G.n_m / 8);
+    if (row > G.n_m) row = G.n_m;
+    c.least = row << c.row_bits;
+    // (a group more than each has on average, for compute units that get more of them)
+    const size_t per_cu = c.groups <= n_cu ? 1 : c.groups / n_cu + 2, share = device_info().lds_per_cu / per_cu;
+    const size_t other = CUT_ROWS_STATIC_LDS + (size_t)cut_rows_lds(0, 64 * c.waves);
+    if (share > other) {
+        const size_t fit = (share - other) / (size_t)cut_rows_lds(1 << c.row_bits, 0);
+        if (fit > (size_t)row) row = fit < (size_t)G.n_m ? (int)fit : G.n_m;
+    }
+    c.cap = row << c.row_bits;
+    if (c.groups && (size_t)c.cap > entries / c.groups) c.cap = (int)(entries / c.groups);
+    return c;
+}
+
+hipError_t cutover_init()
+{
+    for (const bool stream : {false, true}) {
+        const void *k = reinterpret_cast<const void *>(stream ? k_cut_rows<true> : k_cut_rows<false>);
+        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 (int)device_info().lds_per_cu - CUT_ROWS_STATIC_LDS);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 
 size_t cutover_items(const DeviceGrid &G, int n_tables)
 {
@@ -533,7 +590,7 @@ size_t cutover_items(const DeviceGrid &G, int n_tables)
     return (size_t)n_tables * G.n_ops * G.n_P * n_tiles;
 }
 
-static size_t cut_layout(const DeviceGrid &G, int n_tables, size_t n_rows, void *base, CutScratch *C)
+static size_t cut_layout(const DeviceGrid &G, int n_tables, size_t n_rows, size_t most, void *base, CutScratch *C)
 {
     size_t at = 0;
     auto take = [&](size_t bytes) {
@@ -544,7 +601,7 @@ static size_t cut_layout(const DeviceGrid &G, int n_tables, size_t n_rows, void 
     CutScratch c = {};
     c.slice_rows = n_rows;
     const size_t few = n_rows < cut_few_rows() ? n_rows : cut_few_rows();
-    // (for either size of group: a call with fewer tables on the same block never needs a longer one)
+    // (for either size of group; fewer tables on the same block share out its room for starts)
     size_t counts = (n_rows + 63) / 64;
     if (counts < (few + 15) / 16) counts = (few + 15) / 16;
     if (!cutover_by_rows(G)) counts = cutover_items(G, n_tables);
@@ -552,11 +609,11 @@ static size_t cut_layout(const DeviceGrid &G, int n_tables, size_t n_rows, void 
     c.local = static_cast<uint32_t *>(take(counts * sizeof(uint32_t)));
     c.group_total = static_cast<uint64_t *>(take((counts + CUT_SCAN_WG - 1) / CUT_SCAN_WG * sizeof(uint64_t)));
     if (cutover_by_rows(G)) {
-        size_t entries = (n_rows + 63) / 64 * 64 * cut_keep(G, false);
-        const size_t few_entries = (few + 15) / 16 * 16 * cut_keep(G, true);
-        if (entries < few_entries) entries = few_entries;
-        c.keys = take(entries * sizeof(uint2));
-        c.sizes = static_cast<uint16_t *>(take(entries * sizeof(uint16_t)));
+        const CutRowsShape shape = cutover_rows_shape(G, n_rows, SIZE_MAX);
+        constexpr size_t each = sizeof(uint2) + sizeof(uint16_t);
+        c.entries = shape.groups * (shape.groups * shape.cap <= most / each ? shape.cap : shape.least);
+        c.keys = take(c.entries * sizeof(uint2));
+        c.sizes = static_cast<uint16_t *>(take(c.entries * sizeof(uint16_t)));
         c.row_first = static_cast<uint32_t *>(take(n_rows * sizeof(uint32_t)));
     } else {
         c.flags = static_cast<uint32_t *>(take(counts * sizeof(uint32_t)));
@@ -570,12 +627,12 @@ size_t cutover_scratch(const DeviceGrid &G, int n_tables, size_t most, void *bas
     const size_t n_rows = (size_t)n_tables * G.n_ops * G.n_P;
     size_t rows = n_rows;
     if (cutover_by_rows(G)) {
-        const size_t all = cut_layout(G, n_tables, n_rows, nullptr, nullptr);
+        const size_t all = cut_layout(G, n_tables, n_rows, most, nullptr, nullptr);
         if (all > most) rows = n_rows / (all / (most ? most : 1) + 1) & ~(size_t)63;
         if (rows < CUT_SLICE_LEAST) rows = CUT_SLICE_LEAST;
         if (rows > n_rows) rows = n_rows;
     }
-    return cut_layout(G, n_tables, rows, base, C);
+    return cut_layout(G, n_tables, rows, most, base, C);
 }
 
 // Rows taken whole: one stage of rows row0 .. row1 - 1.
@@ -584,19 +641,16 @@ static hipError_t launch_cut_rows(int stage, const CutShape &sh, const DeviceGri
                                   u64 *d_row_offsets, void *d_runs, u64 capacity, hipStream_t st)
 {
     const size_t n_rows = row1 - row0;
-    const bool few = n_rows < cut_few_rows();
+    const CutRowsShape shape = cutover_rows_shape(G, n_rows, C.entries);
+    const size_t n_wg = shape.groups;
+    if (n_wg > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    const int threads = 64 * shape.waves;
     CutRowsArgs A;
     A.row0 = row0;
     A.n_rows = row1;
-    A.row_bits = few ? 4 : 6;
-    const size_t n_wg = (n_rows + (1u << A.row_bits) - 1) >> A.row_bits;
-    if (n_wg > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    // 16 sizes to a thread, 64 and more on many long rows
-    const int tiles = (G.n_m + 15) / 16, most = few ? 32 : 4, per = (tiles + most - 1) / most;
-    const int wave_parts = 64 >> A.row_bits, waves = ((tiles + per - 1) / per + wave_parts - 1) / wave_parts;
-    const int parts = waves * wave_parts;
-    A.seg = 16 * per;
-    A.cap = cut_keep(G, few) << A.row_bits;
+    A.row_bits = shape.row_bits;
+    A.seg = shape.seg;
+    A.cap = shape.cap;
     A.keys = reinterpret_cast<uint2 *>(C.keys);
     A.sizes = C.sizes;
     A.row_first = C.row_first;
@@ -604,8 +658,8 @@ static hipError_t launch_cut_rows(int stage, const CutShape &sh, const DeviceGri
     const bool own_sums = n_wg <= (size_t)CUT_OWN_SUMS;
     if (stage == 0) {
         const bool stream = n_rows * G.n_m * sizeof(plogp_cell_dev) > ((size_t)256 << 20);
-        hipLaunchKernelGGL(stream ? k_cut_rows<true> : k_cut_rows<false>, dim3((unsigned)n_wg), dim3(64 * waves),
-                           cut_rows_lds(A.cap, 64 * waves), st, sh, d_cells, key_mode, A);
+        hipLaunchKernelGGL(stream ? k_cut_rows<true> : k_cut_rows<false>, dim3((unsigned)n_wg), dim3(threads),
+                           cut_rows_lds(A.cap, threads), st, sh, d_cells, key_mode, A);
     } else if (stage == 1) {
         if (!own_sums) {
             const size_t n_sums = (n_wg + CUT_SCAN_WG - 1) / CUT_SCAN_WG;
@@ -616,9 +670,13 @@ static hipError_t launch_cut_rows(int stage, const CutShape &sh, const DeviceGri
             hipLaunchKernelGGL(k_cut_scan2, dim3(1), dim3(1024), 0, st, sums, n_sums, d_row_offsets + row1);
         }
     } else {
-        const int per_wg = few ? 1 : 4;
-        hipLaunchKernelGGL(k_cut_place, dim3((unsigned)((n_wg + per_wg - 1) / per_wg)), dim3(256), 0, st, sh, d_cells,
-                           reinterpret_cast<const u64 *>(G.m), key_mode, A, (unsigned)n_wg, parts, per_wg,
+        // four groups of 64 rows to a workgroup; one where few of them have short rows, as four in turn
+        // would leave most of the chip idle (96 000 rows x 16 sizes 11.9 us, 14.6 with four; x 6 11.0, 13.5)
+        const bool few = shape.row_bits < 6;
+        const int per_wg = few || (G.n_m <= 32 && n_wg < (size_t)8 * device_info().n_cu) ? 1 : 4;
+        hipLaunchKernelGGL(few ? k_cut_place<true> : k_cut_place<false>,
+                           dim3((unsigned)((n_wg + per_wg - 1) / per_wg)), dim3(256), 0, st, sh, d_cells,
+                           reinterpret_cast<const u64 *>(G.m), key_mode, A, (unsigned)n_wg, shape.parts, per_wg,
                            own_sums ? nullptr : C.local, reinterpret_cast<const u64 *>(C.group_total),
                            d_row_offsets, reinterpret_cast<plogp_run_dev *>(d_runs), capacity);
     }

@@ -212,6 +212,7 @@ struct CutScratch {
     uint16_t *sizes;         // ... and the index of the message size
     uint32_t *row_first;     // [rows] starts of the group before each row
     size_t slice_rows;       // rows: so many at a time
+    size_t entries;          // ... with room for so many starts
 };
 constexpr int CUT_ROWS_MAX_M = 512;        // most sizes of a row that is taken whole
 constexpr int CUT_ROWS_MAX_WAVES = 8;      // waves of a workgroup: 64 rows x 4 parts, 16 rows x 32 parts
@@ -224,6 +225,17 @@ constexpr size_t CUT_SLICE_LEAST = 4096;   // rows of a slice at least
 // Bytes of the scratch for n_tables tables or fewer, laid out at `base` in C; rows taken whole stay within
 // `most`, or at CUT_SLICE_LEAST rows to a slice.
 size_t cutover_scratch(const DeviceGrid &G, int n_tables, size_t most, void *base, CutScratch *C);
+
+// How rows taken whole are shared out: a workgroup takes 2^row_bits rows, a thread `seg` sizes of one, and
+// `cap` starts of the group are kept (of a group with more, only their number).
+struct CutRowsShape {
+    int row_bits, seg, waves, parts;         // parts: of a row's sizes
+    int cap, least;                          // least: kept where room is short
+    size_t groups;
+};
+// For a slice of n_rows in scratch with room for `entries` starts.
+CutRowsShape cutover_rows_shape(const DeviceGrid &G, size_t n_rows, size_t entries);
+hipError_t cutover_init();
 
 // Number of (row, tile) entries for n_tables tables over grid G.
 size_t cutover_items(const DeviceGrid &G, int n_tables);

@@ -4750,7 +4750,7 @@ hipError_t kernels_init()
         e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)BATCH_T_LDS_MAX);
         if (e != hipSuccess) return e;
     }
-    return e;
+    return cutover_init();
 }
 
 hipError_t launch_slopes(const DeviceTables &T, double *slope_out, hipStream_t st)

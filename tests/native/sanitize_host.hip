@@ -142,6 +142,15 @@ int main()
         const size_t limit = per_tile > plogp::CUT_SCRATCH_MOST ? per_tile : plogp::CUT_SCRATCH_MOST;
         CHECK(bytes <= limit + (limit >> 6));
         CHECK(C.slice_rows >= 1 && C.slice_rows <= n_rows && (C.slice_rows == n_rows || C.slice_rows % 64 == 0));
+        // a group's starts fit the scratch and a workgroup's LDS, or, where they are too many, its threads' counts do
+        for (int k = 0; k < 8 && G.n_m <= plogp::CUT_ROWS_MAX_M; ++k) {
+            const size_t rows = k == 0 ? C.slice_rows : 1 + next_u64() % C.slice_rows;
+            const plogp::CutRowsShape c = plogp::cutover_rows_shape(G, rows, C.entries);
+            CHECK(c.groups << c.row_bits >= rows && c.groups * c.cap <= C.entries && c.seg * c.parts >= G.n_m);
+            CHECK(64 * c.waves == c.parts << c.row_bits && c.waves <= plogp::CUT_ROWS_MAX_WAVES && c.seg % 16 == 0);
+            CHECK(14 * c.cap + 4 * 64 * c.waves + 512 <= 160 * 1024 && c.cap <= G.n_m << c.row_bits && c.cap < 65536);
+            CHECK(c.cap == G.n_m << c.row_bits || 64 * c.waves * sizeof(uint32_t) <= (size_t)c.cap * 8);
+        }
         for (size_t most = bytes / 4, before = bytes;; most = before / 4) {
             const size_t fewer = plogp::cutover_scratch(G, n_tables, most, nullptr, &C);
             CHECK(fewer <= before && C.slice_rows >= 1 && C.slice_rows <= n_rows);
@@ -151,6 +160,17 @@ int main()
             }
             before = fewer;
         }
+    }
+
+    // starts per row that are kept (reading a group of rows again more than doubles the call)
+    const struct { int n_m; size_t rows; int kept; } keeps[] = {{16, 96000, 16}, {128, 480000, 26}, {256, 480000, 40},
+                                                                {256, 96000, 40}, {512, 384000, 77}, {512, 19200, 77},
+                                                                {512, 48, 512}, {512, 4096, 512}, {256, 960, 256}};
+    for (const auto &k : keeps) {
+        plogp::DeviceGrid G = {};
+        G.n_m = k.n_m;
+        const plogp::CutRowsShape c = plogp::cutover_rows_shape(G, k.rows, SIZE_MAX);
+        CHECK(c.cap >> c.row_bits >= k.kept);
     }
 
     // ---- slices of tables of the robustness summary: a launch dimension, at any number of tables
