@@ -4865,6 +4865,54 @@ static bool use_row_path(const DeviceTables &T, const DeviceGrid &G)
            (long)T.n_tables * G.n_m <= 65535 * 16;
 }
 
+// Masks with Gather or Barrier rows: (table, m) rows per compute unit up to which one workgroup per row beats
+// the staged path, which for these masks has one launch more and reads its terms more often.  How far that
+// carries depends on what the staged path has to do anyway: most where Broadcast, Scatter and Gather share
+// launches and sums, least where there are Broadcast rows and no sums; further with many process counts (of
+// which the staged path makes more passes) and with many candidates for few process counts (a lane of its
+// sweep then takes all of a size); not as far where a table of more than 128 samples has to be staged per
+// row.  Every line lies where whole calls on 16, 64 and 300 samples, 5 to 50 candidates, 5 to 1500 process
+// counts and 250 to 50 000 rows cross, to 4 % on the staged side (us per row and staged in brackets; 64
+// samples, 15 candidates):
+//   all 18 rows            5 process counts up to 6     4100 rows  23  (25)    8100  42  (34)
+//                         36 up to 1500                 6000       44  (48)    8100  57  (56)
+//                        100 up to 1500                 8100       58  (63)  16 000 109 (104)
+//                        300 up to 1500               16 000      125 (161)
+//   Gather                12 up to 200                  2000       15  (17)    4100  27  (22)
+//                        255 up to 1500                 8100       67  (70)  16 000 128 (115)
+//   Barrier                5 up to 6                    3000       12  (12)    6000  21  (13)  16 000 51 (16)
+//                        300 up to 1500                 8100       32  (39)  16 000  58  (62)
+//   Tables 1, 2, Barrier  36 up to 1500                 2000       17  (19)    6000  44  (34)
+//   Broadcast, Barrier    36 up to 60                   2000       14  (15)    4100  27  (20)
+//                        512 up to 513                  8100       58  (59)  16 000 109  (90)
+static long row_path_most(const DeviceTables &T, const DeviceGrid &G)
+{
+    constexpr long kAny = 1L << 40;
+    const bool bcast = (G.mask & 0x3FFu) != 0, scatter = (G.mask & 0x1C00u) != 0;
+    const bool chain = (G.need & (1u << 11)) != 0, gather_chain = (G.extra & 2u) != 0;
+    const bool big = T.n > 128, long_sums = G.n_blk >= 16, wide = G.n_P >= 256;
+    const bool candidates = bcast && G.n_s > 32 && G.n_P < 32;
+    const long n_P = G.n_P;
+    const auto at_least = [](long a, long b) { return a > b ? a : b; };
+    if (n_P >= 1024 || (n_P >= 512 && gather_chain && (scatter || !bcast)))
+        return kAny;
+    if (gather_chain && scatter) {
+        if (wide) return 64;
+        if (bcast) return n_P >= 64 ? 32 : candidates ? 28 : long_sums ? 24 : 17;
+        return at_least(12, n_P / 6);
+    }
+    if (gather_chain) {
+        const long most = candidates ? 20 : at_least(big ? 10 : 11, (big ? 9 : 12) * n_P / 100);
+        return wide && (!bcast || n_P >= 512) ? most * 3 / 2 : most;
+    }
+    if (chain)
+        return candidates ? 22 : at_least(bcast ? (n_P < 32 || !long_sums ? 12 : 10) : long_sums ? 7 : 10,
+                                          (big ? 6 : 9) * n_P / 128 * (wide ? 2 : 1));
+    if (bcast || scatter)
+        return candidates ? 15 : at_least(8, big || !wide ? n_P / 21 : n_P / 14);
+    return at_least(big ? 10 : n_P < 32 ? 12 : 13, big ? (wide ? n_P / 10 : n_P / 15) : wide ? n_P / 6 : n_P / 9);
+}
+
 // LDS of a k_batch_t workgroup: 64 tables by interval, their g(s), the output staging.
 static size_t batch_t_lds(int n, int n_s)
 {
@@ -4945,6 +4993,18 @@ static bool plan_tiles(const DeviceTables &T, const DeviceGrid &G, int tile_m, T
     return (long)T.n_tables * p.n_tiles <= kMaxLaunch;
 }
 
+// The row path's part, the same.
+static bool plan_rows(const DeviceTables &T, const DeviceGrid &G, TunePlan &p)
+{
+    p.path = G.extra == 0 ? TUNE_ROW : TUNE_STAGED;
+    p.whole = G.extra != 0;
+    // two process counts per lane when there are more groups of 64 than waves
+    p.row_two = G.n_P > 64 * (ROW_THREADS / 64);
+    p.row_lds = row_lds_bytes(T.n, G.n_blk, G.n_P);
+    p.lay.total = LayoutBuilder().at;
+    return true;
+}
+
 static bool plan_fastest(const DeviceTables &T, const DeviceGrid &G, bool terms_only, TunePlan &p)
 {
     p = TunePlan{};
@@ -5005,22 +5065,14 @@ static bool plan_fastest(const DeviceTables &T, const DeviceGrid &G, bool terms_
     const long rows = (long)T.n_tables * G.n_m;
     const long few_cells = G.n_P >= 32 && G.n_P < 64 && T.n <= 128 && G.n_s <= 16 ? G.n_blk / 4 : 0;
     // Masks with Gather or Barrier rows take the same launch in place of the staged path's (as its plan,
-    // with `whole` set), and from twice as many rows on only: one more launch and three reads of the
-    // terms less (all 18 rows, 64 sizes x 49 process counts 5.8 us (16.4), 3900 x 36 33 (33), 5000 x 36
-    // 36 (42), 8000 x 7 44 (44), x 24 46 (54), 9000 x 100 52 (51), 16 000 x 100 88 (78); 300 process counts
-    // 9000 80 (101), 16 000 137 (162)).
-    const bool by_row = !terms_only && use_row_path(T, G) &&
-                        (G.n_P >= 512 || rows / (G.extra ? 2 : 1) < (G.n_P >= 256 ? ROW_MAX_ROWS : ROW_MAX_ROWS / 2 - few_cells) * n_cu);
+    // with `whole` set), up to a number of rows of their own (64 sizes x 49 process counts, all 18 rows 5.8 us
+    // (16.4)).
+    const bool few_rows = G.extra != 0 ? rows < row_path_most(T, G) * n_cu
+                                       : G.n_P >= 512 || rows < (G.n_P >= 256 ? ROW_MAX_ROWS : ROW_MAX_ROWS / 2 - few_cells) * n_cu;
+    const bool by_row = !terms_only && use_row_path(T, G) && few_rows;
     const int tile_m = fast_ok && !by_row ? tile_sizes(T, G, true) : 0;
-    if (by_row) {
-        p.path = G.extra == 0 ? TUNE_ROW : TUNE_STAGED;
-        p.whole = G.extra != 0;
-        // two process counts per lane when there are more groups of 64 than waves
-        p.row_two = G.n_P > 64 * (ROW_THREADS / 64);
-        p.row_lds = row_lds_bytes(T.n, G.n_blk, G.n_P);
-        p.lay.total = lb.at;
-        return true;
-    }
+    if (by_row)
+        return plan_rows(T, G, p);
     if (tile_m > 0)
         return plan_tiles(T, G, tile_m, p);
     p.path = TUNE_STAGED;
@@ -5192,9 +5244,18 @@ static bool plan_fastest(const DeviceTables &T, const DeviceGrid &G, bool terms_
 bool plan_tune(const DeviceTables &T, const DeviceGrid &G, bool terms_only, TunePlan &p, size_t most_scratch)
 {
     const bool ok = plan_fastest(T, G, terms_only, p);
-    if (terms_only || G.extra != 0 || T.n <= TILE_FEW_N || (ok && p.lay.total <= most_scratch))
+    if (terms_only || (ok && p.lay.total <= most_scratch))
         return ok;
-    // large tables that the staged path is faster for but has no room for: tiles need no scratch
+    // jobs that the staged path is faster for but has no room for: rows and tiles need no scratch
+    if (G.extra != 0) {
+        if (ok && p.path == TUNE_STAGED && use_row_path(T, G)) {
+            p = TunePlan{};
+            return plan_rows(T, G, p);
+        }
+        return ok;
+    }
+    if (T.n <= TILE_FEW_N)
+        return ok;
     const int tile_m = tile_sizes(T, G, false);
     TunePlan tiles = {};
     if (tile_m > 0 && plan_tiles(T, G, tile_m, tiles)) {

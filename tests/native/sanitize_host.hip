@@ -120,6 +120,9 @@ int main()
                 CHECK(plan.path == plogp::TUNE_STAGED && lean.path == plogp::TUNE_TILE && lean.lay.total == 256);
                 CHECK(!terms_only && G.extra == 0 && T.n > 512 && lean.tile_lds <= 160 * 1024 - 256);
             }
+            if (G.extra != 0 && !terms_only && plan.path == plogp::TUNE_STAGED && T.n <= 512 && G.n_blk <= 32 &&
+                G.n_s <= 64 && (long)T.n_tables * G.n_m <= 65535 * 16)
+                CHECK(lean.whole && lean.lay.total == 256);
             if (plan.path == plogp::TUNE_STAGED && plan.pairs)
                 CHECK(l.segA != 0 && l.segB != 0 && l.amin != 0 && G.n_s > 0);
             if (plan.path == plogp::TUNE_STAGED && plan.lanes_s && !terms_only)
@@ -171,6 +174,32 @@ int main()
         G.n_m = k.n_m;
         const plogp::CutRowsShape c = plogp::cutover_rows_shape(G, k.rows, SIZE_MAX);
         CHECK(c.cap >> c.row_bits >= k.kept);
+    }
+
+    // masks with Gather or Barrier rows: whole rows to a workgroup where that is the faster path
+    const struct { unsigned mask; int n_m, n_P, p_max, whole; } routes[] = {
+        {PLOGP_MASK_EVERY, 4000, 5, 6, 1},      {PLOGP_MASK_EVERY, 8000, 5, 6, 0},      {PLOGP_MASK_EVERY, 8000, 100, 1500, 1},
+        {PLOGP_MASK_EVERY, 16000, 300, 1500, 1}, {PLOGP_MASK_EVERY, 50000, 600, 2000, 1}, {PLOGP_MASK_GATHER, 2000, 12, 200, 1},
+        {PLOGP_MASK_GATHER, 5000, 12, 200, 0},  {PLOGP_MASK_BARRIER, 2000, 5, 6, 1},    {PLOGP_MASK_BARRIER, 5000, 5, 6, 0},
+        {PLOGP_MASK_BARRIER, 5000, 100, 1500, 0}, {PLOGP_MASK_BARRIER, 50000, 512, 513, 0},
+        {PLOGP_MASK_ALL | PLOGP_MASK_BARRIER, 5000, 36, 1500, 0}, {PLOGP_MASK_BCAST | PLOGP_MASK_GATHER, 5000, 12, 200, 0},
+        {PLOGP_MASK_BARRIER, 50000, 1500, 2048, 1}};
+    for (const auto &r : routes) {
+        plogp::DeviceTables T = {};
+        plogp::DeviceGrid G = {};
+        T.n_tables = 1;
+        T.n = 64;
+        G.n_m = G.n_mu = r.n_m;
+        G.n_P = r.n_P;
+        G.n_s = 15;
+        G.n_blk = (r.p_max - 1) / 64 + 1;
+        while ((1 << G.cl_max) < r.p_max) ++G.cl_max;
+        G.mask = r.mask & PLOGP_MASK_ALL;
+        G.extra = r.mask >> 13;
+        G.need = (((r.mask >> 11) | (r.mask >> 14)) & 1u) << 11 | (((r.mask >> 12) | (r.mask >> 15)) & 1u) << 12;
+        G.n_ops = 4;
+        plogp::TunePlan plan;
+        CHECK(plogp::plan_tune(T, G, false, plan) && plan.whole == r.whole);
     }
 
     // ---- slices of tables of the robustness summary: a launch dimension, at any number of tables
