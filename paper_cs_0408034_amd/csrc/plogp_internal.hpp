@@ -147,8 +147,8 @@ struct TunePlan {
     // table-lane batch path
     int n_stage, prep_wg, n_tg, m_per_wave, batch_mchunks;
     size_t setup_lds, batch_lds;
-    // whole-row path (whole: in place of the staged path's launches, for masks with rows beyond the tables)
-    int row_two, whole;
+    // whole-row path
+    int row_two;
     size_t row_lds;
     // tile path (a table and tile_m message sizes per workgroup)
     int tile_m, n_tiles;

@@ -4996,8 +4996,7 @@ static bool plan_tiles(const DeviceTables &T, const DeviceGrid &G, int tile_m, T
 // The row path's part, the same.
 static bool plan_rows(const DeviceTables &T, const DeviceGrid &G, TunePlan &p)
 {
-    p.path = G.extra == 0 ? TUNE_ROW : TUNE_STAGED;
-    p.whole = G.extra != 0;
+    p.path = TUNE_ROW;
     // two process counts per lane when there are more groups of 64 than waves
     p.row_two = G.n_P > 64 * (ROW_THREADS / 64);
     p.row_lds = row_lds_bytes(T.n, G.n_blk, G.n_P);
@@ -5064,9 +5063,8 @@ static bool plan_fastest(const DeviceTables &T, const DeviceGrid &G, bool terms_
     // process counts 3000 rows 21 (23)).
     const long rows = (long)T.n_tables * G.n_m;
     const long few_cells = G.n_P >= 32 && G.n_P < 64 && T.n <= 128 && G.n_s <= 16 ? G.n_blk / 4 : 0;
-    // Masks with Gather or Barrier rows take the same launch in place of the staged path's (as its plan,
-    // with `whole` set), up to a number of rows of their own (64 sizes x 49 process counts, all 18 rows 5.8 us
-    // (16.4)).
+    // Masks with Gather or Barrier rows take the same launch up to a number of rows of their own (64 sizes x
+    // 49 process counts, all 18 rows 5.8 us (16.4)).
     const bool few_rows = G.extra != 0 ? rows < row_path_most(T, G) * n_cu
                                        : G.n_P >= 512 || rows < (G.n_P >= 256 ? ROW_MAX_ROWS : ROW_MAX_ROWS / 2 - few_cells) * n_cu;
     const bool by_row = !terms_only && use_row_path(T, G) && few_rows;
@@ -5289,7 +5287,7 @@ hipError_t launch_tune_stage(const TunePlan &p, int stage, const DeviceTables &T
         }
         return hipGetLastError();
     }
-    if (p.path == TUNE_ROW || p.whole) {
+    if (p.path == TUNE_ROW) {
         if (stage == TUNE_STAGE_SWEEP) {
             const bool all = G.mask == 0x1FFFu, two = p.row_two != 0;
             const auto kern = G.extra == 0 ? (all ? (two ? k_row<true, 2, false> : k_row<true, 1, false>)

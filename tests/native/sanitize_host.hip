@@ -104,25 +104,30 @@ int main()
             for (size_t o : offs)
                 CHECK(o < l.total && o % 256 == 0);
             CHECK(plan.path >= 0 && plan.path <= 3);
-            // rows beyond the tables: the staged path, or the table-lane kernel when the Gather
-            // rows are enabled exactly as the Scatter rows are (or one of the two is absent)
+            // rows beyond the tables: the staged path, a row to a workgroup, or the table-lane kernel when
+            // the Gather rows are enabled exactly as the Scatter rows are (or one of the two is absent)
             const unsigned scatter_rows = G.mask & 0x1C00u, gather_rows = (G.extra & 7u) << 10;
             const bool lanes_may = gather_rows == 0 || scatter_rows == 0 || gather_rows == scatter_rows;
             if (terms_only)
                 CHECK(plan.path == plogp::TUNE_STAGED);
             else if (G.extra != 0)
-                CHECK(plan.path == plogp::TUNE_STAGED || (plan.path == plogp::TUNE_TABLE_LANES && lanes_may));
-            // without room for scratch: the same plan, or tiles of a big table
+                CHECK(plan.path == plogp::TUNE_STAGED || plan.path == plogp::TUNE_ROW ||
+                      (plan.path == plogp::TUNE_TABLE_LANES && lanes_may));
+            // without room for scratch: the same plan, rows where there are some beyond the tables, or tiles
+            // of a big table
             plogp::TunePlan lean;
             CHECK(plogp::plan_tune(T, G, terms_only != 0, lean, 0));
             if (lean.path != plan.path) {
                 ++leaner;
-                CHECK(plan.path == plogp::TUNE_STAGED && lean.path == plogp::TUNE_TILE && lean.lay.total == 256);
-                CHECK(!terms_only && G.extra == 0 && T.n > 512 && lean.tile_lds <= 160 * 1024 - 256);
+                CHECK(plan.path == plogp::TUNE_STAGED && !terms_only && lean.lay.total == 256);
+                if (G.extra != 0)
+                    CHECK(lean.path == plogp::TUNE_ROW && lean.row_lds <= 64 * 1024);
+                else
+                    CHECK(lean.path == plogp::TUNE_TILE && T.n > 512 && lean.tile_lds <= 160 * 1024 - 256);
             }
             if (G.extra != 0 && !terms_only && plan.path == plogp::TUNE_STAGED && T.n <= 512 && G.n_blk <= 32 &&
                 G.n_s <= 64 && (long)T.n_tables * G.n_m <= 65535 * 16)
-                CHECK(lean.whole && lean.lay.total == 256);
+                CHECK(lean.path == plogp::TUNE_ROW);
             if (plan.path == plogp::TUNE_STAGED && plan.pairs)
                 CHECK(l.segA != 0 && l.segB != 0 && l.amin != 0 && G.n_s > 0);
             if (plan.path == plogp::TUNE_STAGED && plan.lanes_s && !terms_only)
@@ -177,7 +182,7 @@ int main()
     }
 
     // masks with Gather or Barrier rows: whole rows to a workgroup where that is the faster path
-    const struct { unsigned mask; int n_m, n_P, p_max, whole; } routes[] = {
+    const struct { unsigned mask; int n_m, n_P, p_max, by_row; } routes[] = {
         {PLOGP_MASK_EVERY, 4000, 5, 6, 1},      {PLOGP_MASK_EVERY, 8000, 5, 6, 0},      {PLOGP_MASK_EVERY, 8000, 100, 1500, 1},
         {PLOGP_MASK_EVERY, 16000, 300, 1500, 1}, {PLOGP_MASK_EVERY, 50000, 600, 2000, 1}, {PLOGP_MASK_GATHER, 2000, 12, 200, 1},
         {PLOGP_MASK_GATHER, 5000, 12, 200, 0},  {PLOGP_MASK_BARRIER, 2000, 5, 6, 1},    {PLOGP_MASK_BARRIER, 5000, 5, 6, 0},
@@ -199,7 +204,7 @@ int main()
         G.need = (((r.mask >> 11) | (r.mask >> 14)) & 1u) << 11 | (((r.mask >> 12) | (r.mask >> 15)) & 1u) << 12;
         G.n_ops = 4;
         plogp::TunePlan plan;
-        CHECK(plogp::plan_tune(T, G, false, plan) && plan.whole == r.whole);
+        CHECK(plogp::plan_tune(T, G, false, plan) && (plan.path == plogp::TUNE_ROW) == (r.by_row != 0));
     }
 
     // ---- slices of tables of the robustness summary: a launch dimension, at any number of tables
