@@ -1345,10 +1345,12 @@ __device__ __forceinline__ void gaps_within_by_index(const ChainCtx &C, int i0, 
     }
 }
 
-// g((64 b + 1) m) + ... + g((64 b + terms) m), terms < 64 of them in this lane (0: none).  BY_INDEX: for
-// workgroups of 768 threads beside a big table, which the search on addresses made slower (2000 samples,
-// 300 000 points with P up to 300: 219 us by index, 240), while all others gained (3000 points with P up
-// to 64: 600 samples 24.4 us by index, 19.2; 4000 samples 34.3 and 29.1).
+// g((64 b + 1) m) + ... + g((64 b + terms) m), terms < 64 of them in this lane (0: none).  BY_INDEX: where
+// there are many points, of which a workgroup takes 768, or 256 up to 640 samples.  The search on addresses
+// makes those of 768 slower (300 000 points: 2000 samples with P up to 300 218 us by index, 239; 1500 with P
+// up to 64 65 and 82) and those of 256 mostly faster, but not all (600 samples with P up to 64 48.0 by index,
+// 44.5; 512 with P up to 300 83.4 and 87.3).  Few points gain (3000 with P up to 64: 600 samples 24.4 us by
+// index, 19.2; 4000 samples 34.3 and 29.1).
 template <bool BY_INDEX>
 __device__ __forceinline__ double chain_rest_sum(const ChainCtx &C, u64 b, u64 m, int terms)
 {
