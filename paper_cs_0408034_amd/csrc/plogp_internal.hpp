@@ -155,7 +155,7 @@ struct TunePlan {
     size_t tile_lds;
     // staged path
     int lanes_s, lanes_p, pairs, terms_mode, n_chunks, n_mchunks, terms_wg;
-    int chain, chain_row, together, row_together, terms_in_chain, chain_threads;
+    int chain, chain_row, together, row_together, chain_threads;
     int n_single, n_search, chain_wg, n_chain_wg, n_mgroups;
     size_t terms_lds, chain_lds, both_lds, crow_lds;
     int sweep_gp, sweep_dense, sweep_ptiles;    // lanes over s

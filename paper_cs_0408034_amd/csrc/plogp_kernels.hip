@@ -1056,12 +1056,11 @@ __device__ __forceinline__ void chain_small_body(const DeviceTables &T, const De
     }
 }
 
-template <bool TERMS>
 __global__ void __launch_bounds__(1024) k_chain_blocks(DeviceTables T, DeviceGrid G, Scratch S, int wg_per_table,
                                                        int n_single, int n_search, int terms_mode)
 {
     extern __shared__ __align__(16) double chain_lds[];   // the table as intervals, the candidates
-    chain_body<TERMS>(T, G, S, wg_per_table, n_single, n_search, terms_mode, (int)blockIdx.x, chain_lds);
+    chain_body<true>(T, G, S, wg_per_table, n_single, n_search, terms_mode, (int)blockIdx.x, chain_lds);
 }
 
 // ---------------------------------------------------------------- block sums of the chain row, a block per lane
@@ -4716,11 +4715,9 @@ hipError_t kernels_init()
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_terms),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxTableLds);
     if (e != hipSuccess) return e;
-    for (const bool terms : {false, true}) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(terms ? k_chain_blocks<true> : k_chain_blocks<false>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxChainLds);
-        if (e != hipSuccess) return e;
-    }
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_chain_blocks),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxChainLds);
+    if (e != hipSuccess) return e;
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_terms_chain),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxTableLds);
     if (e != hipSuccess) return e;
@@ -5135,9 +5132,9 @@ static bool plan_fastest(const DeviceTables &T, const DeviceGrid &G, bool terms_
     p.together = chain && !big && !p.chain_row;
     // (terms beside the per-row chain sums: when the terms need little LDS)
     p.row_together = p.chain_row && p.terms_lds <= 65536;
-    // a big table: the workgroups of the chain sums do the terms when they run out of sums
-    p.terms_in_chain = chain && big && !p.chain_row;
-    if (p.terms_in_chain && stage_s)
+    // a big table: the workgroups of the chain sums do the terms when they run out of sums, with the
+    // candidates in LDS beside the table
+    if (big && stage_s)
         p.chain_lds += n_s * D;
     if (p.chain_row) {
         if ((long)p.terms_wg + (long)T.n_tables * G.n_mu > kMaxLaunch) return false;
@@ -5317,7 +5314,7 @@ hipError_t launch_tune_stage(const TunePlan &p, int stage, const DeviceTables &T
     }
     switch (stage) {
     case TUNE_STAGE_TERMS:
-        if (!p.together && !p.row_together && !p.terms_in_chain)
+        if (!p.chain || (p.chain_row && !p.row_together))      // else they come with the chain sums
             hipLaunchKernelGGL(k_terms, dim3((unsigned)p.terms_wg), dim3(256), p.terms_lds, st, T, G, S,
                                p.n_chunks, p.n_mchunks, p.terms_mode);
         break;
@@ -5336,9 +5333,8 @@ hipError_t launch_tune_stage(const TunePlan &p, int stage, const DeviceTables &T
                                    p.both_lds, st, T, G, S, p.n_chain_wg, p.chain_wg, p.n_single, p.n_search,
                                    p.n_chunks, p.n_mchunks, p.terms_mode);
             else
-                hipLaunchKernelGGL(p.terms_in_chain ? k_chain_blocks<true> : k_chain_blocks<false>, dim3((unsigned)p.n_chain_wg), dim3(p.chain_threads),
-                                   p.chain_lds, st, T, G, S, p.chain_wg, p.n_single, p.n_search,
-                                   p.terms_mode);
+                hipLaunchKernelGGL(k_chain_blocks, dim3((unsigned)p.n_chain_wg), dim3(p.chain_threads), p.chain_lds, st,
+                                   T, G, S, p.chain_wg, p.n_single, p.n_search, p.terms_mode);
         }
         break;
     case TUNE_STAGE_PREFIX:
