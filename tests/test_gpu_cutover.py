@@ -88,23 +88,26 @@ def test_random_tables_match_the_definition(shape, p_change, key_mode):
     check(random_table(rng, nt, n_ops, n_m, n_P, p_change), m, P, key_mode)
 
 
+@pytest.mark.timeout(300)
 def test_scan_over_many_groups():
-    # more than 2048 * 1024 (row, tile) pieces: the second level of the prefix loops
+    # tiles of more than 512 sizes, more than 2048 * 1024 (row, tile) pieces: the second level of the
+    # prefix is a launch of its own and loops, and the table is streamed
     rng = np.random.default_rng(7)
-    nt, n_ops, n_m, n_P = 700, 2, 16 * 25, 64
+    nt, n_ops, n_m, n_P = 500, 2, 513, 64
     cells = random_table(rng, nt, n_ops, n_m, n_P, 0.01)
     m = (np.arange(n_m) * 8 + 8).astype(np.uint64)
     P = (np.arange(n_P) + 2).astype(np.uint32)
-    assert nt * n_ops * n_P * (n_m // 16) > 2048 * 1024
+    assert nt * n_ops * n_P * ((n_m + 15) // 16) > 2048 * 1024
     check(cells, m, P, 1)
 
 
 @pytest.mark.parametrize("key_mode", [0, 1])
 @pytest.mark.parametrize("shape,p_change", [
-    ((700, 2, 37, 24), 0.2),      # 33 600 rows: one thread per row; sizes end inside a flag word
-    ((1100, 2, 33, 15), 0.5),     # 33 000 rows: the last workgroup is ragged
-    ((300, 2, 257, 64), 0.03),    # more than 256 sizes: sixteen flag words, one size into the ninth
-    ((180, 1, 512, 200), 0.01),   # the most sizes this path takes
+    # fewer than 256 rows per compute unit: groups of 16 rows, a thread per row and 16 sizes
+    ((700, 2, 37, 24), 0.2),      # 2100 groups of a wave, its last sixteen threads without a size
+    ((1100, 2, 33, 15), 0.5),     # the last group has eight rows, the third thread of a row one size
+    ((300, 2, 257, 64), 0.03),    # five waves, one size in the last
+    ((180, 1, 512, 200), 0.01),   # eight waves, the most sizes that are taken in groups
     ((40000, 1, 1, 1), 0.5),      # one cell per row
     ((600, 2, 64, 30), 1.0),      # every cell starts a run
     ((600, 2, 64, 30), 0.0),      # one run per row
@@ -118,13 +121,23 @@ def test_tables_of_many_rows_take_one_pass_and_match_the_definition(shape, p_cha
 
 
 @pytest.mark.parametrize("shape,p_change", [
-    ((3, 2, 512, 40), 1.0),       # few groups of 64 rows: sixteen waves to a group, starts that do not fit
-    ((3, 2, 241, 11), 0.4),       # sixteen waves, the last with one size; 66 rows: a ragged second group
-    ((2200, 2, 70, 15), 1.0),     # 1032 groups: two waves to a group, read again
+    # groups of 16 rows: of one per compute unit every start is kept, of more than one what LDS has room for
+    ((3, 2, 512, 40), 1.0),       # 15 groups, 8192 starts in each
+    ((3, 2, 241, 11), 0.4),       # four waves, one size in the last thread of a row; the fifth group has two rows
+    ((400, 2, 512, 24), 0.5),     # 1200 groups whose starts do not fit: read again
+    ((400, 2, 512, 24), 0.22),    # the same about as many as fit: some kept, some read again
+    # from 65 536 rows on groups of 64, a thread per row and part of its sizes
+    ((1400, 2, 16, 24), 1.0),     # a wave, every start kept
+    ((1400, 2, 17, 24), 0.3),     # two waves, one size in the second
+    ((2800, 2, 20, 24), 0.2),     # 2100 groups: four at a time where their runs are placed
+    ((2200, 2, 70, 15), 1.0),     # three waves of 32, 32 and 6 sizes, read again; the last group has 16 rows
     ((2200, 2, 70, 15), 0.2),     # the same, kept
-    ((1100, 2, 209, 31), 0.06),   # 1066 groups, four waves, the last with seventeen sizes
+    ((1100, 2, 209, 31), 0.06),   # four waves, the last with seventeen sizes; the last group has 40 rows
+    ((1100, 2, 209, 31), 0.204),  # the same about as many as fit
+    ((2800, 1, 512, 24), 0.5),    # eight times sixteen sizes to a thread, read again
     ((350000, 1, 2, 3), 0.5),     # 16 407 groups: their counts go through the two-level prefix
 ])
+@pytest.mark.timeout(300)
 def test_rows_in_groups_match_the_definition(shape, p_change):
     rng = np.random.default_rng(sum(shape) + int(100 * p_change))
     nt, n_ops, n_m, n_P = shape
@@ -165,18 +178,19 @@ def test_more_rows_than_the_scratch_holds_go_in_slices():
         assert (runs[n:].view(np.uint8) == 0xEE).all()
 
 
-def test_one_grid_handle_many_rows_then_fewer_then_many_again():
-    """The same handle serves a batch on the one-pass path, a smaller one on the tiled path and
-    the first again: whatever a call leaves in the handle's scratch, the next one starts clean."""
+@pytest.mark.parametrize("n_m,p_change", [(40, 0.1), (40, 1.0), (512, 0.02)])
+def test_one_grid_handle_many_rows_then_fewer_then_many_again(n_m, p_change):
+    """The same handle serves a batch in groups of 64 rows, smaller ones in groups of 16 and the first again, on
+    scratch laid out once: whatever a call leaves there, the next one starts clean."""
     torch = torch_cuda()
     plogp = _plogp()
     rng = np.random.default_rng(23)
-    n_ops, n_m, n_P = 2, 40, 24
+    n_ops, n_P = 2, 24
     m = (np.arange(n_m) * 8 + 8).astype(np.uint64)
     P = (np.arange(n_P) + 2).astype(np.uint32)
     grid = plogp.plogp_grid_create(m, P, [], plogp.NO_CAP, 1, plogp.MASK_ALL)
-    big = random_table(rng, 800, n_ops, n_m, n_P, 0.1)
-    for nt in (800, 5, 800, 799):
+    big = random_table(rng, 1500, n_ops, n_m, n_P, p_change)
+    for nt in (1500, 5, 1500, 1365, 800, 1499):          # 72 000, 240, 72 000, 65 520, 38 400, 71 952 rows
         cells = big[:nt]
         want_off, want_runs = oc.cutovers(cells, m, 1)
         rows = nt * n_ops * n_P
@@ -194,13 +208,20 @@ def test_one_grid_handle_many_rows_then_fewer_then_many_again():
     grid.free()
 
 
-def test_capacity_smaller_than_the_number_of_runs_on_the_one_pass_path():
+@pytest.mark.parametrize("shape,p_change", [
+    ((700, 2, 20, 24), 0.3),      # groups of 16 rows, kept
+    ((400, 2, 512, 24), 0.5),     # groups of 16 rows, read again
+    ((1500, 2, 20, 24), 0.3),     # groups of 64 rows, kept
+    ((1500, 2, 70, 24), 1.0),     # groups of 64 rows, read again
+])
+def test_capacity_smaller_than_the_number_of_runs_on_the_one_pass_path(shape, p_change):
     rng = np.random.default_rng(29)
-    cells = random_table(rng, 700, 2, 20, 24, 0.3)
-    m = (np.arange(20) * 8 + 8).astype(np.uint64)
-    P = (np.arange(24) + 2).astype(np.uint32)
+    nt, n_ops, n_m, n_P = shape
+    cells = random_table(rng, nt, n_ops, n_m, n_P, p_change)
+    m = (np.arange(n_m) * 8 + 8).astype(np.uint64)
+    P = (np.arange(n_P) + 2).astype(np.uint32)
     want_off, want_runs = oc.cutovers(cells, m, 0)
-    cap = len(want_runs) // 3
+    cap = len(want_runs) // 3 + 1
     off, runs = gpu_cutovers(cells, m, P, 0, capacity=cap)
     assert (off == want_off).all() and int(off[-1]) > cap
     assert (runs == want_runs[:cap]).all()
