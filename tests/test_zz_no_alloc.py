@@ -68,6 +68,21 @@ def test_static_scratch_big_tables_in_tiles():
     assert got.tobytes() == want.tobytes()
 
 
+def test_static_scratch_rows_beyond_the_tables_go_a_row_to_a_workgroup():
+    # 35 000 rows x 255 process counts under the Scatter and Barrier rows: the staged path, which the
+    # allocating entry point takes, needs 71 MB for the sums inside blocks; a row to a workgroup needs none
+    from paper_cs_0408034_amd import plogp
+    rng = np.random.default_rng(19)
+    x = np.cumsum(rng.integers(1, 4000, size=(5000, 20)), axis=1).astype(np.float64)
+    gaps = 20.0 + x * rng.uniform(0.02, 0.1, size=(5000, 1)) * (1.0 + 0.4 * rng.random(x.shape))
+    m = 8 * np.sort(rng.integers(1, 1 << 10, size=7))
+    wl = Workload("many rows", x, gaps, rng.uniform(1.0, 90.0, 5000), m.astype(np.uint64),
+                  np.arange(2, 257, dtype=np.uint32), (64 << np.arange(5)).astype(np.uint64), (1 << 64) - 1,
+                  plogp.MASK_SCATTER | plogp.MASK_BARRIER)
+    want, got = _both(wl)
+    assert got.tobytes() == want.tobytes()
+
+
 def test_static_scratch_refuses_a_job_that_does_not_fit():
     torch = torch_cuda()
     from paper_cs_0408034_amd import plogp
