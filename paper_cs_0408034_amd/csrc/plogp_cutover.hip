@@ -292,7 +292,7 @@ __global__ void __launch_bounds__(256) k_cut_emit(CutShape sh, const plogp_cell_
 // Small jobs: 254 rows x 256 sizes 9.8 us in groups of 16 rows (11.5 in groups of 64; 13 as mark,
 // prefix and emit).
 struct CutRowsArgs {
-    u64 row0, n_rows;      // the slice: rows row0 .. n_rows - 1; groups and scratch count from row0
+    u64 row0, n_rows;      // the slice: n_rows rows from row0 on; everything but the cells counts from there
     int row_bits;          // log2 of the rows of a group
     int seg, cap;          // sizes of a thread; starts that fit the pool
     uint2 *keys;           // [groups][cap] starts in the order of the output: (s, strategy), ...
@@ -327,9 +327,9 @@ k_cut_rows(CutShape sh, const plogp_cell_dev *cells, int key_mode, CutRowsArgs A
     uint32_t *found = reinterpret_cast<uint32_t *>(key_of + A.cap);            // [cap] thread, its start, its size
     uint32_t *first = found + A.cap;                                           // [threads] starts before (row, part)
     unsigned short *place = reinterpret_cast<unsigned short *>(first + threads);   // [cap] by order of output
-    const u64 group = blockIdx.x, row = A.row0 + (group << A.row_bits) + my_row;
+    const u64 group = blockIdx.x, row = (group << A.row_bits) + my_row;
     const bool live = row < A.n_rows;
-    const u64 rr = live ? row : A.n_rows - 1;          // padding threads read a valid row
+    const u64 rr = A.row0 + (live ? row : A.n_rows - 1);       // padding threads read a valid row
     const size_t base = (size_t)(rr / (u64)sh.n_P) * sh.n_m * sh.n_P + (size_t)(rr % (u64)sh.n_P);
     const int m_lo = my_part * A.seg, m_hi = m_lo + A.seg < sh.n_m ? m_lo + A.seg : sh.n_m;
     uint2 prev = make_uint2(0u, 0u);
@@ -405,7 +405,7 @@ k_cut_rows(CutShape sh, const plogp_cell_dev *cells, int key_mode, CutRowsArgs A
     first[tid] = inside;                               // (every thread replaces the entry it read)
     __syncthreads();
     if (tid < rows && live)
-        A.row_first[row - A.row0] = first[tid * parts];
+        A.row_first[row] = first[tid * parts];
     if (tid == 0)
         A.count[group] = total;
     uint2 *keys = A.keys + group * A.cap;
@@ -426,10 +426,12 @@ k_cut_rows(CutShape sh, const plogp_cell_dev *cells, int key_mode, CutRowsArgs A
     }
 }
 
-// `per_wg` groups to a workgroup.  FEW: groups of 16 rows.  local, before: the prefix of the counts in two
-// levels, or null: then the workgroup adds up the counts before its first group itself.  The number of runs
-// in the slices before is what the one before left in row_offsets[row0]; this one writes it there again.
-template <bool FEW>
+// `per_wg` groups to a workgroup.  ALONE: no more groups than compute units, so that nothing hides the loads
+// of a group with many runs (48 rows x 512 sizes, every cell a run: 17.7 us, 20.4 one by one; 32 000 rows x
+// 28 sizes would lose 1 us of 12 to the registers this takes).  local, before: the prefix of the counts in
+// two levels, or null: then the workgroup adds up the counts before its first group itself.  The number of
+// runs in the slices before is what the one before left in row_offsets[0]; this one writes it there again.
+template <bool ALONE>
 __global__ void __launch_bounds__(256) k_cut_place(CutShape sh, const plogp_cell_dev *cells, const u64 *m, int key_mode,
                                                    CutRowsArgs A, unsigned n_groups, int parts, int per_wg,
                                                    const uint32_t *local, const u64 *before_of, u64 *row_offsets,
@@ -453,7 +455,7 @@ __global__ void __launch_bounds__(256) k_cut_place(CutShape sh, const plogp_cell
     __syncthreads();
     u64 before = local == nullptr ? wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3]
                                   : before_of[g0 / CUT_SCAN_WG] + local[g0];
-    before += A.row0 > 0 ? row_offsets[A.row0] : 0ull;
+    before += A.row0 > 0 ? row_offsets[0] : 0ull;
     auto emit = [&](u64 at, int mi, const uint2 &key) {
         union {
             plogp_run_dev r;
@@ -468,9 +470,9 @@ __global__ void __launch_bounds__(256) k_cut_place(CutShape sh, const plogp_cell
         const unsigned total = A.count[g];
         const uint2 *keys = A.keys + (size_t)g * A.cap;
         if (tid < 1 << A.row_bits) {
-            const u64 row = A.row0 + ((u64)g << A.row_bits) + tid;
+            const u64 row = ((u64)g << A.row_bits) + tid;
             if (row < A.n_rows)
-                row_offsets[row] = before + A.row_first[row - A.row0];
+                row_offsets[row] = before + A.row_first[row];
             if (row == A.n_rows - 1)
                 row_offsets[A.n_rows] = before + total;        // the grand total, or the next slice's first
         }
@@ -479,7 +481,7 @@ __global__ void __launch_bounds__(256) k_cut_place(CutShape sh, const plogp_cell
             const u64 room = capacity > before ? capacity - before : 0ull;
             const unsigned n = total < room ? total : (unsigned)room;
             unsigned d = (unsigned)tid;
-            for (; FEW && d + 768 < n; d += 1024) {    // four loads before the first store
+            for (; ALONE && d + 768 < n; d += 1024) {  // four loads before the first store
                 uint2 key[4];
                 int mi[4];
 #pragma unroll
@@ -496,10 +498,10 @@ __global__ void __launch_bounds__(256) k_cut_place(CutShape sh, const plogp_cell
         } else {
             // a (row, part) of k_cut_rows to a thread: its sizes are read again
             for (int t = tid; t < parts << A.row_bits; t += 256) {
-                const u64 row = A.row0 + ((u64)g << A.row_bits) + t / parts;
+                const u64 row = ((u64)g << A.row_bits) + t / parts, rr = A.row0 + row;
                 if (row >= A.n_rows)
                     continue;
-                const size_t base = (size_t)(row / (u64)sh.n_P) * sh.n_m * sh.n_P + (size_t)(row % (u64)sh.n_P);
+                const size_t base = (size_t)(rr / (u64)sh.n_P) * sh.n_m * sh.n_P + (size_t)(rr % (u64)sh.n_P);
                 const int m_lo = t % parts * A.seg, m_hi = m_lo + A.seg < sh.n_m ? m_lo + A.seg : sh.n_m;
                 u64 at = before + reinterpret_cast<const uint32_t *>(keys)[t];
                 uint2 prev = make_uint2(0u, 0u);
@@ -647,7 +649,7 @@ static hipError_t launch_cut_rows(int stage, const CutShape &sh, const DeviceGri
     const int threads = 64 * shape.waves;
     CutRowsArgs A;
     A.row0 = row0;
-    A.n_rows = row1;
+    A.n_rows = n_rows;
     A.row_bits = shape.row_bits;
     A.seg = shape.seg;
     A.cap = shape.cap;
@@ -674,11 +676,12 @@ static hipError_t launch_cut_rows(int stage, const CutShape &sh, const DeviceGri
         // would leave most of the chip idle (96 000 rows x 16 sizes 11.9 us, 14.6 with four; x 6 11.0, 13.5)
         const bool few = shape.row_bits < 6;
         const int per_wg = few || (G.n_m <= 32 && n_wg < (size_t)8 * device_info().n_cu) ? 1 : 4;
-        hipLaunchKernelGGL(few ? k_cut_place<true> : k_cut_place<false>,
+        const bool alone = n_wg <= (size_t)device_info().n_cu;
+        hipLaunchKernelGGL(alone ? k_cut_place<true> : k_cut_place<false>,
                            dim3((unsigned)((n_wg + per_wg - 1) / per_wg)), dim3(256), 0, st, sh, d_cells,
                            reinterpret_cast<const u64 *>(G.m), key_mode, A, (unsigned)n_wg, shape.parts, per_wg,
                            own_sums ? nullptr : C.local, reinterpret_cast<const u64 *>(C.group_total),
-                           d_row_offsets, reinterpret_cast<plogp_run_dev *>(d_runs), capacity);
+                           d_row_offsets + row0, reinterpret_cast<plogp_run_dev *>(d_runs), capacity);
     }
     return hipGetLastError();
 }
