@@ -2821,7 +2821,7 @@ static size_t sweep_s_lds(int n_s, bool with_static)
 // branch), more (eight terms side by side, each with the interval it lies in: see gaps_ascending).
 //
 // 333 tables of 57 samples x 203 sizes x 37 process counts up to 1500, 19 candidates, 80 MB of
-// cells: 68 us (a lane per message size that walks its whole row alone took 175; 10 000 rows x
+// cells: 68 us a call (a lane per message size that walks its whole row alone took 175; 10 000 rows x
 // 1000 process counts 2500 us, now the row path's 82).  Bound by instruction issue, much of it for
 // the chain sums.  With few process counts a tile has few items, often all of them of the searched
 // kind and less than a wave of them: eight lanes share each of those (6 process counts up to 100:
