@@ -65,6 +65,7 @@ static int static_scratch(void **out)
         void *p = nullptr;
         HIP_TRY(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
         if (!p) return device_error(hipErrorInvalidSymbol);
+        HIP_TRY(cutover_init());         // per device as well
         g_static_scratch[dev] = p;
     }
     *out = g_static_scratch[dev];

@@ -235,7 +235,7 @@ struct CutRowsShape {
 };
 // For a slice of n_rows in scratch with room for `entries` starts.
 CutRowsShape cutover_rows_shape(const DeviceGrid &G, size_t n_rows, size_t entries);
-hipError_t cutover_init();
+hipError_t cutover_init();                     // once per device, before the first launch there
 
 // Number of (row, tile) entries for n_tables tables over grid G.
 size_t cutover_items(const DeviceGrid &G, int n_tables);

@@ -307,7 +307,8 @@ __device__ __forceinline__ double from_ordered_bits(unsigned long long k)
 // own lookups), g(m), the number of
 // candidates that compete for m and the prefix sums over j of g(2^j m) for its
 // rows, g(s) for its candidates and (first table only) the reciprocals 1/s used
-// to get k = ceil(m/s) without a division per (m, s); chunk 0 also g(1).
+// to get k = ceil(m/s) without a division per (m, s); chunk 0 also g(1).  (terms_piece does the same on
+// the table as intervals, with the same expressions: what changes here changes there.)
 __device__ __forceinline__ void terms_body(const DeviceTables &T, const DeviceGrid &G, const Scratch &S,
                                            int n_chunks, int n_mchunks, int with_pairs, int block_id,
                                            double *lds)
@@ -4749,7 +4750,7 @@ hipError_t kernels_init()
         e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)BATCH_T_LDS_MAX);
         if (e != hipSuccess) return e;
     }
-    return cutover_init();
+    return e;
 }
 
 hipError_t launch_slopes(const DeviceTables &T, double *slope_out, hipStream_t st)
