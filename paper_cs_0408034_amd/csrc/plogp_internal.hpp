@@ -156,7 +156,7 @@ struct TunePlan {
     // staged path
     int lanes_s, lanes_p, pairs, terms_mode, n_chunks, n_mchunks, terms_wg;
     int chain, chain_row, together, row_together, chain_threads;
-    int n_single, n_search, chain_wg, n_chain_wg, n_mgroups;
+    int n_single, chain_wg, n_chain_wg, n_mgroups;
     size_t terms_lds, chain_lds, both_lds, crow_lds;
     int sweep_gp, sweep_dense, sweep_ptiles;    // lanes over s
     int ppl, n_pg, n_w;            // lanes over P

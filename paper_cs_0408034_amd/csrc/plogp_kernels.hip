@@ -476,16 +476,15 @@ __global__ void __launch_bounds__(256) k_terms(DeviceTables T, DeviceGrid G, Scr
 
 // ---------------------------------------------------------------- tune, step 2: Scatter-chain sum
 
-// sum_{j=1}^{P-1} g(j m) (Table 2, chain row).  One lane per message size; a
-// lane walks U consecutive blocks of SUM_BLOCK terms side by side (they
-// are independent chains of additions, so their instructions interleave and
-// hide each other's latency).  Inside a chain the arguments j*m ascend, so the
-// interval of the table only moves forward: one search at the start, then a
-// pointer walk that keeps d = j*m - x_i (exact: integers below 2^53) and the
-// interval width, so a term costs an add, a compare, an fma and the
-// accumulation.  Sizes below the first sample fall into a virtual interval of
-// slope 0 and gap y_0 (the clamp).  Emits each block total and, for every P of
-// the grid whose P-1 falls inside a block, the running sum at that point.
+// sum_{j=1}^{P-1} g(j m) (Table 2, chain row).  One lane per message size.  The
+// arguments j*m ascend, so the interval of the table only moves forward: one
+// search at the start, then a walk that keeps d = j*m - x_i (exact: integers
+// below 2^53) and takes eight terms at a time, each an add, an fma and the
+// accumulation; lanes that leave their interval among the eight form those from
+// there on once more (walk_terms).  Sizes below the first sample fall into a
+// virtual interval of slope 0 and gap y_0 (the clamp).  Emits each block total
+// and, for every P of the grid whose P-1 falls inside a block, the running sum at
+// that point.
 
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
@@ -576,179 +575,162 @@ __device__ __forceinline__ void gaps_located(const ChainCtx &C, const double (&z
     }
 }
 
-// Dense part of the table (small j): after moving into interval i the size is
-// still at or past its end (d >= w), i.e. several intervals on.  Looks four
-// intervals ahead a few times, then searches the rest of the table for the size
-// itself (exact: integers below 2^53).  Leaves i, d and the interval's terms.
-__device__ __forceinline__ void chain_skip_ahead(const ChainCtx &C, int &i, double &d, double &w,
-                                                 double &yi, double &si)
+// Formed again for the lanes that are on: g of the terms of eight that lie at or past `end` (an offset, as d;
+// that of the next interval, whose gap and slope ys holds).  d ascends and d[7] >= end in every one of these
+// lanes, so that, from the last term down, fewer and fewer are left.  A comparison, a subtraction and an fma
+// per term; as selects (the compiler's form) a term costs two more, for both halves of g.
+__device__ __forceinline__ void terms_past(const double (&d)[8], double end, f64x2 ys, double (&g)[8])
 {
-    const double *X = C.X;
-    double xb = X[i + 1];         // end of interval i
-    double e = d - w;             // size - end of interval i
-    int hops = 0;
-    for (;;) {
-        const double r1 = X[i + 2] - xb, r2 = X[i + 3] - xb;
-        const double r3 = X[i + 4] - xb, r4 = X[i + 5] - xb;
-        if (e >= r4) {
-            if (++hops == 3) {
-                const double z[1] = {xb + e};
+    u64 lanes;
+    double e;
+    asm volatile("s_mov_b64 %[lanes], exec\n\t"
+                 "v_add_f64 %[e], %[d7], -%[end]\n\t"
+                 "v_fma_f64 %[g7], %[s], %[e], %[y]\n\t"
+#define PLOGP_TERM(k)                                                                                                \
+                 "v_cmpx_le_f64_e32 vcc, %[end], %[d" #k "]\n\t"                                                    \
+                 "v_add_f64 %[e], %[d" #k "], -%[end]\n\t"                                                          \
+                 "v_fma_f64 %[g" #k "], %[s], %[e], %[y]\n\t"
+                 PLOGP_TERM(6) PLOGP_TERM(5) PLOGP_TERM(4) PLOGP_TERM(3) PLOGP_TERM(2) PLOGP_TERM(1) PLOGP_TERM(0)
+#undef PLOGP_TERM
+                 "s_mov_b64 exec, %[lanes]\n\t"
+                 "s_nop 4"
+                 : [lanes] "=&s"(lanes), [e] "=&v"(e), [g0] "+v"(g[0]), [g1] "+v"(g[1]), [g2] "+v"(g[2]),
+                   [g3] "+v"(g[3]), [g4] "+v"(g[4]), [g5] "+v"(g[5]), [g6] "+v"(g[6]), [g7] "+v"(g[7])
+                 : [d0] "v"(d[0]), [d1] "v"(d[1]), [d2] "v"(d[2]), [d3] "v"(d[3]), [d4] "v"(d[4]), [d5] "v"(d[5]),
+                   [d6] "v"(d[6]), [d7] "v"(d[7]), [end] "v"(end), [y] "v"(ys.x), [s] "v"(ys.y)
+                 : "vcc");
+}
+
+// Where a lane is in the table: interval, the next term's offset in it (exact: integers below 2^53), its
+// width, gap and slope.
+struct WalkAt {
+    int i;
+    double d, w;
+    f64x2 ys;
+};
+
+__device__ __forceinline__ WalkAt walk_from(const ChainCtx &C, double z)
+{
+    const double z0[1] = {z};
+    int i[1];
+    chain_locate<1>(C.X, C.n, z0, i);
+    WalkAt at;
+    at.i = i[0];
+    at.d = z - C.X[i[0]];
+    at.w = C.W[i[0]];
+    at.ys = C.YS[i[0]];
+    return at;
+}
+
+// g at the next eight sizes, md apart.  All eight are formed on the line of the interval that the lane is in;
+// lanes whose last one lies past its end then form those from there on once more on the next line, and so on.
+// Where the sizes of a wave cross an interval every hundred terms, some lane crosses at most of them: a branch
+// per term, with the reads of the next interval behind it, cost 8 vector, 4 scalar and 1.3 branch instructions
+// a term on average (one table of 4096 samples, 3215 sizes x 65 536 terms), 7.4, 2.9 and 0.5 this way, and 3
+// where no lane crosses.
+constexpr int WALK_V = 8;
+constexpr int WALK_HOPS = 12;        // intervals after which the next is searched for: some may have no term in them
+
+__device__ __forceinline__ void walk_terms(const ChainCtx &C, WalkAt &at, double md, double (&g)[WALK_V])
+{
+    const double md2 = md + md, md4 = md2 + md2;
+    double d[WALK_V];
+    d[0] = at.d;
+    d[1] = at.d + md;
+    d[2] = at.d + md2;
+    d[3] = d[1] + md2;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        d[4 + k] = d[k] + md4;
+#pragma unroll
+    for (int k = 0; k < WALK_V; ++k)
+        g[k] = __builtin_fma(at.ys.y, d[k], at.ys.x);
+    at.d = d[7] + md;
+    if (d[7] >= at.w) {
+        double start = 0.0, end = at.w;          // of the interval, as offsets from the first
+        int hops = 0;
+        do {
+            ++at.i;
+            double to = end;
+            if (hops == WALK_HOPS) {             // to that of the first term not yet in its own
+                const double x0 = C.X[at.i] - end;
+                double z[1] = {d[7]};
+#pragma unroll
+                for (int k = 6; k >= 0; --k)
+                    z[0] = d[k] >= end ? d[k] : z[0];
+                z[0] = x0 + z[0];
                 int iz[1];
-                chain_locate<1>(X, C.n, z, iz);
-                i = iz[0];
-                d = z[0] - X[i];
-                break;
+                chain_locate<1>(C.X, C.n, z, iz);
+                at.i = iz[0];
+                to = C.X[at.i] - x0;
+            } else {
+                ++hops;
             }
-            i += 4;
-            e -= r4;
-            xb += r4;
-            continue;
-        }
-        const int c = (e >= r1 ? 1 : 0) + (e >= r2 ? 1 : 0) + (e >= r3 ? 1 : 0);
-        const double lo = c == 0 ? 0.0 : (c == 1 ? r1 : (c == 2 ? r2 : r3));
-        d = e - lo;
-        i += 1 + c;
-        break;
+            at.ys = C.YS[at.i];
+            start = to;
+            terms_past(d, start, at.ys, g);
+            end = start + C.W[at.i];
+        } while (d[7] >= end);
+        at.d -= start;
+        at.w = end - start;
     }
-    const f64x2 ys = C.YS[i];
-    w = C.W[i];
-    yi = ys.x;
-    si = ys.y;
 }
 
-// U consecutive blocks from block b0 on, walked side by side for the size m of
-// this lane.  part: this size's row of in-block partial sums; tot: its column of
-// block totals.
-template <int U>
-__device__ __forceinline__ void chain_walk(const ChainCtx &C, int b0, u64 m, double *part, double *tot)
+// The sum of a block for a lane that is `at` its first term, which moves to that of the next block.  Bit r of
+// wanted: the sum before term r goes to *out and on; any: all lanes' wanted or'ed.
+__device__ __forceinline__ double walk_block(const ChainCtx &C, WalkAt &at, double md, u64 wanted, u64 any, double *out)
 {
-    const int n = C.n;
-    const int n_act = C.n_blk - b0 < U ? C.n_blk - b0 : U;      // chains that have a block
-    const double md = (double)m;
-    // per chain (wave-uniform): the points of its block at which some grid P needs the
-    // running sum (bit r: after r terms), and where the next such sum goes
-    u64 wanted[U], any_wanted = 0;
-    int pi[U];
-#pragma unroll
-    for (int c = 0; c < U; ++c) {
-        wanted[c] = c < n_act ? C.blk_mask[b0 + c] : 0ull;
-        pi[c] = c < n_act ? C.blk_off[b0 + c] : 0;
-        any_wanted |= wanted[c];
-    }
-    // A chain without a block repeats the first one and is not stored.
-    double z0[U];
-    int i[U];
-#pragma unroll
-    for (int c = 0; c < U; ++c)
-        z0[c] = (double)(((u64)(c < n_act ? b0 + c : b0) * SUM_BLOCK + 1) * m);
-    chain_locate<U>(C.X, n, z0, i);
-    double d[U], w[U], yi[U], si[U], run[U];
-    bool beyond = true;         // every chain already above the last sample
-#pragma unroll
-    for (int c = 0; c < U; ++c) {
-        d[c] = z0[c] - C.X[i[c]];         // d = z - start of the interval (exact)
-        w[c] = C.W[i[c]];
-        const f64x2 ys = C.YS[i[c]];
-        yi[c] = ys.x;
-        si[c] = ys.y;
-        run[c] = 0.0;
-        beyond = beyond && i[c] == n;
-    }
-    // Above the last sample nothing is crossed any more: when every size of the wave is
-    // there already, the walk needs no comparison at all.
-    const bool no_crossing = __ballot(!beyond) == 0;
-    int jj = 0;
-    for (;;) {
-        // run without any bookkeeping up to the next point where a sum is wanted
-        const int hit = any_wanted != 0 ? __builtin_ctzll(any_wanted) : SUM_BLOCK;
-        if (no_crossing) {
-            for (; jj < hit; ++jj) {
-#pragma unroll
-                for (int c = 0; c < U; ++c) {
-                    run[c] = run[c] + __builtin_fma(si[c], d[c], yi[c]);
-                    d[c] += md;
-                }
-            }
-        }
-        for (; jj < hit; ++jj) {
-            bool cross[U], any_cross = false;
-#pragma unroll
-            for (int c = 0; c < U; ++c) {
-                cross[c] = d[c] >= w[c];
-                any_cross = any_cross || cross[c];
-            }
-            if (any_cross) {            // some chain enters its next interval
-#pragma unroll
-                for (int c = 0; c < U; ++c) {
-                    if (cross[c]) {
-                        d[c] -= w[c];
-                        ++i[c];
-                        const f64x2 ys = C.YS[i[c]];
-                        w[c] = C.W[i[c]];
-                        yi[c] = ys.x;
-                        si[c] = ys.y;
-                        if (d[c] >= w[c])
-                            chain_skip_ahead(C, i[c], d[c], w[c], yi[c], si[c]);
-                    }
-                }
-            }
-#pragma unroll
-            for (int c = 0; c < U; ++c) {
-                run[c] = run[c] + __builtin_fma(si[c], d[c], yi[c]);
-                d[c] += md;
-            }
-        }
-        if (hit == SUM_BLOCK)
-            break;
-#pragma unroll
-        for (int c = 0; c < U; ++c) {
-            if ((wanted[c] >> hit) & 1ull) {
-                part[pi[c]] = run[c];
-                ++pi[c];
-            }
-        }
-        any_wanted &= any_wanted - 1;
-    }
-#pragma unroll
-    for (int c = 0; c < U; ++c)
-        if (c < n_act && b0 + c < C.n_blk - 1)     // the last block is never complete
-            tot[(size_t)(b0 + c) * C.n_m] = run[c];
-}
-
-// One block whose consecutive sizes j m lie many intervals apart (small j on a
-// table with many samples): every term gets its own search of the table, four
-// terms side by side; the terms are added in ascending j as everywhere.
-__device__ __forceinline__ void chain_search_block(const ChainCtx &C, int b, u64 m, double *part,
-                                                   double *tot)
-{
-    constexpr int V = 4;
-    const u64 wanted = C.blk_mask[b];
-    int pi = C.blk_off[b];
-    const u64 j0 = (u64)b * SUM_BLOCK + 1;
     double run = 0.0;
-    for (int r0 = 0; r0 < SUM_BLOCK; r0 += V) {
-        double z[V], g[V];
-        int i[V];
+    const double next = __builtin_fma((double)SUM_BLOCK, md, at.d);
+    if (__ballot(next - md >= at.w) == 0) {      // no lane leaves its interval: as above the last sample
+        double d = at.d;
+        int k = 0;
+        for (;;) {
+            const int hit = any != 0 ? __builtin_ctzll(any) : SUM_BLOCK;
+#pragma unroll 1
+            for (; k + WALK_V <= hit; k += WALK_V) {
 #pragma unroll
-        for (int c = 0; c < V; ++c)
-            z[c] = (double)((j0 + r0 + c) * m);
-        chain_locate<V>(C.X, C.n, z, i);
-#pragma unroll
-        for (int c = 0; c < V; ++c) {
-            const f64x2 ys = C.YS[i[c]];
-            g[c] = __builtin_fma(ys.y, z[c] - C.X[i[c]], ys.x);
-        }
-#pragma unroll
-        for (int c = 0; c < V; ++c) {
-            if ((wanted >> (r0 + c)) & 1ull) {      // bit r: the sum after r terms is wanted
-                part[pi] = run;
-                ++pi;
+                for (int u = 0; u < WALK_V; ++u) {
+                    run = run + __builtin_fma(at.ys.y, d, at.ys.x);
+                    d += md;
+                }
             }
-            run = run + g[c];
+#pragma unroll 1
+            for (; k < hit; ++k) {
+                run = run + __builtin_fma(at.ys.y, d, at.ys.x);
+                d += md;
+            }
+            if (hit == SUM_BLOCK)
+                break;
+            if ((wanted >> hit) & 1ull)
+                *out++ = run;
+            any &= any - 1;
+        }
+        at.d = next;
+        return run;
+    }
+#pragma unroll 1
+    for (int k0 = 0; k0 < SUM_BLOCK; k0 += WALK_V) {
+        double g[WALK_V];
+        walk_terms(C, at, md, g);
+        const unsigned some = (unsigned)(any >> k0) & 0xFFu;
+        if (some == 0u) {
+#pragma unroll
+            for (int k = 0; k < WALK_V; ++k)
+                run = run + g[k];
+        } else {
+            const unsigned mine = (unsigned)(wanted >> k0) & 0xFFu;
+#pragma unroll
+            for (int k = 0; k < WALK_V; ++k) {
+                if ((some >> k) & 1u) {
+                    if ((mine >> k) & 1u)
+                        *out++ = run;
+                }
+                run = run + g[k];
+            }
         }
     }
-    if (b < C.n_blk - 1)
-        tot[(size_t)b * C.n_m] = run;
+    return run;
 }
 
 // The tuning's first step (see terms_body) in pieces of a wave, on a table that is there as intervals:
@@ -877,83 +859,6 @@ __device__ __forceinline__ bool terms_piece(const ChainCtx &C, const DeviceTable
     return true;
 }
 
-// Work items of one table, in this order: (block b, group of 64 sizes mg) for the
-// n_single leading blocks, one block each -- small j, where the walk crosses
-// many intervals per term and an item takes longest; the first n_search of them
-// search per term -- then (unit u, mg) with CHAIN_U blocks each.  The items are
-// dealt to the workgroups of the table in rounds, every other round in reverse
-// order, so that every workgroup gets its share of the heavy items and meets
-// them first; inside a workgroup the waves take the next item of its list from
-// a counter in LDS, because how long an item takes depends on how often its
-// sizes cross an interval.
-// TERMS: the workgroups do the tuning's first step as well, in pieces of a wave that come after the
-// items: chains of dependent steps, which leave the vector units idle, for waves that have nothing left
-// while others finish their last item, on the table that is there.  (Behind a barrier, on the table
-// staged and its slopes formed once more, they took 5 to 8 us of a call: 4000 samples, 300 sizes x P up
-// to 65 536 63.6 us, 57.6 now; 4000 x P up to 4000 51 and 45.6; 4096 sizes x 976 process counts 137.4 and
-// 132.1.  A launch of their own takes 13.)
-constexpr int CHAIN_U = 4;           // blocks walked side by side by a lane in the sparse part
-constexpr int CHAIN_MAX_S = 1024;    // candidates kept in LDS for these pieces
-
-template <bool TERMS>
-__device__ __forceinline__ void chain_body(const DeviceTables &T, const DeviceGrid &G, const Scratch &S,
-                                           int wg_per_table, int n_single, int n_search, int terms_mode,
-                                           int block_id, double *chain_lds)
-{
-    __shared__ unsigned next_item;
-    const int t = block_id / wg_per_table, wg = block_id % wg_per_table;
-    ChainCtx C;
-    stage_intervals(C, chain_lds, T, t);
-    double *const sd = chain_lds + 4 * T.n + CHAIN_PAD;
-    if (TERMS && (terms_mode & 2))
-        for (int si = threadIdx.x; si < G.n_s; si += blockDim.x)
-            sd[si] = (double)G.s[si];
-    if (threadIdx.x == 0)
-        next_item = 0u;
-    __syncthreads();
-    const int lane = threadIdx.x & 63;
-    const int n_mg = (G.n_mu + 63) / 64;      // groups of 64 distinct sizes
-    const unsigned n_single_items = (unsigned)n_single * (unsigned)n_mg;
-    const unsigned n_units = (unsigned)((G.n_blk - n_single + CHAIN_U - 1) / CHAIN_U);
-    const unsigned n_items = n_single_items + n_units * (unsigned)n_mg;
-    const unsigned W_ = (unsigned)wg_per_table;
-    C.n_blk = G.n_blk;
-    C.n_m = (size_t)G.n_mu;
-    C.blk_mask = G.blk_mask;
-    C.blk_off = G.blk_off;
-    for (;;) {
-        unsigned k = 0;
-        if (lane == 0)
-            k = atomicAdd(&next_item, 1u);
-        k = __builtin_amdgcn_readfirstlane(k);
-        // round k of the deal: this workgroup's place is wg, or W_ - 1 - wg in odd rounds
-        const unsigned item = k * W_ + ((k & 1u) ? W_ - 1u - (unsigned)wg : (unsigned)wg);
-        if (item >= n_items) {            // later rounds lie further on still
-            const unsigned rounds = n_items / W_, in_last = (rounds & 1u) ? W_ - 1u - (unsigned)wg : (unsigned)wg;
-            const unsigned my_items = rounds + (in_last < n_items - rounds * W_ ? 1u : 0u);
-            if (TERMS && terms_piece(C, T, G, S, t, wg, wg_per_table, (int)(blockDim.x >> 6), terms_mode, k - my_items,
-                                     (terms_mode & 2) ? sd : nullptr))
-                continue;
-            break;
-        }
-        const bool single = item < n_single_items;
-        const unsigned rest = single ? item : item - n_single_items;
-        const int u = (int)(rest / (unsigned)n_mg), mg = (int)(rest % (unsigned)n_mg);
-        const int mi = mg * 64 + lane;
-        if (mi >= G.n_mu)
-            continue;
-        const u64 m = G.mu[mi];
-        double *part = S.part + ((size_t)t * C.n_m + mi) * G.n_P;     // [m][P index]
-        double *tot = S.blk + (size_t)t * G.n_blk * C.n_m + mi;       // [block][m]
-        if (!single)
-            chain_walk<CHAIN_U>(C, n_single + u * CHAIN_U, m, part, tot);
-        else if (u < n_search)
-            chain_search_block(C, u, m, part, tot);
-        else
-            chain_walk<1>(C, u, m, part, tot);
-    }
-}
-
 // The same sums for a small job (few samples, about a million terms or fewer), where the
 // walk above is bound by the latency of one lane's 64 dependent steps and the chip is
 // nearly idle: a workgroup takes one (block, 64 sizes) item at a time; its four waves
@@ -1057,13 +962,6 @@ __device__ __forceinline__ void chain_small_body(const DeviceTables &T, const De
     }
 }
 
-__global__ void __launch_bounds__(1024) k_chain_blocks(DeviceTables T, DeviceGrid G, Scratch S, int wg_per_table,
-                                                       int n_single, int n_search, int terms_mode)
-{
-    extern __shared__ __align__(16) double chain_lds[];   // the table as intervals, the candidates
-    chain_body<true>(T, G, S, wg_per_table, n_single, n_search, terms_mode, (int)blockIdx.x, chain_lds);
-}
-
 // ---------------------------------------------------------------- block sums of the chain row, a block per lane
 
 // The points at which the running sum of some lane of the wave is wanted (bit r: after r terms): the
@@ -1133,17 +1031,28 @@ __device__ __forceinline__ double block_walk(const ChainCtx &C, int i, double md
     return run;
 }
 
-// A number of intervals, the same in every lane: the last of a block's terms, which starts at z0 in
-// interval i0, lies below interval i0 + reach.
-__device__ __forceinline__ int block_reach(const ChainCtx &C, double z0, double md, int i0)
+// A power of two of intervals, or the whole table, the same in every lane: none enters so many.
+__device__ __forceinline__ int wave_reach(const ChainCtx &C, int enters)
 {
-    const double last[1] = {__builtin_fma((double)(SUM_BLOCK - 1), md, z0)};
-    int il[1], reach = 1;
-    chain_locate<1>(C.X, C.n, last, il);
-    while (__ballot(il[0] - i0 >= reach) != 0)
+    int reach = 1;
+    while (__ballot(enters >= reach) != 0)
         reach <<= 1;
     return reach < C.n + 2 ? reach : C.n + 2;
 }
+
+// That of a block's terms, the first of which is z0 in interval i0.
+__device__ __forceinline__ int block_reach(const ChainCtx &C, double z0, double md, int i0)
+{
+    const double last[1] = {__builtin_fma((double)(SUM_BLOCK - 1), md, z0)};
+    int il[1];
+    chain_locate<1>(C.X, C.n, last, il);
+    return wave_reach(C, il[0] - i0);
+}
+
+// Blocks of which some lane's enters more intervals than this are searched for, term by term, not walked: a
+// walk takes as many turns over its eight terms as some lane enters intervals (1000 sizes x P up to 8192 on 4000
+// samples: all blocks walked 65 us, 50 with this; 16 or 32 make no difference, 64 56).
+constexpr int WALK_REACH = 32;
 
 // Addresses in LDS as numbers: a step of a search is then an addition, a read, a comparison and a select.
 typedef __attribute__((address_space(3))) const double lds_double;
@@ -1230,11 +1139,10 @@ __device__ __forceinline__ void gaps_ascending(const ChainCtx &C, int &i, int re
 }
 
 // The same for a block whose terms enter several intervals.
-__device__ __forceinline__ double block_search(const ChainCtx &C, int i, double md, double zb, u64 wanted, u64 any,
-                                               double *out)
+__device__ __forceinline__ double block_search(const ChainCtx &C, int i, int reach, double md, double zb, u64 wanted,
+                                               u64 any, double *out)
 {
     constexpr int V = 8;
-    const int reach = block_reach(C, zb, md, i);
     double run = 0.0;
 #pragma unroll 1
     for (int k = 0; k < SUM_BLOCK; k += V) {
@@ -1260,60 +1168,213 @@ __device__ __forceinline__ double block_search(const ChainCtx &C, int i, double 
     return run;
 }
 
-// ---------------------------------------------------------------- the chain row at n points
+// ---------------------------------------------------------------- chain sums of a big table
 
-// g((64 b + 1) m) + ... + g((64 b + terms) m) added in ascending j from +0.0, `terms` <= 64 of them
-// in this lane (the loop runs to the wave's largest).  What counts here is the number of
-// instructions: the sum and the distance are pinned to their registers after every term (left to
-// itself the compiler carries a copy of every state variable past each branch: 300 000 points
-// 102 us instead of 78); a test four sizes ahead that skips the comparisons costs more than it
-// saves (90 us), and so does fetching the next interval before it is entered (89 us).
-template <bool FULL>
-__device__ __forceinline__ double chain_block_sum(const ChainCtx &C, u64 b, u64 m, int terms)
+// `n` consecutive blocks from block b on, one after the other, for the size m of this lane.  part: this
+// size's row of in-block partial sums; tot: its column of block totals.
+__device__ __forceinline__ void chain_item(const ChainCtx &C, int b, int n, u64 m, double *part, double *tot)
 {
     const double md = (double)m;
-    const double z0[1] = {(double)((b * SUM_BLOCK + 1) * m)};
-    int iz[1];
-    chain_locate<1>(C.X, C.n, z0, iz);
-    int i = iz[0];
-    double d = z0[0] - C.X[i], w = C.W[i];
-    f64x2 ys = C.YS[i];
+    const double ends[2] = {(double)(((u64)b * SUM_BLOCK + 1) * m), (double)(((u64)b * SUM_BLOCK + SUM_BLOCK) * m)};
+    int i[2];
+    chain_locate<2>(C.X, C.n, ends, i);
+    WalkAt at = {i[0], ends[0] - C.X[i[0]], C.W[i[0]], C.YS[i[0]]};
+    const int b_end = C.n_blk - b < n ? C.n_blk : b + n;
+    if (wave_reach(C, i[1] - i[0]) > WALK_REACH) {
+        for (; b < b_end; ++b) {
+            const WalkAt from = walk_from(C, (double)(((u64)b * SUM_BLOCK + 1) * m));
+            const double z0 = C.X[from.i] + from.d;
+            // bit r (wave-uniform): some grid P needs the running sum after r terms
+            const u64 wanted = C.blk_mask[b];
+            const double run = block_search(C, from.i, block_reach(C, z0, md, from.i), md, z0, wanted, wanted,
+                                            part + C.blk_off[b]);
+            if (b < C.n_blk - 1)                          // the last block is never complete
+                tot[(size_t)b * C.n_m] = run;
+        }
+        return;
+    }
+    for (; b < b_end; ++b) {
+        const u64 wanted = C.blk_mask[b];
+        const double run = walk_block(C, at, md, wanted, wanted, part + C.blk_off[b]);
+        if (b < C.n_blk - 1)
+            tot[(size_t)b * C.n_m] = run;
+    }
+}
+
+// Work items of one table, in this order: (block b, group of 64 sizes mg) for the
+// n_single leading blocks, one block each -- small j, which enter many intervals
+// per term, so that an item takes longest -- then (unit u, mg) with CHAIN_U blocks each.  The items are
+// dealt to the workgroups of the table in rounds, every other round in reverse
+// order, so that every workgroup gets its share of the heavy items and meets
+// them first; inside a workgroup the waves take the next item of its list from
+// a counter in LDS, because how long an item takes depends on how often its
+// sizes cross an interval.
+// TERMS: the workgroups do the tuning's first step as well, in pieces of a wave that come after the
+// items: chains of dependent steps, which leave the vector units idle, for waves that have nothing left
+// while others finish their last item, on the table that is there.  (Behind a barrier, on the table
+// staged and its slopes formed once more, they took 5 to 8 us of a call: 4000 samples, 300 sizes x P up
+// to 65 536 63.6 us, 57.6 now; 4000 x P up to 4000 51 and 45.6; 4096 sizes x 976 process counts 137.4 and
+// 132.1.  A launch of their own takes 13.)
+// Bound by vector instructions, 24.7 million (27.1 with a branch per term, see walk_terms): one table of 4096
+// samples, 4096 sizes x 976 process counts up to 65 536 the call 132 -> 125 us, 1000 x up to 8192 56 -> 50.5, 300
+// sizes x up to 65 536 59 -> 55; 300 samples, 3000 sizes 96 -> 89.  (Units of one, two or four blocks make no
+// difference.)
+constexpr int CHAIN_U = 4;           // blocks walked one after the other by a lane in the sparse part
+constexpr int CHAIN_MAX_S = 1024;    // candidates kept in LDS for these pieces
+
+template <bool TERMS>
+__device__ __forceinline__ void chain_body(const DeviceTables &T, const DeviceGrid &G, const Scratch &S,
+                                           int wg_per_table, int n_single, int terms_mode,
+                                           int block_id, double *chain_lds)
+{
+    __shared__ unsigned next_item;
+    const int t = block_id / wg_per_table, wg = block_id % wg_per_table;
+    ChainCtx C;
+    stage_intervals(C, chain_lds, T, t);
+    double *const sd = chain_lds + 4 * T.n + CHAIN_PAD;
+    if (TERMS && (terms_mode & 2))
+        for (int si = threadIdx.x; si < G.n_s; si += blockDim.x)
+            sd[si] = (double)G.s[si];
+    if (threadIdx.x == 0)
+        next_item = 0u;
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    const int n_mg = (G.n_mu + 63) / 64;      // groups of 64 distinct sizes
+    const unsigned n_single_items = (unsigned)n_single * (unsigned)n_mg;
+    const unsigned n_units = (unsigned)((G.n_blk - n_single + CHAIN_U - 1) / CHAIN_U);
+    const unsigned n_items = n_single_items + n_units * (unsigned)n_mg;
+    const unsigned W_ = (unsigned)wg_per_table;
+    C.n_blk = G.n_blk;
+    C.n_m = (size_t)G.n_mu;
+    C.blk_mask = G.blk_mask;
+    C.blk_off = G.blk_off;
+    for (;;) {
+        unsigned k = 0;
+        if (lane == 0)
+            k = atomicAdd(&next_item, 1u);
+        k = __builtin_amdgcn_readfirstlane(k);
+        // round k of the deal: this workgroup's place is wg, or W_ - 1 - wg in odd rounds
+        const unsigned item = k * W_ + ((k & 1u) ? W_ - 1u - (unsigned)wg : (unsigned)wg);
+        if (item >= n_items) {            // later rounds lie further on still
+            const unsigned rounds = n_items / W_, in_last = (rounds & 1u) ? W_ - 1u - (unsigned)wg : (unsigned)wg;
+            const unsigned my_items = rounds + (in_last < n_items - rounds * W_ ? 1u : 0u);
+            if (TERMS && terms_piece(C, T, G, S, t, wg, wg_per_table, (int)(blockDim.x >> 6), terms_mode, k - my_items,
+                                     (terms_mode & 2) ? sd : nullptr))
+                continue;
+            break;
+        }
+        const bool single = item < n_single_items;
+        const unsigned rest = single ? item : item - n_single_items;
+        const int u = (int)(rest / (unsigned)n_mg), mg = (int)(rest % (unsigned)n_mg);
+        const int mi = mg * 64 + lane;
+        if (mi >= G.n_mu)
+            continue;
+        const u64 m = G.mu[mi];
+        double *part = S.part + ((size_t)t * C.n_m + mi) * G.n_P;     // [m][P index]
+        double *tot = S.blk + (size_t)t * G.n_blk * C.n_m + mi;       // [block][m]
+        chain_item(C, single ? u : n_single + u * CHAIN_U, single ? 1 : CHAIN_U, m, part, tot);
+    }
+}
+
+__global__ void __launch_bounds__(1024) k_chain_blocks(DeviceTables T, DeviceGrid G, Scratch S, int wg_per_table,
+                                                       int n_single, int terms_mode)
+{
+    extern __shared__ __align__(16) double chain_lds[];   // the table as intervals, the candidates
+    chain_body<true>(T, G, S, wg_per_table, n_single, terms_mode, (int)blockIdx.x, chain_lds);
+}
+
+// ---------------------------------------------------------------- the chain row at n points
+
+// g((64 b + 1) m) + ... + g((64 b + 64) m) added in ascending j from +0.0.  Bound by the number of
+// instructions.  A table of few samples is walked without a look at how many intervals the block enters (64
+// samples: 72.7 us for 300 000 points with P up to 1024, 74.4 with it).
+constexpr int EVAL_DENSE_N = 128;
+
+__device__ __forceinline__ double chain_block_sum(const ChainCtx &C, u64 b, u64 m)
+{
+    const double md = (double)m, z0 = (double)((b * SUM_BLOCK + 1) * m);
+    if (C.n <= EVAL_DENSE_N) {
+        WalkAt at = walk_from(C, z0);
+        return walk_block(C, at, md, 0, 0, nullptr);
+    }
+    const double ends[2] = {z0, (double)((b * SUM_BLOCK + SUM_BLOCK) * m)};
+    int i[2];
+    chain_locate<2>(C.X, C.n, ends, i);
+    const int reach = wave_reach(C, i[1] - i[0]);
+    if (reach > WALK_REACH)
+        return block_search(C, i[0], reach, md, z0, 0, 0, nullptr);
+    WalkAt at = {i[0], z0 - C.X[i[0]], C.W[i[0]], C.YS[i[0]]};
+    return walk_block(C, at, md, 0, 0, nullptr);
+}
+
+// After moving into interval i the size is
+// still at or past its end (d >= w), i.e. several intervals on.  Looks four
+// intervals ahead a few times, then searches the rest of the table for the size
+// itself (exact: integers below 2^53).  Leaves i, d and the interval's terms.
+__device__ __forceinline__ void chain_skip_ahead(const ChainCtx &C, int &i, double &d, double &w,
+                                                 double &yi, double &si)
+{
+    const double *X = C.X;
+    double xb = X[i + 1];         // end of interval i
+    double e = d - w;             // size - end of interval i
+    int hops = 0;
+    for (;;) {
+        const double r1 = X[i + 2] - xb, r2 = X[i + 3] - xb;
+        const double r3 = X[i + 4] - xb, r4 = X[i + 5] - xb;
+        if (e >= r4) {
+            if (++hops == 3) {
+                const double z[1] = {xb + e};
+                int iz[1];
+                chain_locate<1>(X, C.n, z, iz);
+                i = iz[0];
+                d = z[0] - X[i];
+                break;
+            }
+            i += 4;
+            e -= r4;
+            xb += r4;
+            continue;
+        }
+        const int c = (e >= r1 ? 1 : 0) + (e >= r2 ? 1 : 0) + (e >= r3 ? 1 : 0);
+        const double lo = c == 0 ? 0.0 : (c == 1 ? r1 : (c == 2 ? r2 : r3));
+        d = e - lo;
+        i += 1 + c;
+        break;
+    }
+    const f64x2 ys = C.YS[i];
+    w = C.W[i];
+    yi = ys.x;
+    si = ys.y;
+}
+
+// The first `terms` < 64 of them in this lane (0: none), a step per term (the loop runs to the wave's
+// largest), with a branch where some lane enters an interval: eight at a time, as above, is no faster where
+// most lanes have left before the last term (100 000 points with P up to 300 on 100 samples 31.7 us this way,
+// 35.9 so; 290 000 with P up to 1024 on 256 samples 99, 117).  The sum and the distance are pinned to their
+// registers after every term: left to itself the compiler carries a copy of every state variable past each
+// branch.
+__device__ __forceinline__ double chain_rest_walk(const ChainCtx &C, u64 b, u64 m, int terms)
+{
+    const double md = (double)m;
+    WalkAt at = walk_from(C, (double)((b * SUM_BLOCK + 1) * m));
     double run = 0.0;
-    auto step = [&](bool use) {
-        const double g = run + __builtin_fma(ys.y, d, ys.x);
-        run = FULL || use ? g : run;
-        d += md;
-        asm volatile("" : "+v"(run), "+v"(d));
-    };
-    auto cross = [&] {
-        if (d >= w) {
-            d -= w;
-            ++i;
-            w = C.W[i];
-            ys = C.YS[i];
-            if (d >= w) {                         // several intervals on
+    for (int k = 0; __ballot(k < terms) != 0; ++k) {
+        if (k < terms && at.d >= at.w) {
+            at.d -= at.w;
+            ++at.i;
+            at.w = C.W[at.i];
+            at.ys = C.YS[at.i];
+            if (at.d >= at.w) {                       // several intervals on
                 double yi, si;
-                chain_skip_ahead(C, i, d, w, yi, si);
-                ys.x = yi;
-                ys.y = si;
+                chain_skip_ahead(C, at.i, at.d, at.w, yi, si);
+                at.ys.x = yi;
+                at.ys.y = si;
             }
         }
-    };
-    if (FULL) {
-#pragma unroll 1
-        for (int k = 0; k < SUM_BLOCK; k += 8) {
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                cross();
-                step(true);
-            }
-        }
-    } else {
-        for (int k = 0; __ballot(k < terms) != 0; ++k) {
-            if (k < terms)
-                cross();
-            step(k < terms);
-        }
+        const double g = run + __builtin_fma(at.ys.y, at.d, at.ys.x);
+        run = k < terms ? g : run;
+        at.d += md;
+        asm volatile("" : "+v"(run), "+v"(at.d));
     }
     return run;
 }
@@ -1394,11 +1455,13 @@ __device__ __forceinline__ double chain_rest_sum(const ChainCtx &C, u64 b, u64 m
 // there (300 000 points with P up to 64: 64 samples 19 us walked, 35 searched; 4096 samples 291 and
 // 88; at 512 as fast, and with P up to 16 30 and 20).
 //
-// Bound by the fp64 and scalar instructions of the walk (300 000 points with P up to 1024, 64
-// samples: 79 us; 555 with a thread that walks its point alone and searches the table per term).
-// LEVELS: eight when there are few points, whose blocks would not fill the chip otherwise (3000
-// points, 64 samples: 51 us, 57 with four), four when there are many on a table that leaves LDS for
-// few waves (512 samples: 142 us, 185 with eight).
+// Bound by the vector instructions of the walk (300 000 points with P up to 1024, 64 samples: 73 us, 76
+// with a branch per term, which few lanes take but some nearly always; 555 with a thread that walks its
+// point alone and searches the table per term).  Few points, where a wave's latency counts, gain most by
+// the walk of eight terms at a time: 30 000 points 56 -> 42 us, 3000 51 -> 39, 30 000 with P up to 5000
+// 183 -> 126; on 2000 samples, of which blocks are searched for, 290 000 with P up to 300 214 -> 165.
+// LEVELS: eight when there are few points, whose blocks would not fill the chip otherwise, four when
+// there are many on a table that leaves LDS for few waves (512 samples: 142 us, 185 with eight).
 constexpr int EVAL_SEARCH_N = 256;       // more samples: the rest of a sum is searched for
 
 template <int LEVELS>
@@ -1466,7 +1529,7 @@ k_eval_chain(DeviceTables T, int t, const u64 *dm, const uint32_t *dP, size_t n,
                 }
             }
             const int p = order[r];
-            const double v = chain_block_sum<true>(C, (u64)b0 + k, m_of[p], SUM_BLOCK);
+            const double v = chain_block_sum(C, (u64)b0 + k, m_of[p]);
             if (real)
                 tot[(size_t)k * threads + p] = v;
         }
@@ -1475,7 +1538,7 @@ k_eval_chain(DeviceTables T, int t, const u64 *dm, const uint32_t *dP, size_t n,
             done = done + tot[(size_t)k * threads + tid];
     }
     const double rest = C.n > EVAL_SEARCH_N ? chain_rest_sum<LEVELS == 4>(C, full, m_of[tid], tail)
-                                            : chain_block_sum<false>(C, full, m_of[tid], tail);
+                                            : chain_rest_walk(C, full, m_of[tid], tail);
     if (i < n)
         out[i] = ok ? __builtin_fma((double)(P - 1u), T.L[t], done + rest) : NAN;
 }
@@ -1631,7 +1694,7 @@ __global__ void __launch_bounds__(CROW_THREADS) k_terms_chain_row(DeviceTables T
 // in the grid) and those of the terms run side by side.  For tables small enough that
 // workgroups of both kinds share a CU.
 __global__ void __launch_bounds__(256) k_terms_chain(DeviceTables T, DeviceGrid G, Scratch S, int n_chain_wg,
-                                                     int wg_per_table, int n_single, int n_search,
+                                                     int wg_per_table, int n_single,
                                                      int n_chunks, int n_mchunks, int with_pairs)
 {
     extern __shared__ __align__(16) double both_lds[];
@@ -1639,7 +1702,7 @@ __global__ void __launch_bounds__(256) k_terms_chain(DeviceTables T, DeviceGrid 
         if (n_single < 0)                 // a small job: terms by search, side by side
             chain_small_body(T, G, S, wg_per_table, (int)blockIdx.x, both_lds);
         else
-            chain_body<false>(T, G, S, wg_per_table, n_single, n_search, 0, (int)blockIdx.x, both_lds);
+            chain_body<false>(T, G, S, wg_per_table, n_single, 0, (int)blockIdx.x, both_lds);
     } else
         terms_body(T, G, S, n_chunks, n_mchunks, with_pairs, (int)blockIdx.x - n_chain_wg, both_lds);
 }
@@ -2885,7 +2948,7 @@ __device__ __forceinline__ void tile_sum(const ChainCtx &C, unsigned item, bool 
     const u64 wanted = real ? blk_mask[b] : 0ull;
     double *out = part + ml * n_P + blk_off[b];
     const u64 any = wave_any_wanted(wanted);
-    const double run = KIND == 2 ? block_search(C, i, md, z0, wanted, any, out)
+    const double run = KIND == 2 ? block_search(C, i, block_reach(C, z0, md, i), md, z0, wanted, any, out)
                                  : block_walk<KIND == 1>(C, i, md, z0, wanted, any, out);
     if (real)
         tot[b * M + ml] = run;
@@ -5143,12 +5206,11 @@ static bool plan_fastest(const DeviceTables &T, const DeviceGrid &G, bool terms_
         p.chain_threads = big ? 1024 : 256;
         const int n_mg = (G.n_mu + 63) / 64;
         // leading blocks that are items of their own: the dense part of a table with many
-        // samples (its first blocks search per term), or every block when the whole sum is
+        // samples, or every block when the whole sum is
         // too small to fill the chip with units of CHAIN_U blocks
-        int n_single = T.n > 256 ? 32 : 0, n_search = T.n > 256 ? 4 : 0;
+        int n_single = T.n > 256 ? 32 : 0;
         if ((long)T.n_tables * n_mg * ((G.n_blk + CHAIN_U - 1) / CHAIN_U) < 8 * n_cu) n_single = G.n_blk;
         if (n_single > G.n_blk) n_single = G.n_blk;
-        if (n_search > n_single) n_search = n_single;
         const long items = (long)n_mg * (n_single + (G.n_blk - n_single + CHAIN_U - 1) / CHAIN_U);
         if (items > kMaxLaunch) return false;
         long wg = (big ? n_cu : 4 * n_cu) / T.n_tables;
@@ -5175,7 +5237,6 @@ static bool plan_fastest(const DeviceTables &T, const DeviceGrid &G, bool terms_
             if (wg < 1) wg = 1;
         }
         p.n_single = n_single;
-        p.n_search = n_search;
         p.chain_wg = (int)wg;
         if ((long)T.n_tables * wg + p.terms_wg > kMaxLaunch) return false;
         p.n_chain_wg = (int)(T.n_tables * wg);
@@ -5331,11 +5392,11 @@ hipError_t launch_tune_stage(const TunePlan &p, int stage, const DeviceTables &T
         } else if (p.chain) {
             if (p.together)
                 hipLaunchKernelGGL(k_terms_chain, dim3((unsigned)(p.n_chain_wg + p.terms_wg)), dim3(256),
-                                   p.both_lds, st, T, G, S, p.n_chain_wg, p.chain_wg, p.n_single, p.n_search,
+                                   p.both_lds, st, T, G, S, p.n_chain_wg, p.chain_wg, p.n_single,
                                    p.n_chunks, p.n_mchunks, p.terms_mode);
             else
                 hipLaunchKernelGGL(k_chain_blocks, dim3((unsigned)p.n_chain_wg), dim3(p.chain_threads), p.chain_lds, st,
-                                   T, G, S, p.chain_wg, p.n_single, p.n_search, p.terms_mode);
+                                   T, G, S, p.chain_wg, p.n_single, p.terms_mode);
         }
         break;
     case TUNE_STAGE_PREFIX:

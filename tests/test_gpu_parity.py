@@ -836,6 +836,39 @@ def test_tiles_whose_terms_enter_intervals_at_an_even_pace(n, m):
     assert assert_tables_equal(gpu_tune(wl), want, "n=%d m=%d" % (n, m)), "times not bit-identical"
 
 
+@pytest.mark.parametrize("together", [1, 11, 12, 13, 31, 32, 33, 70])
+@pytest.mark.parametrize("route", ["sums", "tiles", "points"])
+def test_walks_past_samples_that_lie_together(together, route):
+    # groups of samples one byte apart, 4000 from the next: a term enters all intervals of a group at once,
+    # most of them without a term in them (a walk looks for the next after twelve; a wave of which some block
+    # enters more than 32, or 16, searches).  Sums wanted around every eighth term
+    rng = np.random.default_rng(together)
+    n = {"sums": 1100, "tiles": 200, "points": 180}[route]
+    n_tables = 700 if route == "tiles" else 1
+    x = np.array([4000.0 * (1 + k // together) + k % together for k in range(n)])[None].repeat(n_tables, axis=0)
+    x[:, 0] -= rng.integers(0, 500, size=n_tables)             # the tables share no sample sizes
+    gaps = np.abs(20.0 + x * 0.05 * (1.0 + 0.4 * rng.standard_normal(x.shape)))
+    m = np.array([8, 96, 328, 1000, 1992, 2000, 3992, 4000, 4008, 9000], dtype=np.uint64)
+    P = np.unique(np.concatenate([64 * b + np.array([2, 8, 9, 10, 16, 17, 40, 63, 64, 65]) for b in (0, 1, 2, 5, 9)]))
+    L = rng.uniform(0.0, 90.0, size=n_tables)
+    if route == "points":
+        torch, plogp = torch_cuda(), _plogp()
+        mm, PP = [v.ravel() for v in np.meshgrid(m, P.astype(np.uint32))]
+        tab = plogp.plogp_load_table(x[0], gaps[0], L[0])
+        out = torch.empty(mm.size, dtype=torch.float64, device="cuda")
+        dm, dP = _dev(mm, np.uint64), _dev(PP, np.uint32)
+        plogp.plogp_eval_strategy(tab, 0, 11, dm.data_ptr(), dP.data_ptr(), 0, mm.size, out.data_ptr(), stream_handle())
+        torch.cuda.synchronize()
+        want = np.array([oracle.eval_strategy(x[0], gaps[0], L[0], 11, int(a), int(b), 0) for a, b in zip(mm, PP)])
+        assert (out.cpu().numpy().view(np.uint64) == want.view(np.uint64)).all()
+        tab.free()
+        return
+    wl = Workload("together", x, gaps, L, m, P.astype(np.uint32), np.array([8, 16], dtype=np.uint64), NO_CAP,
+                  ALL_STRATEGIES_MASK)
+    want, _ = oracle.tune_workload(wl)
+    assert assert_tables_equal(gpu_tune(wl), want, "%d together, %s" % (together, route)), "times not bit-identical"
+
+
 # ------------------------------------------------------------------ many candidates, chunks left out by their bounds
 
 @pytest.mark.parametrize("n_s,n_P,shape", [
