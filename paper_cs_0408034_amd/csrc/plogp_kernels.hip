@@ -981,56 +981,6 @@ __device__ __forceinline__ u64 wave_any_wanted(u64 wanted)
     return all((int)(unsigned)wanted) | all((int)(unsigned)(wanted >> 32)) << 32;
 }
 
-// The sum of one block per lane, of size md and first term z0 in interval i, whose terms stay there
-// (ONE: enter the next interval).  The running sums wanted go to *out and on.
-template <bool ONE>
-__device__ __forceinline__ double block_walk(const ChainCtx &C, int i, double md, double z0, u64 wanted, u64 any,
-                                             double *out)
-{
-    double d = z0 - C.X[i], md_enter = 0.0;
-    f64x2 ys = C.YS[i], ys_next = ys;
-    int enters = 0;
-    if (ONE) {
-        // the first term in the next interval (the rounded quotient of two integers below 2^53
-        // does not reach an integer it is not equal to), and the way there
-        const double start = C.X[i + 1];
-        enters = (int)ceil((start - z0) / md);
-        md_enter = md - (start - C.X[i]);
-        ys_next = C.YS[i + 1];
-    }
-    double run = 0.0;
-    auto step = [&](int k) {
-        run = run + __builtin_fma(ys.y, d, ys.x);
-        if (ONE) {
-            const bool now = enters == k + 1;
-            d += now ? md_enter : md;
-            ys.x = now ? ys_next.x : ys.x;
-            ys.y = now ? ys_next.y : ys.y;
-        } else {
-            d += md;
-        }
-    };
-    int k = 0;
-    for (;;) {
-        const int hit = any != 0 ? __builtin_ctzll(any) : SUM_BLOCK;
-#pragma unroll 1
-        for (; k + 8 <= hit; k += 8) {
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                step(k + u);
-        }
-#pragma unroll 1
-        for (; k < hit; ++k)
-            step(k);
-        if (hit == SUM_BLOCK)
-            break;
-        if ((wanted >> hit) & 1ull)
-            *out++ = run;
-        any &= any - 1;
-    }
-    return run;
-}
-
 // A power of two of intervals, or the whole table, the same in every lane: none enters so many.
 __device__ __forceinline__ int wave_reach(const ChainCtx &C, int enters)
 {
@@ -2875,23 +2825,29 @@ static size_t sweep_s_lds(int n_s, bool with_static)
 // every (m, s); the Scatter-chain sums; then the cells, lanes over (m, P) in the order of the
 // output, so that a wave stores whole cache lines.
 //
-// The chain sums are most of the work.  Their items are (block of SUM_BLOCK terms, m); within a
+// The chain sums are half of the work.  Their items are (block of SUM_BLOCK terms, m); within a
 // block most items stay inside one interval of the table or enter one other, and only the first
-// blocks cross many.  A wave that mixes the kinds pays for the worst: some lane enters an
-// interval at almost every term, and the branch, its LDS reads and the scalar bookkeeping cost
-// more than the terms.  So every item is first placed (one search) and put on the list of its
-// kind: no crossing (three fp64 instructions per term), one crossing at a term known beforehand
-// (the two intervals sit in registers, the change is six selects on an integer compare, no
-// branch), more (eight terms side by side, each with the interval it lies in: see gaps_ascending).
+// blocks enter many.  A wave that mixes the kinds pays for the worst.  So every item is first
+// placed (one search) and sorted: by whether it enters no interval (three fp64 instructions per
+// term), one, and among which eight of its terms (lanes that enter together cost a walk one turn
+// more over these eight, see walk_terms, and none elsewhere), or more; and the waves take 64 of
+// that order at a time, from its end, whatever the kind: a list per kind left lanes idle in the
+// last wave of each.  Waves whose items enter more than TILE_REACH intervals search for eight terms
+// side by side (gaps_ascending).
 //
 // 333 tables of 57 samples x 203 sizes x 37 process counts up to 1500, 19 candidates, 80 MB of
-// cells: 68 us a call (a lane per message size that walks its whole row alone took 175; 10 000 rows x
-// 1000 process counts 2500 us, now the row path's 82).  Bound by instruction issue, much of it for
-// the chain sums.  With few process counts a tile has few items, often all of them of the searched
-// kind and less than a wave of them: eight lanes share each of those (6 process counts up to 100:
-// 39 us, 48 with a lane per item, 43 with a lane per message size).
-// Tried: lists for two and three crossings as well, and the searched terms of large jobs spread
-// over all threads through LDS (94 us: more lists, more waves with idle lanes).
+// cells: 63 us a call (68 with the change of interval as six selects per term of the items that
+// enter one, a list per kind and the mask of rows read at run time; a lane per message size that
+// walks its whole row alone took 175; 10 000 rows x 1000 process counts 2500 us, now the row path's
+// 82); 1000 tables 177 -> 163; 300 tables of 30 samples x 150 sizes x 20 process counts up to 300
+// 31.4 -> 28.3.  Bound by vector instruction issue (25.8 million, 29.8 before), a third of it the
+// cells.  With few process counts a tile has few items, often all of them of the searched kind: eight
+// lanes share each of those where the items would not fill the workgroup's waves otherwise (6 process
+// counts up to 100: 32 us, 35 with a lane per item; with five blocks and 140 items a lane per item is
+// the faster: 27.7, 28.8 to 30.3 shared).
+// Tried: the cells of the Broadcast plane handed out with the items, for waves that have nothing left
+// of these (the same time: there is no idle time to fill, and a lane has to find its cell by a
+// division); the searched terms of large jobs spread over all threads through LDS (94 us).
 constexpr int TILE_THREADS = 256;
 constexpr int TILE_MAX_M = TILE_THREADS / 8;
 constexpr int TILE_NS = 24;              // candidates at most
@@ -2899,7 +2855,8 @@ constexpr int TILE_MAX_BLK = 32;         // blocks of the chain sum at most
 constexpr size_t TILE_STATIC_LDS = 256;  // room for the counters
 constexpr long TILE_MIN_ROWS = 16;       // (table, m) rows per compute unit at least (more than TILE_FEW_N samples: twice)
 constexpr int TILE_FEW_N = 512;
-constexpr unsigned TILE_SHARED = 64;     // up to so many searched items: eight lanes to each
+constexpr int TILE_SHARED = 128;     // up to so many items: eight lanes to each of those that enter several intervals
+constexpr int TILE_REACH = 16;       // intervals entered by some lane's block: above, the wave searches (as WALK_REACH)
 
 // Where the arrays of a workgroup start in LDS, in 8-byte slots.  The lists of the chain items lie
 // where A and B of every (m, s) go afterwards.
@@ -2911,7 +2868,7 @@ struct TileLds {
         nsp = (n_s + 3) & ~3;
         int at = 4 * n + (int)CHAIN_PAD;
         ab = list = at;
-        const int after = list + M * n_blk;
+        const int after = list + (M * n_blk + 1) / 2;
         at += 2 * M * nsp;
         at = at > after ? at : after;
         c = at; at += nsp;
@@ -2931,6 +2888,8 @@ struct TileLds {
     }
 };
 
+constexpr int TILE_KINDS = 10;           // no interval entered, one at the 8k-th term or after, more
+
 // An item of the chain sums on a list: size within the tile, block, interval of its first term.
 __device__ __forceinline__ unsigned tile_item(int ml, int b, int i)
 {
@@ -2938,8 +2897,7 @@ __device__ __forceinline__ unsigned tile_item(int ml, int b, int i)
 }
 
 // One item per lane, of one kind: no interval entered, one, more.  `real` lanes store.
-template <int KIND>
-__device__ __forceinline__ void tile_sum(const ChainCtx &C, unsigned item, bool real, const double *m_of, int M,
+__device__ __forceinline__ void tile_sum(const ChainCtx &C, unsigned item, bool real, bool dense, const double *m_of, int M,
                                          const u64 *blk_mask, const int *blk_off, int n_P, double *part, double *tot)
 {
     const int ml = (int)(item & 31u), b = (int)((item >> 5) & 31u), i = (int)(item >> 10);
@@ -2948,8 +2906,18 @@ __device__ __forceinline__ void tile_sum(const ChainCtx &C, unsigned item, bool 
     const u64 wanted = real ? blk_mask[b] : 0ull;
     double *out = part + ml * n_P + blk_off[b];
     const u64 any = wave_any_wanted(wanted);
-    const double run = KIND == 2 ? block_search(C, i, block_reach(C, z0, md, i), md, z0, wanted, any, out)
-                                 : block_walk<KIND == 1>(C, i, md, z0, wanted, any, out);
+    double run;
+    if (dense) {
+        const int reach = block_reach(C, z0, md, i);
+        if (reach > TILE_REACH) {
+            run = block_search(C, i, reach, md, z0, wanted, any, out);
+            if (real)
+                tot[b * M + ml] = run;
+            return;
+        }
+    }
+    WalkAt at = {i, z0 - C.X[i], C.W[i], C.YS[i]};
+    run = walk_block(C, at, md, wanted, any, out);
     if (real)
         tot[b * M + ml] = run;
 }
@@ -3002,20 +2970,21 @@ __device__ __forceinline__ void tile_search_shared(const ChainCtx &C, unsigned i
         tot[b * M + ml] = run;
 }
 
+template <bool ALL>
 __global__ void __launch_bounds__(TILE_THREADS, 6) k_tile(DeviceTables T, DeviceGrid G, plogp_cell_dev *out, int n_tiles,
                                                           int M)
 {
     // (a name of its own: under a name that another kernel declares without it the alignment is lost,
     // and 16-byte reads of misaligned LDS take twice the kernel's time)
     extern __shared__ __align__(16) double tile_lds[];
-    __shared__ unsigned count[3], next_wave, nv_tile;
+    __shared__ unsigned count[TILE_KINDS], next_wave, nv_tile;
     __shared__ double sh_g1;
     const int n_s = G.n_s, n_P = G.n_P, n_blk = G.n_blk, cl_max = G.cl_max;
     const TileLds A(T.n, n_s, n_P, n_blk, cl_max, M);
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int t = (int)blockIdx.x / n_tiles, m0 = (int)blockIdx.x % n_tiles * M;
     const int n_m = G.n_m - m0 < M ? G.n_m - m0 : M;           // sizes of this tile
-    const uint32_t mask = G.mask;
+    const uint32_t mask = ALL ? 0x1FFFu : G.mask;
     const bool chain = (mask & (1u << 11)) != 0, binom = (mask & (1u << 12)) != 0;
     f64x2 *sAB = reinterpret_cast<f64x2 *>(tile_lds + A.ab);
     double *sC = tile_lds + A.c, *sG = tile_lds + A.gs, *sR = tile_lds + A.rcp, *sGm = tile_lds + A.gm, *sM = tile_lds + A.md;
@@ -3036,7 +3005,7 @@ __global__ void __launch_bounds__(TILE_THREADS, 6) k_tile(DeviceTables T, Device
     }
     if (tid < n_m)
         sM[tid] = (double)G.m[m0 + tid];
-    if (tid < 3)
+    if (tid < TILE_KINDS)
         count[tid] = 0u;
     if (tid == 64)
         next_wave = 0u;
@@ -3070,11 +3039,17 @@ __global__ void __launch_bounds__(TILE_THREADS, 6) k_tile(DeviceTables T, Device
             for (int j = tid & 7; j < cl_max; j += 8)
                 sum2[ml * (cl_max + 1) + j + 1] = gap(sM[ml] * (double)(1ull << j));  // exact: below 2^53
     const int n_items = chain ? n_m * n_blk : 0;
+    constexpr int PER = TILE_MAX_M * TILE_MAX_BLK / TILE_THREADS;              // items of a thread at most
+    unsigned item[PER], place[PER];                                            // kind, its place among those of its kind
     {
         const int step_b = TILE_THREADS / n_m, step_m = TILE_THREADS % n_m;
         int b = tid / n_m, ml = tid % n_m;     // the next item of this thread: b n_m + ml
-        for (int e0 = wave * 64; e0 < n_items; e0 += 2 * TILE_THREADS) {       // two searches side by side
-            double z[2], md[2];
+#pragma unroll
+        for (int h = 0; h < PER; h += 2) {
+            place[h] = place[h + 1] = ~0u;
+            if (wave * 64 + h * TILE_THREADS >= n_items)
+                continue;
+            double z[2], md[2];                                                // two searches side by side
             int i[2], bb[2], mm[2];
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
@@ -3092,27 +3067,46 @@ __global__ void __launch_bounds__(TILE_THREADS, 6) k_tile(DeviceTables T, Device
             chain_locate<2>(C.X, C.n, z, i);
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
-                const double last = __builtin_fma((double)(SUM_BLOCK - 1), md[c], z[c]);
-                int kind = last < C.X[i[c] + 1] ? 0 : (last < C.X[i[c] + 2] ? 1 : 2);
-                kind = bb[c] < n_blk ? kind : 3;
-                const unsigned v = tile_item(mm[c], bb[c], i[c]);
-#pragma unroll
-                for (int h = 0; h < 3; ++h) {
-                    const u64 who = __ballot(kind == h);
-                    if (who == 0)
-                        continue;
-                    unsigned at = 0;
-                    if (lane == 0)
-                        at = atomicAdd(&count[h], (unsigned)__builtin_popcountll(who));
-                    at = __builtin_amdgcn_readfirstlane(at);
-                    at = __builtin_amdgcn_mbcnt_hi((unsigned)(who >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)who, at));
-                    if (kind == h)             // two lists from the front of an array, one from the back
-                        list[h == 0 ? (int)at : (h == 1 ? n_items - 1 - (int)at : n_items + (int)at)] = v;
+                if (bb[c] >= n_blk)
+                    continue;
+                const double last = __builtin_fma((double)(SUM_BLOCK - 1), md[c], z[c]), x1 = C.X[i[c] + 1];
+                unsigned kind = 0;
+                if (last >= x1) {
+                    // terms before the next interval, near enough
+                    const int before = (int)((float)(x1 - z[c]) * __builtin_amdgcn_rcpf((float)md[c]));
+                    kind = last >= C.X[i[c] + 2] ? TILE_KINDS - 1 : 1u + (unsigned)(before < 0 ? 0 : before >= SUM_BLOCK ? SUM_BLOCK - 1 : before) / 8u;
                 }
+                item[h + c] = tile_item(mm[c], bb[c], i[c]);
+                place[h + c] = kind << 16 | atomicAdd(&count[kind], 1u);
             }
         }
     }
     __syncthreads();
+    unsigned n0 = 0, n1 = 0, n2 = 0;
+    if (chain) {
+        // in the order of their kinds
+        unsigned at = 0;
+        unsigned first[TILE_KINDS];
+#pragma unroll
+        for (int k = 0; k < TILE_KINDS; ++k) {
+            first[k] = at;
+            at += count[k];
+        }
+        n0 = first[1];
+        n2 = count[TILE_KINDS - 1];
+        n1 = at - n0 - n2;
+#pragma unroll
+        for (int h = 0; h < PER; ++h) {
+            if (place[h] != ~0u) {
+                unsigned to = 0;
+#pragma unroll
+                for (int k = 1; k < TILE_KINDS; ++k)
+                    to = place[h] >> 16 == (unsigned)k ? first[k] : to;
+                list[to + (place[h] & 0xFFFFu)] = item[h];
+            }
+        }
+        __syncthreads();
+    }
 
     // the prefix of g(2^j m)
     if (binom && tid >= TILE_THREADS - 64 && tid - (TILE_THREADS - 64) < n_m) {
@@ -3124,29 +3118,21 @@ __global__ void __launch_bounds__(TILE_THREADS, 6) k_tile(DeviceTables T, Device
         }
     }
     if (chain) {
-        // 64 items of a kind at a time, the slowest kind first
-        const unsigned n0 = count[0], n1 = count[1], n2 = count[2];
-        const unsigned per2 = n2 <= TILE_SHARED ? 8u : 64u;
-        const unsigned w2 = (n2 + per2 - 1) / per2, w1 = (n1 + 63) / 64, w0 = (n0 + 63) / 64;
+        // 64 items at a time, the slowest first
+        const unsigned w2 = n2 <= 64u && n_items <= TILE_SHARED ? (n2 + 7) / 8 : 0u, rest = w2 != 0u ? n0 + n1 : (unsigned)n_items;
         for (;;) {
             unsigned k = 0;
             if (lane == 0)
                 k = atomicAdd(&next_wave, 1u);
             k = __builtin_amdgcn_readfirstlane(k);
-            if (k >= w2 + w1 + w0)
+            if (k >= w2 + (rest + 63) / 64)
                 break;
-            if (k < w2 && per2 == 8u) {
+            if (k < w2) {
                 const unsigned e = k * 8 + (lane >> 3);
-                tile_search_shared(C, list[n_items + (e < n2 ? e : n2 - 1)], e < n2, sM, M, sMask, sOff, n_P, part, tot);
-            } else if (k < w2) {
-                const unsigned e = k * 64 + lane;
-                tile_sum<2>(C, list[n_items + (e < n2 ? e : n2 - 1)], e < n2, sM, M, sMask, sOff, n_P, part, tot);
-            } else if (k < w2 + w1) {
-                const unsigned e = (k - w2) * 64 + lane;
-                tile_sum<1>(C, list[n_items - 1 - (e < n1 ? e : n1 - 1)], e < n1, sM, M, sMask, sOff, n_P, part, tot);
+                tile_search_shared(C, list[n0 + n1 + (e < n2 ? e : n2 - 1)], e < n2, sM, M, sMask, sOff, n_P, part, tot);
             } else {
-                const unsigned e = (k - w2 - w1) * 64 + lane;
-                tile_sum<0>(C, list[e < n0 ? e : n0 - 1], e < n0, sM, M, sMask, sOff, n_P, part, tot);
+                const unsigned e = (k - w2) * 64, at = e + lane;
+                tile_sum(C, list[at < rest ? rest - 1 - at : 0u], at < rest, rest - e > n0 + n1, sM, M, sMask, sOff, n_P, part, tot);
             }
         }
         __syncthreads();
@@ -4785,9 +4771,10 @@ hipError_t kernels_init()
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_terms_chain),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxTableLds);
     if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_tile), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)(g_device.lds_per_cu - TILE_STATIC_LDS));
-    if (e != hipSuccess) return e;
+    for (const void *k : {reinterpret_cast<const void *>(k_tile<false>), reinterpret_cast<const void *>(k_tile<true>)}) {
+        e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(g_device.lds_per_cu - TILE_STATIC_LDS));
+        if (e != hipSuccess) return e;
+    }
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_score_points),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxTableLds);
     if (e != hipSuccess) return e;
@@ -5362,8 +5349,8 @@ hipError_t launch_tune_stage(const TunePlan &p, int stage, const DeviceTables &T
     }
     if (p.path == TUNE_TILE) {
         if (stage == TUNE_STAGE_SWEEP)
-            hipLaunchKernelGGL(k_tile, dim3((unsigned)T.n_tables * p.n_tiles), dim3(TILE_THREADS), p.tile_lds, st, T,
-                               G, d_out, p.n_tiles, p.tile_m);
+            hipLaunchKernelGGL(G.mask == 0x1FFFu ? k_tile<true> : k_tile<false>, dim3((unsigned)T.n_tables * p.n_tiles),
+                               dim3(TILE_THREADS), p.tile_lds, st, T, G, d_out, p.n_tiles, p.tile_m);
         return hipGetLastError();
     }
     if (stage == TUNE_STAGE_MORE) {
