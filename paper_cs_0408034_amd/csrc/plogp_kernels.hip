@@ -3258,6 +3258,10 @@ __global__ void __launch_bounds__(TILE_THREADS, 6) k_tile(DeviceTables T, Device
 // process counts as in k_sweep_p: per candidate one fma and one min for row 5 of
 // Table 1, min_s A for rows 2 and 9, the winning candidate looked for only where a
 // segmented row wins, two coalesced stores per cell.
+// The slopes are read, as they were formed when the table was loaded, beside the
+// samples: a division and a barrier less in a chain of dependent steps that is all
+// of a small call (64 sizes x 49 process counts, 21 samples: 4.24 us in a graph of
+// such calls, 4.05 so, where an empty kernel takes 1.6; 200 x 100 5.16 and 5.05).
 constexpr int ROW_THREADS = 512;
 constexpr int ROW_MAX_BLK = 32;          // at most 2048 terms of the chain sum
 constexpr int ROW_NS = 64;               // candidates at most
@@ -3278,7 +3282,7 @@ static size_t row_lds_bytes(int n, int n_blk, int n_P)
 template <bool ALL, int PPL, bool EXTRA>
 __global__ void __launch_bounds__(ROW_THREADS) k_row(DeviceTables T, DeviceGrid G, plogp_cell_dev *out)
 {
-    extern __shared__ double lds[];
+    extern __shared__ __align__(16) double row_lds[];
     __shared__ double sh_gm, sh_g1, sh_amin;
     __shared__ int sh_nv;
     __shared__ unsigned next_group;
@@ -3288,8 +3292,9 @@ __global__ void __launch_bounds__(ROW_THREADS) k_row(DeviceTables T, DeviceGrid 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // the rows of large sizes (the most candidates) first when the sizes ascend
     const int t = (int)blockIdx.x / G.n_m, mi = G.n_m - 1 - (int)blockIdx.x % G.n_m;
-    double *x = lds, *y = x + n, *sl = y + n;
-    double *sA = sl + n, *sB = sA + ROW_SPAD, *sC = sB + ROW_SPAD;     // per candidate
+    f64x2 *ys = reinterpret_cast<f64x2 *>(row_lds);                    // {gap, slope} of every sample
+    double *x = row_lds + 2 * n;
+    double *sA = x + n, *sB = sA + ROW_SPAD, *sC = sB + ROW_SPAD;     // per candidate
     double *sum2 = sC + ROW_SPAD, *g2 = sum2 + 36;                     // prefix of g(2^j m); its terms
     double *pre = g2 + 36;                     // [block][65]: the terms, then the sums before each
     double *tot = pre + (size_t)n_blk * (SUM_BLOCK + 1), *done = tot + ROW_MAX_BLK;
@@ -3302,21 +3307,24 @@ __global__ void __launch_bounds__(ROW_THREADS) k_row(DeviceTables T, DeviceGrid 
     // (the division does not wait for the table: it runs while the samples are on their way)
     const double my_sd = (double)my_s, my_rcp = 1.0 / my_sd;
     {
-        const double *gx = T.x + (size_t)t * n, *gy = T.y + (size_t)t * n;
+        const double *gx = T.x + (size_t)t * n, *gy = T.y + (size_t)t * n, *gs = T.slope + (size_t)t * n;
         for (int i = tid; i < n; i += ROW_THREADS) {
             x[i] = gx[i];
-            y[i] = gy[i];
+            const f64x2 v = {gy[i], gs[i]};
+            ys[i] = v;
         }
         for (int i = tid; i < n_P; i += ROW_THREADS)
             sP[i] = G.P[i];
         if (tid == 0)
             next_group = 0u;
         __syncthreads();
-        for (int i = tid; i < n; i += ROW_THREADS)
-            sl[i] = interval_slope(x, y, n, i);
-        __syncthreads();
     }
-    const LdsTable tab = {x, y, sl, n};
+    const auto gap = [&](double z) {
+        const int i = last_not_above(x, n, z);
+        const f64x2 v = ys[i];
+        const double x0 = x[0];
+        return __builtin_fma(v.y, (z > x0 ? z : x0) - x[i], v.x);
+    };
     const double md = (double)m;
     const uint32_t need = EXTRA ? G.need : mask;       // the sums that some row adds up
     const bool chain = (need & (1u << 11)) != 0, binom = (need & (1u << 12)) != 0;
@@ -3326,7 +3334,7 @@ __global__ void __launch_bounds__(ROW_THREADS) k_row(DeviceTables T, DeviceGrid 
         bool valid = false;
         if (lane < n_s) {
             const u64 lim = m < G.s_cap ? m : G.s_cap;
-            const double sd = my_sd, gs = gap_at(tab, sd);
+            const double sd = my_sd, gs = gap(sd);
             C = gs + L;
             valid = my_s <= lim;
             if (valid) {
@@ -3352,10 +3360,10 @@ __global__ void __launch_bounds__(ROW_THREADS) k_row(DeviceTables T, DeviceGrid 
         }
     } else if (wave == 1) {
         if (binom && lane < G.cl_max)
-            g2[lane] = gap_at(tab, (double)(m << lane));
+            g2[lane] = gap((double)(m << lane));
         if (lane == 63) {
-            sh_gm = gap_at(tab, md);
-            sh_g1 = gap_at(tab, 1.0);
+            sh_gm = gap(md);
+            sh_g1 = gap(1.0);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -3374,7 +3382,7 @@ __global__ void __launch_bounds__(ROW_THREADS) k_row(DeviceTables T, DeviceGrid 
         for (int r = tid; r < n_blk * SUM_BLOCK; r += ROW_THREADS) {
             double v = 0.0;
             if (r < n_terms)
-                v = gap_at(tab, (double)((u64)(r + 1) * m));
+                v = gap((double)((u64)(r + 1) * m));
             pre[r + r / SUM_BLOCK] = v;
         }
     }
