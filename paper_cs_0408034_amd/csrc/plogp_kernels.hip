@@ -204,6 +204,56 @@ __device__ __forceinline__ void wave_min_each(double (&v)[N])
     }
 }
 
+__device__ __forceinline__ double lane_value(double v, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// Row 5, min over s of fma(q, C, B), for all q between q_lo and q_hi at once: which of 64 candidates, one per
+// lane (lane < nv; elsewhere B = +inf), can be the first to attain the minimum for some q.  Before rounding a
+// value is a line in q, so a candidate above another at either end by a margin is above it by that in between:
+// the two that are least at the ends leave out nearly all others.  The margin makes it certain after rounding
+// too: nothing between the ends is larger than M, the largest magnitude at the ends, the values at the ends and
+// in between are each off by up to 2^-53 M, and it is 2^-49 M.  (Values that are not finite stay in.)
+// 70 instructions, where a pass over 64 process counts, eight candidates at a time, took 35 for every eight: 1024
+// sizes x 1023 process counts, 34 candidates 16.0 -> 13.2 us, x 600, 8 candidates (2000 sizes) 17.0 -> 16.5; 13
+// candidates for 49 process counts, the least, 4.05 -> 4.14; 4096 sizes x 976, 43 candidates (k_sweep_p) the call
+// 126.5 -> 121.  Not used for up to 8, or 13, candidates: the same or slower everywhere.
+__device__ __forceinline__ u64 row5_candidates(double C, double B, int nv, double q_lo, double q_hi)
+{
+    const u64 there = nv >= 64 ? ~0ull : (1ull << nv) - 1ull;
+    const double at_lo = __builtin_fma(q_lo, C, B), at_hi = __builtin_fma(q_hi, C, B);
+    double least[2] = {at_lo, at_hi};
+    wave_min_each<2>(least);
+    const int a = __builtin_ctzll(__ballot(at_lo == least[0]) | 1ull << 63);
+    const int b = __builtin_ctzll(__ballot(at_hi == least[1]) | 1ull << 63);
+    const double a_hi = lane_value(at_hi, a), b_lo = lane_value(at_lo, b);
+    const double mine = fmax(fabs(at_lo), fabs(at_hi));
+    const double over_a = 0x1p-49 * fmax(mine, fmax(fabs(least[0]), fabs(a_hi)));
+    const double over_b = 0x1p-49 * fmax(mine, fmax(fabs(b_lo), fabs(least[1])));
+    const bool out = (at_lo - least[0] > over_a && at_hi - a_hi > over_a) ||
+                     (at_lo - b_lo > over_b && at_hi - least[1] > over_b);
+    return there & ~__ballot(out);
+}
+
+// The minimum over the candidates `which`, in ascending order, and the first that attains it.
+template <int PPL>
+__device__ __forceinline__ void row5_least(double C, double B, u64 which, const double (&q)[PPL],
+                                           double (&least)[PPL], int (&at)[PPL])
+{
+    for (; which != 0; which &= which - 1) {
+        const int c = __builtin_ctzll(which);
+        const double Cv = lane_value(C, c), Bv = lane_value(B, c);
+#pragma unroll
+        for (int h = 0; h < PPL; ++h) {
+            const double v = __builtin_fma(q[h], Cv, Bv);
+            at[h] = v < least[h] ? c : at[h];
+            least[h] = min_f64(least[h], v);
+        }
+    }
+}
+
 // ---------------------------------------------------------------- slopes (table load)
 
 __global__ void __launch_bounds__(256) k_slopes(DeviceTables T, double *slope_out)
@@ -551,9 +601,18 @@ __device__ __forceinline__ void chain_locate(const double *X, int n, const doubl
 #pragma unroll
         for (int c = 0; c < U; ++c)
             xv[c] = X[1 + i[c] + half];
+        // all comparisons first, their results in scalar registers: a select right behind its comparison
+        // waits for it (a call of 49 sizes x 26 process counts up to 4096, bound by this, 18.6 and 18.3 us)
+        u64 past[U];
+#pragma unroll
+        for (int c = 0; c < U; ++c) {
+            past[c] = __ballot(xv[c] <= z[c]);
+            if (U >= 4)
+                asm("" : "+s"(past[c]));
+        }
 #pragma unroll
         for (int c = 0; c < U; ++c)
-            i[c] = xv[c] <= z[c] ? i[c] + half : i[c];
+            i[c] = __builtin_amdgcn_inverse_ballot_w64(past[c]) ? i[c] + half : i[c];
         len -= half;
     }
     const double x_first = X[1];
@@ -1642,14 +1701,16 @@ __global__ void __launch_bounds__(CROW_THREADS) k_terms_chain_row(DeviceTables T
 // Both first steps in one launch: they do not depend on each other (each stages the
 // table from the raw samples), so the workgroups of the chain sums (the longer job, first
 // in the grid) and those of the terms run side by side.  For tables small enough that
-// workgroups of both kinds share a CU.
+// workgroups of both kinds share a CU.  SMALL: a small job, terms by search, side by side (a kernel
+// of its own: 49 sizes x 26 process counts up to 4096 took 0.5 us of 8 longer beside the walk's code).
+template <bool SMALL>
 __global__ void __launch_bounds__(256) k_terms_chain(DeviceTables T, DeviceGrid G, Scratch S, int n_chain_wg,
                                                      int wg_per_table, int n_single,
                                                      int n_chunks, int n_mchunks, int with_pairs)
 {
     extern __shared__ __align__(16) double both_lds[];
     if ((int)blockIdx.x < n_chain_wg) {
-        if (n_single < 0)                 // a small job: terms by search, side by side
+        if (SMALL)
             chain_small_body(T, G, S, wg_per_table, (int)blockIdx.x, both_lds);
         else
             chain_body<false>(T, G, S, wg_per_table, n_single, 0, (int)blockIdx.x, both_lds);
@@ -2164,19 +2225,27 @@ __global__ void __launch_bounds__(256) k_sweep_m(DeviceTables T, DeviceGrid G, S
 // k_terms), C, the candidate count, g(m) -- is the same in all lanes then: per
 // candidate the lanes do one fma, one compare, the index select and the running
 // minimum for row 5 of Table 1; min_s A for rows 2 and 9 is one reduction over the
-// wave per m.  A cell costs two coalesced 16-byte stores.  The sizes of a wave lie
-// n_w apart, so every wave meets the same mix of short and long candidate lists;
-// the loads for the next size are issued before the current one is worked on.
+// wave per m.  A cell
+// costs two coalesced 16-byte stores.  The sizes of a wave lie n_w apart, so every
+// wave meets the same mix of short and long candidate lists; the loads for the next
+// size are issued before the current one is worked on.
 // NSV: candidates per lane when a row of (m, s) terms is moved (n_s <= 64 NSV).
-template <int NSV, bool ALL, int PPL>
+// FEW (NSV 1): row 5 for the candidates alone that can win it for some process count of
+// the wave (row5_candidates), in place of a loop over all, eight a round trip to LDS.
+// With two process counts per lane that is the faster (4096 sizes x 976, 43 candidates:
+// 38 us, 33), with one where the list is close (at least half of all counts up to the
+// largest; 9000 x 300 up to 301, 34 candidates: the call 63.6, 58.0), and not where a
+// wave's counts lie far apart (1638 x 100 up to 2612, 40: 8.1 us, 9.2; 5000 x 40 up to
+// 1500, 34: the call 31.9, 33.1).
+template <int NSV, bool ALL, int PPL, bool FEW>
 __global__ void __launch_bounds__(256) k_sweep_p(DeviceTables T, DeviceGrid G, Scratch S,
                                                  plogp_cell_dev *out, int t0, int n_w)
 {
     // the loops below read up to 7 entries past the last candidate: rows are 8 longer
     constexpr int ROW = 64 * NSV + 8;
-    __shared__ double sC[ROW];                       // g(s) + L (0 past the end)
     __shared__ uint32_t sSv[ROW];                    // s
-    __shared__ double rowB[4][ROW];                  // B of the current size (+inf past the end)
+    __shared__ double sC[FEW ? 1 : ROW];             // g(s) + L (0 past the end)
+    __shared__ double rowB[4][FEW ? 1 : ROW];        // B of the current size (+inf past the end)
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     // grid: x = group of four waves, y = group of 64 PPL process counts, z = table (from t0)
@@ -2276,14 +2345,19 @@ __global__ void __launch_bounds__(256) k_sweep_p(DeviceTables T, DeviceGrid G, S
     if (has_work)
         fetch(w);
     for (int si = threadIdx.x; si < ROW; si += blockDim.x) {
-        sC[si] = si < G.n_s ? S.segC[(size_t)t * G.n_s + si] : 0.0;
         sSv[si] = si < G.n_s ? (uint32_t)G.s[si] : 0u;
-        if (si >= 64 * NSV) {
+        if (!FEW) {
+            sC[si] = si < G.n_s ? S.segC[(size_t)t * G.n_s + si] : 0.0;
+            if (si >= 64 * NSV) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                rowB[k][si] = INFINITY;
+                for (int k = 0; k < 4; ++k)
+                    rowB[k][si] = INFINITY;
+            }
         }
     }
+    // a candidate per lane (0 past the end)
+    const double C = FEW && seg && lane < n_s ? S.segC[(size_t)t * n_s + lane] : 0.0;
+    const double q_lo = lane_value(q[0], 0), q_hi = lane_value(q[PPL - 1], 63);
     __syncthreads();
     if (!has_work)
         return;
@@ -2299,19 +2373,22 @@ __global__ void __launch_bounds__(256) k_sweep_p(DeviceTables T, DeviceGrid G, S
         const int nv = f_nv;
         const double amin = f_amin;      // min over s of A = g(s) k, from k_terms
         const size_t row_now = (size_t)t * n_m + mi;
-        if (seg) {
+        const double B = FEW ? fB[0] : 0.0;
+        if (!FEW && seg) {
 #pragma unroll
             for (int k = 0; k < NSV; ++k)
                 rowB[wave][lane + 64 * k] = fB[k];
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+        if (!FEW) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
         if (mi + n_w < (int)n_m)
             fetch(mi + n_w);
 
-        // row 5: min over s of fma(q, C, B).  The loop keeps the minimum and in which batch of
-        // eight candidates it first appeared; the candidate itself is looked for afterwards,
-        // and only where row 5 wins the cell.
+        // row 5: min over s of fma(q, C, B), and where it first appeared (FEW: the candidate, else
+        // the batch of eight; the candidate itself is then looked for, where row 5 wins the cell)
+
         double b5[PPL];
         int i5[PPL];
 #pragma unroll
@@ -2320,23 +2397,27 @@ __global__ void __launch_bounds__(256) k_sweep_p(DeviceTables T, DeviceGrid G, S
             i5[h] = 0;
         }
         if (mask & 0x20u) {
-            // eight candidates per round trip to LDS; past the last competing one B is
-            // +inf (and C is finite), so the value is +inf and never taken
-            for (int s0 = 0; s0 < nv; s0 += 8) {
-                double Bv[8], Cv[8];
+            if (FEW) {
+                row5_least<PPL>(C, B, row5_candidates(C, B, nv, q_lo, q_hi), q, b5, i5);
+            } else {
+                // eight candidates per round trip to LDS; past the last competing one B is
+                // +inf (and C is finite), so the value is +inf and never taken
+                for (int s0 = 0; s0 < nv; s0 += 8) {
+                    double Bv[8], Cv[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    Bv[u] = rowB[wave][s0 + u];
-                    Cv[u] = sC[s0 + u];
-                }
+                    for (int u = 0; u < 8; ++u) {
+                        Bv[u] = rowB[wave][s0 + u];
+                        Cv[u] = sC[s0 + u];
+                    }
 #pragma unroll
-                for (int h = 0; h < PPL; ++h) {
-                    double cur = INFINITY;
+                    for (int h = 0; h < PPL; ++h) {
+                        double cur = INFINITY;
 #pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        cur = min_f64(cur, __builtin_fma(q[h], Cv[u], Bv[u]));
-                    i5[h] = cur < b5[h] ? s0 : i5[h];
-                    b5[h] = min_f64(b5[h], cur);
+                        for (int u = 0; u < 8; ++u)
+                            cur = min_f64(cur, __builtin_fma(q[h], Cv[u], Bv[u]));
+                        i5[h] = cur < b5[h] ? s0 : i5[h];
+                        b5[h] = min_f64(b5[h], cur);
+                    }
                 }
             }
         }
@@ -2348,9 +2429,12 @@ __global__ void __launch_bounds__(256) k_sweep_p(DeviceTables T, DeviceGrid G, S
                 const double t2 = amin < INFINITY ? __builtin_fma(q[h], amin, L) : INFINITY;
                 const double t9 = amin < INFINITY ? __builtin_fma(fl[h], amin, clL[h]) : INFINITY;
                 Best bc = decide_bcast(mask, q[h], fl[h], cl[h], gm, L, g1, t2, 0u, b5[h], 0u, t9, 0u);
-                // a winning row 5: the first candidate of the remembered batch that attains the
-                // minimum (lanes differ in their batch: per-lane LDS reads of its eight candidates)
-                if (__ballot(active[h] && bc.id == 5u) != 0) {
+                if (FEW) {
+                    if (bc.id == 5u)
+                        bc.s = sSv[i5[h]];
+                } else if (__ballot(active[h] && bc.id == 5u) != 0) {
+                    // the first candidate of the remembered batch that attains the minimum (lanes
+                    // differ in their batch: per-lane LDS reads of its eight candidates)
                     double Bv[8], Cv[8];
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
@@ -2435,7 +2519,8 @@ __global__ void __launch_bounds__(256) k_sweep_p(DeviceTables T, DeviceGrid G, S
                 if (active[h])
                     store_cell(o + 64 * h, decide_scatter(mask, q[h], cl[h], gm, L, s11[h], s12[h]));
         }
-        __builtin_amdgcn_wave_barrier();
+        if (!FEW)
+            __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -3255,9 +3340,9 @@ __global__ void __launch_bounds__(TILE_THREADS, 6) k_tile(DeviceTables T, Device
 // and the prefix of g(2^j m); all threads the terms g(j m) of the chain sum, one
 // search each; wave 0 the sums inside the blocks (a lane per block, 64 dependent
 // additions) and then over the blocks; then the waves run their lanes over the
-// process counts as in k_sweep_p: per candidate one fma and one min for row 5 of
-// Table 1, min_s A for rows 2 and 9, the winning candidate looked for only where a
-// segmented row wins, two coalesced stores per cell.
+// process counts as in k_sweep_p: the few candidates that can win row 5 of Table 1
+// for some process count of the group, min_s A for rows 2 and 9, whose candidate is
+// looked for only where one of them wins, two coalesced stores per cell.
 // The slopes are read, as they were formed when the table was loaded, beside the
 // samples: a division and a barrier less in a chain of dependent steps that is all
 // of a small call (64 sizes x 49 process counts, 21 samples: 4.24 us in a graph of
@@ -3424,9 +3509,8 @@ __global__ void __launch_bounds__(ROW_THREADS) k_row(DeviceTables T, DeviceGrid 
     const int nv = sh_nv;
     const size_t plane = (size_t)G.n_m * n_P;
     plogp_cell_dev *const orow = out + (size_t)t * G.n_ops * plane + (size_t)mi * n_P;
-    // lane si keeps C of candidate si (lanes past the candidates: 0, never taken as B is +inf)
-    const double c_mine = sC[lane];
-    const int c_lo = __double2loint(c_mine), c_hi = __double2hiint(c_mine);
+    // lane si keeps candidate si (lanes past the candidates: B is +inf)
+    const double c_mine = sC[lane], b_mine = sB[lane];
     // a lane takes PPL process counts, 64 apart: a candidate read from LDS serves them all
     const unsigned n_groups = (unsigned)((n_P + 64 * PPL - 1) / (64 * PPL));
     if (mask & 0x3FFu) {
@@ -3453,44 +3537,17 @@ __global__ void __launch_bounds__(ROW_THREADS) k_row(DeviceTables T, DeviceGrid 
                 b5[h] = INFINITY;
                 i5[h] = 0;
             }
-            // row 5: min over s of fma(q, C, B), eight candidates per round trip to LDS; the
-            // batch in which the minimum first appeared is remembered
-            if (mask & 0x20u) {
-                for (int s0 = 0; s0 < nv; s0 += 8) {
-                    // B from LDS (the same address in every lane), C from the lane that holds
-                    // it, through scalar registers: half the LDS traffic
-                    double Bv[8], Cv[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        Bv[u] = sB[s0 + u];
-                        Cv[u] = __hiloint2double(__builtin_amdgcn_readlane(c_hi, s0 + u),
-                                                 __builtin_amdgcn_readlane(c_lo, s0 + u));
-                    }
-#pragma unroll
-                    for (int h = 0; h < PPL; ++h) {
-                        double cur = INFINITY;
-#pragma unroll
-                        for (int u = 0; u < 8; ++u)
-                            cur = min_f64(cur, __builtin_fma(q[h], Cv[u], Bv[u]));
-                        i5[h] = cur < b5[h] ? s0 : i5[h];
-                        b5[h] = min_f64(b5[h], cur);
-                    }
-                }
-            }
+            if (mask & 0x20u)
+                row5_least<PPL>(c_mine, b_mine,
+                                row5_candidates(c_mine, b_mine, nv, lane_value(q[0], 0), lane_value(q[PPL - 1], 63)),
+                                q, b5, i5);
 #pragma unroll
             for (int h = 0; h < PPL; ++h) {
                 const double t2 = amin < INFINITY ? __builtin_fma(q[h], amin, L) : INFINITY;
                 const double t9 = amin < INFINITY ? __builtin_fma(fl[h], amin, clL[h]) : INFINITY;
                 Best bc = decide_bcast(mask, q[h], fl[h], cl[h], gm, L, g1, t2, 0u, b5[h], 0u, t9, 0u);
-                if (__ballot(active[h] && bc.id == 5u) != 0) {
-                    // the first candidate of the remembered batch that attains the minimum
-                    int at5 = i5[h];
-#pragma unroll
-                    for (int u = 7; u >= 0; --u)        // descending: the first match stays
-                        at5 = __builtin_fma(q[h], sC[i5[h] + u], sB[i5[h] + u]) == b5[h] ? i5[h] + u : at5;
-                    const uint32_t s_at = sSv[at5];
-                    bc.s = bc.id == 5u ? s_at : bc.s;
-                }
+                if (bc.id == 5u)
+                    bc.s = sSv[i5[h]];
                 bool open = active[h] && (bc.id == 2u || bc.id == 9u);
                 if (__ballot(open) != 0) {
                     // a winning row 2 or 9: the first candidate whose value equals the minimum
@@ -4776,7 +4833,10 @@ hipError_t kernels_init()
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_chain_blocks),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxChainLds);
     if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_terms_chain),
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_terms_chain<false>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxTableLds);
+    if (e != hipSuccess) return e;
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_terms_chain<true>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxTableLds);
     if (e != hipSuccess) return e;
     for (const void *k : {reinterpret_cast<const void *>(k_tile<false>), reinterpret_cast<const void *>(k_tile<true>)}) {
@@ -5386,7 +5446,7 @@ hipError_t launch_tune_stage(const TunePlan &p, int stage, const DeviceTables &T
                                    p.crow_lds, st, T, G, S);
         } else if (p.chain) {
             if (p.together)
-                hipLaunchKernelGGL(k_terms_chain, dim3((unsigned)(p.n_chain_wg + p.terms_wg)), dim3(256),
+                hipLaunchKernelGGL(p.n_single < 0 ? k_terms_chain<true> : k_terms_chain<false>, dim3((unsigned)(p.n_chain_wg + p.terms_wg)), dim3(256),
                                    p.both_lds, st, T, G, S, p.n_chain_wg, p.chain_wg, p.n_single,
                                    p.n_chunks, p.n_mchunks, p.terms_mode);
             else
@@ -5413,14 +5473,14 @@ hipError_t launch_tune_stage(const TunePlan &p, int stage, const DeviceTables &T
             for (int t0 = 0; t0 < T.n_tables; t0 += 65535) {
                 const int nt = T.n_tables - t0 < 65535 ? T.n_tables - t0 : 65535;
                 const dim3 blocks((unsigned)(p.n_w / 4), (unsigned)p.n_pg, (unsigned)nt);
-                if (G.n_s <= 64 && all && p.ppl == 2)
-                    hipLaunchKernelGGL((k_sweep_p<1, true, 2>), blocks, dim3(256), 0, st, T, G, S, d_out, t0, p.n_w);
-                else if (G.n_s <= 64 && all)
-                    hipLaunchKernelGGL((k_sweep_p<1, true, 1>), blocks, dim3(256), 0, st, T, G, S, d_out, t0, p.n_w);
-                else if (G.n_s <= 64)
-                    hipLaunchKernelGGL((k_sweep_p<1, false, 1>), blocks, dim3(256), 0, st, T, G, S, d_out, t0, p.n_w);
-                else
-                    hipLaunchKernelGGL((k_sweep_p<4, false, 1>), blocks, dim3(256), 0, st, T, G, S, d_out, t0, p.n_w);
+                const bool close = 2L * G.n_P >= (long)G.n_blk * SUM_BLOCK;
+                const auto kern = G.n_s > 64 ? k_sweep_p<4, false, 1, false>
+                                  : all      ? (p.ppl == 2 ? k_sweep_p<1, true, 2, true>
+                                                : close    ? k_sweep_p<1, true, 1, true>
+                                                           : k_sweep_p<1, true, 1, false>)
+                                  : close    ? k_sweep_p<1, false, 1, true>
+                                             : k_sweep_p<1, false, 1, false>;
+                hipLaunchKernelGGL(kern, blocks, dim3(256), 0, st, T, G, S, d_out, t0, p.n_w);
             }
         } else {
             hipLaunchKernelGGL(k_sweep_m<4>, dim3((unsigned)T.n_tables * p.n_mg * p.n_pcg), dim3(256), 0, st, T, G,

@@ -869,6 +869,30 @@ def test_walks_past_samples_that_lie_together(together, route):
     assert assert_tables_equal(gpu_tune(wl), want, "%d together, %s" % (together, route)), "times not bit-identical"
 
 
+# ------------------------------------------------------------------ candidates that can win row 5
+
+@pytest.mark.parametrize("n_m,n_P,p_hi", [(9, 1, 2), (9, 1, 700), (9, 64, 65), (9, 130, 1900), (9, 513, 514), (5, 700, 2048),
+                                          (4200, 33, 40), (4100, 70, 4000), (300, 520, 4000)])
+@pytest.mark.parametrize("n_s", [1, 2, 63, 64, 65, 130, 256])
+@pytest.mark.parametrize("table", ["noise", "flat", "falling", "line"])
+def test_candidates_that_can_win_row_5(n_m, n_P, p_hi, n_s, table):
+    # a row to a workgroup and lanes over process counts, one and two to a lane; up to 64 candidates in one
+    # turn, more in several.  flat: equal gaps, so that candidates of the same number of segments tie;
+    # falling: gaps and times below zero past the last sample; line: times that differ in their last bits
+    rng = np.random.default_rng(n_m + n_P + n_s)
+    n = 40
+    x = np.cumsum(rng.integers(1, 3000, size=n)).astype(np.float64)[None]
+    gaps = {"noise": np.abs(25.0 + 0.07 * x * (1.0 + 0.3 * rng.standard_normal(x.shape))), "flat": np.full(x.shape, 12.5),
+            "falling": 30.0 * (1.0 - 0.9 * x / x[0, -1]), "line": 1.0 + x * 2.0 ** -9}[table]
+    m = np.maximum(8 * np.floor(np.exp(rng.uniform(np.log(8.0), np.log(5e6), size=n_m)) / 8), 8).astype(np.uint64)
+    P = np.union1d(rng.choice(np.arange(2, p_hi + 1), size=n_P - 1, replace=False), [p_hi]).astype(np.uint32)
+    s = 8 * np.unique(np.concatenate([np.arange(1, n_s // 2 + 1), np.floor(np.geomspace(200, 60000, 2 * n_s))]))[:n_s]
+    wl = Workload("row 5", x, gaps, np.array([0.0 if table == "line" else 40.0]), m, P, s.astype(np.uint64), NO_CAP,
+                  ALL_STRATEGIES_MASK if n_s != 63 else 0x20)
+    want, _ = oracle.tune_workload(wl)
+    assert assert_tables_equal(gpu_tune(wl), want, "n_s=%d %s" % (n_s, table)), "times not bit-identical"
+
+
 # ------------------------------------------------------------------ many candidates, chunks left out by their bounds
 
 @pytest.mark.parametrize("n_s,n_P,shape", [
