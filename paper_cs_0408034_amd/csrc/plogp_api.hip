@@ -270,9 +270,12 @@ int plogp_load_tables(const double *sizes, const double *gaps, size_t n, const d
         for (size_t i = 0; i < n; ++i)
             if (sizes[t * n + i] != sizes[i]) { h->shared_x = false; break; }
     // One allocation [x | y | L | slope]: an allocation or a release costs more than the copy of a
-    // table (one table of 64 samples loaded in 35 us, 61 with four allocations and three copies;
-    // loaded, tuned and replaced 54 us, 101 before).  A small batch is also packed on the host and
-    // copied at once; a large one is copied from where it is.
+    // table.  The samples of one small table or a few travel in the arguments of the kernel that forms
+    // the slopes: one launch and one wait, where the copy was a wait and a kernel of the runtime's of its
+    // own (64 samples, loaded, tuned over 256 sizes x 127 process counts and the thresholds extracted, in
+    // place of the table before: 43.2 us with the copy, 31.4 so; on a stream of its own, which does not
+    // wait for the table before, but whose work and releases the runtime takes longer over, 37.5).  A batch
+    // of up to 4096 numbers is packed on the host and copied at once; a large one is copied from where it is.
     const size_t count = n_tables * n;
     hipError_t e;
     if ((e = hipMalloc((void **)&h->d_x, (3 * count + n_tables) * sizeof(double))) != hipSuccess) {
@@ -284,18 +287,28 @@ int plogp_load_tables(const double *sizes, const double *gaps, size_t n, const d
     h->d_L = h->d_y + count;
     h->d_slope = h->d_L + n_tables;
     constexpr size_t kPacked = 4096;                    // doubles
-    if (2 * count + n_tables <= kPacked) {
-        double packed[kPacked];
-        std::copy(sizes, sizes + count, packed);
-        std::copy(gaps, gaps + count, packed + count);
-        std::copy(L, L + n_tables, packed + 2 * count);
-        e = hipMemcpy(h->d_x, packed, (2 * count + n_tables) * sizeof(double), hipMemcpyHostToDevice);
-    } else if ((e = hipMemcpy(h->d_x, sizes, count * sizeof(double), hipMemcpyHostToDevice)) == hipSuccess &&
-               (e = hipMemcpy(h->d_y, gaps, count * sizeof(double), hipMemcpyHostToDevice)) == hipSuccess) {
-        e = hipMemcpy(h->d_L, L, n_tables * sizeof(double), hipMemcpyHostToDevice);
+    const auto pack = [&](double *to) {
+        std::copy(sizes, sizes + count, to);
+        std::copy(gaps, gaps + count, to + count);
+        std::copy(L, L + n_tables, to + 2 * count);
+    };
+    if (2 * count + n_tables <= (size_t)PACKED_DOUBLES) {
+        PackedTables packed;
+        pack(packed.v);
+        e = launch_load_packed(packed, h->d_x, (int)n, (int)n_tables, nullptr);
+    } else {
+        if (2 * count + n_tables <= kPacked) {
+            double packed[kPacked];
+            pack(packed);
+            e = hipMemcpy(h->d_x, packed, (2 * count + n_tables) * sizeof(double), hipMemcpyHostToDevice);
+        } else if ((e = hipMemcpy(h->d_x, sizes, count * sizeof(double), hipMemcpyHostToDevice)) == hipSuccess &&
+                   (e = hipMemcpy(h->d_y, gaps, count * sizeof(double), hipMemcpyHostToDevice)) == hipSuccess) {
+            e = hipMemcpy(h->d_L, L, n_tables * sizeof(double), hipMemcpyHostToDevice);
+        }
+        if (e == hipSuccess)
+            e = launch_slopes(h->view(), h->d_slope, nullptr);
     }
-    if (e != hipSuccess || (e = launch_slopes(h->view(), h->d_slope, nullptr)) != hipSuccess ||
-        (e = hipStreamSynchronize(nullptr)) != hipSuccess) {
+    if (e != hipSuccess || (e = hipStreamSynchronize(nullptr)) != hipSuccess) {
         delete h;
         return device_error(e);
     }

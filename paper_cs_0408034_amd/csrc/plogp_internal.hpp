@@ -178,6 +178,13 @@ Scratch bind_scratch(void *base, const ScratchLayout &lay);
 
 // Each returns the hipError_t of the launch (hipGetLastError after it).
 hipError_t launch_slopes(const DeviceTables &T, double *slope_out, hipStream_t st);
+// A few small tables as [x | y | L], passed by value as a kernel's argument.
+constexpr int PACKED_DOUBLES = 448;
+struct PackedTables {
+    double v[PACKED_DOUBLES];
+};
+// Writes [x | y | L | slope] at d_block.  2 n n_tables + n_tables <= PACKED_DOUBLES.
+hipError_t launch_load_packed(const PackedTables &packed, double *d_block, int n, int n_tables, hipStream_t st);
 hipError_t launch_interp(const DeviceTables &T, int table, const uint64_t *d_z, size_t n,
                          double *d_out, hipStream_t st);
 hipError_t launch_eval(const DeviceTables &T, int table, int strategy, const uint64_t *d_m,

@@ -266,6 +266,18 @@ __global__ void __launch_bounds__(256) k_slopes(DeviceTables T, double *slope_ou
 
 // ---------------------------------------------------------------- g() at arbitrary sizes
 
+// The same for tables that come as the argument, written out beside their slopes.
+__global__ void __launch_bounds__(256) k_load_packed(PackedTables packed, double *block, int n, int n_tables)
+{
+    const int count = n * n_tables, last = 2 * count + n_tables;
+    for (int i = threadIdx.x; i < last; i += blockDim.x)
+        block[i] = packed.v[i];
+    for (int i = threadIdx.x; i < count; i += blockDim.x) {
+        const int t = i / n;
+        block[last + i] = interval_slope(packed.v + t * n, packed.v + count + t * n, n, i - t * n);
+    }
+}
+
 __global__ void __launch_bounds__(256) k_interp(DeviceTables T, int t, const u64 *z, size_t n,
                                                 double *out)
 {
@@ -4874,6 +4886,12 @@ hipError_t kernels_init()
 hipError_t launch_slopes(const DeviceTables &T, double *slope_out, hipStream_t st)
 {
     hipLaunchKernelGGL(k_slopes, dim3(T.n_tables), dim3(256), 0, st, T, slope_out);
+    return hipGetLastError();
+}
+
+hipError_t launch_load_packed(const PackedTables &packed, double *d_block, int n, int n_tables, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_load_packed, dim3(1), dim3(256), 0, st, packed, d_block, n, n_tables);
     return hipGetLastError();
 }
 

@@ -57,6 +57,24 @@ def test_slopes_and_interpolation_bit_exact(cfg):
 
 # ------------------------------------------------------------------ each row of Tables 1 and 2
 
+@pytest.mark.parametrize("n_tables,n", [(1, 2), (1, 223), (1, 224), (2, 111), (2, 112), (89, 2), (90, 2), (1, 2047), (1, 2048)])
+def test_tables_around_the_sizes_at_which_they_travel_otherwise(n_tables, n):
+    # samples in the arguments of a kernel up to 448 numbers, in one copy up to 4096, in three from there on
+    plogp = _plogp()
+    rng = np.random.default_rng(n)
+    x = np.cumsum(rng.integers(1, 900, size=(n_tables, n)), axis=1).astype(np.float64)
+    y, L = rng.uniform(1.0, 90.0, size=x.shape), rng.uniform(0.0, 90.0, size=n_tables)
+    tab = plogp.plogp_load_tables(x, y, L)
+    for t in range(n_tables):
+        slopes = np.diff(y[t]) / np.diff(x[t])
+        assert (plogp.plogp_table_slopes(tab, t) == np.append(slopes, slopes[-1])).all()
+    tab.free()
+    wl = Workload("loaded", x, y, L, np.array([8, 800, 90000], dtype=np.uint64), np.array([2, 3, 70], dtype=np.uint32),
+                  np.array([8, 64, 512], dtype=np.uint64), NO_CAP, ALL_STRATEGIES_MASK)
+    want, _ = oracle.tune_workload(wl)
+    assert assert_tables_equal(gpu_tune(wl), want, "%d x %d" % (n_tables, n)), "times not bit-identical"
+
+
 @pytest.mark.parametrize("cfg", [2, 5])
 def test_every_strategy_at_random_points(cfg):
     torch = torch_cuda()
