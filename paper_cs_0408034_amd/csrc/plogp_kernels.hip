@@ -565,6 +565,23 @@ struct ChainCtx {
     const int *blk_off;
 };
 
+// Scratch::blk: [block][m], or, where the totals are turned into their prefix, the sizes of one workgroup
+// of that step (k_chain_prefix) together: [group of PFX_M sizes][block][m of the group].
+constexpr int PFX_M = 8;
+
+struct BlkAt {
+    size_t first, stride;      // of block 0, from a block to the next
+};
+
+__device__ __forceinline__ BlkAt blk_of(const DeviceGrid &G, int t, int mi)
+{
+    const size_t table = (size_t)t * G.n_blk * G.n_mu;
+    if (!G.blk_is_prefix)
+        return {table + mi, (size_t)G.n_mu};
+    const int first = mi / PFX_M * PFX_M, width = G.n_mu - first < PFX_M ? G.n_mu - first : PFX_M;
+    return {table + (size_t)first * G.n_blk + (mi - first), (size_t)width};
+}
+
 // Builds the table as intervals in LDS (4 n + CHAIN_PAD doubles at `lds`).  The caller synchronises.
 // The slopes are formed here (the same expression as everywhere) where many tables are staged once
 // or twice each, or read (SLOPES) where every workgroup stages the same one, from its cache (one
@@ -1003,6 +1020,7 @@ __device__ __forceinline__ void chain_small_body(const DeviceTables &T, const De
         }
         __syncthreads();
         if (wave == 0) {
+            const BlkAt at_total = blk_of(G, t, mi < n_mu ? mi : 0);
             double run = 0.0;
             for (int r0 = 0; r0 < SUM_BLOCK; r0 += 8) {
                 double g[8];
@@ -1016,7 +1034,7 @@ __device__ __forceinline__ void chain_small_body(const DeviceTables &T, const De
                 }
             }
             if (mi < n_mu && b < G.n_blk - 1)
-                S.blk[((size_t)t * G.n_blk + b) * n_mu + mi] = run;
+                S.blk[at_total.first + b * at_total.stride] = run;
         }
         __syncthreads();
         {
@@ -1192,8 +1210,9 @@ __device__ __forceinline__ double block_search(const ChainCtx &C, int i, int rea
 // ---------------------------------------------------------------- chain sums of a big table
 
 // `n` consecutive blocks from block b on, one after the other, for the size m of this lane.  part: this
-// size's row of in-block partial sums; tot: its column of block totals.
-__device__ __forceinline__ void chain_item(const ChainCtx &C, int b, int n, u64 m, double *part, double *tot)
+// size's row of in-block partial sums; tot: its block totals, `stride` apart.
+__device__ __forceinline__ void chain_item(const ChainCtx &C, int b, int n, u64 m, double *part, double *tot,
+                                           size_t stride)
 {
     const double md = (double)m;
     const double ends[2] = {(double)(((u64)b * SUM_BLOCK + 1) * m), (double)(((u64)b * SUM_BLOCK + SUM_BLOCK) * m)};
@@ -1210,7 +1229,7 @@ __device__ __forceinline__ void chain_item(const ChainCtx &C, int b, int n, u64 
             const double run = block_search(C, from.i, block_reach(C, z0, md, from.i), md, z0, wanted, wanted,
                                             part + C.blk_off[b]);
             if (b < C.n_blk - 1)                          // the last block is never complete
-                tot[(size_t)b * C.n_m] = run;
+                tot[b * stride] = run;
         }
         return;
     }
@@ -1218,7 +1237,7 @@ __device__ __forceinline__ void chain_item(const ChainCtx &C, int b, int n, u64 
         const u64 wanted = C.blk_mask[b];
         const double run = walk_block(C, at, md, wanted, wanted, part + C.blk_off[b]);
         if (b < C.n_blk - 1)
-            tot[(size_t)b * C.n_m] = run;
+            tot[b * stride] = run;
     }
 }
 
@@ -1292,8 +1311,9 @@ __device__ __forceinline__ void chain_body(const DeviceTables &T, const DeviceGr
             continue;
         const u64 m = G.mu[mi];
         double *part = S.part + ((size_t)t * C.n_m + mi) * G.n_P;     // [m][P index]
-        double *tot = S.blk + (size_t)t * G.n_blk * C.n_m + mi;       // [block][m]
-        chain_item(C, single ? u : n_single + u * CHAIN_U, single ? 1 : CHAIN_U, m, part, tot);
+        const BlkAt at_total = blk_of(G, t, mi);
+        chain_item(C, single ? u : n_single + u * CHAIN_U, single ? 1 : CHAIN_U, m, part,
+                   S.blk + at_total.first, at_total.stride);
     }
 }
 
@@ -1734,18 +1754,18 @@ __global__ void __launch_bounds__(256) k_terms_chain(DeviceTables T, DeviceGrid 
 // ascending block order (the sum of all finished blocks before block b) and
 // writes, per process count of the grid, the prefix of the block it ends in:
 // pre[m][P index], which the sweeps read side by side with the partial sums.  The sum is
-// sequential per m: one wave adds (lane m, two blocks per access to LDS), the others meanwhile write
-// out the tile before, put the next one into LDS and ask for the one after next two steps ahead; three
-// tiles of PFX_TILE blocks take turns, so that a step is one barrier.
+// sequential per m: one wave adds (lane m, two blocks per access to LDS, the next sixteen on their
+// way), the others meanwhile write out the tile before, put the next one into LDS and ask for the one
+// after next two steps ahead; three tiles of PFX_TILE blocks take turns, so that a step is one barrier.
 //
-// 3215 distinct sizes x 1024 blocks, 976 process counts: 19.9 us for 51 MB (25.7 when a workgroup of four
-// waves loaded, added and wrote in turn; 23.6 with four waves, 19.7 with sixteen, 22.9 with eight sizes to
-// a workgroup).  Without the additions it is 16.8, without the writes 17.8: what bounds it is the memory,
-// read 128 bytes at a time.
+// 3215 distinct sizes x 1024 blocks, 976 process counts: 18.7 us in the trace for 51 MB, 300 sizes 15.0
+// (20.0 and 17.3 with sixteen sizes to a workgroup, whose totals lay 128 bytes at a time among those of all
+// sizes, and each sixteen asked for when those before had been added; 19.9 and 16.2 with eight sizes, their
+// totals together, alone; 32 and 14.7 with four; tiles of 64 blocks 20.2 and 16.7; 25.7 for the first when a
+// workgroup of four waves loaded, added and wrote in turn).  What bounds it is the additions, 13 cycles each.
 constexpr int PFX_TILE = 128;
-constexpr int PFX_M = 16;
 constexpr int PFX_THREADS = 512;
-constexpr int PFX_LD = PFX_TILE + 2;     // row of a size: the sixteen lanes' pairs lie in different banks
+constexpr int PFX_LD = PFX_TILE + 2;     // row of a size: the lanes' pairs lie in different banks
 constexpr int PFX_MAX_P = 4096;          // process counts whose block index is kept in LDS
 
 __host__ __device__ inline bool pfx_in_lds(const DeviceGrid &G) { return G.n_P <= PFX_MAX_P && G.n_blk <= 65536; }
@@ -1761,7 +1781,8 @@ __global__ void __launch_bounds__(PFX_THREADS) k_chain_prefix(DeviceGrid G, Scra
     const int mi = mg * PFX_M + ml;
     const bool active = mi < G.n_mu;
     const size_t n_m = (size_t)G.n_mu;       // rows: the distinct sizes
-    const double *src = S.blk + (size_t)t * G.n_blk * n_m + (active ? mi : 0);
+    const BlkAt from = blk_of(G, t, active ? mi : mg * PFX_M);
+    const double *src = S.blk + from.first;
     const int full = G.n_blk - 1;                        // blocks that have a total
     const int n_tiles = (G.n_blk + PFX_TILE - 1) / PFX_TILE;
     const bool p_in_lds = pfx_in_lds(G);
@@ -1771,7 +1792,7 @@ __global__ void __launch_bounds__(PFX_THREADS) k_chain_prefix(DeviceGrid G, Scra
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             const int row = br + ROWS * u, b = k * PFX_TILE + row;
-            r[u] = (active && row < PFX_TILE && b < full) ? src[(size_t)b * n_m] : 0.0;
+            r[u] = (active && row < PFX_TILE && b < full) ? src[b * from.stride] : 0.0;
         }
     };
     auto put = [&](int k, const double (&r)[N]) {
@@ -1808,20 +1829,31 @@ __global__ void __launch_bounds__(PFX_THREADS) k_chain_prefix(DeviceGrid G, Scra
             if (k < n_tiles && tid < PFX_M) {
                 f64x2 *row = reinterpret_cast<f64x2 *>(&tile[k % 3][tid * PFX_LD]);
                 const int left = G.n_blk - k * PFX_TILE, nb = left < PFX_TILE ? left : PFX_TILE;
-                for (int bb = 0; bb < nb; bb += 16) {    // (blocks past the last hold zeros)
-                    f64x2 tot[8];
+                // sixteen at a time, the next sixteen on their way (blocks past the last hold zeros)
+                f64x2 tot[2][8];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        tot[u] = row[bb / 2 + u];
+                for (int u = 0; u < 8; ++u)
+                    tot[0][u] = row[u];
+#pragma unroll
+                for (int h = 0; h < PFX_TILE / 16; ++h) {
+                    if (16 * h >= nb)
+                        break;
+                    if (h + 1 < PFX_TILE / 16) {
+#pragma unroll
+                        for (int u = 0; u < 8; ++u)
+                            tot[(h + 1) & 1][u] = row[8 * (h + 1) + u];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
                         f64x2 before;
                         before.x = done;
-                        done = done + tot[u].x;
+                        done = done + tot[h & 1][u].x;
                         before.y = done;
-                        done = done + tot[u].y;
-                        row[bb / 2 + u] = before;
+                        done = done + tot[h & 1][u].y;
+                        row[8 * h + u] = before;
                     }
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
         } else {
