@@ -51,10 +51,10 @@ UNSEG_FLOPS = {0: 3, 1: 3, 3: 3, 4: 3, 6: 4, 7: 4, 8: 4, 10: 3, 11: 4, 12: 3}
 # (SQ_INSTS_VALU, in wave instructions).  A kernel change makes them stale until the profiles
 # are taken again; the line names its source.
 OFFLINE_COUNTERS = {
-    2: {"kernel": "k_row", "hbm_bytes": 0.336e6 + 34.329e6, "valu_insts": 4.864e6},
+    2: {"kernel": "k_row", "hbm_bytes": 0.326e6 + 34.281e6, "valu_insts": 3.856e6},
     3: {"kernel": "k_sweep_s", "hbm_bytes": 3.819e6 + 2.494e6, "valu_insts": 11.67e6},
     4: {"kernel": "k_batch_t", "hbm_bytes": 87.187e6 + 1966.527e6, "valu_insts": 175.7e6},
-    5: {"kernel": "k_chain_blocks", "hbm_bytes": 1.348e6 + 73.374e6, "valu_insts": 26.19e6},
+    5: {"kernel": "k_chain_blocks", "hbm_bytes": 1.270e6 + 83.121e6, "valu_insts": 23.98e6},
 }
 
 
@@ -63,7 +63,8 @@ def algorithmic_work(wl):
     per segmented value for each of the three segmented rows, 6 flop per Scatter-chain term for
     every grid m, repeats included) and the ones the kernels have to execute after the exact
     shortcuts ("executed": rows 2 and 9 of Table 1 through min_s A, one min per (m, s); the
-    chain sums once per distinct m)."""
+    chain sums once per distinct m; row 5 for every candidate, an upper limit where the kernels
+    leave out those that cannot win it for any process count of a wave)."""
     c = wl.counts()
     mask, nt, n = wl.strategy_mask, wl.n_tables, wl.sizes.shape[1]
     n_m, n_P, n_s = len(wl.m), len(wl.P), len(wl.s)
