@@ -2972,8 +2972,10 @@ static size_t sweep_s_lds(int n_s, bool with_static)
 // 31.4 -> 28.3.  Bound by vector instruction issue (25.8 million, 29.8 before), a third of it the
 // cells.  With few process counts a tile has few items, often all of them of the searched kind: eight
 // lanes share each of those where the items would not fill the workgroup's waves otherwise (6 process
-// counts up to 100: 32 us, 35 with a lane per item; with five blocks and 140 items a lane per item is
-// the faster: 27.7, 28.8 to 30.3 shared).
+// counts up to 100: 32 us, 35 with a lane per item; with five blocks and 150 items a lane per item is
+// the faster on 30 samples, 28.6 and 30.8 shared, and in a big job; on 49 samples and eight blocks, 176
+// items, the first blocks' walks take many turns: 97 tables x 66 sizes 17.5 shared, 19.1 with a lane per item,
+// 300 tables 24.7 and 26.0; on 100 samples and five blocks 24.8 and 25.0).
 // Tried: the cells of the Broadcast plane handed out with the items, for waves that have nothing left
 // of these (the same time: there is no idle time to fill, and a lane has to find its cell by a
 // division); the searched terms of large jobs spread over all threads through LDS (94 us).
@@ -2985,6 +2987,7 @@ constexpr size_t TILE_STATIC_LDS = 256;  // room for the counters
 constexpr long TILE_MIN_ROWS = 16;       // (table, m) rows per compute unit at least (more than TILE_FEW_N samples: twice)
 constexpr int TILE_FEW_N = 512;
 constexpr int TILE_SHARED = 128;     // up to so many items: eight lanes to each of those that enter several intervals
+constexpr int TILE_SHARED_N = 40;    // from so many samples on, of up to eight blocks: up to twice as many items
 constexpr int TILE_REACH = 16;       // intervals entered by some lane's block: above, the wave searches (as WALK_REACH)
 
 // Where the arrays of a workgroup start in LDS, in 8-byte slots.  The lists of the chain items lie
@@ -3248,7 +3251,8 @@ __global__ void __launch_bounds__(TILE_THREADS, 6) k_tile(DeviceTables T, Device
     }
     if (chain) {
         // 64 items at a time, the slowest first
-        const unsigned w2 = n2 <= 64u && n_items <= TILE_SHARED ? (n2 + 7) / 8 : 0u, rest = w2 != 0u ? n0 + n1 : (unsigned)n_items;
+        const bool share = n2 <= 64u && (n_items <= TILE_SHARED || (n_items <= 2 * TILE_SHARED && n_blk <= 8 && C.n >= TILE_SHARED_N));
+        const unsigned w2 = share ? (n2 + 7) / 8 : 0u, rest = w2 != 0u ? n0 + n1 : (unsigned)n_items;
         for (;;) {
             unsigned k = 0;
             if (lane == 0)

@@ -804,6 +804,8 @@ def test_random_tiles(seed):
     (9, 31, 600, 24, ALL_STRATEGIES_MASK), (57, 33, 1026, 37, ALL_STRATEGIES_MASK), (120, 200, 2048, 250, ALL_STRATEGIES_MASK),
     (300, 32, 65, 9, ALL_STRATEGIES_MASK),     # two blocks, the second of one term: 64 items, all of them searched
     (300, 32, 129, 9, ALL_STRATEGIES_MASK),    # three blocks: 96, a lane each
+    (39, 32, 400, 9, ALL_STRATEGIES_MASK), (40, 32, 400, 9, ALL_STRATEGIES_MASK),       # seven blocks, 224: by the samples
+    (45, 32, 512, 30, ALL_STRATEGIES_MASK), (45, 32, 514, 30, ALL_STRATEGIES_MASK),     # eight and nine
     (300, 31, 64, 40, 0x1C00),                 # one block, most of its points wanted
     (300, 33, 200, 300, ALL_STRATEGIES_MASK),  # tiles of 17 and 16; four blocks, every point wanted
     (512, 40, 256, 255, ALL_STRATEGIES_MASK),  # three workgroups' worth of LDS: tiles of fewer sizes
