@@ -2961,14 +2961,14 @@ static size_t sweep_s_lds(int n_s, bool with_static)
 // term), one, and among which eight of its terms (lanes that enter together cost a walk one turn
 // more over these eight, see walk_terms, and none elsewhere), or more; and the waves take 64 of
 // that order at a time, from its end, whatever the kind: a list per kind left lanes idle in the
-// last wave of each.  Waves whose items enter more than TILE_REACH intervals search for eight terms
-// side by side (gaps_ascending).
+// last wave of each.  Waves whose items enter more intervals than TILE_REACH says search for eight
+// terms side by side (gaps_ascending).
 //
 // 333 tables of 57 samples x 203 sizes x 37 process counts up to 1500, 19 candidates, 80 MB of
 // cells: 63 us a call (68 with the change of interval as six selects per term of the items that
 // enter one, a list per kind and the mask of rows read at run time; a lane per message size that
 // walks its whole row alone took 175; 10 000 rows x 1000 process counts 2500 us, now the row path's
-// 82); 1000 tables 177 -> 163; 300 tables of 30 samples x 150 sizes x 20 process counts up to 300
+// 82); 1000 tables 178 -> 168; 300 tables of 30 samples x 150 sizes x 20 process counts up to 300
 // 31.4 -> 28.3.  Bound by vector instruction issue (25.8 million, 29.8 before), a third of it the
 // cells.  With few process counts a tile has few items, often all of them of the searched kind: eight
 // lanes share each of those where the items would not fill the workgroup's waves otherwise (6 process
@@ -2987,8 +2987,12 @@ constexpr size_t TILE_STATIC_LDS = 256;  // room for the counters
 constexpr long TILE_MIN_ROWS = 16;       // (table, m) rows per compute unit at least (more than TILE_FEW_N samples: twice)
 constexpr int TILE_FEW_N = 512;
 constexpr int TILE_SHARED = 128;     // up to so many items: eight lanes to each of those that enter several intervals
-constexpr int TILE_SHARED_N = 40;    // from so many samples on, of up to eight blocks: up to twice as many items
-constexpr int TILE_REACH = 16;       // intervals entered by some lane's block: above, the wave searches (as WALK_REACH)
+constexpr int TILE_DENSE_N = 40;     // from so many samples on, of up to eight blocks: up to twice as many items
+// Intervals entered by some lane's block above which a wave searches (as WALK_REACH): the second from TILE_DENSE_N
+// samples on, where the blocks of the last kind enter many (95 samples, 32 tables x 137 sizes 21.9 us with 16, 20.2 so,
+// 300 tables 31.9 and 30.5; 57 samples, 333 tables no difference), the first else (25 samples, 60 tables x 95 sizes 17.2,
+// 18.1 with 4).
+constexpr int TILE_REACH = 16, TILE_REACH_DENSE = 4;
 
 // Where the arrays of a workgroup start in LDS, in 8-byte slots.  The lists of the chain items lie
 // where A and B of every (m, s) go afterwards.
@@ -3041,7 +3045,7 @@ __device__ __forceinline__ void tile_sum(const ChainCtx &C, unsigned item, bool 
     double run;
     if (dense) {
         const int reach = block_reach(C, z0, md, i);
-        if (reach > TILE_REACH) {
+        if (reach > (C.n >= TILE_DENSE_N ? TILE_REACH_DENSE : TILE_REACH)) {
             run = block_search(C, i, reach, md, z0, wanted, any, out);
             if (real)
                 tot[b * M + ml] = run;
@@ -3251,7 +3255,7 @@ __global__ void __launch_bounds__(TILE_THREADS, 6) k_tile(DeviceTables T, Device
     }
     if (chain) {
         // 64 items at a time, the slowest first
-        const bool share = n2 <= 64u && (n_items <= TILE_SHARED || (n_items <= 2 * TILE_SHARED && n_blk <= 8 && C.n >= TILE_SHARED_N));
+        const bool share = n2 <= 64u && (n_items <= TILE_SHARED || (n_items <= 2 * TILE_SHARED && n_blk <= 8 && C.n >= TILE_DENSE_N));
         const unsigned w2 = share ? (n2 + 7) / 8 : 0u, rest = w2 != 0u ? n0 + n1 : (unsigned)n_items;
         for (;;) {
             unsigned k = 0;
