@@ -3209,8 +3209,9 @@ __global__ void __launch_bounds__(TILE_THREADS, 6) k_tile(DeviceTables T, Device
                 unsigned kind = 0;
                 if (last >= x1) {
                     // terms before the next interval, near enough
-                    const int before = (int)((float)(x1 - z[c]) * __builtin_amdgcn_rcpf((float)md[c]));
-                    kind = last >= C.X[i[c] + 2] ? TILE_KINDS - 1 : 1u + (unsigned)(before < 0 ? 0 : before >= SUM_BLOCK ? SUM_BLOCK - 1 : before) / 8u;
+                    int before = (int)((float)(x1 - z[c]) * __builtin_amdgcn_rcpf((float)md[c]));
+                    before = before < 0 ? 0 : before >= SUM_BLOCK ? SUM_BLOCK - 1 : before;
+                    kind = last >= C.X[i[c] + 2] ? TILE_KINDS - 1 : 1u + (unsigned)before / 8u;
                 }
                 item[h + c] = tile_item(mm[c], bb[c], i[c]);
                 place[h + c] = kind << 16 | atomicAdd(&count[kind], 1u);
@@ -3255,7 +3256,8 @@ __global__ void __launch_bounds__(TILE_THREADS, 6) k_tile(DeviceTables T, Device
     }
     if (chain) {
         // 64 items at a time, the slowest first
-        const bool share = n2 <= 64u && (n_items <= TILE_SHARED || (n_items <= 2 * TILE_SHARED && n_blk <= 8 && C.n >= TILE_DENSE_N));
+        const bool short_dense = n_blk <= 8 && C.n >= TILE_DENSE_N;
+        const bool share = n2 <= 64u && n_items <= (short_dense ? 2 * TILE_SHARED : TILE_SHARED);
         const unsigned w2 = share ? (n2 + 7) / 8 : 0u, rest = w2 != 0u ? n0 + n1 : (unsigned)n_items;
         for (;;) {
             unsigned k = 0;
@@ -3269,7 +3271,8 @@ __global__ void __launch_bounds__(TILE_THREADS, 6) k_tile(DeviceTables T, Device
                 tile_search_shared(C, list[n0 + n1 + (e < n2 ? e : n2 - 1)], e < n2, sM, M, sMask, sOff, n_P, part, tot);
             } else {
                 const unsigned e = (k - w2) * 64, at = e + lane;
-                tile_sum(C, list[at < rest ? rest - 1 - at : 0u], at < rest, rest - e > n0 + n1, sM, M, sMask, sOff, n_P, part, tot);
+                tile_sum(C, list[at < rest ? rest - 1 - at : 0u], at < rest, rest - e > n0 + n1, sM, M, sMask, sOff, n_P,
+                         part, tot);
             }
         }
         __syncthreads();
@@ -5504,9 +5507,9 @@ hipError_t launch_tune_stage(const TunePlan &p, int stage, const DeviceTables &T
                                    p.crow_lds, st, T, G, S);
         } else if (p.chain) {
             if (p.together)
-                hipLaunchKernelGGL(p.n_single < 0 ? k_terms_chain<true> : k_terms_chain<false>, dim3((unsigned)(p.n_chain_wg + p.terms_wg)), dim3(256),
-                                   p.both_lds, st, T, G, S, p.n_chain_wg, p.chain_wg, p.n_single,
-                                   p.n_chunks, p.n_mchunks, p.terms_mode);
+                hipLaunchKernelGGL(p.n_single < 0 ? k_terms_chain<true> : k_terms_chain<false>,
+                                   dim3((unsigned)(p.n_chain_wg + p.terms_wg)), dim3(256), p.both_lds, st, T, G, S,
+                                   p.n_chain_wg, p.chain_wg, p.n_single, p.n_chunks, p.n_mchunks, p.terms_mode);
             else
                 hipLaunchKernelGGL(k_chain_blocks, dim3((unsigned)p.n_chain_wg), dim3(p.chain_threads), p.chain_lds, st,
                                    T, G, S, p.chain_wg, p.n_single, p.terms_mode);
