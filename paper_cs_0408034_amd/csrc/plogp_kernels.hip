@@ -682,8 +682,10 @@ __device__ __forceinline__ void terms_past(const double (&d)[8], double end, f64
 #undef PLOGP_TERM
                  "s_mov_b64 exec, %[lanes]\n\t"
                  "s_nop 4"
-                 : [lanes] "=&s"(lanes), [e] "=&v"(e), [g0] "+v"(g[0]), [g1] "+v"(g[1]), [g2] "+v"(g[2]),
-                   [g3] "+v"(g[3]), [g4] "+v"(g[4]), [g5] "+v"(g[5]), [g6] "+v"(g[6]), [g7] "+v"(g[7])
+                 // (&: a g is written before the last input is read, so that an input of the same value must not
+                 // share its registers)
+                 : [lanes] "=&s"(lanes), [e] "=&v"(e), [g0] "+&v"(g[0]), [g1] "+&v"(g[1]), [g2] "+&v"(g[2]),
+                   [g3] "+&v"(g[3]), [g4] "+&v"(g[4]), [g5] "+&v"(g[5]), [g6] "+&v"(g[6]), [g7] "+&v"(g[7])
                  : [d0] "v"(d[0]), [d1] "v"(d[1]), [d2] "v"(d[2]), [d3] "v"(d[3]), [d4] "v"(d[4]), [d5] "v"(d[5]),
                    [d6] "v"(d[6]), [d7] "v"(d[7]), [end] "v"(end), [y] "v"(ys.x), [s] "v"(ys.y)
                  : "vcc");
