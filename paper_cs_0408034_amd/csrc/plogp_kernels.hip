@@ -2336,6 +2336,9 @@ __global__ void __launch_bounds__(256) k_sweep_p(DeviceTables T, DeviceGrid G, S
 #pragma unroll
     for (int h = 0; h < PPL; ++h)
         f_part[h] = f_s12[h] = f_done[h] = 0.0;
+#pragma unroll
+    for (int k = 0; k < NSV; ++k)
+        fB[k] = INFINITY;                // of a grid without candidates, which fetches none
     // row of the chain sums (kept per distinct size) of the size fetched next: read one size
     // earlier still, so that the fetch does not wait for it
     int um_next = chain && has_work ? G.m_map[w] : 0;

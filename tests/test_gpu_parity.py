@@ -277,6 +277,22 @@ def test_no_candidates_with_many_sizes_on_the_sweep_over_process_counts():
         assert assert_tables_equal(gpu_tune(wl), want, "no candidates, mask %x" % mask)
 
 
+@pytest.mark.parametrize("n_P,p_hi", [(33, 34), (63, 100), (700, 701), (150, 290)])
+def test_no_candidates_where_row_5_goes_by_the_few_that_can_win(n_P, p_hi):
+    # the same with process counts that lie close or, in great number, two to a lane
+    base = make_workload(2)
+    rng = np.random.default_rng(n_P)
+    m = (rng.integers(1, 1 << 20, size=9000).astype(np.uint64)) * np.uint64(8)
+    P = np.union1d(rng.choice(np.arange(2, p_hi + 1), size=n_P - 1, replace=False), [p_hi]).astype(np.uint32)
+    x = np.cumsum(rng.integers(1, 3000, size=600)).astype(np.float64)[None]
+    gaps = np.abs(25.0 + 0.07 * x * (1.0 + 0.3 * rng.standard_normal(x.shape)))
+    for sizes, g in ((base.sizes, base.gaps), (x, gaps)):
+        for mask in (ALL_STRATEGIES_MASK, 0x1FFE, 0x3FF):
+            wl = Workload("no candidates", sizes, g, base.L, m, P, np.array([], dtype=np.uint64), NO_CAP, mask)
+            want, _ = oracle.tune_workload(wl)
+            assert assert_tables_equal(gpu_tune(wl), want, "no candidates, mask %x" % mask)
+
+
 def test_cap_below_m_and_scatter_only_and_bcast_only():
     base = make_workload(2, m_slice=slice(0, 1024, 97), P_subset=[2, 6, 33, 512])
     for mask, cap in ((0x1C00, NO_CAP), (0x3FF, 4096), (ALL_STRATEGIES_MASK, 64)):
