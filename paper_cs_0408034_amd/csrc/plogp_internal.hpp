@@ -151,7 +151,7 @@ struct TunePlan {
     int row_two;
     size_t row_lds;
     // tile path (a table and tile_m message sizes per workgroup)
-    int tile_m, n_tiles;
+    int tile_m, n_tiles, tile_shared;
     size_t tile_lds;
     // staged path
     int lanes_s, lanes_p, pairs, terms_mode, n_chunks, n_mchunks, terms_wg;

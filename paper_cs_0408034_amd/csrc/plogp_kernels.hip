@@ -2975,12 +2975,13 @@ static size_t sweep_s_lds(int n_s, bool with_static)
 // walks its whole row alone took 175; 10 000 rows x 1000 process counts 2500 us, now the row path's
 // 82); 1000 tables 178 -> 168; 300 tables of 30 samples x 150 sizes x 20 process counts up to 300
 // 31.4 -> 28.3.  Bound by vector instruction issue (25.8 million, 29.8 before), a third of it the
-// cells.  With few process counts a tile has few items, often all of them of the searched kind: eight
-// lanes share each of those where the items would not fill the workgroup's waves otherwise (6 process
-// counts up to 100: 32 us, 35 with a lane per item; with five blocks and 150 items a lane per item is
-// the faster on 30 samples, 28.6 and 30.8 shared, and in a big job; on 49 samples and eight blocks, 176
-// items, the first blocks' walks take many turns: 97 tables x 66 sizes 17.5 shared, 19.1 with a lane per item,
-// 300 tables 24.7 and 26.0; on 100 samples and five blocks 24.8 and 25.0).
+// cells.  With few process counts a tile has few items, often less than a wave of the slowest kind, which the
+// other waves wait for: eight lanes share each of these then, where the chip waits too (see tile_shared), and
+// the items that enter one interval, a wave of walks of many turns, go first, so that the shared ones fill up
+// the time of the other waves (227 tables of 20 samples x 22 sizes x 7 process counts up to 667, 242 items of
+// a tile, 25 of them shared: 12.6 us, 13.9 with the shared ones first, 15.1 with a lane per item, 13.4
+// shared before lists of one interval's items as selects; on 50 samples, 40 shared of 176 and 8 up to 455, 14.6,
+// 16.0 and 16.2).
 // Tried: the cells of the Broadcast plane handed out with the items, for waves that have nothing left
 // of these (the same time: there is no idle time to fill, and a lane has to find its cell by a
 // division); the searched terms of large jobs spread over all threads through LDS (94 us).
@@ -2991,8 +2992,8 @@ constexpr int TILE_MAX_BLK = 32;         // blocks of the chain sum at most
 constexpr size_t TILE_STATIC_LDS = 256;  // room for the counters
 constexpr long TILE_MIN_ROWS = 16;       // (table, m) rows per compute unit at least (more than TILE_FEW_N samples: twice)
 constexpr int TILE_FEW_N = 512;
-constexpr int TILE_SHARED = 128;     // up to so many items: eight lanes to each of those that enter several intervals
-constexpr int TILE_DENSE_N = 40;     // from so many samples on, of up to eight blocks: up to twice as many items
+constexpr int TILE_WG_PER_CU = 6;        // that their registers leave room for
+constexpr int TILE_DENSE_N = 40;
 // Intervals entered by some lane's block above which a wave searches (as WALK_REACH): the second from TILE_DENSE_N
 // samples on, where the blocks of the last kind enter many (95 samples, 32 tables x 137 sizes 21.9 us with 16, 20.2 so,
 // 300 tables 31.9 and 30.5; 57 samples, 333 tables no difference), the first else (25 samples, 60 tables x 95 sizes 17.2,
@@ -3037,7 +3038,7 @@ __device__ __forceinline__ unsigned tile_item(int ml, int b, int i)
     return (unsigned)ml | (unsigned)b << 5 | (unsigned)i << 10;
 }
 
-// One item per lane, of one kind: no interval entered, one, more.  `real` lanes store.
+// One item per lane; dense: some lane's enters several intervals.  `real` lanes store.
 __device__ __forceinline__ void tile_sum(const ChainCtx &C, unsigned item, bool real, bool dense, const double *m_of, int M,
                                          const u64 *blk_mask, const int *blk_off, int n_P, double *part, double *tot)
 {
@@ -3112,8 +3113,8 @@ __device__ __forceinline__ void tile_search_shared(const ChainCtx &C, unsigned i
 }
 
 template <bool ALL>
-__global__ void __launch_bounds__(TILE_THREADS, 6) k_tile(DeviceTables T, DeviceGrid G, plogp_cell_dev *out, int n_tiles,
-                                                          int M)
+__global__ void __launch_bounds__(TILE_THREADS, TILE_WG_PER_CU) k_tile(DeviceTables T, DeviceGrid G, plogp_cell_dev *out, int n_tiles,
+                                                          int M, int shared)
 {
     // (a name of its own: under a name that another kernel declares without it the alignment is lost,
     // and 16-byte reads of misaligned LDS take twice the kernel's time)
@@ -3228,14 +3229,14 @@ __global__ void __launch_bounds__(TILE_THREADS, 6) k_tile(DeviceTables T, Device
     if (chain) {
         // in the order of their kinds
         unsigned at = 0;
-        unsigned first[TILE_KINDS];
+        unsigned first[TILE_KINDS];                                           // in scalar registers: nothing spills
 #pragma unroll
         for (int k = 0; k < TILE_KINDS; ++k) {
             first[k] = at;
-            at += count[k];
+            at += (unsigned)__builtin_amdgcn_readfirstlane((int)count[k]);
         }
         n0 = first[1];
-        n2 = count[TILE_KINDS - 1];
+        n2 = at - first[TILE_KINDS - 1];
         n1 = at - n0 - n2;
 #pragma unroll
         for (int h = 0; h < PER; ++h) {
@@ -3261,9 +3262,9 @@ __global__ void __launch_bounds__(TILE_THREADS, 6) k_tile(DeviceTables T, Device
     }
     if (chain) {
         // 64 items at a time, the slowest first
-        const bool short_dense = n_blk <= 8 && C.n >= TILE_DENSE_N;
-        const bool share = n2 <= 64u && n_items <= (short_dense ? 2 * TILE_SHARED : TILE_SHARED);
-        const unsigned w2 = share ? (n2 + 7) / 8 : 0u, rest = w2 != 0u ? n0 + n1 : (unsigned)n_items;
+        const bool share = n2 <= 64u && n_items <= shared;
+        const unsigned w1 = share ? (n1 + 63) / 64 : 0u, w2 = share ? (n2 + 7) / 8 : 0u;
+        const unsigned rest = w2 != 0u ? n0 + n1 : (unsigned)n_items;
         for (;;) {
             unsigned k = 0;
             if (lane == 0)
@@ -3271,11 +3272,11 @@ __global__ void __launch_bounds__(TILE_THREADS, 6) k_tile(DeviceTables T, Device
             k = __builtin_amdgcn_readfirstlane(k);
             if (k >= w2 + (rest + 63) / 64)
                 break;
-            if (k < w2) {
-                const unsigned e = k * 8 + (lane >> 3);
+            if (k - w1 < w2) {                                                // (k >= w1)
+                const unsigned e = (k - w1) * 8 + (lane >> 3);
                 tile_search_shared(C, list[n0 + n1 + (e < n2 ? e : n2 - 1)], e < n2, sM, M, sMask, sOff, n_P, part, tot);
             } else {
-                const unsigned e = (k - w2) * 64, at = e + lane;
+                const unsigned e = (k < w1 ? k : k - w2) * 64, at = e + lane;
                 tile_sum(C, list[at < rest ? rest - 1 - at : 0u], at < rest, rest - e > n0 + n1, sM, M, sMask, sOff, n_P,
                          part, tot);
             }
@@ -5166,6 +5167,30 @@ Scratch bind_scratch(void *base, const ScratchLayout &lay)
     return S;
 }
 
+// Up to how many chain items of a tile eight lanes share each of those that enter several intervals (if these
+// are no more than a wave).  It saves a workgroup the wait for its slowest wave and costs instructions, so it
+// depends on whether the workgroups are on the chip at once, or, where a table has several tiles, some of which
+// have little to wait for, two thirds of what is.  If so, up to 312: 7 process counts up to 667, 30 samples, 1136
+// tables x 22 sizes, 242 items, 20.7 us shared, 22.9 with a lane per item; 12 samples, 250 x 56 sizes, 308, 15.0
+// and 16.2, 70 x 200 sizes, 319, 15.9 and 15.5; and with few process counts, sums at which cost the shared ones
+// most, and one or two tiles as long as a lane per item takes the four waves no more than two turns (12 up to
+// 1480, 30 samples, 350 x 20 sizes, 480 items 17.3 and 19.0, 12 samples, 233 x 30, 720 18.1 and 16.9; 30 up to
+// 1174, 20 samples, 1136 x 22, 418 28.2 and 27.2).  If not, few: 12 samples, 300 x 200 sizes x 8 up to 455, 232
+// items, 31.5 and 30.0; 30 samples, 150 sizes x 20 up to 300, 300 tables 28.4 and 27.5, 166 19.0 and 19.0, 93
+// 14.8 and 15.8; more of up to eight blocks on tables from TILE_DENSE_N samples on, which enter more intervals (49
+// samples, 300 tables x 66 sizes, 176 items 24.7 and 26.0).
+static int tile_shared(const DeviceTables &T, const DeviceGrid &G, const TunePlan &p)
+{
+    const long by_lds = (long)(device_info().lds_per_cu / (p.tile_lds + TILE_STATIC_LDS));
+    const long at_once = device_info().n_cu * (by_lds < TILE_WG_PER_CU ? by_lds : TILE_WG_PER_CU);
+    const long wg = (long)T.n_tables * p.n_tiles, most = at_once * 2 / 3;
+    if (wg <= most && p.n_tiles <= 2 && G.n_P <= 16)
+        return 2 * TILE_THREADS;
+    if (wg <= (p.n_tiles == 1 ? at_once : most))
+        return 312;
+    return G.n_blk <= 8 && T.n >= TILE_DENSE_N ? 256 : 128;
+}
+
 // The tile path's part of a plan: one launch, and no scratch beside the spare.
 static bool plan_tiles(const DeviceTables &T, const DeviceGrid &G, int tile_m, TunePlan &p)
 {
@@ -5173,6 +5198,7 @@ static bool plan_tiles(const DeviceTables &T, const DeviceGrid &G, int tile_m, T
     p.tile_m = tile_m;
     p.n_tiles = (G.n_m + tile_m - 1) / tile_m;
     p.tile_lds = (size_t)TileLds(T.n, G.n_s, G.n_P, G.n_blk, G.cl_max, tile_m).slots * sizeof(double);
+    p.tile_shared = tile_shared(T, G, p);
     p.lay.total = LayoutBuilder().at;
     return (long)T.n_tables * p.n_tiles <= kMaxLaunch;
 }
@@ -5484,7 +5510,8 @@ hipError_t launch_tune_stage(const TunePlan &p, int stage, const DeviceTables &T
     if (p.path == TUNE_TILE) {
         if (stage == TUNE_STAGE_SWEEP)
             hipLaunchKernelGGL(G.mask == 0x1FFFu ? k_tile<true> : k_tile<false>, dim3((unsigned)T.n_tables * p.n_tiles),
-                               dim3(TILE_THREADS), p.tile_lds, st, T, G, d_out, p.n_tiles, p.tile_m);
+                               dim3(TILE_THREADS), p.tile_lds, st, T, G, d_out, p.n_tiles, p.tile_m,
+                               p.tile_shared);
         return hipGetLastError();
     }
     if (stage == TUNE_STAGE_MORE) {

@@ -820,7 +820,7 @@ def test_random_tiles(seed):
     (9, 31, 600, 24, ALL_STRATEGIES_MASK), (57, 33, 1026, 37, ALL_STRATEGIES_MASK), (120, 200, 2048, 250, ALL_STRATEGIES_MASK),
     (300, 32, 65, 9, ALL_STRATEGIES_MASK),     # two blocks, the second of one term: 64 items, all of them searched
     (300, 32, 129, 9, ALL_STRATEGIES_MASK),    # three blocks: 96, a lane each
-    (39, 32, 400, 9, ALL_STRATEGIES_MASK), (40, 32, 400, 9, ALL_STRATEGIES_MASK),       # seven blocks, 224: by the samples
+    (39, 32, 400, 9, ALL_STRATEGIES_MASK), (40, 32, 400, 9, ALL_STRATEGIES_MASK),       # seven blocks, 224
     (45, 32, 512, 30, ALL_STRATEGIES_MASK), (45, 32, 514, 30, ALL_STRATEGIES_MASK),     # eight and nine
     (300, 31, 64, 40, 0x1C00),                 # one block, most of its points wanted
     (300, 33, 200, 300, ALL_STRATEGIES_MASK),  # tiles of 17 and 16; four blocks, every point wanted
@@ -851,6 +851,27 @@ def test_tiles_at_the_edges_of_their_rules(n, n_m, p_hi, n_P, mask, dense):
     s = (8 * np.unique(rng.integers(1, 2000, size=17))).astype(np.uint64)
     wl = Workload("tiles", x, gaps, rng.uniform(0.0, 90.0, size=n_tables), m.astype(np.uint64), P.astype(np.uint32), s,
                   NO_CAP, mask)
+    want, _ = oracle.tune_workload(wl)
+    assert assert_tables_equal(gpu_tune(wl), want, "tiles n=%d m=%d P=%d" % (n, n_m, len(P))), "times not bit-identical"
+
+
+@pytest.mark.parametrize("n,n_m,p_hi,n_P,n_tables", [
+    (20, 22, 667, 7, 200), (60, 22, 667, 7, 200),             # 242 items, up to a wave of which enter several intervals
+    (30, 24, 800, 20, 180), (30, 26, 800, 20, 170),           # 312 and 338 of one tile
+    (30, 32, 1020, 16, 140), (30, 32, 1020, 17, 140), (30, 32, 1030, 16, 140),          # 512, more points, 544
+    (12, 64, 667, 8, 70), (12, 96, 667, 8, 50),               # 352 in two and in three tiles
+    (20, 28, 300, 9, 1500), (20, 28, 300, 9, 1560), (49, 28, 300, 9, 1560),             # workgroups that wait for others
+])
+def test_tiles_that_share_their_longest_items(n, n_m, p_hi, n_P, n_tables):
+    # samples and message sizes spread evenly over their logarithm: most blocks enter no interval, some one,
+    # the first ones several
+    rng = np.random.default_rng(n + n_m + p_hi + n_P + n_tables)
+    x = np.floor(np.geomspace(1.0, 2.0 ** 22, n) * rng.uniform(1.0, 1.2, size=(n_tables, 1))) + 20.0 * np.arange(n)
+    gaps = np.abs(20.0 + x * rng.uniform(0.02, 0.1, size=(n_tables, 1)) * (1.0 + 0.2 * rng.standard_normal(x.shape)))
+    m = np.maximum(8, 8 * np.floor(np.geomspace(8, 2.0 ** 23, n_m) / 8))
+    P = np.union1d(rng.choice(np.arange(2, p_hi), size=n_P - 1, replace=False), [p_hi])
+    wl = Workload("tiles", x, gaps, rng.uniform(0.0, 90.0, size=n_tables), m.astype(np.uint64), P.astype(np.uint32),
+                  np.array([8, 64, 512, 4096], dtype=np.uint64), NO_CAP, ALL_STRATEGIES_MASK)
     want, _ = oracle.tune_workload(wl)
     assert assert_tables_equal(gpu_tune(wl), want, "tiles n=%d m=%d P=%d" % (n, n_m, len(P))), "times not bit-identical"
 
