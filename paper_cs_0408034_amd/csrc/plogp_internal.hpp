@@ -148,7 +148,7 @@ struct TunePlan {
     int n_stage, prep_wg, n_tg, m_per_wave, batch_mchunks;
     size_t setup_lds, batch_lds;
     // whole-row path
-    int row_two;
+    int row_two, row_few;
     size_t row_lds;
     // tile path (a table and tile_m message sizes per workgroup)
     int tile_m, n_tiles, tile_shared;

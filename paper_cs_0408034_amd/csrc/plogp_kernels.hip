@@ -219,7 +219,7 @@ __device__ __forceinline__ double lane_value(double v, int lane)
 // 70 instructions, where a pass over 64 process counts, eight candidates at a time, took 35 for every eight: 1024
 // sizes x 1023 process counts, 34 candidates 16.0 -> 13.2 us, x 600, 8 candidates (2000 sizes) 17.0 -> 16.5; 13
 // candidates for 49 process counts, the least, 4.05 -> 4.14; 4096 sizes x 976, 43 candidates (k_sweep_p) the call
-// 126.5 -> 121.  Not used for up to 8, or 13, candidates: the same or slower everywhere.
+// 126.5 -> 121.  Which calls use it: row_few and, for k_sweep_p, the launch.
 __device__ __forceinline__ u64 row5_candidates(double C, double B, int nv, double q_lo, double q_hi)
 {
     const u64 there = nv >= 64 ? ~0ull : (1ull << nv) - 1ull;
@@ -250,6 +250,31 @@ __device__ __forceinline__ void row5_least(double C, double B, u64 which, const 
             const double v = __builtin_fma(q[h], Cv, Bv);
             at[h] = v < least[h] ? c : at[h];
             least[h] = min_f64(least[h], v);
+        }
+    }
+}
+
+// The minimum over the first nv, eight per round trip to LDS, and the eight among which it first appeared.  B comes
+// from there (the same address in every lane), C from the lane that holds it, which halves the traffic.
+template <int PPL>
+__device__ __forceinline__ void row5_all(double C, const double *sB, int nv, const double (&q)[PPL], double (&least)[PPL],
+                                         int (&at)[PPL])
+{
+    for (int s0 = 0; s0 < nv; s0 += 8) {
+        double Bv[8], Cv[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            Bv[u] = sB[s0 + u];
+            Cv[u] = lane_value(C, s0 + u);
+        }
+#pragma unroll
+        for (int h = 0; h < PPL; ++h) {
+            double cur = INFINITY;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                cur = min_f64(cur, __builtin_fma(q[h], Cv[u], Bv[u]));
+            at[h] = cur < least[h] ? s0 : at[h];
+            least[h] = min_f64(least[h], cur);
         }
     }
 }
@@ -3423,9 +3448,9 @@ static size_t row_lds_bytes(int n, int n_blk, int n_P)
 
 // PPL: process counts per lane in the Broadcast plane.  EXTRA: the planes of Gather and Barrier too,
 // the first from the sums that are in LDS, the second by the waves that wait for them (501 sizes x
-// 300 process counts, 37 candidates, all 18 rows: 11.1 us; terms and sums, sweep and planes in three
-// launches 20.8).
-template <bool ALL, int PPL, bool EXTRA>
+// 300 process counts, 37 candidates, all 18 rows: 10.6 us; terms and sums, sweep and planes in three
+// launches 20.8).  FEW: row 5 for the candidates alone that can win it (see row_few).
+template <bool ALL, int PPL, bool EXTRA, bool FEW>
 __global__ void __launch_bounds__(ROW_THREADS) k_row(DeviceTables T, DeviceGrid G, plogp_cell_dev *out)
 {
     extern __shared__ __align__(16) double row_lds[];
@@ -3567,12 +3592,12 @@ __global__ void __launch_bounds__(ROW_THREADS) k_row(DeviceTables T, DeviceGrid 
     }
 
     const double gm = sh_gm, g1 = sh_g1, amin = sh_amin;
-    const int nv = sh_nv;
+    const int nv = __builtin_amdgcn_readfirstlane(sh_nv);
     const size_t plane = (size_t)G.n_m * n_P;
     plogp_cell_dev *const orow = out + (size_t)t * G.n_ops * plane + (size_t)mi * n_P;
     // lane si keeps candidate si (lanes past the candidates: B is +inf)
     const double c_mine = sC[lane], b_mine = sB[lane];
-    // a lane takes PPL process counts, 64 apart: a candidate read from LDS serves them all
+    // a lane takes PPL process counts, 64 apart: a candidate read serves them all
     const unsigned n_groups = (unsigned)((n_P + 64 * PPL - 1) / (64 * PPL));
     if (mask & 0x3FFu) {
         for (;;) {
@@ -3598,17 +3623,28 @@ __global__ void __launch_bounds__(ROW_THREADS) k_row(DeviceTables T, DeviceGrid 
                 b5[h] = INFINITY;
                 i5[h] = 0;
             }
-            if (mask & 0x20u)
-                row5_least<PPL>(c_mine, b_mine,
-                                row5_candidates(c_mine, b_mine, nv, lane_value(q[0], 0), lane_value(q[PPL - 1], 63)),
-                                q, b5, i5);
+            if (mask & 0x20u) {
+                if (FEW)
+                    row5_least<PPL>(c_mine, b_mine,
+                                    row5_candidates(c_mine, b_mine, nv, lane_value(q[0], 0), lane_value(q[PPL - 1], 63)),
+                                    q, b5, i5);
+                else
+                    row5_all<PPL>(c_mine, sB, nv, q, b5, i5);
+            }
 #pragma unroll
             for (int h = 0; h < PPL; ++h) {
                 const double t2 = amin < INFINITY ? __builtin_fma(q[h], amin, L) : INFINITY;
                 const double t9 = amin < INFINITY ? __builtin_fma(fl[h], amin, clL[h]) : INFINITY;
                 Best bc = decide_bcast(mask, q[h], fl[h], cl[h], gm, L, g1, t2, 0u, b5[h], 0u, t9, 0u);
+                int at5 = i5[h];
+                if (!FEW && __ballot(active[h] && bc.id == 5u) != 0) {
+                    // the first candidate of the remembered eight that attains the minimum
+#pragma unroll
+                    for (int u = 7; u >= 0; --u)        // descending: the first match stays
+                        at5 = __builtin_fma(q[h], sC[i5[h] + u], sB[i5[h] + u]) == b5[h] ? i5[h] + u : at5;
+                }
                 if (bc.id == 5u)
-                    bc.s = sSv[i5[h]];
+                    bc.s = sSv[at5];
                 bool open = active[h] && (bc.id == 2u || bc.id == 9u);
                 if (__ballot(open) != 0) {
                     // a winning row 2 or 9: the first candidate whose value equals the minimum
@@ -5203,12 +5239,31 @@ static bool plan_tiles(const DeviceTables &T, const DeviceGrid &G, int tile_m, T
     return (long)T.n_tables * p.n_tiles <= kMaxLaunch;
 }
 
+// Whether a workgroup per row leaves out the candidates that cannot win row 5 (row5_candidates) or evaluates all.
+// The former is 70 instructions that wait for one another and a candidate at a time after them, the latter two
+// round trips for 16 candidates: it is the shorter wait where a call waits for nothing else, which is where no chain
+// sum is needed, beside which the others wait, up to 24 candidates for a few waves of process counts (64 sizes of
+// up to 8 MB, 30 samples, the Broadcast rows: 13 candidates x 64 up to 640 4.53 us, 4.84 with those left out that
+// cannot win; 4000 sizes x 200, 26 candidates 14.1 and 13.8) and up to 8 for any number (1000 x 1000, 5 candidates
+// 10.4 and 10.7); and beside chain sums two or three round trips for few process counts far apart, for which
+// many candidates can win (30 tables x 24 sizes x 10 up to 512, 18 candidates 7.1 and 7.3; 49 up to 50, 13: 4.05
+// and 4.12, left as it is; 100 up to 101, 17, 300 sizes 5.5 and 5.35).
+static bool row_few(const DeviceGrid &G)
+{
+    const bool chain = (G.need & (1u << 11)) != 0;
+    const int P_top = SUM_BLOCK * (G.n_blk - 1) + G.last_terms + 1;
+    if (!chain)
+        return G.n_s > 8 && (G.n_s > 24 || G.n_P > 256);
+    return !(G.n_s > 12 && G.n_s <= 24 && G.n_P <= 64 && P_top >= 4 * G.n_P);
+}
+
 // The row path's part, the same.
 static bool plan_rows(const DeviceTables &T, const DeviceGrid &G, TunePlan &p)
 {
     p.path = TUNE_ROW;
     // two process counts per lane when there are more groups of 64 than waves
     p.row_two = G.n_P > 64 * (ROW_THREADS / 64);
+    p.row_few = row_few(G);
     p.row_lds = row_lds_bytes(T.n, G.n_blk, G.n_P);
     p.lay.total = LayoutBuilder().at;
     return true;
@@ -5498,10 +5553,16 @@ hipError_t launch_tune_stage(const TunePlan &p, int stage, const DeviceTables &T
     if (p.path == TUNE_ROW) {
         if (stage == TUNE_STAGE_SWEEP) {
             const bool all = G.mask == 0x1FFFu, two = p.row_two != 0;
-            const auto kern = G.extra == 0 ? (all ? (two ? k_row<true, 2, false> : k_row<true, 1, false>)
-                                                  : (two ? k_row<false, 2, false> : k_row<false, 1, false>))
-                                           : (all ? (two ? k_row<true, 2, true> : k_row<true, 1, true>)
-                                                  : (two ? k_row<false, 2, true> : k_row<false, 1, true>));
+            const bool more = G.extra != 0;
+            // (all 13 rows and two process counts to a lane: always those that can win alone)
+            const auto kern = p.row_few || (all && two)
+                                  ? (all ? (two ? (more ? k_row<true, 2, true, true> : k_row<true, 2, false, true>)
+                                                : (more ? k_row<true, 1, true, true> : k_row<true, 1, false, true>))
+                                         : (two ? (more ? k_row<false, 2, true, true> : k_row<false, 2, false, true>)
+                                                : (more ? k_row<false, 1, true, true> : k_row<false, 1, false, true>)))
+                              : all ? (more ? k_row<true, 1, true, false> : k_row<true, 1, false, false>)
+                                    : (two ? (more ? k_row<false, 2, true, false> : k_row<false, 2, false, false>)
+                                           : (more ? k_row<false, 1, true, false> : k_row<false, 1, false, false>));
             hipLaunchKernelGGL(kern, dim3((unsigned)(T.n_tables * G.n_m)), dim3(ROW_THREADS), p.row_lds, st,
                                T, G, d_out);
         }

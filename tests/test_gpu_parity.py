@@ -1033,3 +1033,21 @@ def test_small_jobs_a_row_per_workgroup(n_m, n_P, p_hi, n_s, n, mask):
                   NO_CAP, mask)
     want, _ = oracle.tune_workload(wl)
     assert assert_tables_equal(gpu_tune(wl), want, "small rows, mask %x" % mask), "times not bit-identical"
+
+
+@pytest.mark.parametrize("n_s,n_P,p_hi", [(1, 1, 2), (8, 1000, 1001), (9, 256, 300), (9, 257, 300), (24, 256, 2000), (25, 256, 2000),
+                                          (12, 64, 640), (13, 64, 255), (13, 64, 256), (24, 64, 640), (25, 64, 640),
+                                          (13, 65, 640)])
+@pytest.mark.parametrize("mask", [ALL_STRATEGIES_MASK, 0x3FF, 0x20, 0x203FF, 0x3FFFF, 0x10024])
+def test_which_rows_evaluate_every_candidate(n_s, n_P, p_hi, mask):
+    # on both sides of the limits at which a workgroup per row evaluates all candidates of row 5, or leaves
+    # out those that cannot win; equal gaps at the smallest sizes, so that candidates tie
+    rng = np.random.default_rng(n_s * 1000 + n_P)
+    x = np.cumsum(rng.integers(1, 3000, size=40)).astype(np.float64)[None]
+    gaps = np.maximum(25.0 + 0.07 * x * (1.0 + 0.3 * rng.standard_normal(x.shape)), 900.0)
+    m = np.maximum(8, 8 * np.floor(np.exp(rng.uniform(np.log(8.0), np.log(5e6), size=45)) / 8)).astype(np.uint64)
+    P = np.union1d(rng.choice(np.arange(2, p_hi), size=n_P - 1, replace=False), [p_hi]).astype(np.uint32)
+    s = (8 * np.unique(np.floor(np.geomspace(1, 60000, 2 * n_s))))[:n_s].astype(np.uint64)
+    wl = Workload("row 5", x, gaps, np.array([3.0]), m, P, s, NO_CAP, mask)
+    want, _ = oracle.tune_workload(wl)
+    assert assert_tables_equal(gpu_tune(wl), want, "n_s=%d mask %x" % (len(s), mask)), "times not bit-identical"
