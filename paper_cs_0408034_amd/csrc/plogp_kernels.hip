@@ -3435,15 +3435,14 @@ __global__ void __launch_bounds__(TILE_THREADS, TILE_WG_PER_CU) k_tile(DeviceTab
 // such calls, 4.05 so, where an empty kernel takes 1.6; 200 x 100 5.16 and 5.05).
 constexpr int ROW_THREADS = 512;
 constexpr int ROW_MAX_BLK = 32;          // at most 2048 terms of the chain sum
-constexpr int ROW_NS = 64;               // candidates at most
-constexpr int ROW_SPAD = ROW_NS + 8;     // the candidate loops read up to 7 entries past the last
+constexpr int ROW_NS = 64;               // candidates at most (the loops over them read up to the next eight)
 constexpr int ROW_MAX_N = 512;           // samples at most (LDS per workgroup stays small)
 constexpr long ROW_MAX_ROWS = 32;        // (table, m) rows per compute unit: 256 to 511 process counts (fewer: half, or less)
 
 static size_t row_lds_bytes(int n, int n_blk, int n_P)
 {
-    return ((size_t)3 * n + 3 * ROW_SPAD + 36 + 36 + (size_t)n_blk * (SUM_BLOCK + 1) + 2 * ROW_MAX_BLK +
-            ROW_SPAD / 2 + (size_t)(n_P + 1) / 2) * sizeof(double);
+    return ((size_t)3 * n + 3 * ROW_NS + 36 + 36 + (size_t)n_blk * (SUM_BLOCK + 1) + 2 * ROW_MAX_BLK +
+            ROW_NS / 2 + (size_t)(n_P + 1) / 2) * sizeof(double);
 }
 
 // PPL: process counts per lane in the Broadcast plane.  EXTRA: the planes of Gather and Barrier too,
@@ -3465,12 +3464,12 @@ __global__ void __launch_bounds__(ROW_THREADS) k_row(DeviceTables T, DeviceGrid 
     const int t = (int)blockIdx.x / G.n_m, mi = G.n_m - 1 - (int)blockIdx.x % G.n_m;
     f64x2 *ys = reinterpret_cast<f64x2 *>(row_lds);                    // {gap, slope} of every sample
     double *x = row_lds + 2 * n;
-    double *sA = x + n, *sB = sA + ROW_SPAD, *sC = sB + ROW_SPAD;     // per candidate
-    double *sum2 = sC + ROW_SPAD, *g2 = sum2 + 36;                     // prefix of g(2^j m); its terms
+    double *sA = x + n, *sB = sA + ROW_NS, *sC = sB + ROW_NS;          // per candidate (past the last: +inf, +inf, 0)
+    double *sum2 = sC + ROW_NS, *g2 = sum2 + 36;                       // prefix of g(2^j m); its terms
     double *pre = g2 + 36;                     // [block][65]: the terms, then the sums before each
     double *tot = pre + (size_t)n_blk * (SUM_BLOCK + 1), *done = tot + ROW_MAX_BLK;
     uint32_t *sSv = reinterpret_cast<uint32_t *>(done + ROW_MAX_BLK);  // the candidates
-    uint32_t *sP = sSv + ROW_SPAD;                                     // the process counts
+    uint32_t *sP = sSv + ROW_NS;                                       // the process counts
     // everything that comes from device memory is asked for at once
     const u64 m = G.m[mi];
     const double L = T.L[t];
@@ -3517,12 +3516,6 @@ __global__ void __launch_bounds__(ROW_THREADS) k_row(DeviceTables T, DeviceGrid 
         sB[lane] = B;
         sC[lane] = C;
         sSv[lane] = (uint32_t)my_s;
-        if (lane < ROW_SPAD - ROW_NS) {        // past the end: never taken (B = +inf, C finite)
-            sA[ROW_NS + lane] = INFINITY;
-            sB[ROW_NS + lane] = INFINITY;
-            sC[ROW_NS + lane] = 0.0;
-            sSv[ROW_NS + lane] = 0u;
-        }
         const double amin = wave_min(A);
         const int nv = __builtin_popcountll(__ballot(valid));       // the candidates ascend
         if (lane == 0) {
@@ -5095,17 +5088,16 @@ static bool use_row_path(const DeviceTables &T, const DeviceGrid &G)
 // row.  Every line lies where whole calls on 16, 64 and 300 samples, 5 to 50 candidates, 5 to 1500 process
 // counts and 250 to 50 000 rows cross, to 4 % on the staged side (us per row and staged in brackets; 64
 // samples, 15 candidates):
-//   all 18 rows            5 process counts up to 6     4100 rows  23  (25)    8100  42  (34)
-//                         36 up to 1500                 6000       44  (48)    8100  57  (56)
-//                        100 up to 1500                 8100       58  (63)  16 000 109 (104)
-//                        300 up to 1500               16 000      125 (161)
-//   Gather                12 up to 200                  2000       15  (17)    4100  27  (22)
-//                        255 up to 1500                 8100       67  (70)  16 000 128 (115)
-//   Barrier                5 up to 6                    3000       12  (12)    6000  21  (13)  16 000 51 (16)
-//                        300 up to 1500                 8100       32  (39)  16 000  58  (62)
-//   Tables 1, 2, Barrier  36 up to 1500                 2000       17  (19)    6000  44  (34)
-//   Broadcast, Barrier    36 up to 60                   2000       14  (15)    4100  27  (20)
-//                        512 up to 513                  8100       58  (59)  16 000 109  (90)
+//   all 18 rows            5 process counts up to 6     4100 rows  21  (25)    8100  38  (33)
+//                         36 up to 1500                 6000       43  (46)    8100  56  (54)
+//                        100 up to 1500                 8100       56  (62)  16 000 105  (97)
+//                        300 up to 1500               16 000      118 (155)
+//   Gather                12 up to 200                  2000       14  (17)    4100  26  (22)
+//                        255 up to 1500                 8100       65  (69)  16 000 124 (109)
+//   Barrier                5 up to 6                    3000       11  (13)    6000  20  (13)  16 000 47 (16)
+//                        300 up to 1500                 8100       30  (39)  16 000  54  (62)
+//   Tables 1, 2, Barrier  36 up to 1500                 2000       16  (19)    6000  42  (34)
+//   Broadcast, Barrier    36 up to 60                   2000       11  (14)    4100  21  (16)
 static long row_path_most(const DeviceTables &T, const DeviceGrid &G)
 {
     constexpr long kAny = 1L << 40;
@@ -5315,17 +5307,16 @@ static bool plan_fastest(const DeviceTables &T, const DeviceGrid &G, bool terms_
     // A row per workgroup while there are few rows or many process counts.  It is one launch where
     // the staged path has two or three, and a small job is their latency.  Whole calls on tables of 64
     // samples, all 13 rows, staged in brackets (1000 rows and more: sums up to 64 terms for 12, 1500
-    // for 36, 256 for 255 process counts): 64 sizes x 49 process counts x 13 candidates 5.9 us (13),
-    // 20 x 16 x 34 7.5 (27), 1000 x 12 x 13 6.5 (15), 1000 x 36 x 37 9.8 (17), 3000 x 12 x 37 17 (33),
-    // 4000 x 255 x 13 24 (29), 6000 x 36 x 37 39 (39), 10 000 62 (55).  Tables of 512 samples gain more
-    // (4000 x 12 x 13 21 (38)), although every workgroup forms their slopes.  Against tiles: 4000 rows x
-    // 12 process counts 20 (21), x 127 23 (30), 6000 x 36 39 (26); 4000 x 300 29 (34), 10 000 x 300 62
-    // (48); 10 000 x 1000 82 (118).
+    // for 36, 256 for 255 process counts): 64 sizes x 49 process counts x 13 candidates 5.3 us (12),
+    // 20 x 16 x 34 7.5 (28), 1000 x 12 x 13 6.4 (15), 1000 x 36 x 37 9.7 (16), 3000 x 12 x 37 15 (32),
+    // 4000 x 255 x 13 23 (28), 6000 x 36 x 37 39 (34), 10 000 61 (45).  Tables of 512 samples gain more
+    // (4000 x 12 x 13 20 (34)).  Against tiles: 4000 rows x 127 process counts 22 (22), 6000 x 36 37 (22);
+    // 10 000 x 300 51 (34), x 1000 78 (96).
     // Chain sums for few cells are the one kind of row that the staged path does cheaper from fewer
     // rows on, the longer the sums the fewer, where neither the table nor the candidates are many (36
-    // process counts, 13 candidates: up to 1500 2000 rows 15 (15), 3000 21 (20), 4000 27 (23); up to 700
-    // 3000 rows 18 (18), 4000 23 (20); 256 samples, up to 1500 30 (29), 37 candidates 27 (29), 12
-    // process counts 3000 rows 21 (23)).
+    // process counts, 13 candidates: up to 1500 2000 rows 14 (15), 3000 20 (19), 4000 26 (22); up to 700
+    // 3000 rows 17 (18), 4000 22 (20); up to 1500, 2000 rows, 256 samples 16 (17), 37 candidates 16 (18), 12
+    // process counts 3000 rows 20 (23)).
     const long rows = (long)T.n_tables * G.n_m;
     const long few_cells = G.n_P >= 32 && G.n_P < 64 && T.n <= 128 && G.n_s <= 16 ? G.n_blk / 4 : 0;
     // Masks with Gather or Barrier rows take the same launch up to a number of rows of their own (64 sizes x
