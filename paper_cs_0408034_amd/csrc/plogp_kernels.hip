@@ -1353,27 +1353,7 @@ __global__ void __launch_bounds__(1024) k_chain_blocks(DeviceTables T, DeviceGri
 
 // ---------------------------------------------------------------- the chain row at n points
 
-// g((64 b + 1) m) + ... + g((64 b + 64) m) added in ascending j from +0.0.  Bound by the number of
-// instructions.  A table of few samples is walked without a look at how many intervals the block enters (64
-// samples: 72.7 us for 300 000 points with P up to 1024, 74.4 with it).
-constexpr int EVAL_DENSE_N = 128;
-
-__device__ __forceinline__ double chain_block_sum(const ChainCtx &C, u64 b, u64 m)
-{
-    const double md = (double)m, z0 = (double)((b * SUM_BLOCK + 1) * m);
-    if (C.n <= EVAL_DENSE_N) {
-        WalkAt at = walk_from(C, z0);
-        return walk_block(C, at, md, 0, 0, nullptr);
-    }
-    const double ends[2] = {z0, (double)((b * SUM_BLOCK + SUM_BLOCK) * m)};
-    int i[2];
-    chain_locate<2>(C.X, C.n, ends, i);
-    const int reach = wave_reach(C, i[1] - i[0]);
-    if (reach > WALK_REACH)
-        return block_search(C, i[0], reach, md, z0, 0, 0, nullptr);
-    WalkAt at = {i[0], z0 - C.X[i[0]], C.W[i[0]], C.YS[i[0]]};
-    return walk_block(C, at, md, 0, 0, nullptr);
-}
+// Sums of g((64 b + 1) m), ..., g((64 b + 64) m) added in ascending j from +0.0.
 
 // After moving into interval i the size is
 // still at or past its end (d >= w), i.e. several intervals on.  Looks four
@@ -1415,19 +1395,20 @@ __device__ __forceinline__ void chain_skip_ahead(const ChainCtx &C, int &i, doub
     si = ys.y;
 }
 
-// The first `terms` < 64 of them in this lane (0: none), a step per term (the loop runs to the wave's
-// largest), with a branch where some lane enters an interval: eight at a time, as above, is no faster where
-// most lanes have left before the last term (100 000 points with P up to 300 on 100 samples 31.7 us this way,
+// The first `terms` of them in this lane (0: none; FULL: all 64), a step per term (the loop runs to the wave's
+// largest), with a branch where some lane enters an interval: eight at a time, as walk_block does, is no faster
+// where most lanes have left before the last term (100 000 points with P up to 300 on 100 samples 31.7 us this way,
 // 35.9 so; 290 000 with P up to 1024 on 256 samples 99, 117).  The sum and the distance are pinned to their
 // registers after every term: left to itself the compiler carries a copy of every state variable past each
 // branch.
-__device__ __forceinline__ double chain_rest_walk(const ChainCtx &C, u64 b, u64 m, int terms)
+template <bool FULL>
+__device__ __forceinline__ double chain_step_walk(const ChainCtx &C, u64 b, u64 m, int terms)
 {
     const double md = (double)m;
     WalkAt at = walk_from(C, (double)((b * SUM_BLOCK + 1) * m));
     double run = 0.0;
-    for (int k = 0; __ballot(k < terms) != 0; ++k) {
-        if (k < terms && at.d >= at.w) {
+    const auto step = [&](bool use) {
+        if (use && at.d >= at.w) {
             at.d -= at.w;
             ++at.i;
             at.w = C.W[at.i];
@@ -1440,11 +1421,57 @@ __device__ __forceinline__ double chain_rest_walk(const ChainCtx &C, u64 b, u64 
             }
         }
         const double g = run + __builtin_fma(at.ys.y, at.d, at.ys.x);
-        run = k < terms ? g : run;
+        run = use ? g : run;
         at.d += md;
         asm volatile("" : "+v"(run), "+v"(at.d));
+    };
+    if (FULL) {
+#pragma unroll 1
+        for (int k = 0; k < SUM_BLOCK; k += 8) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                step(true);
+        }
+    } else {
+        for (int k = 0; __ballot(k < terms) != 0; ++k)
+            step(k < terms);
     }
     return run;
+}
+
+// All 64.  Bound by the number of instructions, or, for few points, by the time that a wave takes.  What matters is
+// the first block, whose sizes are six octaves apart; the others are walked eight terms at a time (or searched for
+// where they enter many intervals all the same).  On a table of few samples the first is walked too, without a look
+// at how many intervals it enters.  On others a wave with some lane's first block searches for its terms, unless
+// there are so many points that their instructions count, not the wait: then it walks a term at a time (122 samples,
+// P up to 122: 290 000 points 30.0 us so, 32.3 searched for, 38.0 walked eight terms at a time; 3500 points 23.1,
+// 20.9 and 23.2; 72 samples 20.2, 20.0 and 18.2).  The rule: launch_eval.
+enum EvalBlocks : int { EVAL_WALK, EVAL_SEARCH, EVAL_STEP };
+constexpr int EVAL_LOOK_N = 128;         // up to which blocks other than the first are walked without a look
+constexpr int EVAL_REACH = 16;           // intervals entered from which on it searches in the first block
+
+// BIG: more than EVAL_SEARCH_N samples (without the walk that is not looked for there, the kernel for these keeps
+// to 80 registers, with which two workgroups of 768 threads share a compute unit: 900 samples, 290 000 points with
+// P up to 70 76 us, 91 with 85).
+template <int BLOCKS, bool BIG>
+__device__ __forceinline__ double chain_block_sum(const ChainCtx &C, u64 b, u64 m)
+{
+    const bool first = BLOCKS != EVAL_WALK && __ballot(b == 0) != 0;
+    if (BLOCKS == EVAL_STEP && first)
+        return chain_step_walk<true>(C, b, m, SUM_BLOCK);
+    const double md = (double)m, z0 = (double)((b * SUM_BLOCK + 1) * m);
+    if (BLOCKS == EVAL_WALK || (!BIG && C.n <= EVAL_LOOK_N && !first)) {
+        WalkAt at = walk_from(C, z0);
+        return walk_block(C, at, md, 0, 0, nullptr);
+    }
+    const double ends[2] = {z0, (double)((b * SUM_BLOCK + SUM_BLOCK) * m)};
+    int i[2];
+    chain_locate<2>(C.X, C.n, ends, i);
+    const int reach = wave_reach(C, i[1] - i[0]);
+    if (reach > (!BIG && C.n <= EVAL_LOOK_N ? EVAL_REACH : WALK_REACH))
+        return block_search(C, i[0], reach, md, z0, 0, 0, nullptr);
+    WalkAt at = {i[0], z0 - C.X[i[0]], C.W[i[0]], C.YS[i[0]]};
+    return walk_block(C, at, md, 0, 0, nullptr);
 }
 
 // As gaps_within, on indices in place of addresses (reach: a power of two).
@@ -1532,7 +1559,7 @@ __device__ __forceinline__ double chain_rest_sum(const ChainCtx &C, u64 b, u64 m
 // there are many on a table that leaves LDS for few waves (512 samples: 142 us, 185 with eight).
 constexpr int EVAL_SEARCH_N = 256;       // more samples: the rest of a sum is searched for
 
-template <int LEVELS>
+template <int LEVELS, int BLOCKS>
 __global__ void __launch_bounds__(LEVELS == 4 ? 768 : 384)
 k_eval_chain(DeviceTables T, int t, const u64 *dm, const uint32_t *dP, size_t n, double *out)
 {
@@ -1597,7 +1624,7 @@ k_eval_chain(DeviceTables T, int t, const u64 *dm, const uint32_t *dP, size_t n,
                 }
             }
             const int p = order[r];
-            const double v = chain_block_sum(C, (u64)b0 + k, m_of[p]);
+            const double v = chain_block_sum<BLOCKS, LEVELS == 4>(C, (u64)b0 + k, m_of[p]);
             if (real)
                 tot[(size_t)k * threads + p] = v;
         }
@@ -1606,7 +1633,7 @@ k_eval_chain(DeviceTables T, int t, const u64 *dm, const uint32_t *dP, size_t n,
             done = done + tot[(size_t)k * threads + tid];
     }
     const double rest = C.n > EVAL_SEARCH_N ? chain_rest_sum<LEVELS == 4>(C, full, m_of[tid], tail)
-                                            : chain_rest_walk(C, full, m_of[tid], tail);
+                                            : chain_step_walk<false>(C, full, m_of[tid], tail);
     if (i < n)
         out[i] = ok ? __builtin_fma((double)(P - 1u), T.L[t], done + rest) : NAN;
 }
@@ -4911,12 +4938,17 @@ hipError_t kernels_init()
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_eval),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxTableLds);
     if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_eval_chain<4>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)eval_chain_lds(4096, 4, 768));
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_eval_chain<8>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)eval_chain_lds(4096, 8, 384));
-    if (e != hipSuccess) return e;
+    for (const void *k : {reinterpret_cast<const void *>(k_eval_chain<4, EVAL_SEARCH>),
+                          reinterpret_cast<const void *>(k_eval_chain<4, EVAL_STEP>)}) {
+        e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)eval_chain_lds(4096, 4, 768));
+        if (e != hipSuccess) return e;
+    }
+    for (const void *k : {reinterpret_cast<const void *>(k_eval_chain<8, EVAL_WALK>),
+                          reinterpret_cast<const void *>(k_eval_chain<8, EVAL_SEARCH>),
+                          reinterpret_cast<const void *>(k_eval_chain<8, EVAL_STEP>)}) {
+        e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)eval_chain_lds(4096, 8, 384));
+        if (e != hipSuccess) return e;
+    }
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_terms),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxTableLds);
     if (e != hipSuccess) return e;
@@ -4998,9 +5030,15 @@ hipError_t launch_eval(const DeviceTables &T, int table, int strategy, const uin
         // 1500 samples: 313 us with 768, 468 with 384; 600 samples 203 with 256, 227 with 384)
         const bool many = n > (size_t)384 * device_info().n_cu && T.n > EVAL_SEARCH_N;
         const int levels = many ? 4 : 8, threads = T.n <= (many ? 640 : 512) ? 256 : many ? 768 : 384;
-        hipLaunchKernelGGL(many ? k_eval_chain<4> : k_eval_chain<8>, dim3((unsigned)((n + threads - 1) / threads)),
-                           dim3(threads), eval_chain_lds(T.n, levels, threads), st, T, table,
-                           reinterpret_cast<const u64 *>(d_m), d_P, n, d_out);
+        // (step: 450 samples, 290 000 points with P up to 300 80 us, 85 searched for, up to 70 65 and 62; 600: 108
+        // and 104, 74 and 62; 256 samples, 100 000 points up to 122 30 and 28)
+        const bool step = n >= (size_t)768 * device_info().n_cu && T.n <= 512;
+        const auto kern = T.n <= (step ? 64 : 72) ? k_eval_chain<8, EVAL_WALK>
+                          : many ? (step ? k_eval_chain<4, EVAL_STEP> : k_eval_chain<4, EVAL_SEARCH>)
+                                 : (step ? k_eval_chain<8, EVAL_STEP> : k_eval_chain<8, EVAL_SEARCH>);
+        hipLaunchKernelGGL(kern, dim3((unsigned)((n + threads - 1) / threads)), dim3(threads),
+                           eval_chain_lds(T.n, levels, threads), st, T, table, reinterpret_cast<const u64 *>(d_m), d_P,
+                           n, d_out);
         return hipGetLastError();
     }
     const size_t lds = (size_t)3 * T.n * sizeof(double);

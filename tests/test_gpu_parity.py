@@ -714,6 +714,34 @@ def test_chain_row_at_many_points(n_x):
     tab.free()
 
 
+@pytest.mark.parametrize("n_x", [64, 65, 72, 73, 128, 129, 256, 257, 512, 513])
+@pytest.mark.parametrize("together", [1, 13, 33, 70])
+def test_complete_blocks_of_many_points_and_of_few(n_x, together):
+    # from 768 points per compute unit on, and from 65 samples up to 512, the first block of a sum is walked a
+    # term at a time; with fewer points it is searched for from 73 samples on, and from 129 on the others where
+    # they enter many intervals.  Groups of samples one byte apart, the next 1500 on: a term enters all of a group
+    torch, plogp = torch_cuda(), _plogp()
+    rng = np.random.default_rng(n_x + together)
+    n_points = 768 * torch.cuda.get_device_properties(0).multi_processor_count
+    x = np.array([1500.0 * (1 + k // together) + k % together for k in range(n_x)])
+    y = np.abs(30.0 + 0.1 * x * (1.0 + 0.3 * rng.standard_normal(n_x)))
+    P = rng.integers(60, rng.choice([67, 130, 400], n_points)).astype(np.uint32)
+    m = np.maximum(np.floor(2.0 ** rng.uniform(0, 15, n_points)), 1.0).astype(np.uint64)
+    tab = plogp.plogp_load_table(x, y, 7.5)
+    out = torch.empty(n_points, dtype=torch.float64, device="cuda")
+    dm, dP = _dev(m, np.uint64), _dev(P, np.uint32)
+    got = {}
+    for n in (n_points, n_points - 1, 5000):
+        plogp.plogp_eval_strategy(tab, 0, 11, dm.data_ptr(), dP.data_ptr(), 0, n, out.data_ptr(), stream_handle())
+        torch.cuda.synchronize()
+        got[n] = out.cpu().numpy().view(np.uint64)[:n]
+    assert (got[n_points][:-1] == got[n_points - 1]).all() and (got[n_points][:5000] == got[5000]).all()
+    some = np.append(np.arange(0, n_points, 411), n_points - 1)
+    want = np.array([oracle.eval_strategy(x, y, 7.5, 11, int(mv), int(pv), 0) for mv, pv in zip(m[some], P[some])])
+    assert (got[n_points][some] == want.view(np.uint64)).all()
+    tab.free()
+
+
 @pytest.mark.parametrize("n_m,n_P,p_hi,n_s,n", [
     (2559, 36, 1500, 13, 64), (2560, 36, 1500, 13, 64),   # 24 blocks of the chain sum: ten rows a compute unit
     (2560, 31, 1500, 13, 64), (2560, 36, 1500, 17, 64), (2560, 36, 1500, 13, 129),    # no longer one of these
