@@ -2330,11 +2330,7 @@ __global__ void __launch_bounds__(256) k_sweep_m(DeviceTables T, DeviceGrid G, S
 // NSV: candidates per lane when a row of (m, s) terms is moved (n_s <= 64 NSV).
 // FEW (NSV 1): row 5 for the candidates alone that can win it for some process count of
 // the wave (row5_candidates), in place of a loop over all, eight a round trip to LDS.
-// With two process counts per lane that is the faster (4096 sizes x 976, 43 candidates:
-// 38 us, 33), with one where the list is close (at least half of all counts up to the
-// largest; 9000 x 300 up to 301, 34 candidates: the call 63.6, 58.0), and not where a
-// wave's counts lie far apart (1638 x 100 up to 2612, 40: 8.1 us, 9.2; 5000 x 40 up to
-// 1500, 34: the call 31.9, 33.1).
+// Which calls: sweep_few.
 template <int NSV, bool ALL, int PPL, bool FEW>
 __global__ void __launch_bounds__(256) k_sweep_p(DeviceTables T, DeviceGrid G, Scratch S,
                                                  plogp_cell_dev *out, int t0, int n_w)
@@ -5287,6 +5283,21 @@ static bool row_few(const DeviceGrid &G)
     return !(G.n_s > 12 && G.n_s <= 24 && G.n_P <= 64 && P_top >= 4 * G.n_P);
 }
 
+// The same for the sweep over process counts.  With two of them per lane it is the faster to leave candidates out
+// (4096 sizes x 976, 43 candidates: 38 us, 33), with one where the list is close (at least half of all counts up to
+// the largest; 9000 x 300 up to 301, 34 candidates: the call 63.6, 58.0), and not where a wave's counts lie far apart
+// (1638 x 100 up to 2612, 40: 8.1 us, 9.2; 5000 x 40 up to 1500, 34: the call 31.9, 33.1); not for a few candidates
+// (700 samples, 6000 sizes x 1000 up to 1800: 3 candidates 2 % slower, 8 the same); and where no chain sum is read,
+// so that a wave waits for little else, for many candidates and process counts alone (the Broadcast rows, 6000 x
+// 300: 3 candidates 8 % slower, 8 3 %, 17 to 24 the same, 34 3 % faster; 34 x 64 3 % slower).
+static bool sweep_few(const DeviceGrid &G, int ppl)
+{
+    const bool close = 2L * G.n_P >= (long)G.n_blk * SUM_BLOCK;
+    if ((G.need & (1u << 11)) != 0)
+        return G.n_s > 4 && (ppl == 2 || close);
+    return G.n_s > 24 && G.n_P >= 256 && close;
+}
+
 // The row path's part, the same.
 static bool plan_rows(const DeviceTables &T, const DeviceGrid &G, TunePlan &p)
 {
@@ -5656,13 +5667,11 @@ hipError_t launch_tune_stage(const TunePlan &p, int stage, const DeviceTables &T
             for (int t0 = 0; t0 < T.n_tables; t0 += 65535) {
                 const int nt = T.n_tables - t0 < 65535 ? T.n_tables - t0 : 65535;
                 const dim3 blocks((unsigned)(p.n_w / 4), (unsigned)p.n_pg, (unsigned)nt);
-                const bool close = 2L * G.n_P >= (long)G.n_blk * SUM_BLOCK;
-                const auto kern = G.n_s > 64 ? k_sweep_p<4, false, 1, false>
-                                  : all      ? (p.ppl == 2 ? k_sweep_p<1, true, 2, true>
-                                                : close    ? k_sweep_p<1, true, 1, true>
-                                                           : k_sweep_p<1, true, 1, false>)
-                                  : close    ? k_sweep_p<1, false, 1, true>
-                                             : k_sweep_p<1, false, 1, false>;
+                const bool few = sweep_few(G, p.ppl);
+                const auto kern = G.n_s > 64   ? k_sweep_p<4, false, 1, false>
+                                  : !all       ? (few ? k_sweep_p<1, false, 1, true> : k_sweep_p<1, false, 1, false>)
+                                  : p.ppl == 2 ? (few ? k_sweep_p<1, true, 2, true> : k_sweep_p<1, true, 2, false>)
+                                               : (few ? k_sweep_p<1, true, 1, true> : k_sweep_p<1, true, 1, false>);
                 hipLaunchKernelGGL(kern, blocks, dim3(256), 0, st, T, G, S, d_out, t0, p.n_w);
             }
         } else {

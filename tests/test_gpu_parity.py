@@ -1079,3 +1079,19 @@ def test_which_rows_evaluate_every_candidate(n_s, n_P, p_hi, mask):
     wl = Workload("row 5", x, gaps, np.array([3.0]), m, P, s, NO_CAP, mask)
     want, _ = oracle.tune_workload(wl)
     assert assert_tables_equal(gpu_tune(wl), want, "n_s=%d mask %x" % (len(s), mask)), "times not bit-identical"
+
+
+@pytest.mark.parametrize("n_s,n_P,p_hi", [(4, 40, 41), (5, 40, 41), (4, 600, 700), (5, 600, 700), (24, 256, 300), (25, 255, 300),
+                                          (25, 256, 300), (25, 256, 2000)])
+@pytest.mark.parametrize("mask", [ALL_STRATEGIES_MASK, 0x3FF, 0x9FF])
+def test_which_sweeps_evaluate_every_candidate(n_s, n_P, p_hi, mask):
+    # the same of the sweep over process counts, on a table too long for a workgroup per row
+    rng = np.random.default_rng(n_s * 1000 + n_P)
+    x = np.cumsum(rng.integers(1, 3000, size=600)).astype(np.float64)[None]
+    gaps = np.maximum(25.0 + 0.07 * x * (1.0 + 0.3 * rng.standard_normal(x.shape)), 900.0)
+    m = np.maximum(8, 8 * np.floor(np.exp(rng.uniform(np.log(8.0), np.log(5e6), size=300)) / 8)).astype(np.uint64)
+    P = np.union1d(rng.choice(np.arange(2, p_hi), size=n_P - 1, replace=False), [p_hi]).astype(np.uint32)
+    s = (8 * np.unique(np.floor(np.geomspace(1, 60000, 2 * n_s))))[:n_s].astype(np.uint64)
+    wl = Workload("row 5", x, gaps, np.array([3.0]), m, P, s, NO_CAP, mask)
+    want, _ = oracle.tune_workload(wl)
+    assert assert_tables_equal(gpu_tune(wl), want, "n_s=%d mask %x" % (len(s), mask)), "times not bit-identical"
