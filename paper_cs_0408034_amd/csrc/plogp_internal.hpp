@@ -178,7 +178,7 @@ Scratch bind_scratch(void *base, const ScratchLayout &lay);
 
 // Each returns the hipError_t of the launch (hipGetLastError after it).
 hipError_t launch_slopes(const DeviceTables &T, double *slope_out, hipStream_t st);
-// A few small tables as [x | y | L], passed by value as a kernel's argument.
+// A few small tables as [x | y | L], passed by value as a kernel's argument (which, with the others, has 4 KB).
 constexpr int PACKED_DOUBLES = 448;
 struct PackedTables {
     double v[PACKED_DOUBLES];

@@ -217,9 +217,8 @@ __device__ __forceinline__ double lane_value(double v, int lane)
 // too: nothing between the ends is larger than M, the largest magnitude at the ends, the values at the ends and
 // in between are each off by up to 2^-53 M, and it is 2^-49 M.  (Values that are not finite stay in.)
 // 70 instructions, where a pass over 64 process counts, eight candidates at a time, took 35 for every eight: 1024
-// sizes x 1023 process counts, 34 candidates 16.0 -> 13.2 us, x 600, 8 candidates (2000 sizes) 17.0 -> 16.5; 13
-// candidates for 49 process counts, the least, 4.05 -> 4.14; 4096 sizes x 976, 43 candidates (k_sweep_p) the call
-// 126.5 -> 121.  Which calls use it: row_few and, for k_sweep_p, the launch.
+// sizes x 1023 process counts, 34 candidates 16.0 -> 13.2 us, x 600, 8 candidates (2000 sizes) 17.0 -> 16.5; 4096
+// sizes x 976, 43 candidates (k_sweep_p) the call 126.5 -> 121.  Where the pass is the shorter: row_few, sweep_few.
 __device__ __forceinline__ u64 row5_candidates(double C, double B, int nv, double q_lo, double q_hi)
 {
     const u64 there = nv >= 64 ? ~0ull : (1ull << nv) - 1ull;
@@ -289,9 +288,8 @@ __global__ void __launch_bounds__(256) k_slopes(DeviceTables T, double *slope_ou
         slope_out[(size_t)t * n + i] = interval_slope(x, y, n, i);
 }
 
-// ---------------------------------------------------------------- g() at arbitrary sizes
-
-// The same for tables that come as the argument, written out beside their slopes.
+// The same for tables that come as the argument (448 numbers: a kernel's arguments are 4 KB at most), written out
+// beside their slopes.
 __global__ void __launch_bounds__(256) k_load_packed(PackedTables packed, double *block, int n, int n_tables)
 {
     const int count = n * n_tables, last = 2 * count + n_tables;
@@ -302,6 +300,8 @@ __global__ void __launch_bounds__(256) k_load_packed(PackedTables packed, double
         block[last + i] = interval_slope(packed.v + t * n, packed.v + count + t * n, n, i - t * n);
     }
 }
+
+// ---------------------------------------------------------------- g() at arbitrary sizes
 
 __global__ void __launch_bounds__(256) k_interp(DeviceTables T, int t, const u64 *z, size_t n,
                                                 double *out)
@@ -1115,10 +1115,13 @@ __device__ __forceinline__ int block_reach(const ChainCtx &C, double z0, double 
     return wave_reach(C, il[0] - i0);
 }
 
-// Blocks of which some lane's enters more intervals than this are searched for, term by term, not walked: a
-// walk takes as many turns over its eight terms as some lane enters intervals (1000 sizes x P up to 8192 on 4000
-// samples: all blocks walked 65 us, 50 with this; 16 or 32 make no difference, 64 56).
+// From so many intervals on, a power of two, that some lane's block enters, a wave's blocks are searched for, term
+// by term, not walked: a walk takes as many turns over its eight terms as some lane enters intervals (1000 sizes x P
+// up to 8192 on 4000 samples: all blocks walked 65 us, 50 with this; 16 or 32 make no difference, 64 56).
 constexpr int WALK_REACH = 32;
+
+constexpr bool power_of_two(int v) { return v > 0 && (v & (v - 1)) == 0; }
+static_assert(power_of_two(WALK_REACH), "compared with what wave_reach gives");
 
 // Addresses in LDS as numbers: a step of a search is then an addition, a read, a comparison and a select.
 typedef __attribute__((address_space(3))) const double lds_double;
@@ -1174,7 +1177,7 @@ __device__ __forceinline__ void gaps_within(const ChainCtx &C, int i0, int reach
 // terms, few enter more than three intervals: then the bounds between these are read once for all eight
 // and compared with; else there is a search each, over as many intervals as the eight span in some lane.
 // Which of the two is decided for the wave (333 tables of 57 samples x 203 sizes x 37 process counts up to
-// 1500: 76.7 us with a search over the whole block's intervals per term, 68.2 now; 100 tables of 120
+// 1500: 76.7 us with a search over the whole block's intervals per term, 68.2 so; 100 tables of 120
 // samples x 200 sizes: 44.5 and 37.0).
 template <int V>
 __device__ __forceinline__ void gaps_ascending(const ChainCtx &C, int &i, int reach, const double (&z)[V], double (&g)[V])
@@ -1449,6 +1452,7 @@ __device__ __forceinline__ double chain_step_walk(const ChainCtx &C, u64 b, u64 
 enum EvalBlocks : int { EVAL_WALK, EVAL_SEARCH, EVAL_STEP };
 constexpr int EVAL_LOOK_N = 128;         // up to which blocks other than the first are walked without a look
 constexpr int EVAL_REACH = 16;           // intervals entered from which on it searches in the first block
+static_assert(power_of_two(EVAL_REACH), "compared with what wave_reach gives");
 
 // BIG: more than EVAL_SEARCH_N samples (without the walk that is not looked for there, the kernel for these keeps
 // to 80 registers, with which two workgroups of 768 threads share a compute unit: 900 samples, 290 000 points with
@@ -1550,7 +1554,7 @@ __device__ __forceinline__ double chain_rest_sum(const ChainCtx &C, u64 b, u64 m
 // there (300 000 points with P up to 64: 64 samples 19 us walked, 35 searched; 4096 samples 291 and
 // 88; at 512 as fast, and with P up to 16 30 and 20).
 //
-// Bound by the vector instructions of the walk (300 000 points with P up to 1024, 64 samples: 73 us, 76
+// Bound by the vector instructions of the walk (300 000 points with P up to 1024, 64 samples: 71 us, 76
 // with a branch per term, which few lanes take but some nearly always; 555 with a thread that walks its
 // point alone and searches the table per term).  Few points, where a wave's latency counts, gain most by
 // the walk of eight terms at a time: 30 000 points 56 -> 42 us, 3000 51 -> 39, 30 000 with P up to 5000
@@ -1816,7 +1820,10 @@ __global__ void __launch_bounds__(256) k_terms_chain(DeviceTables T, DeviceGrid 
 // (20.0 and 17.3 with sixteen sizes to a workgroup, whose totals lay 128 bytes at a time among those of all
 // sizes, and each sixteen asked for when those before had been added; 19.9 and 16.2 with eight sizes, their
 // totals together, alone; 32 and 14.7 with four; tiles of 64 blocks 20.2 and 16.7; 25.7 for the first when a
-// workgroup of four waves loaded, added and wrote in turn).  What bounds it is the additions, 13 cycles each.
+// workgroup of four waves loaded, added and wrote in turn).  What bounds it is the way of the adding wave through
+// LDS: of the 14.8 us of 300 sizes 13.0 remain with nothing loaded and nothing written out by the others (14.2
+// without the loads, 13.5 without the stores; of 18.9 with 3215 sizes 14.3), and with the totals passed on in place
+// of sums, no addition waiting for another, it takes no less (17.1).
 constexpr int PFX_TILE = 128;
 constexpr int PFX_THREADS = 512;
 constexpr int PFX_LD = PFX_TILE + 2;     // row of a size: the lanes' pairs lie in different banks
@@ -3014,8 +3021,8 @@ static size_t sweep_s_lds(int n_s, bool with_static)
 // term), one, and among which eight of its terms (lanes that enter together cost a walk one turn
 // more over these eight, see walk_terms, and none elsewhere), or more; and the waves take 64 of
 // that order at a time, from its end, whatever the kind: a list per kind left lanes idle in the
-// last wave of each.  Waves whose items enter more intervals than TILE_REACH says search for eight
-// terms side by side (gaps_ascending).
+// last wave of each.  Waves of which some item enters as many intervals as TILE_REACH says search for
+// eight terms side by side (gaps_ascending).
 //
 // 333 tables of 57 samples x 203 sizes x 37 process counts up to 1500, 19 candidates, 80 MB of
 // cells: 63 us a call (68 with the change of interval as six selects per term of the items that
@@ -3042,11 +3049,12 @@ constexpr long TILE_MIN_ROWS = 16;       // (table, m) rows per compute unit at 
 constexpr int TILE_FEW_N = 512;
 constexpr int TILE_WG_PER_CU = 6;        // that their registers leave room for
 constexpr int TILE_DENSE_N = 40;
-// Intervals entered by some lane's block above which a wave searches (as WALK_REACH): the second from TILE_DENSE_N
+// Intervals entered by some lane's block from which on a wave searches (as WALK_REACH): the second from TILE_DENSE_N
 // samples on, where the blocks of the last kind enter many (95 samples, 32 tables x 137 sizes 21.9 us with 16, 20.2 so,
 // 300 tables 31.9 and 30.5; 57 samples, 333 tables no difference), the first else (25 samples, 60 tables x 95 sizes 17.2,
 // 18.1 with 4).
 constexpr int TILE_REACH = 16, TILE_REACH_DENSE = 4;
+static_assert(power_of_two(TILE_REACH) && power_of_two(TILE_REACH_DENSE), "compared with what wave_reach gives");
 
 // Where the arrays of a workgroup start in LDS, in 8-byte slots.  The lists of the chain items lie
 // where A and B of every (m, s) go afterwards.
@@ -3450,12 +3458,12 @@ __global__ void __launch_bounds__(TILE_THREADS, TILE_WG_PER_CU) k_tile(DeviceTab
 // search each; wave 0 the sums inside the blocks (a lane per block, 64 dependent
 // additions) and then over the blocks; then the waves run their lanes over the
 // process counts as in k_sweep_p: the few candidates that can win row 5 of Table 1
-// for some process count of the group, min_s A for rows 2 and 9, whose candidate is
-// looked for only where one of them wins, two coalesced stores per cell.
+// for some process count of the group (or all: row_few), min_s A for rows 2 and 9, whose
+// candidate is looked for only where one of them wins, two coalesced stores per cell.
 // The slopes are read, as they were formed when the table was loaded, beside the
 // samples: a division and a barrier less in a chain of dependent steps that is all
 // of a small call (64 sizes x 49 process counts, 21 samples: 4.24 us in a graph of
-// such calls, 4.05 so, where an empty kernel takes 1.6; 200 x 100 5.16 and 5.05).
+// such calls, 4.03 so, where an empty kernel takes 1.6; 200 x 100 5.16 and 5.05).
 constexpr int ROW_THREADS = 512;
 constexpr int ROW_MAX_BLK = 32;          // at most 2048 terms of the chain sum
 constexpr int ROW_NS = 64;               // candidates at most (the loops over them read up to the next eight)

@@ -786,10 +786,11 @@ def test_terms_beside_the_sums_of_a_big_table(n_tables, n, n_m, n_s, n_P, mask):
 # ------------------------------------------------------------------ prefix of the block sums
 
 @pytest.mark.parametrize("blocks,n_m,n_P", [(33, 15, 9), (97, 1, 300), (128, 16, 600), (129, 17, 600), (256, 5, 40), (257, 33, 40),
-                                            (384, 3, 5), (385, 16, 5), (513, 2, 4096), (513, 2, 4097), (65536, 1, 40),
+                                            (384, 3, 5), (385, 16, 5), (300, 7, 40), (300, 8, 40), (300, 9, 40),
+                                            (513, 2, 4096), (513, 2, 4097), (65536, 1, 40),
                                             (65537, 1, 40)])
 def test_prefix_of_the_block_sums_at_the_edges_of_its_tiles(blocks, n_m, n_P):
-    # tiles of 128 blocks, groups of 16 distinct sizes; block indices in LDS for up to 4096 process counts
+    # tiles of 128 blocks, groups of eight distinct sizes; block indices in LDS for up to 4096 process counts
     # and 65 536 blocks; the sum ends with the first term of its last block
     rng = np.random.default_rng(blocks + n_P)
     n = 700
@@ -926,7 +927,7 @@ def test_tiles_whose_terms_enter_intervals_at_an_even_pace(n, m):
 def test_walks_past_samples_that_lie_together(together, route):
     # groups of samples one byte apart, 4000 from the next: a term enters all intervals of a group at once,
     # most of them without a term in them (a walk looks for the next after twelve; a wave of which some block
-    # enters more than 32, or 16, searches).  Sums wanted around every eighth term
+    # enters 32 or more, in tiles 16, or 4 from 40 samples on, searches).  Sums wanted around every eighth term
     rng = np.random.default_rng(together)
     n = {"sums": 1100, "tiles": 200, "points": 180}[route]
     n_tables = 700 if route == "tiles" else 1
