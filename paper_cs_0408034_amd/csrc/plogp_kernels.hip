@@ -3048,7 +3048,7 @@ constexpr size_t TILE_STATIC_LDS = 256;  // room for the counters
 constexpr long TILE_MIN_ROWS = 16;       // (table, m) rows per compute unit at least (more than TILE_FEW_N samples: twice)
 constexpr int TILE_FEW_N = 512;
 constexpr int TILE_WG_PER_CU = 6;        // that their registers leave room for
-constexpr int TILE_DENSE_N = 40;
+constexpr int TILE_DENSE_N = 40;         // from so many samples on a table's blocks enter more intervals
 // Intervals entered by some lane's block from which on a wave searches (as WALK_REACH): the second from TILE_DENSE_N
 // samples on, where the blocks of the last kind enter many (95 samples, 32 tables x 137 sizes 21.9 us with 16, 20.2 so,
 // 300 tables 31.9 and 30.5; 57 samples, 333 tables no difference), the first else (25 samples, 60 tables x 95 sizes 17.2,
@@ -3169,8 +3169,8 @@ __device__ __forceinline__ void tile_search_shared(const ChainCtx &C, unsigned i
 }
 
 template <bool ALL>
-__global__ void __launch_bounds__(TILE_THREADS, TILE_WG_PER_CU) k_tile(DeviceTables T, DeviceGrid G, plogp_cell_dev *out, int n_tiles,
-                                                          int M, int shared)
+__global__ void __launch_bounds__(TILE_THREADS, TILE_WG_PER_CU)
+k_tile(DeviceTables T, DeviceGrid G, plogp_cell_dev *out, int n_tiles, int M, int shared)
 {
     // (a name of its own: under a name that another kernel declares without it the alignment is lost,
     // and 16-byte reads of misaligned LDS take twice the kernel's time)
@@ -5140,6 +5140,7 @@ static bool use_row_path(const DeviceTables &T, const DeviceGrid &G)
 //                        300 up to 1500                 8100       30  (39)  16 000  54  (62)
 //   Tables 1, 2, Barrier  36 up to 1500                 2000       16  (19)    6000  42  (34)
 //   Broadcast, Barrier    36 up to 60                   2000       11  (14)    4100  21  (16)
+//                        512 up to 513                  8100       54  (59)  16 000 102  (89)
 static long row_path_most(const DeviceTables &T, const DeviceGrid &G)
 {
     constexpr long kAny = 1L << 40;
@@ -5367,8 +5368,8 @@ static bool plan_fastest(const DeviceTables &T, const DeviceGrid &G, bool terms_
     // for 36, 256 for 255 process counts): 64 sizes x 49 process counts x 13 candidates 5.3 us (12),
     // 20 x 16 x 34 7.5 (28), 1000 x 12 x 13 6.4 (15), 1000 x 36 x 37 9.7 (16), 3000 x 12 x 37 15 (32),
     // 4000 x 255 x 13 23 (28), 6000 x 36 x 37 39 (34), 10 000 61 (45).  Tables of 512 samples gain more
-    // (4000 x 12 x 13 20 (34)).  Against tiles: 4000 rows x 127 process counts 22 (22), 6000 x 36 37 (22);
-    // 10 000 x 300 51 (34), x 1000 78 (96).
+    // (4000 x 12 x 13 20 (34)).  Against tiles: 4000 rows x 12 process counts 18 (21), x 127 22 (22), 6000 x 36
+    // 37 (22); 4000 x 300 24 (30), 10 000 x 300 51 (34); 10 000 x 1000 78 (96).
     // Chain sums for few cells are the one kind of row that the staged path does cheaper from fewer
     // rows on, the longer the sums the fewer, where neither the table nor the candidates are many (36
     // process counts, 13 candidates: up to 1500 2000 rows 14 (15), 3000 20 (19), 4000 26 (22); up to 700
