@@ -5457,9 +5457,12 @@ static bool plan_fastest(const DeviceTables &T, const DeviceGrid &G, bool terms_
         p.chain_threads = big ? 1024 : 256;
         const int n_mg = (G.n_mu + 63) / 64;
         // leading blocks that are items of their own: the dense part of a table with many
-        // samples, or every block when the whole sum is
-        // too small to fill the chip with units of CHAIN_U blocks
-        int n_single = T.n > 256 ? 32 : 0;
+        // samples, the first blocks of one of which they enter so many intervals that a unit that begins
+        // with them is searched for as a whole (100 tables of 150 samples x 3 sizes x 100 process counts
+        // up to 8000 56 -> 27 us, one x 1500 sizes x 300 up to 30 000 44 -> 37; 30 samples, 100 tables x 3
+        // x 40 up to 20 000 33 and 35), or every block when the whole sum is too small to fill the chip
+        // with units of CHAIN_U blocks
+        int n_single = T.n > 256 ? 32 : T.n > 64 ? CHAIN_U : 0;
         if ((long)T.n_tables * n_mg * ((G.n_blk + CHAIN_U - 1) / CHAIN_U) < 8 * n_cu) n_single = G.n_blk;
         if (n_single > G.n_blk) n_single = G.n_blk;
         const long items = (long)n_mg * (n_single + (G.n_blk - n_single + CHAIN_U - 1) / CHAIN_U);

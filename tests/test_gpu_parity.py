@@ -783,6 +783,22 @@ def test_terms_beside_the_sums_of_a_big_table(n_tables, n, n_m, n_s, n_P, mask):
     assert assert_tables_equal(gpu_tune(wl), want, "n=%d m=%d s=%d" % (n, n_m, n_s)), "times not bit-identical"
 
 
+@pytest.mark.parametrize("n,n_tables,n_m,p_hi", [(64, 3, 5, 2200), (65, 3, 5, 2200), (65, 40, 70, 9000), (150, 100, 3, 8000),
+                                                 (256, 12, 70, 5000), (257, 12, 70, 5000)])
+def test_leading_blocks_of_the_sums_of_small_tables(n, n_tables, n_m, p_hi):
+    # the first four blocks are items of their own from 65 samples on (the first 32 from 257), samples and
+    # sizes over many octaves, so that the first block enters many intervals
+    rng = np.random.default_rng(n + n_tables)
+    x = np.floor(np.geomspace(1.0, 2.0 ** 22, n) * rng.uniform(1.0, 1.2, size=(n_tables, 1))) + 20.0 * np.arange(n)
+    gaps = np.abs(20.0 + x * 0.05 * (1.0 + 0.3 * rng.standard_normal(x.shape)))
+    m = np.unique(np.maximum(8, 8 * np.floor(np.geomspace(8, 2.0 ** 23, n_m) / 8)))
+    P = np.union1d(rng.choice(np.arange(2, p_hi), size=12, replace=False), [65, 129, 257, 258, p_hi]).astype(np.uint32)
+    wl = Workload("leading", x, gaps, rng.uniform(0.0, 90.0, size=n_tables), m.astype(np.uint64), P,
+                  np.array([8, 64, 512], dtype=np.uint64), NO_CAP, ALL_STRATEGIES_MASK)
+    want, _ = oracle.tune_workload(wl)
+    assert assert_tables_equal(gpu_tune(wl), want, "n=%d" % n), "times not bit-identical"
+
+
 # ------------------------------------------------------------------ prefix of the block sums
 
 @pytest.mark.parametrize("blocks,n_m,n_P", [(33, 15, 9), (97, 1, 300), (128, 16, 600), (129, 17, 600), (256, 5, 40), (257, 33, 40),
