@@ -110,6 +110,7 @@ struct Scratch {
     int *nv;          // [n_m]                            candidates s <= min(m, s_cap)
     BatchPrep batch;  // shared sample sizes only
     double *batch_ys; // [n+2][n_tables][2]               {gap, slope} by interval (shared sample sizes only)
+    int blk_group;    // log2 of the sizes whose block totals lie together (more than 32 blocks)
 };
 
 struct plogp_cell_dev {
@@ -132,6 +133,7 @@ struct ScratchLayout {
     size_t g1, gs, gm, sum2, blk, pre, part, rcp, segC, segA, segB, amin, minG, nv;
     size_t rec, tab, batch_ys;     // table-lane batch path
     size_t score_rows;             // scoring only: 2 doubles per (strategy, m)
+    int blk_group;                 // as in Scratch
     size_t total;                  // bytes of the block
 };
 

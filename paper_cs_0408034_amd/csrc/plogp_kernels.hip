@@ -591,19 +591,18 @@ struct ChainCtx {
 };
 
 // Scratch::blk: [block][m], or, where the totals are turned into their prefix, the sizes of one workgroup
-// of that step (k_chain_prefix) together: [group of PFX_M sizes][block][m of the group].
-constexpr int PFX_M = 8;
+// of that step (k_chain_prefix) together: [group of 2^blk_group sizes][block][m of the group].
 
 struct BlkAt {
     size_t first, stride;      // of block 0, from a block to the next
 };
 
-__device__ __forceinline__ BlkAt blk_of(const DeviceGrid &G, int t, int mi)
+__device__ __forceinline__ BlkAt blk_of(const DeviceGrid &G, const Scratch &S, int t, int mi)
 {
     const size_t table = (size_t)t * G.n_blk * G.n_mu;
     if (!G.blk_is_prefix)
         return {table + mi, (size_t)G.n_mu};
-    const int first = mi / PFX_M * PFX_M, width = G.n_mu - first < PFX_M ? G.n_mu - first : PFX_M;
+    const int most = 1 << S.blk_group, first = mi & -most, width = G.n_mu - first < most ? G.n_mu - first : most;
     return {table + (size_t)first * G.n_blk + (mi - first), (size_t)width};
 }
 
@@ -1047,7 +1046,7 @@ __device__ __forceinline__ void chain_small_body(const DeviceTables &T, const De
         }
         __syncthreads();
         if (wave == 0) {
-            const BlkAt at_total = blk_of(G, t, mi < n_mu ? mi : 0);
+            const BlkAt at_total = blk_of(G, S, t, mi < n_mu ? mi : 0);
             double run = 0.0;
             for (int r0 = 0; r0 < SUM_BLOCK; r0 += 8) {
                 double g[8];
@@ -1341,7 +1340,7 @@ __device__ __forceinline__ void chain_body(const DeviceTables &T, const DeviceGr
             continue;
         const u64 m = G.mu[mi];
         double *part = S.part + ((size_t)t * C.n_m + mi) * G.n_P;     // [m][P index]
-        const BlkAt at_total = blk_of(G, t, mi);
+        const BlkAt at_total = blk_of(G, S, t, mi);
         chain_item(C, single ? u : n_single + u * CHAIN_U, single ? 1 : CHAIN_U, m, part,
                    S.blk + at_total.first, at_total.stride);
     }
@@ -1808,7 +1807,7 @@ __global__ void __launch_bounds__(256) k_terms_chain(DeviceTables T, DeviceGrid 
         terms_body(T, G, S, n_chunks, n_mchunks, with_pairs, (int)blockIdx.x - n_chain_wg, both_lds);
 }
 
-// Turns the block totals of PFX_M message sizes into their exclusive prefix in
+// Turns the block totals of M message sizes into their exclusive prefix in
 // ascending block order (the sum of all finished blocks before block b) and
 // writes, per process count of the grid, the prefix of the block it ends in:
 // pre[m][P index], which the sweeps read side by side with the partial sums.  The sum is
@@ -1827,27 +1826,29 @@ __global__ void __launch_bounds__(256) k_terms_chain(DeviceTables T, DeviceGrid 
 constexpr int PFX_TILE = 128;
 constexpr int PFX_THREADS = 512;
 constexpr int PFX_LD = PFX_TILE + 2;     // row of a size: the lanes' pairs lie in different banks
+constexpr int PFX_WG_PER_CU = 4;         // at once, of eight sizes (the line at 2 or 8: 60 x 200 sizes 171 and 183 us)
 constexpr int PFX_MAX_P = 4096;          // process counts whose block index is kept in LDS
 
 __host__ __device__ inline bool pfx_in_lds(const DeviceGrid &G) { return G.n_P <= PFX_MAX_P && G.n_blk <= 65536; }
 
+template <int M>
 __global__ void __launch_bounds__(PFX_THREADS) k_chain_prefix(DeviceGrid G, Scratch S, int n_mgroups)
 {
-    __shared__ __align__(16) double tile[3][PFX_M * PFX_LD];     // [m][block]
+    __shared__ __align__(16) double tile[3][M * PFX_LD];     // [m][block]
     extern __shared__ unsigned short pfx_blk_of[];               // [n_P] if pfx_in_lds
     const int t = blockIdx.x / n_mgroups, mg = blockIdx.x % n_mgroups;
     const int tid = threadIdx.x, hid = tid - 64;         // hid: thread of the helping waves
-    constexpr int HELPERS = PFX_THREADS - 64, ROWS = HELPERS / PFX_M, N = (PFX_TILE + ROWS - 1) / ROWS;
-    const int ml = tid % PFX_M, br = hid / PFX_M;
-    const int mi = mg * PFX_M + ml;
+    constexpr int HELPERS = PFX_THREADS - 64, ROWS = HELPERS / M, N = (PFX_TILE + ROWS - 1) / ROWS;
+    const int ml = tid % M, br = hid / M;
+    const int mi = mg * M + ml;
     const bool active = mi < G.n_mu;
     const size_t n_m = (size_t)G.n_mu;       // rows: the distinct sizes
-    const BlkAt from = blk_of(G, t, active ? mi : mg * PFX_M);
+    const BlkAt from = blk_of(G, S, t, active ? mi : mg * M);
     const double *src = S.blk + from.first;
     const int full = G.n_blk - 1;                        // blocks that have a total
     const int n_tiles = (G.n_blk + PFX_TILE - 1) / PFX_TILE;
     const bool p_in_lds = pfx_in_lds(G);
-    const int m_valid = G.n_mu - mg * PFX_M < PFX_M ? G.n_mu - mg * PFX_M : PFX_M;   // sizes of this group
+    const int m_valid = G.n_mu - mg * M < M ? G.n_mu - mg * M : M;   // sizes of this group
     double v[2][N], done = 0.0;
     auto load = [&](int k, double (&r)[N]) {             // totals of tile k (0 where there is none)
 #pragma unroll
@@ -1872,13 +1873,13 @@ __global__ void __launch_bounds__(PFX_THREADS) k_chain_prefix(DeviceGrid G, Scra
         for (int pi = G.blk_off[b0] + hid; pi < pi_hi; pi += HELPERS) {
             const int bb = (p_in_lds ? (int)pfx_blk_of[pi] : (int)((G.P[pi] - 1u) / SUM_BLOCK)) - b0;
             // all the sums of the row first (one wait for LDS), then the stores
-            double row[PFX_M];
+            double row[M];
 #pragma unroll
-            for (int mm = 0; mm < PFX_M; ++mm)
+            for (int mm = 0; mm < M; ++mm)
                 row[mm] = tile[k % 3][mm * PFX_LD + bb];
-            double *o = S.pre + ((size_t)t * n_m + (size_t)mg * PFX_M) * G.n_P + pi;
+            double *o = S.pre + ((size_t)t * n_m + (size_t)mg * M) * G.n_P + pi;
 #pragma unroll
-            for (int mm = 0; mm < PFX_M; ++mm) {
+            for (int mm = 0; mm < M; ++mm) {
                 if (mm < m_valid)
                     o[(size_t)mm * G.n_P] = row[mm];
             }
@@ -1887,7 +1888,7 @@ __global__ void __launch_bounds__(PFX_THREADS) k_chain_prefix(DeviceGrid G, Scra
     // Step k: tile k is added up, k - 1 written out, k + 1 put into LDS, k + 3 asked for.
     auto step = [&](int k, double (&next)[N]) {
         if (hid < 0) {
-            if (k < n_tiles && tid < PFX_M) {
+            if (k < n_tiles && tid < M) {
                 f64x2 *row = reinterpret_cast<f64x2 *>(&tile[k % 3][tid * PFX_LD]);
                 const int left = G.n_blk - k * PFX_TILE, nb = left < PFX_TILE ? left : PFX_TILE;
                 // sixteen at a time, the next sixteen on their way (blocks past the last hold zeros)
@@ -5218,6 +5219,7 @@ Scratch bind_scratch(void *base, const ScratchLayout &lay)
 {
     char *b = static_cast<char *>(base);
     Scratch S = {};
+    S.blk_group = lay.blk_group;
     S.g1 = reinterpret_cast<double *>(b + lay.g1);
     S.gs = reinterpret_cast<double *>(b + lay.gs);
     S.gm = reinterpret_cast<double *>(b + lay.gm);
@@ -5494,7 +5496,11 @@ static bool plan_fastest(const DeviceTables &T, const DeviceGrid &G, bool terms_
         p.chain_wg = (int)wg;
         if ((long)T.n_tables * wg + p.terms_wg > kMaxLaunch) return false;
         p.n_chain_wg = (int)(T.n_tables * wg);
-        p.n_mgroups = (G.n_mu + PFX_M - 1) / PFX_M;
+        // eight sizes to a workgroup of the prefix, sixteen where the workgroups of eight would not be on the
+        // chip at once: their adding waves then use twice the lanes for the same time (100 tables x 1000 sizes x
+        // P up to 20 000: the kernel 111 us with eight, 60 so; the call 20 x 3000 224 and 201, 300 x 200 317 and 289)
+        p.lay.blk_group = (long)T.n_tables * ((G.n_mu + 7) / 8) > PFX_WG_PER_CU * n_cu ? 4 : 3;
+        p.n_mgroups = (G.n_mu + (1 << p.lay.blk_group) - 1) >> p.lay.blk_group;
         if ((long)T.n_tables * p.n_mgroups > kMaxLaunch) return false;
     }
     if (!terms_only) {
@@ -5662,7 +5668,7 @@ hipError_t launch_tune_stage(const TunePlan &p, int stage, const DeviceTables &T
         break;
     case TUNE_STAGE_PREFIX:
         if (p.chain && !p.chain_row && G.blk_is_prefix)
-            hipLaunchKernelGGL(k_chain_prefix, dim3((unsigned)T.n_tables * p.n_mgroups), dim3(PFX_THREADS),
+            hipLaunchKernelGGL(S.blk_group == 4 ? k_chain_prefix<16> : k_chain_prefix<8>, dim3((unsigned)T.n_tables * p.n_mgroups), dim3(PFX_THREADS),
                                pfx_in_lds(G) ? (size_t)G.n_P * sizeof(unsigned short) : 0, st, G, S, p.n_mgroups);
         break;
     default:

@@ -821,6 +821,23 @@ def test_prefix_of_the_block_sums_at_the_edges_of_its_tiles(blocks, n_m, n_P):
     assert assert_tables_equal(gpu_tune(wl), want, "%d blocks" % blocks), "times not bit-identical"
 
 
+@pytest.mark.parametrize("n_tables,n_m,blocks", [(1024, 8, 33), (1025, 8, 33), (513, 9, 34), (342, 17, 33), (342, 24, 129),
+                                                 (260, 31, 33), (205, 33, 40)])
+def test_prefix_of_the_block_sums_of_many_tables(n_tables, n_m, blocks):
+    # sixteen sizes to a group where there are more than four groups of eight to a compute unit: 1024 groups,
+    # 1025, and groups of one, eight and fifteen sizes behind full ones
+    rng = np.random.default_rng(n_tables + n_m)
+    x = np.cumsum(rng.integers(1, 9000, size=(n_tables, 20)), axis=1).astype(np.float64)
+    gaps = np.abs(20.0 + x * 0.05 * (1.0 + 0.4 * rng.standard_normal(x.shape)))
+    top = 64 * (blocks - 1) + 2
+    P = np.union1d(rng.choice(np.arange(2, top), size=5, replace=False), [64, 65, 129, top]).astype(np.uint32)
+    m = 8 * rng.choice(np.arange(1, 4000), size=n_m, replace=False)
+    wl = Workload("prefix", x, gaps, rng.uniform(0.0, 90.0, size=n_tables), m.astype(np.uint64), P,
+                  np.array([8, 64], dtype=np.uint64), NO_CAP, ALL_STRATEGIES_MASK)
+    want, _ = oracle.tune_workload(wl)
+    assert assert_tables_equal(gpu_tune(wl), want, "%d x %d" % (n_tables, n_m)), "times not bit-identical"
+
+
 # ------------------------------------------------------------------ tiles of message sizes
 
 def _tile_problem(rng, seed):
