@@ -5278,20 +5278,23 @@ static bool plan_tiles(const DeviceTables &T, const DeviceGrid &G, int tile_m, T
 
 // Whether a workgroup per row leaves out the candidates that cannot win row 5 (row5_candidates) or evaluates all.
 // The former is 70 instructions that wait for one another and a candidate at a time after them, the latter two
-// round trips for 16 candidates: it is the shorter wait where a call waits for nothing else, which is where no chain
-// sum is needed, beside which the others wait, up to 24 candidates for a few waves of process counts (64 sizes of
-// up to 8 MB, 30 samples, the Broadcast rows: 13 candidates x 64 up to 640 4.53 us, 4.84 with those left out that
-// cannot win; 4000 sizes x 200, 26 candidates 14.1 and 13.8) and up to 8 for any number (1000 x 1000, 5 candidates
-// 10.4 and 10.7); and beside chain sums two or three round trips for few process counts far apart, for which
-// many candidates can win (30 tables x 24 sizes x 10 up to 512, 18 candidates 7.1 and 7.3; 49 up to 50, 13: 4.05
-// and 4.12, left as it is; 100 up to 101, 17, 300 sizes 5.5 and 5.35).
+// round trips for 16 candidates.  The latter is the shorter wait where a call waits for nothing else, which is where no
+// chain sum is needed, beside which the others wait: up to 24 candidates for a few waves of process counts (64 sizes
+// of up to 8 MB, 30 samples, the Broadcast rows: 13 candidates x 64 up to 640 4.53 us, 4.84 with those left out that
+// cannot win; 4000 sizes x 200, 26 candidates 14.1 and 13.8), up to 8 for any number (1000 x 1000, 5 candidates 10.4
+// and 10.7), and for a wave of process counts far apart, for which many can win, any number (2000 sizes x 64 up to
+// 2047, 48 candidates 11.7 and 12.6; x 6 up to 30, 26, 60 sizes 4.3 and 4.0).  Beside chain sums for such process
+// counts alone (30 tables x 24 sizes x 10 up to 512, 18 candidates 7.1 and 7.3; 35 sizes x 14 up to 2048, 35, 8.7 and
+// 9.1; 60 x 20 up to 100, 26 5 % slower; 49 up to 50, 13, 4.05 and 4.12, left as it is; 300 sizes x 100 up to 101, 17,
+// 5.5 and 5.35).
 static bool row_few(const DeviceGrid &G)
 {
-    const bool chain = (G.need & (1u << 11)) != 0;
     const int P_top = SUM_BLOCK * (G.n_blk - 1) + G.last_terms + 1;
-    if (!chain)
-        return G.n_s > 8 && (G.n_s > 24 || G.n_P > 256);
-    return !(G.n_s > 12 && G.n_s <= 24 && G.n_P <= 64 && P_top >= 4 * G.n_P);
+    if ((G.need & (1u << 11)) != 0) {
+        const int apart = G.n_s > 24 ? 500 : G.n_P > 32 ? 4 * G.n_P : 128;
+        return G.n_s <= 12 || G.n_P > 64 || P_top < apart;
+    }
+    return G.n_s > 8 && (G.n_s > 24 || G.n_P > 256) && (G.n_P > 64 || P_top < 256);
 }
 
 // The same for the sweep over process counts.  With two of them per lane it is the faster to leave candidates out

@@ -1099,7 +1099,8 @@ def test_small_jobs_a_row_per_workgroup(n_m, n_P, p_hi, n_s, n, mask):
 
 @pytest.mark.parametrize("n_s,n_P,p_hi", [(1, 1, 2), (8, 1000, 1001), (9, 256, 300), (9, 257, 300), (24, 256, 2000), (25, 256, 2000),
                                           (12, 64, 640), (13, 64, 255), (13, 64, 256), (24, 64, 640), (25, 64, 640),
-                                          (13, 65, 640)])
+                                          (13, 65, 640), (13, 32, 127), (13, 32, 128), (25, 20, 255), (25, 20, 256),
+                                          (40, 20, 499), (40, 20, 500), (64, 64, 2049)])
 @pytest.mark.parametrize("mask", [ALL_STRATEGIES_MASK, 0x3FF, 0x20, 0x203FF, 0x3FFFF, 0x10024])
 def test_which_rows_evaluate_every_candidate(n_s, n_P, p_hi, mask):
     # on both sides of the limits at which a workgroup per row evaluates all candidates of row 5, or leaves
