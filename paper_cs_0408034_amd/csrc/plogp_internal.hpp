@@ -110,7 +110,6 @@ struct Scratch {
     int *nv;          // [n_m]                            candidates s <= min(m, s_cap)
     BatchPrep batch;  // shared sample sizes only
     double *batch_ys; // [n+2][n_tables][2]               {gap, slope} by interval (shared sample sizes only)
-    int blk_group;    // log2 of the sizes whose block totals lie together (more than 32 blocks)
 };
 
 struct plogp_cell_dev {
@@ -133,7 +132,6 @@ struct ScratchLayout {
     size_t g1, gs, gm, sum2, blk, pre, part, rcp, segC, segA, segB, amin, minG, nv;
     size_t rec, tab, batch_ys;     // table-lane batch path
     size_t score_rows;             // scoring only: 2 doubles per (strategy, m)
-    int blk_group;                 // as in Scratch
     size_t total;                  // bytes of the block
 };
 
@@ -158,7 +156,7 @@ struct TunePlan {
     // staged path
     int lanes_s, lanes_p, pairs, terms_mode, n_chunks, n_mchunks, terms_wg;
     int chain, chain_row, together, row_together, chain_threads;
-    int n_single, chain_wg, n_chain_wg, n_mgroups;
+    int n_single, chain_wg, n_chain_wg, n_mgroups, prefix_m;
     size_t terms_lds, chain_lds, both_lds, crow_lds;
     int sweep_gp, sweep_dense, sweep_ptiles;    // lanes over s
     int ppl, n_pg, n_w;            // lanes over P

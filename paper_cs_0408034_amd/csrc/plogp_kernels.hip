@@ -591,18 +591,19 @@ struct ChainCtx {
 };
 
 // Scratch::blk: [block][m], or, where the totals are turned into their prefix, the sizes of one workgroup
-// of that step (k_chain_prefix) together: [group of 2^blk_group sizes][block][m of the group].
+// of that step (k_chain_prefix), or half of them, together: [group of BLK_GROUP sizes][block][m of the group].
+constexpr int BLK_GROUP = 8;
 
 struct BlkAt {
     size_t first, stride;      // of block 0, from a block to the next
 };
 
-__device__ __forceinline__ BlkAt blk_of(const DeviceGrid &G, const Scratch &S, int t, int mi)
+__device__ __forceinline__ BlkAt blk_of(const DeviceGrid &G, int t, int mi)
 {
     const size_t table = (size_t)t * G.n_blk * G.n_mu;
     if (!G.blk_is_prefix)
         return {table + mi, (size_t)G.n_mu};
-    const int most = 1 << S.blk_group, first = mi & -most, width = G.n_mu - first < most ? G.n_mu - first : most;
+    const int first = mi / BLK_GROUP * BLK_GROUP, width = G.n_mu - first < BLK_GROUP ? G.n_mu - first : BLK_GROUP;
     return {table + (size_t)first * G.n_blk + (mi - first), (size_t)width};
 }
 
@@ -1046,7 +1047,7 @@ __device__ __forceinline__ void chain_small_body(const DeviceTables &T, const De
         }
         __syncthreads();
         if (wave == 0) {
-            const BlkAt at_total = blk_of(G, S, t, mi < n_mu ? mi : 0);
+            const BlkAt at_total = blk_of(G, t, mi < n_mu ? mi : 0);
             double run = 0.0;
             for (int r0 = 0; r0 < SUM_BLOCK; r0 += 8) {
                 double g[8];
@@ -1340,7 +1341,7 @@ __device__ __forceinline__ void chain_body(const DeviceTables &T, const DeviceGr
             continue;
         const u64 m = G.mu[mi];
         double *part = S.part + ((size_t)t * C.n_m + mi) * G.n_P;     // [m][P index]
-        const BlkAt at_total = blk_of(G, S, t, mi);
+        const BlkAt at_total = blk_of(G, t, mi);
         chain_item(C, single ? u : n_single + u * CHAIN_U, single ? 1 : CHAIN_U, m, part,
                    S.blk + at_total.first, at_total.stride);
     }
@@ -1843,7 +1844,7 @@ __global__ void __launch_bounds__(PFX_THREADS) k_chain_prefix(DeviceGrid G, Scra
     const int mi = mg * M + ml;
     const bool active = mi < G.n_mu;
     const size_t n_m = (size_t)G.n_mu;       // rows: the distinct sizes
-    const BlkAt from = blk_of(G, S, t, active ? mi : mg * M);
+    const BlkAt from = blk_of(G, t, active ? mi : mg * M);
     const double *src = S.blk + from.first;
     const int full = G.n_blk - 1;                        // blocks that have a total
     const int n_tiles = (G.n_blk + PFX_TILE - 1) / PFX_TILE;
@@ -5219,7 +5220,6 @@ Scratch bind_scratch(void *base, const ScratchLayout &lay)
 {
     char *b = static_cast<char *>(base);
     Scratch S = {};
-    S.blk_group = lay.blk_group;
     S.g1 = reinterpret_cast<double *>(b + lay.g1);
     S.gs = reinterpret_cast<double *>(b + lay.gs);
     S.gm = reinterpret_cast<double *>(b + lay.gm);
@@ -5502,8 +5502,8 @@ static bool plan_fastest(const DeviceTables &T, const DeviceGrid &G, bool terms_
         // eight sizes to a workgroup of the prefix, sixteen where the workgroups of eight would not be on the
         // chip at once: their adding waves then use twice the lanes for the same time (100 tables x 1000 sizes x
         // P up to 20 000: the kernel 111 us with eight, 60 so; the call 20 x 3000 224 and 201, 300 x 200 317 and 289)
-        p.lay.blk_group = (long)T.n_tables * ((G.n_mu + 7) / 8) > PFX_WG_PER_CU * n_cu ? 4 : 3;
-        p.n_mgroups = (G.n_mu + (1 << p.lay.blk_group) - 1) >> p.lay.blk_group;
+        p.prefix_m = (long)T.n_tables * ((G.n_mu + 7) / 8) > PFX_WG_PER_CU * n_cu ? 16 : 8;
+        p.n_mgroups = (G.n_mu + p.prefix_m - 1) / p.prefix_m;
         if ((long)T.n_tables * p.n_mgroups > kMaxLaunch) return false;
     }
     if (!terms_only) {
@@ -5671,7 +5671,7 @@ hipError_t launch_tune_stage(const TunePlan &p, int stage, const DeviceTables &T
         break;
     case TUNE_STAGE_PREFIX:
         if (p.chain && !p.chain_row && G.blk_is_prefix)
-            hipLaunchKernelGGL(S.blk_group == 4 ? k_chain_prefix<16> : k_chain_prefix<8>, dim3((unsigned)T.n_tables * p.n_mgroups), dim3(PFX_THREADS),
+            hipLaunchKernelGGL(p.prefix_m == 16 ? k_chain_prefix<16> : k_chain_prefix<8>, dim3((unsigned)T.n_tables * p.n_mgroups), dim3(PFX_THREADS),
                                pfx_in_lds(G) ? (size_t)G.n_P * sizeof(unsigned short) : 0, st, G, S, p.n_mgroups);
         break;
     default:
